@@ -204,9 +204,6 @@ def algorithmic_work(kernel, c):
         "mse_row_loss": (2 * f * N * O, 3.0 * N * O),
         "dz": ((3 if not c["loss_kind"] == 0 else 2) * f * N * O, 3.0 * N * O),
         "dwx_tokens": (f * (N * H + I * H), 1.0 * N * H),
-        # float32 matrix in, bf16 hi/lo planes out (row-major and transposed: 4 bytes per element each);
-        # per step: h, V and dZ
-        "split_bf16": (f * 3 * (N * H + H * O + N * O) / 3.0, 6.0 * (N * H + H * O + N * O) / 3.0),
         # time loops: the recurrent matrix once per launch, one state row in and out per step
         "rec_fwd": None, "rec_bwd": None,
         # short-sequence output layer (column strips): V in, Z out, and the strips' shares of the

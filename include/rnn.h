@@ -72,8 +72,9 @@ extern "C" {
  * (and dWh = Delta^T H_prev, dense-input dWx = Delta^T X) run on the bf16 matrix cores with float32 accumulation, every float32
  * operand split into two bf16 numbers (hi + lo) and each product taken as hi*hi + hi*lo + lo*hi
  * (error per product term below 2^-16 relative; parameters, results and everything else stay
- * float32).  Set it on rnn_workspace_bytes, rnn_loss and rnn_bptt alike (the workspace grows by
- * the bf16 copies of the operands).  Ignored where the column-strip kernels of a short single
+ * float32).  Without it the same products split every operand into three bf16 numbers, which hold all
+ * 24 bits, and take six products: float32 accuracy.  Set it on rnn_workspace_bytes, rnn_loss and
+ * rnn_bptt alike.  Ignored where the column-strip kernels of a short single
  * sequence serve the output layer; rnn_gauss_newton_vec takes it too (its five output-layer
  * products); rejected by rnn_window and rnn_train_stream. */
 #define RNN_FLAG_BF16X3_OUTPUT 16u

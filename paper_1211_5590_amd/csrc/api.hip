@@ -21,7 +21,7 @@ inline size_t up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 struct Plan {
     // byte offsets into the workspace
     size_t Z, lse, rowloss, U, G, Delta, WhT, hring, part, splitk, scratch, flags, statbox, gbox, gpart, vy, seen,
-        lstat, HsS, HsT, VS, VT, dZS, dZT, DT, XS, WxS, splitk3, total;
+        lstat, total;
 };
 
 // Which kernel family serves these sizes.
@@ -68,18 +68,21 @@ Sizes sizes_of(const rnn_dims* d) {
     return s;
 }
 
-size_t max_splitk_floats(const Sizes& s) {
+// bf16 numbers an operand of the output layer's and the weight gradients' products is split into
+int output_parts(const rnn_dims* d) { return (d->flags & RNN_FLAG_BF16X3_OUTPUT) ? 2 : 3; }
+
+size_t max_splitk_floats(const Sizes& s, int parts) {
     const int N = (int)s.N, H = s.H, O = s.O, D = s.NVin;
     size_t m = 0;
     auto take = [&](size_t v) { if (v > m) m = v; };
-    take(gemm_splitk_floats(N, O, H));   // Z = Hs V
-    take(gemm_splitk_floats(H, O, N));   // dV = Hs^T dZ
-    take(gemm_splitk_floats(N, H, O));   // G = dZ V^T
-    take(gemm_splitk_floats(H, H, N));   // dWh = Delta^T Hprev
+    take(gemm_splitk_floats(N, O, H, parts));   // Z = Hs V
+    take(gemm_splitk_floats(H, O, N, parts));   // dV = Hs^T dZ
+    take(gemm_splitk_floats(N, H, O, parts));   // G = dZ V^T
+    take(gemm_splitk_floats(H, H, N, parts));   // dWh = Delta^T Hprev
     take(gemm_splitk_floats(s.B, H, H)); // dh0 = delta_0 Wh (stepwise recurrence)
     if (!s.tokens) {
         take(gemm_splitk_floats(N, H, D));  // U = X Wx^T
-        take(gemm_splitk_floats(H, D, N));  // dWx = Delta^T X
+        take(gemm_splitk_floats(H, D, N, parts));  // dWx = Delta^T X
     }
     return m;
 }
@@ -121,7 +124,7 @@ Plan make_plan(const rnn_dims* d) {
     p.hring = take(2 * B * H * 4);
     const size_t widest = O > H ? O : H;
     p.part = take((size_t)colsum_chunks((int)N) * widest * 4);
-    p.splitk = take(max_splitk_floats(s) * 4);
+    p.splitk = take(max_splitk_floats(s, output_parts(d)) * 4);
     p.scratch = take(256);
     p.flags = take(4096 + 16 * B * H);   // state-exchange boxes of the multi-workgroup loops
     const size_t strips = (size_t)skinny_strips(s.O);
@@ -131,33 +134,10 @@ Plan make_plan(const rnn_dims* d) {
     p.gpart = take(small ? strips * N * H * 4 : 0);
     p.vy = take(small ? N * H * 4 : 0);
     p.seen = take(s.tokens && N > 32 ? dwx_table_ints((int)N, s.NVin) * 4 : 0);
-    // row statistics the logits product leaves per 64-column part (fused log-sum-exp)
-    const bool bf3 = (d->flags & RNN_FLAG_BF16X3_OUTPUT) != 0;
-    const bool fuses = bf3 ? bf3_fuses_stats((int)N, s.O, s.H) : gemm_fuses_stats((int)N, s.O, s.H);
-    const size_t parts = bf3 ? (size_t)bf3_stat_parts((int)N, s.O, s.H) : (size_t)gemm_stat_parts(s.O);
-    p.lstat = take(s.ce && fuses ? N * parts * 8 : 0);
-    // bf16 hi/lo plane pairs of the output layer's operands (4 bytes per padded element)
-    const size_t Np = (size_t)bf3_pad((int)N), Hp = (size_t)bf3_pad(s.H), Op = (size_t)bf3_pad(s.O);
-    p.HsS = take(bf3 ? N * Hp * 4 : 0);
-    p.HsT = take(bf3 ? H * Np * 4 : 0);
-    p.VS = take(bf3 ? H * Op * 4 : 0);
-    p.VT = take(bf3 ? O * Hp * 4 : 0);
-    p.dZS = take(bf3 ? N * Op * 4 : 0);
-    p.dZT = take(bf3 ? O * Np * 4 : 0);
-    p.DT = take(bf3 ? H * Np * 4 : 0);
-    // dense input: X transposed, for dWx (the input projection itself stays float32: the hidden
-    // states it feeds are held to a tighter tolerance than the gradients)
-    p.XS = take(bf3 && !s.tokens ? (size_t)s.NVin * Np * 4 : 0);
-    p.WxS = take(0);
-    size_t sk3 = 0;
-    if (bf3) {
-        sk3 = bf3_splitk_floats((int)N, s.O, s.H);
-        if (bf3_splitk_floats(s.H, s.O, (int)N) > sk3) sk3 = bf3_splitk_floats(s.H, s.O, (int)N);
-        if (bf3_splitk_floats((int)N, s.H, s.O) > sk3) sk3 = bf3_splitk_floats((int)N, s.H, s.O);
-        if (bf3_splitk_floats(s.H, s.H, (int)N) > sk3) sk3 = bf3_splitk_floats(s.H, s.H, (int)N);
-        if (!s.tokens && bf3_splitk_floats(s.H, s.NVin, (int)N) > sk3) sk3 = bf3_splitk_floats(s.H, s.NVin, (int)N);
-    }
-    p.splitk3 = take(sk3 * 4);
+    // row statistics the logits product leaves per column part (fused log-sum-exp)
+    const int parts = output_parts(d);
+    p.lstat = take(s.ce && gemm_fuses_stats((int)N, s.O, s.H, parts)
+                       ? N * (size_t)gemm_stat_parts((int)N, s.O, s.H, parts) * 8 : 0);
     p.total = off;
     return p;
 }
@@ -273,34 +253,6 @@ hipError_t run_loss(const rnn_dims* d, const rnn_params* P, const float* h_all, 
         return launch_skinny_logits(k, s);
     }
     float* Z = at<float>(ws, pl.Z);
-    if (d->flags & RNN_FLAG_BF16X3_OUTPUT) {
-        // operands as bf16 hi/lo planes (h also transposed, for dV later; V both ways), then the
-        // product on the bf16 matrix cores
-        const float* Hs = h_all + (size_t)z.B * z.H;
-        RNN_TRY(launch_split_bf16(Hs, N, z.H, z.H, at<uint16_t>(ws, pl.HsS), at<uint16_t>(ws, pl.HsT), s));
-        RNN_TRY(launch_split_bf16(P->V, z.H, z.O, z.O, at<uint16_t>(ws, pl.VS), at<uint16_t>(ws, pl.VT), s));
-        const bool fused = z.ce && bf3_fuses_stats(N, z.O, z.H);
-        Bf3Args b{};
-        b.A = at<uint16_t>(ws, pl.HsS); b.B = at<uint16_t>(ws, pl.VT); b.C = Z;
-        b.M = N; b.N = z.O; b.K = z.H; b.lda = bf3_pad(z.H); b.ldb = bf3_pad(z.H); b.ldc = z.O;
-        b.bias_n = P->c; b.beta = 0; b.splitk_ws = at<float>(ws, pl.splitk3); b.prof_id = K_GEMM_LOGITS;
-        b.row_stats = fused ? at<float>(ws, pl.lstat) : nullptr;
-        RNN_TRY(launch_gemm_bf16x3(b, s));
-        float* rowloss = at<float>(ws, pl.rowloss);
-        if (fused) {
-            RNN_TRY(launch_ce_merge_stats(b.row_stats, bf3_stat_parts(N, z.O, z.H), Z, static_cast<const int32_t*>(targets),
-                                          at<float>(ws, pl.lse), rowloss, N, z.O, s));
-            return launch_loss_reduce(rowloss, N, 1.0f / (float)N, loss, s);
-        }
-        if (z.ce) {
-            RNN_TRY(launch_ce_row_stats(Z, static_cast<const int32_t*>(targets), at<float>(ws, pl.lse),
-                                        rowloss, N, z.O, s));
-            return launch_loss_reduce(rowloss, N, 1.0f / (float)N, loss, s);
-        }
-        int n_partial = 0;
-        RNN_TRY(launch_mse_partial(Z, static_cast<const float*>(targets), rowloss, N, z.O, &n_partial, s));
-        return launch_loss_reduce(rowloss, n_partial, (float)(1.0 / ((double)N * (double)z.O)), loss, s);
-    }
     GemmArgs g{};
     g.A = h_all + (size_t)z.B * z.H;  // rows of h_all[1:]
     g.B = P->V; g.C = Z;
@@ -308,14 +260,15 @@ hipError_t run_loss(const rnn_dims* d, const rnn_params* P, const float* h_all, 
     g.lda = z.H; g.ldb = z.O; g.ldc = z.O;
     g.a_t = false; g.b_t = false; g.bias_n = P->c; g.beta = 0; g.prof_id = K_GEMM_LOGITS;
     g.splitk_ws = at<float>(ws, pl.splitk);
-    // softmax-CE: the product's epilogue leaves (max, sum exp) per row and 64-column part, so the
+    g.parts = output_parts(d);
+    // softmax-CE: the product's epilogue leaves (max, sum exp) per row and column part, so the
     // logits are not read again for the log-sum-exp
-    const bool fused = z.ce && gemm_fuses_stats(N, z.O, z.H);
+    const bool fused = z.ce && gemm_fuses_stats(N, z.O, z.H, g.parts);
     g.row_stats = fused ? at<float>(ws, pl.lstat) : nullptr;
     RNN_TRY(launch_gemm(g, s));
     float* rowloss = at<float>(ws, pl.rowloss);
     if (fused) {
-        RNN_TRY(launch_ce_merge_stats(g.row_stats, gemm_stat_parts(z.O), Z, static_cast<const int32_t*>(targets),
+        RNN_TRY(launch_ce_merge_stats(g.row_stats, gemm_stat_parts(N, z.O, z.H, g.parts), Z, static_cast<const int32_t*>(targets),
                                       at<float>(ws, pl.lse), rowloss, N, z.O, s));
         return launch_loss_reduce(rowloss, N, 1.0f / (float)N, loss, s);
     }
@@ -385,11 +338,9 @@ hipError_t run_reverse_loop(const rnn_dims* d, const float* Wh, const float* WhT
 
 // Everything of backpropagation that follows d loss / d z (held in the logits buffer of the
 // workspace): dV, G, the reverse loop, dWh, db, dWx.  dc is the caller's.
-// bf3: dZ is also there as bf16 plane pairs (row-major and transposed) next to the planes of h and
-// V that run_loss left, and dV, G run on the bf16 matrix cores.
 hipError_t run_backward_from_dz(const rnn_dims* d, const rnn_params* P, const void* x, const float* h_all,
                                 const float* dh_last, const rnn_grads* Gr, float* dh0, void* ws,
-                                const Plan& pl, bool bf3, hipStream_t s) {
+                                const Plan& pl, hipStream_t s) {
     const Sizes z = sizes_of(d);
     const int N = (int)z.N, H = z.H, O = z.O;
     const int beta = (d->flags & RNN_FLAG_ACCUMULATE) ? 1 : 0;
@@ -400,26 +351,14 @@ hipError_t run_backward_from_dz(const rnn_dims* d, const rnn_params* P, const vo
     float* Delta = at<float>(ws, pl.Delta);
     const float* Hs = h_all + (size_t)z.B * H;  // h_t rows
     const int chunks = colsum_chunks(N);
-    if (bf3) {
-        const int Np = bf3_pad(N), Op = bf3_pad(O);
-        Bf3Args b{};   // dV = Hs^T dZ, K = N
-        b.A = at<uint16_t>(ws, pl.HsT); b.B = at<uint16_t>(ws, pl.dZT); b.C = Gr->dV;
-        b.M = H; b.N = O; b.K = N; b.lda = Np; b.ldb = Np; b.ldc = O;
-        b.beta = beta; b.splitk_ws = at<float>(ws, pl.splitk3); b.prof_id = K_GEMM_DV;
-        RNN_TRY(launch_gemm_bf16x3(b, s));
-        Bf3Args c{};   // G = dZ V^T, K = O
-        c.A = at<uint16_t>(ws, pl.dZS); c.B = at<uint16_t>(ws, pl.VS); c.C = G;
-        c.M = N; c.N = H; c.K = O; c.lda = Op; c.ldb = Op; c.ldc = H;
-        c.beta = 0; c.splitk_ws = at<float>(ws, pl.splitk3); c.prof_id = K_GEMM_G;
-        RNN_TRY(launch_gemm_bf16x3(c, s));
-    } else {
+    const int parts = output_parts(d);
     // dV = Hs^T dZ
     {
         GemmArgs g{};
         g.A = Hs; g.B = Z; g.C = Gr->dV;
         g.M = H; g.N = O; g.K = N;
         g.lda = H; g.ldb = O; g.ldc = O;
-        g.a_t = true; g.b_t = false; g.beta = beta; g.splitk_ws = splitk; g.prof_id = K_GEMM_DV;
+        g.a_t = true; g.b_t = false; g.beta = beta; g.splitk_ws = splitk; g.parts = parts; g.prof_id = K_GEMM_DV;
         RNN_TRY(launch_gemm(g, s));
     }
     // G = dZ V^T
@@ -428,28 +367,17 @@ hipError_t run_backward_from_dz(const rnn_dims* d, const rnn_params* P, const vo
         g.A = Z; g.B = P->V; g.C = G;
         g.M = N; g.N = H; g.K = O;
         g.lda = O; g.ldb = O; g.ldc = H;
-        g.a_t = false; g.b_t = true; g.beta = 0; g.splitk_ws = splitk; g.prof_id = K_GEMM_G;
+        g.a_t = false; g.b_t = true; g.beta = 0; g.splitk_ws = splitk; g.parts = parts; g.prof_id = K_GEMM_G;
         RNN_TRY(launch_gemm(g, s));
-    }
     }
     RNN_TRY(run_reverse_loop(d, P->Wh, nullptr, at<float>(ws, pl.WhT), G, h_all, dh_last, Delta, dh0, ws, pl, s));
     // dWh = Delta^T Hprev  (Hprev rows = h_all[0:T])
-    if (bf3) {
-        // both operands transposed into split form (the planes of h^T used by dV are free again)
-        const int Np = bf3_pad(N);
-        RNN_TRY(launch_split_bf16(Delta, N, H, H, nullptr, at<uint16_t>(ws, pl.DT), s));
-        RNN_TRY(launch_split_bf16(h_all, N, H, H, nullptr, at<uint16_t>(ws, pl.HsT), s));
-        Bf3Args b{};
-        b.A = at<uint16_t>(ws, pl.DT); b.B = at<uint16_t>(ws, pl.HsT); b.C = Gr->dWh;
-        b.M = H; b.N = H; b.K = N; b.lda = Np; b.ldb = Np; b.ldc = H;
-        b.beta = beta; b.splitk_ws = at<float>(ws, pl.splitk3); b.prof_id = K_GEMM_DWH;
-        RNN_TRY(launch_gemm_bf16x3(b, s));
-    } else {
+    {
         GemmArgs g{};
         g.A = Delta; g.B = h_all; g.C = Gr->dWh;
         g.M = H; g.N = H; g.K = N;
         g.lda = H; g.ldb = H; g.ldc = H;
-        g.a_t = true; g.b_t = false; g.beta = beta; g.splitk_ws = splitk; g.prof_id = K_GEMM_DWH;
+        g.a_t = true; g.b_t = false; g.beta = beta; g.splitk_ws = splitk; g.parts = parts; g.prof_id = K_GEMM_DWH;
         RNN_TRY(launch_gemm(g, s));
     }
     // db = column sums of Delta
@@ -460,22 +388,12 @@ hipError_t run_backward_from_dz(const rnn_dims* d, const rnn_params* P, const vo
         // the logits buffer is dead by now and serves as scratch for per-range partial rows
         RNN_TRY(launch_dwx_tokens(static_cast<const int32_t*>(x), Delta, Gr->dWx, N, z.NVin, H, beta,
                                   Z, (size_t)N * O, N > 32 ? at<int32_t>(ws, pl.seen) : nullptr, s));
-    } else if (bf3) {
-        // dWx = Delta^T X: Delta^T is in split form already (dWh), X is transposed into it now
-        const int Np = bf3_pad(N);
-        RNN_TRY(launch_split_bf16(static_cast<const float*>(x), N, z.NVin, z.NVin, nullptr,
-                                  at<uint16_t>(ws, pl.XS), s));
-        Bf3Args b{};
-        b.A = at<uint16_t>(ws, pl.DT); b.B = at<uint16_t>(ws, pl.XS); b.C = Gr->dWx;
-        b.M = H; b.N = z.NVin; b.K = N; b.lda = Np; b.ldb = Np; b.ldc = z.NVin;
-        b.beta = beta; b.splitk_ws = at<float>(ws, pl.splitk3); b.prof_id = K_GEMM_DWX;
-        RNN_TRY(launch_gemm_bf16x3(b, s));
     } else {
         GemmArgs g{};
         g.A = Delta; g.B = static_cast<const float*>(x); g.C = Gr->dWx;
         g.M = H; g.N = z.NVin; g.K = N;
         g.lda = H; g.ldb = z.NVin; g.ldc = z.NVin;
-        g.a_t = true; g.b_t = false; g.beta = beta; g.splitk_ws = splitk; g.prof_id = K_GEMM_DWX;
+        g.a_t = true; g.b_t = false; g.beta = beta; g.splitk_ws = splitk; g.parts = parts; g.prof_id = K_GEMM_DWX;
         RNN_TRY(launch_gemm(g, s));
     }
     return hipSuccess;
@@ -514,28 +432,18 @@ hipError_t run_bptt(const rnn_dims* d, const rnn_params* P, const void* x, const
         return launch_rec_bwd_with_strips(r, v.bwd, k, s);
     }
 
-    const bool bf3 = (d->flags & RNN_FLAG_BF16X3_OUTPUT) != 0;
-    if (bf3) {
-        // logits -> d loss / d logits straight into split form (no float32 copy: nothing reads one) and dc
-        int used = 0;
-        RNN_TRY(launch_dz_split(Z, at<float>(ws, pl.lse), z.ce ? static_cast<const int32_t*>(targets) : nullptr,
-                                z.ce ? nullptr : static_cast<const float*>(targets), part, N, O, d->loss_kind,
-                                at<uint16_t>(ws, pl.dZS), at<uint16_t>(ws, pl.dZT), &used, s));
-        RNN_TRY(launch_colsum_finish(part, Gr->dc, used, O, beta, s));
-        return run_backward_from_dz(d, P, x, h_all, dh_last, Gr, dh0, ws, pl, true, s);
-    }
     // logits -> d loss / d logits (in place) and dc
     RNN_TRY(launch_dz(Z, at<float>(ws, pl.lse), z.ce ? static_cast<const int32_t*>(targets) : nullptr,
                       z.ce ? nullptr : static_cast<const float*>(targets), part, N, O,
                       d->loss_kind, s));
     RNN_TRY(launch_colsum_finish(part, Gr->dc, chunks, O, beta, s));
-    return run_backward_from_dz(d, P, x, h_all, dh_last, Gr, dh0, ws, pl, false, s);
+    return run_backward_from_dz(d, P, x, h_all, dh_last, Gr, dh0, ws, pl, s);
 }
 
 // Extra regions of the Gauss-Newton-vector product behind the ordinary plan.
 struct GnPlan {
     Plan base;
-    size_t logits, Rh, hrev, splitk_c, RhS, gVT, total;
+    size_t logits, Rh, hrev, splitk_c, total;
 };
 
 GnPlan make_gn_plan(const rnn_dims* d) {
@@ -549,9 +457,6 @@ GnPlan make_gn_plan(const rnn_dims* d) {
     p.Rh = take(N * H * 4);
     p.hrev = take((N + B) * H * 4);
     p.splitk_c = take(gemm_splitk_floats((int)N, (int)H, (int)H) * 4);   // Hprev gWh^T
-    const bool bf3 = (d->flags & RNN_FLAG_BF16X3_OUTPUT) != 0;                // split forms of R h and gamma.V^T
-    p.RhS = take(bf3 ? N * (size_t)bf3_pad(s.H) * 4 : 0);
-    p.gVT = take(bf3 ? O * (size_t)bf3_pad(s.H) * 4 : 0);
     p.total = off;
     return p;
 }
@@ -583,27 +488,12 @@ hipError_t run_gauss_newton(const rnn_dims* d, const rnn_params* P, const rnn_pa
     const float* Hs = h_all + BH;
     const bool ce_metric = metric == RNN_GN_METRIC_LOSS && z.ce;
 
-    const bool bf3 = (d->flags & RNN_FLAG_BF16X3_OUTPUT) != 0;
-    const int Hp = bf3_pad(H);
-    auto big = [&](const uint16_t* A, const uint16_t* B, float* dst, const float* bias, int acc, int prof) {
-        Bf3Args b{};   // [N,O] = A[N,H] B[O,H]^T (+ bias), the shape of all three forward-side products
-        b.A = A; b.B = B; b.C = dst;
-        b.M = N; b.N = O; b.K = H; b.lda = Hp; b.ldb = Hp; b.ldc = O;
-        b.bias_n = bias; b.beta = acc; b.splitk_ws = at<float>(ws, pl.splitk3); b.prof_id = prof;
-        return launch_gemm_bf16x3(b, s);
-    };
-    if (bf3) {   // operands of the large products in split form
-        RNN_TRY(launch_split_bf16(Hs, N, H, H, at<uint16_t>(ws, pl.HsS), at<uint16_t>(ws, pl.HsT), s));
-        RNN_TRY(launch_split_bf16(P->V, H, O, O, at<uint16_t>(ws, pl.VS), at<uint16_t>(ws, pl.VT), s));
-        RNN_TRY(launch_split_bf16(Ga->V, H, O, O, nullptr, at<uint16_t>(ws, gp.gVT), s));
-    }
-    if (ce_metric && bf3) {
-        RNN_TRY(big(at<uint16_t>(ws, pl.HsS), at<uint16_t>(ws, pl.VT), Zl, P->c, 0, K_GEMM_LOGITS));
-    } else if (ce_metric) {   // logits of the current parameters, for the softmax in the metric
+    const int parts = output_parts(d);
+    if (ce_metric) {   // logits of the current parameters, for the softmax in the metric
         GemmArgs g{};
         g.A = Hs; g.B = P->V; g.C = Zl;
         g.M = N; g.N = O; g.K = H; g.lda = H; g.ldb = O; g.ldc = O;
-        g.a_t = false; g.b_t = false; g.bias_n = P->c; g.beta = 0; g.prof_id = K_GEMM_LOGITS;
+        g.a_t = false; g.b_t = false; g.bias_n = P->c; g.beta = 0; g.parts = parts; g.prof_id = K_GEMM_LOGITS;
         g.splitk_ws = splitk;
         RNN_TRY(launch_gemm(g, s));
     }
@@ -630,15 +520,11 @@ hipError_t run_gauss_newton(const rnn_dims* d, const rnn_params* P, const rnn_pa
     RNN_TRY(launch_transpose(P->Wh, WhT, H, H, s));
     RNN_TRY(run_reverse_loop(d, WhT, P->Wh, nullptr, Crev, hrev, nullptr, Rhrev, nullptr, ws, pl, s));
     RNN_TRY(launch_reverse_rows(Rhrev, Rh, z.T, (int)BH, s));
-    if (bf3) {   // R z = Rh V + gc + Hs gV
-        RNN_TRY(launch_split_bf16(Rh, N, H, H, at<uint16_t>(ws, gp.RhS), nullptr, s));
-        RNN_TRY(big(at<uint16_t>(ws, gp.RhS), at<uint16_t>(ws, pl.VT), U, Ga->c, 0, K_GEMM_LOGITS));
-        RNN_TRY(big(at<uint16_t>(ws, pl.HsS), at<uint16_t>(ws, gp.gVT), U, nullptr, 1, K_GEMM_LOGITS));
-    } else {   // R z = Rh V + gc
+    {   // R z = Rh V + gc
         GemmArgs g{};
         g.A = Rh; g.B = P->V; g.C = U;
         g.M = N; g.N = O; g.K = H; g.lda = H; g.ldb = O; g.ldc = O;
-        g.a_t = false; g.b_t = false; g.bias_n = Ga->c; g.beta = 0; g.prof_id = K_GEMM_LOGITS;
+        g.a_t = false; g.b_t = false; g.bias_n = Ga->c; g.beta = 0; g.parts = parts; g.prof_id = K_GEMM_LOGITS;
         g.splitk_ws = splitk;
         RNN_TRY(launch_gemm(g, s));
         // ... + Hs gV
@@ -654,8 +540,7 @@ hipError_t run_gauss_newton(const rnn_dims* d, const rnn_params* P, const rnn_pa
     // Gc = column sums of u, then the rest of backpropagation
     RNN_TRY(launch_colsum_partial(U, at<float>(ws, pl.part), N, O, s));
     RNN_TRY(launch_colsum_finish(at<float>(ws, pl.part), Out->dc, colsum_chunks(N), O, beta, s));
-    if (bf3) RNN_TRY(launch_split_bf16(U, N, O, O, at<uint16_t>(ws, pl.dZS), at<uint16_t>(ws, pl.dZT), s));
-    return run_backward_from_dz(d, P, x, h_all, nullptr, Out, nullptr, ws, pl, bf3, s);
+    return run_backward_from_dz(d, P, x, h_all, nullptr, Out, nullptr, ws, pl, s);
 }
 
 bool params_ok(const rnn_params* P) {

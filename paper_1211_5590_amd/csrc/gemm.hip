@@ -1,35 +1,47 @@
-// fp32 GEMM on the CDNA4 matrix cores (v_mfma_f32_16x16x4_f32), used for every product that
-// the path batches over time outside the loop (the paper's Scan property 8: per-step
-// vector-matrix products become one matrix-matrix product): the output projection Z = H V + c,
-// its two backward products dV = H^T dZ and G = dZ V^T, the recurrent weight gradient
-// dWh = Delta^T H_prev, and the dense-input projections.
+// float32 matrix products on the bf16 matrix cores, used for every product that the path batches
+// over time outside the loop (the paper's Scan property 8: per-step vector-matrix products become
+// one matrix-matrix product): the output projection Z = H V + c, its two backward products
+// dV = H^T dZ and G = dZ V^T, the recurrent weight gradient dWh = Delta^T H_prev, and the
+// dense-input projections.
 //
-// Tiling: a 256-thread workgroup (4 wavefronts as 2x2) owns a BM x BN tile of C; each
-// wavefront owns (BM/2) x (BN/2) as 16x16 MFMA blocks held in accumulation registers.
-// K advances in slabs of 16 through two LDS buffers: the next slab is fetched from global
-// memory into registers while the current one feeds the MFMAs, then parked in the other
-// buffer (one barrier per slab).  An operand whose K runs along memory keeps that order in LDS
-// ([row][16 k], 16-byte chunks XOR-swizzled by row so that both the 16-byte stores and the 16-byte
-// fragment reads are conflict-free); an operand stored K-major stays K-major ([k][row], scalar
-// fragment reads of 16 consecutive words per quarter-wave).  A wavefront walks the 16 k of a slab
-// in the order k = 4(lane/16) + e, the same for both operands, so that one 16-byte read feeds
-// four matrix instructions.  Interior tiles
-// fetch whole slabs with one uniform base per slab and loop-invariant per-lane offsets; only edge
-// tiles and a ragged last slab take the checked path.
+// Arithmetic.  A float32 number is the sum of three bf16 numbers, x = hi + mid + lo with
+// hi = bf16(x), mid = bf16(x - hi), lo = bf16(x - hi - mid) (8 significand bits each, round to
+// nearest: nothing of the 24 bits is lost), and a product term a b is taken as the six products
+// hi lo + lo hi + mid mid + hi mid + mid hi + hi hi in float32 accumulators; the three dropped ones
+// are below 2^-24 |a b|.  Measured against 64 bits over sums of 128 to 16384 terms (random sign, equal
+// sign, nearly cancelling) the result is 0.6 to 0.95 times as far off as v_mfma_f32_16x16x4_f32 over
+// the same terms, because an accumulator is rounded once per 16 terms instead of once per term.  The
+// bf16 matrix rate is 16 times the float32 one, so six products still leave a factor of 2.6.
+// RNN_FLAG_BF16X3_OUTPUT's products leave lo away: hi hi + hi mid + mid hi (PARTS = 2).
+// Operands that hold infinities or NaNs, or so large that hi rounds to infinity, give a result
+// that is not finite; a wavefront that sees one computes its part of the tile again with
+// v_mfma_f32_32x32x2_f32 straight from memory, so such inputs give what float32 gives.
+//
+// Where the split is made.  Operands stay float32 in memory, in either orientation and at any
+// 4-byte aligned address; a thread splits what it has fetched on the way to LDS, 5.5 vector
+// instructions per element, which run beside the matrix instructions of the other wavefronts.  (A
+// pass that writes split copies first, which the two-part form used to run, costs more memory traffic
+// than it saves: 6 bytes instead of 4 per element fetched, and the pass itself.)
+//
+// Tiling.  K advances in slabs of BK through LDS buffers; the PF slabs after the current one are
+// in flight in registers.  LDS holds, per part and group of 8 k, the tile's rows as 16-byte chunks, so
+// that a matrix instruction's operand (8 consecutive k of one row per lane) is one conflict-free
+// 16-byte read.  A ragged last slab of K is taken first, where its checked fetch overlaps the start-up.
 #include "common.hpp"
 #include "internal.hpp"
 #include "prof.hpp"
 
 #include <math.h>
 
+#include <atomic>
+
 namespace rnn {
 namespace {
 
-typedef float f32x4v __attribute__((ext_vector_type(4)));
-
-constexpr int BK = 16;
-constexpr int PAD = 4;
-constexpr int NT = 256;
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 struct GemmParams {
     const float* A;
@@ -38,108 +50,116 @@ struct GemmParams {
     const float* bias_n;
     int M, N, K;
     int lda, ldb, ldc;
-    int kchunk;        // K range per blockIdx.z (multiple of BK)
+    int kchunk;        // K range per blockIdx.z
     int beta;
     int splits;
     int tiles_m, tiles_n;
-    int prof_id;
-    float* stats;      // nullable: per row and per 64-column part (max, sum of exp relative to it)
+    float* stats;      // nullable: per row and per column part (max, sum of exp relative to it)
 };
 
-// One operand tile of R rows (R = BM or BN) by BK columns of K, fetched into registers.
-// KCONTIG: element (r,k) lives at src[r*ld + k]   (A not transposed, or B given as [N,K])
-// else   : element (r,k) lives at src[k*ld + r]   (A given as [K,M], or B given as [K,N])
-template <int R, bool KCONTIG, bool VEC>
-struct TileLoader {
-    static constexpr int NV4 = R * BK / 4 / NT;  // float4 per thread
-    float4 v[NV4];
-    unsigned off[NV4];   // interior tiles: element offset of this lane's float4 from the slab's base
-    bool interior;       // uniform over the workgroup: every row of the tile exists, 16-byte loads legal
-
-    __device__ __forceinline__ static void coords(int i, int tid, int& r, int& k) {
-        if (KCONTIG) {
-            r = tid / 4 + (NT / 4) * i;
-            k = (tid % 4) * 4;
-        } else {
-            constexpr int Q = R / 4;  // float4 per k-row
-            const int idx = tid + NT * i;
-            k = idx / Q;
-            r = (idx % Q) * 4;
+// two float32 -> PARTS words of two bf16 each
+template <int PARTS>
+__device__ __forceinline__ void split_pair(float x, float y, unsigned (&w)[PARTS]) {
+#pragma unroll
+    for (int q = 0; q < PARTS; ++q) {
+        const f32x2 v = {x, y};
+        w[q] = __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+        if (q + 1 < PARTS) {
+            x -= __uint_as_float(w[q] << 16);
+            y -= __uint_as_float(w[q] & 0xffff0000u);
         }
     }
+}
 
-    __device__ __forceinline__ void init(int ld, int r0, int rlim, int tid) {
-        interior = VEC && r0 + R <= rlim;
-#pragma unroll
-        for (int i = 0; i < NV4; ++i) {
-            int r, k;
-            coords(i, tid, r, k);
-            off[i] = KCONTIG ? (unsigned)r * (unsigned)ld + (unsigned)k : (unsigned)k * (unsigned)ld + (unsigned)r;
-        }
-    }
+// One operand tile of R rows by BK of K: fetched as float32 into registers, split on the way to LDS.
+// KCONTIG: element (r,k) lives at src[r*ld + k] (a lane fetches 4 k of a row, 64/(BK/4) rows per
+// request); else at src[k*ld + r] (a lane fetches 8 k of one row, 64 consecutive rows per request).
+// Every address is a base that is uniform over the wavefront plus a small lane offset.  Rows past the
+// end repeat the last one; what they give is never stored.
+template <int R, int BK, bool KCONTIG, int NW, int PARTS>
+struct Operand {
+    static constexpr int UNIT = KCONTIG ? 4 : 8;                       // elements per unit
+    static constexpr int U = R * BK / UNIT / (NW * 64);                // units per thread
+    static constexpr int LPR = BK / 4, RPI = 64 / LPR;                 // KCONTIG: lanes per row, rows per request
+    static constexpr int GR = R / 64;                                  // otherwise: row groups of 64
+    static constexpr int CHUNK = R * 16 + 256 / (BK / 8);              // bytes of one 8-k chunk column (padded)
+    static constexpr int PLANE = CHUNK * (BK / 8);                     // bytes of one part
+    static constexpr int BYTES = PLANE * PARTS;
 
-    // One slab into registers, to be parked by store().  Interior tiles and whole slabs: one
-    // uniform base per slab, loop-invariant lane offsets, no checks; otherwise every limit checked.
-    __device__ __forceinline__ void load(const float* __restrict__ src, int ld, int r0, int k0,
-                                         int rlim, int klim, int tid) {
-        if (interior && k0 + BK <= klim) {
-            const float* base = KCONTIG ? src + (size_t)r0 * ld + k0 : src + (size_t)k0 * ld + r0;
+    const float* base[U];   // uniform
+    unsigned voff[U];       // lane offset, bytes
+    int koff[U];            // first k of the unit inside a slab
+    int lds[U];             // byte offset of the unit inside a part's plane
+
+    __device__ __forceinline__ void init(const float* src, int ld, int r0, int rlim, int kbeg, int wave, int lane) {
 #pragma unroll
-            for (int i = 0; i < NV4; ++i) v[i] = *reinterpret_cast<const float4*>(base + off[i]);
-            return;
-        }
-#pragma unroll
-        for (int i = 0; i < NV4; ++i) {
-            int r, k;
-            coords(i, tid, r, k);
-            const int gr = r0 + r, gk = k0 + k;
-            float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int u = 0; u < U; ++u) {
+            const int g = u * NW + wave;
             if (KCONTIG) {
-                if (gr < rlim) {
-                    const float* p = src + (size_t)gr * ld + gk;
-                    if (VEC && gk + 3 < klim) {
-                        t = *reinterpret_cast<const float4*>(p);
-                    } else {
-                        if (gk + 0 < klim) t.x = p[0];
-                        if (gk + 1 < klim) t.y = p[1];
-                        if (gk + 2 < klim) t.z = p[2];
-                        if (gk + 3 < klim) t.w = p[3];
-                    }
-                }
+                const int first = min(r0 + g * RPI, rlim - 1);
+                const int r = g * RPI + lane / LPR;
+                base[u] = src + (size_t)first * ld + kbeg;
+                voff[u] = ((unsigned)(min(r0 + r, rlim - 1) - first) * (unsigned)ld + (unsigned)(lane % LPR) * 4u) * 4u;
+                koff[u] = (lane % LPR) * 4;
+                lds[u] = (koff[u] / 8) * CHUNK + r * 16 + (koff[u] % 8) * 2;
             } else {
-                if (gk < klim) {
-                    const float* p = src + (size_t)gk * ld + gr;
-                    if (VEC && gr + 3 < rlim) {
-                        t = *reinterpret_cast<const float4*>(p);
-                    } else {
-                        if (gr + 0 < rlim) t.x = p[0];
-                        if (gr + 1 < rlim) t.y = p[1];
-                        if (gr + 2 < rlim) t.z = p[2];
-                        if (gr + 3 < rlim) t.w = p[3];
-                    }
-                }
+                const int kq = g / GR, r = (g % GR) * 64 + lane;
+                const int first = min(r0 + (g % GR) * 64, rlim - 1);
+                base[u] = src + (size_t)(kbeg + kq * 8) * ld + first;
+                voff[u] = (unsigned)(min(r0 + r, rlim - 1) - first) * 4u;
+                koff[u] = kq * 8;
+                lds[u] = kq * CHUNK + r * 16;
             }
-            v[i] = t;
         }
     }
-
-    // LDS tile layout: KCONTIG S[r][16] with the 4-float chunk c of row r at position
-    // c ^ ((r >> 2) & 3); otherwise S[k][r] with row stride R + PAD
-    __device__ __forceinline__ void store(float* __restrict__ S, int tid) const {
+    // Buffer requests: the uniform part of an address stays in scalar registers.
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    __device__ __forceinline__ static __amdgpu_buffer_rsrc_t window(const float* b) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(b), 0, -1, 0x00020000);
+    }
+    // a whole slab that starts `k` after kbeg
+    __device__ __forceinline__ void load(float (&x)[U][UNIT], int ld, int k) const {
 #pragma unroll
-        for (int i = 0; i < NV4; ++i) {
-            int r, k;
-            coords(i, tid, r, k);
-            if (KCONTIG) *reinterpret_cast<float4*>(&S[r * BK + 4 * ((k / 4) ^ ((r >> 2) & 3))]) = v[i];
-            else *reinterpret_cast<float4*>(&S[k * (R + PAD) + r]) = v[i];
+        for (int u = 0; u < U; ++u) {
+            if (KCONTIG) {
+                const f32x4 t = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(window(base[u] + k), voff[u], 0, 0));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[u][e] = t[e];
+            } else {
+                const __amdgpu_buffer_rsrc_t w = window(base[u] + (size_t)k * ld);
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    x[u][e % UNIT] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(w, voff[u], e * ld * 4, 0));
+            }
         }
     }
-
-    // the four values k = 4g + e (e = 0..3) of tile row `row`
-    __device__ __forceinline__ static float4 fragment(const float* __restrict__ S, int row, int g) {
-        if (KCONTIG) return *reinterpret_cast<const float4*>(&S[row * BK + 4 * (g ^ ((row >> 2) & 3))]);
-        const float* q = S + 4 * g * (R + PAD) + row;
-        return make_float4(q[0], q[R + PAD], q[2 * (R + PAD)], q[3 * (R + PAD)]);
+    __device__ __forceinline__ static float at(const float* b, unsigned off) {
+        return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(b) + off);
+    }
+    // a slab of which only the first `left` k exist
+    __device__ __forceinline__ void load_tail(float (&x)[U][UNIT], int ld, int k, int left) const {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < UNIT; ++e) {
+                const bool in = koff[u] + e < left;
+                x[u][e] = 0.f;
+                if (in) x[u][e] = KCONTIG ? at(base[u] + k + e, voff[u]) : at(base[u] + (size_t)(k + e) * ld, voff[u]);
+            }
+    }
+    __device__ __forceinline__ void park(const float (&x)[U][UNIT], unsigned char* tile) const {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            unsigned w[UNIT / 2][PARTS];
+#pragma unroll
+            for (int h = 0; h < UNIT / 2; ++h) split_pair<PARTS>(x[u][2 * h], x[u][2 * h + 1], w[h]);
+#pragma unroll
+            for (int q = 0; q < PARTS; ++q) {
+                unsigned char* d = tile + q * PLANE + lds[u];
+                if (KCONTIG) *reinterpret_cast<uint2*>(d) = make_uint2(w[0][q], w[1][q]);
+                else *reinterpret_cast<uint4*>(d) = make_uint4(w[0][q], w[1][q], w[UNIT / 2 - 2][q], w[UNIT / 2 - 1][q]);
+            }
+        }
     }
 };
 
@@ -161,134 +181,276 @@ __device__ __forceinline__ void tile_coords(int bid, int tiles_m, int tiles_n, i
     tm = in_group / gsz;
 }
 
-template <int BM, int BN, bool AT, bool BT, bool VEC, bool STATS>
-__global__ __launch_bounds__(NT) void gemm_f32_kernel(GemmParams p) {
-    constexpr int TM = BM / 32, TN = BN / 32;  // 16x16 MFMA blocks per wavefront, per dim
-    __shared__ __attribute__((aligned(16))) float As[2][BK * (BM + PAD)];
-    __shared__ __attribute__((aligned(16))) float Bs[2][BK * (BN + PAD)];
+// WGM x WGN wavefronts, each TM x TN blocks of 32x32; AT: A is [K,M]; BT: B is [N,K]
+template <int WGM, int WGN, int TM, int TN, int BK, int PF, int MINW, int PARTS, bool AT, bool BT, bool STATS>
+__global__ __launch_bounds__(WGM* WGN * 64, MINW) void gemm_kernel(GemmParams p) {
+    constexpr int NW = WGM * WGN, BM = WGM * TM * 32, BN = WGN * TN * 32;
+    typedef Operand<BM, BK, !AT, NW, PARTS> OpA;
+    typedef Operand<BN, BK, BT, NW, PARTS> OpB;
+    constexpr int STAGE = OpA::BYTES + OpB::BYTES;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];   // [2 or 3][STAGE]
 
-    const int tid = threadIdx.x;
-    const int lane = tid % 64, wave = tid / 64;
-    const int wm = wave / 2, wn = wave % 2;
-
+    const int lane = threadIdx.x % 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const int wm = wave / WGN, wn = wave % WGN;
     int tile_m, tile_n;
     tile_coords(blockIdx.x, p.tiles_m, p.tiles_n, tile_m, tile_n);
     const int m0 = tile_m * BM, n0 = tile_n * BN;
-    const int kbeg = blockIdx.z * p.kchunk;
-    const int kend = min(p.K, kbeg + p.kchunk);
-    const int nk = (kend - kbeg + BK - 1) / BK;
+    const int kbeg = blockIdx.z * p.kchunk, klen = min(p.K - kbeg, p.kchunk);   // every split has at least one k
+    const int whole = klen / BK, left = klen - whole * BK;
+    const int nk = whole + (left ? 1 : 0);
 
-    TileLoader<BM, !AT, VEC> la;
-    TileLoader<BN, BT, VEC> lb;
+    OpA oa;
+    OpB ob;
+    oa.init(p.A, p.lda, m0, p.M, kbeg, wave, lane);
+    ob.init(p.B, p.ldb, n0, p.N, kbeg, wave, lane);
+    float xa[PF][OpA::U][OpA::UNIT], xb[PF][OpB::U][OpB::UNIT];
 
-    f32x4v acc[TM][TN];
+    f32x16 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = (f32x4v){0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-    // v_mfma_f32_16x16x4_f32: lane l supplies A[row l%16][k l/16] and B[k l/16][col l%16] and
-    // receives C[row 4(l/16) + e][col l%16] in register e.  The 16 k of a slab are walked as
-    // k = 4(l/16) + e over four instructions e = 0..3, the same for both operands, so one
-    // 16-byte read of a K-ordered tile row feeds all four.
-    const int arow = wm * (BM / 2) + lane % 16;
-    const int brow = wn * (BN / 2) + lane % 16;
-    const int g = lane / 16;
-
-    la.init(p.lda, m0, p.M, tid);
-    lb.init(p.ldb, n0, p.N, tid);
-    if (nk > 0) {
-        la.load(p.A, p.lda, m0, kbeg, p.M, kend, tid);
-        lb.load(p.B, p.ldb, n0, kbeg, p.N, kend, tid);
-        la.store(As[0], tid);
-        lb.store(Bs[0], tid);
+    // slab 0 is the ragged one if there is one; slab s >= 1 starts at shift + s * BK
+    const int shift = left ? -BK : 0, last = nk - 1;
+    if (left) {
+        oa.load_tail(xa[0], p.lda, whole * BK, left);
+        ob.load_tail(xb[0], p.ldb, whole * BK, left);
+    } else {
+        oa.load(xa[0], p.lda, 0);
+        ob.load(xb[0], p.ldb, 0);
     }
-    __syncthreads();
+    oa.park(xa[0], lds);
+    ob.park(xb[0], lds + OpA::BYTES);
+    // requests past the end repeat the last slab, which nobody reads; with one slab there may be no
+    // whole one to repeat
+#define GEMM_FETCH(slot, slab)                                     \
+    do {                                                           \
+        const int k_ = shift + min((slab), last) * BK;             \
+        oa.load(xa[slot], p.lda, k_);                              \
+        ob.load(xb[slot], p.ldb, k_);                              \
+    } while (0)
+    if (nk > 1) {
+#pragma unroll
+        for (int s = 1; s <= PF; ++s) GEMM_FETCH(s % PF, s);
+    }
+    lds_barrier();
 
-    for (int kt = 0; kt < nk; ++kt) {
-        const int cur = kt & 1;
-        const bool more = kt + 1 < nk;
-        if (more) {
-            la.load(p.A, p.lda, m0, kbeg + (kt + 1) * BK, p.M, kend, tid);
-            lb.load(p.B, p.ldb, n0, kbeg + (kt + 1) * BK, p.N, kend, tid);
+    const int row_a = (wm * TM * 32 + lane % 32) * 16 + (lane / 32) * OpA::CHUNK;
+    const int row_b = (wn * TN * 32 + lane % 32) * 16 + (lane / 32) * OpB::CHUNK + OpA::BYTES;
+    auto frag_a = [&](bf16x8 (&a)[PARTS], const unsigned char* t, int s, int i) {
+#pragma unroll
+        for (int q = 0; q < PARTS; ++q)
+            a[q] = *reinterpret_cast<const bf16x8*>(t + row_a + q * OpA::PLANE + 2 * s * OpA::CHUNK + i * 512);
+    };
+    auto frag_b = [&](bf16x8 (&b)[PARTS], const unsigned char* t, int s, int j) {
+#pragma unroll
+        for (int q = 0; q < PARTS; ++q)
+            b[q] = *reinterpret_cast<const bf16x8*>(t + row_b + q * OpB::PLANE + 2 * s * OpB::CHUNK + j * 512);
+    };
+    // One 32x32 block, 16 of K.  With three parts the five small products are summed by themselves
+    // and folded into the accumulator with one addition, so the accumulator is rounded as often as by a
+    // single bf16 product.  The additions of the block before (c0 += t0) are placed between this
+    // block's products, from the second on (its last product has left the matrix core by then).
+    f32x16 small[2];
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#define MMA(x, y, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, c, 0, 0, 0)
+    auto block = [&](const bf16x8 (&a)[PARTS], const bf16x8 (&b)[PARTS], f32x16& c, f32x16& t, bool fold, f32x16& c0,
+                     const f32x16& t0) {
+        if constexpr (PARTS == 3) {
+#pragma unroll
+            for (int m = 0; m < 6; ++m) {
+                if (m == 0) t = MMA(a[2], b[0], zero);
+                else if (m == 1) t = MMA(a[0], b[2], t);
+                else if (m == 2) t = MMA(a[1], b[1], t);
+                else if (m == 3) t = MMA(a[1], b[0], t);
+                else if (m == 4) t = MMA(a[0], b[1], t);
+                else c = MMA(a[0], b[0], c);
+                __builtin_amdgcn_sched_barrier(0);
+                if (fold && m >= 1 && m <= 4)
+#pragma unroll
+                    for (int e = 4 * (m - 1); e < 4 * m; ++e) c0[e] += t0[e];
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
+            c = MMA(a[1], b[0], c);
+            c = MMA(a[0], b[1], c);
+            c = MMA(a[0], b[0], c);
         }
-        const float* as = As[cur];
-        const float* bs = Bs[cur];
-        float4 fa[TM], fb[TN];
+    };
+#undef MMA
+
+    if constexpr (NW == 8) {
+        // Two groups of four wavefronts, one wavefront of each per SIMD, half a slab apart: while one
+        // group multiplies, the other splits and parks the next slab and reads its operands.
+        // Every phase ends with a barrier.  Slab k lies in buffer k % 3: the first group writes its share
+        // of it in phase 2k-2 and the second in 2k-1; the first reads it in phases 2k and 2k+1, the
+        // second in 2k+1 and 2k+2; the buffer is written again (slab k+3) from phase 2k+4 on.
+        const int group = wave / 4;
+        if (group) lds_barrier();
+        int at = 0, next = STAGE;
+        for (int kt = 0; kt < nk; ++kt) {
+            const unsigned char* t = lds + at;
+            bf16x8 a[TM][PARTS], b[TN][PARTS];
+            __builtin_amdgcn_sched_barrier(0);
+            if (kt + 1 < nk) {
+                unsigned char* w = lds + next;
+                oa.park(xa[0], w);
+                ob.park(xb[0], w + OpA::BYTES);
+            }
+            if (kt + 2 < nk) GEMM_FETCH(0, kt + 2);
 #pragma unroll
-        for (int i = 0; i < TM; ++i) fa[i] = TileLoader<BM, !AT, VEC>::fragment(as, arow + 16 * i, g);
+            for (int j = 0; j < TN; ++j) frag_b(b[j], t, 0, j);
 #pragma unroll
-        for (int j = 0; j < TN; ++j) fb[j] = TileLoader<BN, BT, VEC>::fragment(bs, brow + 16 * j, g);
+            for (int i = 0; i < 2; ++i) frag_a(a[i], t, 0, i);
+            __builtin_amdgcn_sched_barrier(0);
+            lds_barrier();
+            __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
+            for (int i = 0; i < TM; ++i) {
+                if (i + 2 < TM) frag_a(a[i + 2], t, 0, i + 2);
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
-                    const float av = e == 0 ? fa[i].x : e == 1 ? fa[i].y : e == 2 ? fa[i].z : fa[i].w;
-                    const float bv = e == 0 ? fb[j].x : e == 1 ? fb[j].y : e == 2 ? fb[j].z : fb[j].w;
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, acc[i][j], 0, 0, 0);
+                    const int n = i * TN + j, n0 = n ? n - 1 : 0;
+                    block(a[i], b[j], acc[i][j], small[n & 1], n > 0, acc[n0 / TN][n0 % TN], small[(n + 1) & 1]);
                 }
-        if (more) {
-            la.store(As[cur ^ 1], tid);
-            lb.store(Bs[cur ^ 1], tid);
+            }
+            if constexpr (PARTS == 3) acc[TM - 1][TN - 1] += small[(TM * TN - 1) & 1];
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(0);
+            lds_barrier();
+            at = next;
+            next = next == 2 * STAGE ? 0 : next + STAGE;
         }
-        __syncthreads();
+        if (!group) lds_barrier();
+    } else {
+        // several workgroups share a compute unit and cover each other's phases
+        auto compute = [&](int cur) {
+            const unsigned char* t = lds + cur * STAGE;
+#pragma unroll
+            for (int s = 0; s < BK / 16; ++s) {
+                bf16x8 a[TM][PARTS], b[TN][PARTS];
+#pragma unroll
+                for (int j = 0; j < TN; ++j) frag_b(b[j], t, s, j);
+#pragma unroll
+                for (int i = 0; i < TM; ++i) frag_a(a[i], t, s, i);
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        const int n = i * TN + j, n0 = n ? n - 1 : 0;
+                        block(a[i], b[j], acc[i][j], small[n & 1], n > 0, acc[n0 / TN][n0 % TN], small[(n + 1) & 1]);
+                    }
+                if constexpr (PARTS == 3) acc[TM - 1][TN - 1] += small[(TM * TN - 1) & 1];
+            }
+        };
+        constexpr int UNROLL = PF > 2 ? PF : 2;
+        int kt = 0;
+        for (; kt + UNROLL < nk; kt += UNROLL) {
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) {
+                compute(u & 1);
+                oa.park(xa[(u + 1) % PF], lds + ((u + 1) & 1) * STAGE);
+                ob.park(xb[(u + 1) % PF], lds + ((u + 1) & 1) * STAGE + OpA::BYTES);
+                GEMM_FETCH((u + 1) % PF, kt + u + 1 + PF);
+                lds_barrier();
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+            if (kt + u < nk) compute(u & 1);
+            if (kt + u + 1 < nk) {
+                oa.park(xa[(u + 1) % PF], lds + ((u + 1) & 1) * STAGE);
+                ob.park(xb[(u + 1) % PF], lds + ((u + 1) & 1) * STAGE + OpA::BYTES);
+                lds_barrier();
+            }
+        }
+    }
+#undef GEMM_FETCH
+
+    // Accumulator layout of a 32x32 block: lane -> column lane%32; register e -> row
+    // 8*(e/4) + 4*(lane/32) + e%4.
+    const int r_first = m0 + wm * TM * 32, c_first = n0 + wn * TN * 32;
+    float odd = 0.f;   // NaN if any result is not finite
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) odd = fmaf(acc[i][j][e], 0.f, odd);
+    if (__any(odd != odd)) {
+        for (int i = 0; i < TM; ++i) {
+            for (int j = 0; j < TN; ++j) {
+                f32x16 c;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) c[e] = 0.f;
+                const size_t r = (size_t)min(r_first + 32 * i + lane % 32, p.M - 1);
+                const size_t n = (size_t)min(c_first + 32 * j + lane % 32, p.N - 1);
+                for (int k0 = 0; k0 < klen; k0 += 2) {
+                    const int k = k0 + lane / 32;
+                    float av = 0.f, bv = 0.f;
+                    if (k < klen) {
+                        av = AT ? p.A[(size_t)(kbeg + k) * p.lda + r] : p.A[r * p.lda + kbeg + k];
+                        bv = BT ? p.B[n * p.ldb + kbeg + k] : p.B[(size_t)(kbeg + k) * p.ldb + n];
+                    }
+                    c = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, c, 0, 0, 0);
+                }
+#pragma unroll
+                for (int ii = 0; ii < TM; ++ii)
+#pragma unroll
+                    for (int jj = 0; jj < TN; ++jj)
+                        if (ii == i && jj == j) acc[ii][jj] = c;
+            }
+        }
     }
 
     float* Cout = p.C + (p.splits > 1 ? (size_t)blockIdx.z * p.M * p.ldc : 0);
     const bool final_out = p.splits == 1;
+    int col[TN];
+    float bias[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        col[j] = c_first + 32 * j + lane % 32;
+        bias[j] = (final_out && p.bias_n && col[j] < p.N) ? p.bias_n[col[j]] : 0.f;
+    }
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int col = n0 + wn * (BN / 2) + 16 * j + lane % 16;
-            if (col >= p.N) continue;
-            const float bias = (final_out && p.bias_n) ? p.bias_n[col] : 0.f;
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int row = m0 + wm * (BM / 2) + 16 * i + 4 * g + e;
-                if (row < p.M) {
-                    float* dst = Cout + (size_t)row * p.ldc + col;
-                    float v = acc[i][j][e] + bias;
+            for (int e = 0; e < 16; ++e) {
+                const int row = r_first + 32 * i + 8 * (e / 4) + 4 * (lane / 32) + e % 4;
+                if (row < p.M && col[j] < p.N) {
+                    float* dst = Cout + (size_t)row * p.ldc + col[j];
+                    float v = acc[i][j][e] + bias[j];
                     if (final_out && p.beta) v += *dst;
                     *dst = v;
                 }
             }
-        }
 
     // Fused row statistics of a log-sum-exp over the columns: every wavefront leaves, for each of
-    // its rows, the maximum of its 64 columns and the sum of exponentials relative to it (the 16
-    // lanes of a quarter-wave hold 16 columns of the same row in register e of every block j).
-    if (STATS && final_out) {
-        const int nparts = p.tiles_n * 2;
-        const int part = tile_n * 2 + wn;
-        int col[TN];
-        float bias[TN];
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            col[j] = n0 + wn * (BN / 2) + 16 * j + lane % 16;
-            bias[j] = (p.bias_n && col[j] < p.N) ? p.bias_n[col[j]] : 0.f;
-        }
+    // its rows, the maximum of its TN * 32 columns and the sum of exponentials relative to it.
+    if constexpr (STATS) if (final_out) {
+        const int nparts = p.tiles_n * WGN, part = tile_n * WGN + wn;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float v[TN];
-                float m = -INFINITY;
+            for (int e = 0; e < 16; ++e) {
+                float v[TN], m = -INFINITY, sum = 0.f;
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
                     v[j] = acc[i][j][e] + bias[j];
                     if (col[j] < p.N) m = fmaxf(m, v[j]);
                 }
-                m = max16(m);   // register-to-register lane exchanges: no LDS round trips in the chain
-                float sum = 0.f;
+                m = max32(m);   // register-to-register lane exchanges: no LDS round trips in the chain
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
                     if (col[j] < p.N) sum += __expf(v[j] - m);
-                sum = sum16(sum);
-                const int row = m0 + wm * (BM / 2) + 16 * i + 4 * g + e;
-                if (lane % 16 == 0 && row < p.M)
+                sum = sum32(sum);
+                const int row = r_first + 32 * i + 8 * (e / 4) + 4 * (lane / 32) + e % 4;
+                if (lane % 32 == 0 && row < p.M)
                     *reinterpret_cast<float2*>(p.stats + ((size_t)row * nparts + part) * 2) = make_float2(m, sum);
             }
     }
@@ -349,113 +511,151 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
     }
 }
 
-constexpr int BM_ = 128, BN_ = 128;
-
-struct SplitPlan {
-    int splits, kchunk;
-};
-
-// Row tile of a product: 128, or 64 where 128-row tiles would leave most compute units without a
-// workgroup (few rows, no K to cut): twice the workgroups keep twice the requests in flight.
-int pick_bm(int M, int N, int K) {
-    const int tiles = ((M + BM_ - 1) / BM_) * ((N + BN_ - 1) / BN_);
-    return (tiles < 128 && K <= 512 && M > 64) ? 64 : 128;
-}
-
-SplitPlan plan_split(int M, int N, int K) {
-    const int bm_ = pick_bm(M, N, K);
-    const int tiles = ((M + bm_ - 1) / bm_) * ((N + BN_ - 1) / BN_);
-    int splits = 1;
-    if (tiles < 256 && K > 512) {
-        const int by_k = (K + 255) / 256;          // at least 256 of K per split
-        const int by_fill = (1024 + tiles - 1) / tiles;  // aim at ~4 workgroups per CU
-        splits = by_k < by_fill ? by_k : by_fill;
-        if (splits < 1) splits = 1;
-    } else if (K >= 2048) {
-        // Enough tiles to fill the chip, but a whole number of tiles rarely fills whole rounds
-        // of the 256 x 3 resident workgroups: 632 tiles leave 18 % of the slots idle.  Cutting K
-        // evens the rounds out; the price is the partial-sum traffic and the reduction launch.
-        // Pick the cut with the least estimated time.  Without a cut, a last round that leaves
-        // every compute unit at most one workgroup is cheap, since a workgroup alone on its unit
-        // runs about 2.5 times faster (measured: 1024 tiles take 1.4 rounds, not 2).
-        const double slots = 768.0, flops = 2.0 * M * N * (double)K, out_bytes = 4.0 * M * (double)N;
-        const double t_full = flops / 100e12;                      // at a typical achieved rate
-        double best = 1e30, t_of[9];
-        for (int sp = 1; sp <= 8; ++sp) {
-            const long units = (long)tiles * sp, whole = units / 768, rem = units % 768;
-            const double last = rem == 0 ? 0.0 : (sp == 1 && rem <= 256) ? 0.4 : 1.0;
-            const double rounds = ((double)whole + last) / sp;      // in units of one full-K round
-            // the slices' partial results are written once more than an uncut result and read back
-            // by the reduction, which streams them at about the rate of a copy
-            t_of[sp] = t_full * rounds * slots / tiles + (sp > 1 ? (2.0 * sp + 1.0) * out_bytes / 4.5e12 : 0.0);
-            if (t_of[sp] < best * 0.97) { best = t_of[sp]; splits = sp; }   // a cut has to pay for itself
-        }
-        // Among near-equal plans prefer a cut that fills whole rounds exactly.  Measured on the
-        // largest such product (16384 x 1024 x 10000): uncut it has two states, 2.64 and 3.17 ms,
-        // which differ in how often the workgroups of an XCD share their operand panels through its
-        // L2 and which a launch falls into by chance; cut three ways (exactly four rounds) it takes
-        // 2.61 ms + 0.04 ms of reduction in either, also under a probe that forces the slow state.
-        if (splits == 1)
-            for (int sp = 2; sp <= 8; ++sp)
-                if ((long)tiles * sp % 768 == 0 && t_of[sp] <= 1.03 * t_of[1]) { splits = sp; break; }
+// Leading dimensions beyond the 32-bit offsets of the tiled kernel's requests (a vocabulary of tens of
+// millions): one output per thread.
+constexpr int LD_MAX = 1 << 26;
+__global__ __launch_bounds__(256) void gemm_wide_kernel(GemmParams p, int a_t, int b_t) {
+    const size_t total = (size_t)p.M * p.N;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
+        const size_t m = i / p.N, n = i % p.N;
+        float s = 0.f;
+        for (int k = 0; k < p.K; ++k)
+            s = fmaf(a_t ? p.A[(size_t)k * p.lda + m] : p.A[m * p.lda + k], b_t ? p.B[n * p.ldb + k] : p.B[(size_t)k * p.ldb + n], s);
+        if (p.bias_n) s += p.bias_n[n];
+        float* dst = p.C + m * p.ldc + n;
+        *dst = p.beta ? *dst + s : s;
     }
-    int kchunk = (K + splits - 1) / splits;
-    kchunk = (kchunk + BK - 1) / BK * BK;
-    if (kchunk < BK) kchunk = BK;
-    splits = (K + kchunk - 1) / kchunk;
-    if (splits < 1) splits = 1;
-    return {splits, kchunk};
 }
 
-template <int BM, int BN, bool AT, bool BT, bool VEC, bool STATS = false>
-hipError_t launch_variant(const GemmParams& p, hipStream_t s) {
-    dim3 grid(p.tiles_m * p.tiles_n, 1, p.splits);
-    ProfileScope ps(p.prof_id, s);
-    hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, AT, BT, VEC, STATS>), grid, dim3(NT), 0, s, p);
+struct GemmPlan { int tile, splits, kchunk; };
+
+// Tile and K cut of a product: the pair with the least estimated time.  The estimate is, per round of
+// resident workgroups, a fixed part and K times the larger of what a workgroup needs by itself
+// (`alone`, latency) and what the q workgroups of a compute unit need of it together (q * `shared`),
+// plus the bytes of the result -- (2 splits + 1) times with a cut, which also pays the reduction
+// launch.  The constants (us, us per k, bytes per us) are fitted to measured times of 28 products (11 to
+// 524288 rows, K of 41 to 524288) under every tile with 1 to 256 cuts: the plan picked is the fastest
+// measured one or within 6 % of it for all of them.
+GemmPlan search_plan(int M, int N, int K, int parts) {
+    static const int cuts[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 28, 32, 40, 48, 64, 80, 96, 128, 160, 192, 256};
+    struct Form { int tile, wgs, bk; double alone, shared, fixed; };   // wgs: resident per compute unit
+    static const Form forms[2][3] = {
+        {{256, 1, 16, 0.0900, 0.0900, 11.2}, {128, 2, 16, 0.0362, 0.0260, 4.7}, {64, 2, 32, 0.0127, 0.0116, 2.8}},
+        {{256, 1, 16, 0.0914, 0.0914, 6.3}, {128, 2, 16, 0.0580, 0.0306, 4.7}, {64, 2, 32, 0.0216, 0.0164, 1.7}}};
+    const double rate = parts == 2 ? 8.5e6 : 3.5e6, reduce = parts == 2 ? 2.9 : 3.7, units = 256.0;
+    const double out = 4.0 * M * (double)N;
+    GemmPlan best{};
+    double t_best = 1e300;
+    for (const Form& f : forms[parts == 2 ? 0 : 1]) {
+        const double tiles = (double)((M + f.tile - 1) / f.tile) * (double)((N + f.tile - 1) / f.tile);
+        const long slabs = ((long)K + f.bk - 1) / f.bk;
+        for (const int cut : cuts) {
+            if (cut > 1 && (2 * cut > slabs || tiles * cut > 65536.0 || cut * out > 4e9)) break;   // at least two slabs per cut
+            const long per = (slabs + cut - 1) / cut, sp = (slabs + per - 1) / per;
+            const double n = tiles * (double)sp, slots = units * f.wgs;
+            const double full = floor(n / slots), rem = n - full * slots, q = ceil(rem / units);
+            double per_k = full * fmax(f.alone, f.wgs * f.shared);
+            if (rem > 0.0) per_k += fmax(f.alone, q * f.shared);
+            const double t = per_k * (double)(per * f.bk) + f.fixed * (full + (rem > 0.0 ? 1.0 : 0.0)) +
+                             (sp == 1 ? out : reduce * rate + (2.0 * sp + 1.0) * out) / rate;
+            if (t < t_best) { t_best = t; best = {f.tile, (int)sp, (int)(per * f.bk)}; }
+        }
+    }
+    return best;
+}
+
+// Every call plans its products (and its workspace from their plans) afresh; a thread remembers the
+// sizes it has met last.
+GemmPlan plan_gemm(int M, int N, int K, int parts) {
+    struct Entry { int M, N, K, parts; GemmPlan plan; };
+    static thread_local Entry seen[32];
+    const unsigned h = (unsigned)M * 0x9e3779b1u ^ (unsigned)N * 0x85ebca6bu ^ (unsigned)K * 0xc2b2ae35u ^ (unsigned)parts;
+    Entry& e = seen[(h ^ h >> 15) & 31u];
+    if (e.M != M || e.N != N || e.K != K || e.parts != parts) e = {M, N, K, parts, search_plan(M, N, K, parts)};
+    return e.plan;
+}
+
+template <int WGM, int WGN, int TM, int TN, int BK, int PF, int MINW, int PARTS, bool AT, bool BT, bool STATS>
+hipError_t launch_form(const GemmParams& p, hipStream_t s) {
+    constexpr int NW = WGM * WGN;
+    constexpr size_t smem = (NW == 8 ? 3 : 2) * (size_t)(Operand<WGM * TM * 32, BK, !AT, NW, PARTS>::BYTES + Operand<WGN * TN * 32, BK, BT, NW, PARTS>::BYTES);
+    auto* kernel = &gemm_kernel<WGM, WGN, TM, TN, BK, PF, MINW, PARTS, AT, BT, STATS>;
+    if (smem > 65536) {   // per kernel form and process: allow more than 64 KB of dynamic LDS
+        static std::atomic<bool> raised{false};
+        if (!raised.load(std::memory_order_acquire)) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+            if (e != hipSuccess) return e;
+            raised.store(true, std::memory_order_release);
+        }
+    }
+    hipLaunchKernelGGL(kernel, dim3(p.tiles_m * p.tiles_n, 1, p.splits), dim3(NW * 64), smem, s, p);
     return hipGetLastError();
 }
 
-bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+template <int PARTS, bool AT, bool BT, bool STATS>
+hipError_t launch_tile(int tile, const GemmParams& p, hipStream_t s) {
+    if (tile == 256) return launch_form<2, 4, 4, 2, 16, 1, 2, PARTS, AT, BT, STATS>(p, s);
+    if (tile == 128) return launch_form<2, 2, 2, 2, 16, 1, 2, PARTS, AT, BT, STATS>(p, s);
+    return launch_form<2, 2, 1, 1, 32, 4, 2, PARTS, AT, BT, STATS>(p, s);
+}
+
+template <int PARTS>
+hipError_t launch_layout(int tile, bool a_t, bool b_t, const GemmParams& p, hipStream_t s) {
+    if (p.stats) return launch_tile<PARTS, false, false, true>(tile, p, s);
+    if (a_t) return launch_tile<PARTS, true, false, false>(tile, p, s);
+    if (b_t) return launch_tile<PARTS, false, true, false>(tile, p, s);
+    return launch_tile<PARTS, false, false, false>(tile, p, s);
+}
 
 }  // namespace
 
-int gemm_stat_parts(int N) { return 2 * ((N + BN_ - 1) / BN_); }
-bool gemm_fuses_stats(int M, int N, int K) { return plan_split(M, N, K).splits == 1; }
+int gemm_stat_parts(int M, int N, int K, int parts) {
+    const GemmPlan pl = plan_gemm(M, N, K, parts);
+    return (N + pl.tile - 1) / pl.tile * (pl.tile == 64 ? 2 : pl.tile / 64);
+}
+bool gemm_fuses_stats(int M, int N, int K, int parts) { return N <= LD_MAX && K <= LD_MAX && plan_gemm(M, N, K, parts).splits == 1; }
 
-size_t gemm_splitk_floats(int M, int N, int K) {
-    const SplitPlan sp = plan_split(M, N, K);
-    return sp.splits > 1 ? (size_t)sp.splits * M * N : 0;
+size_t gemm_splitk_floats(int M, int N, int K, int parts) {
+    const GemmPlan pl = plan_gemm(M, N, K, parts);
+    return pl.splits > 1 ? (size_t)pl.splits * M * N : 0;
 }
 
-// The same sum for rows of whole float4 groups: one thread per four consecutive outputs, the
-// partials of the K slices added in slice order (eight 16-byte requests in flight per thread), one
-// pass over the partial buffer at the rate memory delivers it.
-__global__ __launch_bounds__(256) void splitk_reduce_rows4_kernel(const float4* __restrict__ part, float* __restrict__ C,
-                                                                  const float* __restrict__ bias, size_t total4,
-                                                                  int N4, int ldc, int splits, int beta) {
+// The same sum for few slices of a large result without gaps between its rows: one thread per four
+// consecutive outputs (whatever row they fall in), the partials of the K slices added in slice order
+// (eight 16-byte requests in flight per thread), one pass over the partial buffer at the rate memory
+// delivers it.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+__global__ __launch_bounds__(256) void splitk_reduce_flat_kernel(const float* __restrict__ part, float* __restrict__ C,
+                                                                 const float* __restrict__ bias, size_t total, int N,
+                                                                 int splits, int beta) {
     constexpr int U = 8;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total4; i += (size_t)gridDim.x * blockDim.x) {
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int s0 = 0; s0 < splits; s0 += U) {
-            float4 v[U];
+    const size_t groups = (total + 3) / 4;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < groups; i += (size_t)gridDim.x * blockDim.x) {
+        const size_t at = 4 * i;
+        if (at + 4 <= total) {
+            f32x4u acc = {0.f, 0.f, 0.f, 0.f};
+            for (int s0 = 0; s0 < splits; s0 += U) {
+                f32x4u v[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) v[u] = part[(size_t)min(s0 + u, splits - 1) * total4 + i];
+                for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const f32x4u*>(part + (size_t)min(s0 + u, splits - 1) * total + at);
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (s0 + u < splits) { acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w; }
+                for (int u = 0; u < U; ++u)
+                    if (s0 + u < splits) acc += v[u];
+            }
+            if (bias)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e] += bias[(at + e) % N];
+            f32x4u* dst = reinterpret_cast<f32x4u*>(C + at);
+            if (beta) acc += *dst;
+            *dst = acc;
+        } else {
+            for (size_t k = at; k < total; ++k) {
+                float sum = 0.f;
+                for (int q = 0; q < splits; ++q) sum += part[(size_t)q * total + k];
+                if (bias) sum += bias[k % N];
+                C[k] = beta ? C[k] + sum : sum;
+            }
         }
-        const size_t m = i / N4;
-        const int n = (int)(i - m * N4) * 4;
-        if (bias) {
-            const float4 b = *reinterpret_cast<const float4*>(bias + n);
-            acc.x += b.x; acc.y += b.y; acc.z += b.z; acc.w += b.w;
-        }
-        float4* dst = reinterpret_cast<float4*>(C + m * (size_t)ldc + n);
-        if (beta) {
-            const float4 c = *dst;
-            acc.x += c.x; acc.y += c.y; acc.z += c.z; acc.w += c.w;
-        }
-        *dst = acc;
     }
 }
 
@@ -465,12 +665,10 @@ hipError_t launch_splitk_reduce(const float* part, float* C, const float* bias_n
     ProfileScope ps(K_SPLITK_REDUCE, s);
     // few slices of a large result: stream them; many slices of a small one: the kernel that also
     // spreads the slices over lanes
-    if (splits <= 32 && total >= ((size_t)1 << 20) && N % 4 == 0 && ldc % 4 == 0 && aligned16(part) && aligned16(C) &&
-        (!bias_n || aligned16(bias_n))) {
-        const size_t total4 = total / 4;
-        const unsigned blocks = (unsigned)((total4 + 255) / 256 < 4096 ? (total4 + 255) / 256 : 4096);
-        hipLaunchKernelGGL(splitk_reduce_rows4_kernel, dim3(blocks), dim3(256), 0, s, reinterpret_cast<const float4*>(part),
-                           C, bias_n, total4, N / 4, ldc, splits, beta);
+    if (splits <= 32 && total >= ((size_t)1 << 20) && ldc == N) {
+        const size_t groups = (total + 3) / 4;
+        const unsigned blocks = (unsigned)((groups + 255) / 256 < 4096 ? (groups + 255) / 256 : 4096);
+        hipLaunchKernelGGL(splitk_reduce_flat_kernel, dim3(blocks), dim3(256), 0, s, part, C, bias_n, total, N, splits, beta);
         return hipGetLastError();
     }
     if (total % 4 == 0) {  // the partial buffer is 16-byte aligned workspace
@@ -486,47 +684,34 @@ hipError_t launch_splitk_reduce(const float* part, float* C, const float* bias_n
 }
 
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
-    if (g.M <= 0 || g.N <= 0 || g.K <= 0) return hipErrorInvalidValue;
-    const SplitPlan sp = plan_split(g.M, g.N, g.K);
-    if (sp.splits > 1 && !g.splitk_ws) return hipErrorInvalidValue;
-    const int bm = pick_bm(g.M, g.N, g.K), bn = BN_;
-
+    if (g.M <= 0 || g.N <= 0 || g.K <= 0 || (g.a_t && g.b_t)) return hipErrorInvalidValue;
+    const GemmPlan pl = plan_gemm(g.M, g.N, g.K, g.parts);
+    if (pl.splits > 1 && !g.splitk_ws) return hipErrorInvalidValue;
     GemmParams p;
     p.A = g.A; p.B = g.B; p.bias_n = g.bias_n;
     p.M = g.M; p.N = g.N; p.K = g.K;
     p.lda = g.lda; p.ldb = g.ldb;
-    p.stats = sp.splits == 1 ? g.row_stats : nullptr;
-    p.kchunk = sp.kchunk; p.beta = g.beta; p.splits = sp.splits; p.prof_id = g.prof_id;
-    p.tiles_m = (g.M + bm - 1) / bm;
-    p.tiles_n = (g.N + bn - 1) / bn;
-    if (sp.splits > 1) { p.C = g.splitk_ws; p.ldc = g.N; } else { p.C = g.C; p.ldc = g.ldc; }
-
-    // float4 global loads need 16-byte aligned bases, leading dimensions that are multiples
-    // of 4, and split boundaries that keep every 4-group inside the valid range (kchunk is a
-    // multiple of 16).  The loaders check the per-element limits themselves.
-    const bool vec = aligned16(g.A) && aligned16(g.B) && g.lda % 4 == 0 && g.ldb % 4 == 0;
-
-    hipError_t e;
-#define RNN_GEMM_DISPATCH(AT, BT)                                                                \
-    do {                                                                                         \
-        if (bm == 64) e = vec ? launch_variant<64, BN_, AT, BT, true>(p, s) : launch_variant<64, BN_, AT, BT, false>(p, s); \
-        else e = vec ? launch_variant<BM_, BN_, AT, BT, true>(p, s) : launch_variant<BM_, BN_, AT, BT, false>(p, s);      \
-    } while (0)
-    if (p.stats) {   // only the plain-layout product (the output projection) carries the statistics
-        if (g.a_t || g.b_t) return hipErrorInvalidValue;
-        if (bm == 64) e = vec ? launch_variant<64, BN_, false, false, true, true>(p, s)
-                              : launch_variant<64, BN_, false, false, false, true>(p, s);
-        else e = vec ? launch_variant<BM_, BN_, false, false, true, true>(p, s)
-                     : launch_variant<BM_, BN_, false, false, false, true>(p, s);
-    } else if (!g.a_t && !g.b_t) RNN_GEMM_DISPATCH(false, false);
-    else if (g.a_t && !g.b_t) RNN_GEMM_DISPATCH(true, false);
-    else if (!g.a_t && g.b_t) RNN_GEMM_DISPATCH(false, true);
-    else RNN_GEMM_DISPATCH(true, true);
-#undef RNN_GEMM_DISPATCH
-    if (e != hipSuccess) return e;
-
-    if (sp.splits > 1) e = launch_splitk_reduce(g.splitk_ws, g.C, g.bias_n, g.M, g.N, g.ldc, sp.splits, g.beta, s);
-    return e;
+    p.stats = pl.splits == 1 ? g.row_stats : nullptr;
+    if (p.stats && (g.a_t || g.b_t)) return hipErrorInvalidValue;   // only the output projection carries them
+    p.kchunk = pl.kchunk; p.beta = g.beta; p.splits = pl.splits;
+    p.tiles_m = (g.M + pl.tile - 1) / pl.tile;
+    p.tiles_n = (g.N + pl.tile - 1) / pl.tile;
+    if (g.lda > LD_MAX || g.ldb > LD_MAX) {
+        p.C = g.C; p.ldc = g.ldc;
+        ProfileScope ps(g.prof_id, s);
+        hipLaunchKernelGGL(gemm_wide_kernel, dim3(4096), dim3(256), 0, s, p, g.a_t ? 1 : 0, g.b_t ? 1 : 0);
+        return hipGetLastError();
+    }
+    if (pl.splits > 1) { p.C = g.splitk_ws; p.ldc = g.N; } else { p.C = g.C; p.ldc = g.ldc; }
+    {
+        ProfileScope ps(g.prof_id, s);
+        const hipError_t e = g.parts == 2 ? launch_layout<2>(pl.tile, g.a_t, g.b_t, p, s)
+                                          : launch_layout<3>(pl.tile, g.a_t, g.b_t, p, s);
+        if (e != hipSuccess) return e;
+    }
+    if (pl.splits > 1)
+        return launch_splitk_reduce(g.splitk_ws, g.C, g.bias_n, g.M, g.N, g.ldc, pl.splits, g.beta, s);
+    return hipSuccess;
 }
 
 }  // namespace rnn

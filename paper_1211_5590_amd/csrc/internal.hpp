@@ -7,7 +7,7 @@
 namespace rnn {
 
 // ---------------------------------------------------------------------------------------
-// fp32 MFMA GEMM:  C[M,N] = (beta ? C : 0) + op(A) op(B) + bias_n[col]
+// float32 matrix product:  C[M,N] = (beta ? C : 0) + op(A) op(B) + bias_n[col]
 //   a_t == false : A stored [M,K] (lda >= K)      a_t == true : A stored [K,M] (lda >= M)
 //   b_t == false : B stored [K,N] (ldb >= N)      b_t == true : B stored [N,K] (ldb >= K)
 // splitk_ws must hold gemm_splitk_floats(M,N,K) floats (0 => not needed).
@@ -22,48 +22,19 @@ struct GemmArgs {
     int beta;             // 0 overwrite, 1 accumulate
     float* splitk_ws;     // nullable when gemm_splitk_floats == 0
     int prof_id;          // kernel id under which the profiler books this product (prof.hpp)
-    // nullable: [M][gemm_stat_parts(N)][2] receives, per row and per 64-column part of the final
-    // result, (max, sum of exp relative to that max); written only when gemm_fuses_stats(M,N,K)
+    // nullable: [M][gemm_stat_parts()][2] receives, per row and per column part of the final
+    // result, (max, sum of exp relative to that max); written only when gemm_fuses_stats()
     float* row_stats;
+    int parts = 3;        // bf16 numbers a float32 operand is split into: 3 keeps all of it, 2 its first 16 bits
 };
-size_t gemm_splitk_floats(int M, int N, int K);
-int gemm_stat_parts(int N);
-bool gemm_fuses_stats(int M, int N, int K);
+size_t gemm_splitk_floats(int M, int N, int K, int parts = 3);
+int gemm_stat_parts(int M, int N, int K, int parts = 3);
+bool gemm_fuses_stats(int M, int N, int K, int parts = 3);
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 
 // C[m,n] = (beta ? C : 0) + sum over splits of part[s][m][n] + bias_n[n], fixed order
 hipError_t launch_splitk_reduce(const float* part, float* C, const float* bias_n, int M, int N, int ldc,
                                 int splits, int beta, hipStream_t s);
-
-// ---------------------------------------------------------------------------------------
-// bf16 hi/lo split products (gemm_bf16x3.hip): C[M,N] = A[M,K] B[N,K]^T + bias_n, float32 result,
-// operands K-contiguous in "split form" (per row and slab of 32 k: 32 hi values, then 32 lo values;
-// K padded with zeros to bf3_pad(K)) -- the form launch_split_bf16 writes; 4 bytes per padded element.
-struct Bf3Args {
-    const uint16_t* A;    // [M][2 lda]
-    const uint16_t* B;    // [N][2 ldb]
-    float* C;
-    int M, N, K;
-    int lda, ldb, ldc;
-    const float* bias_n;  // nullable
-    int beta;
-    float* splitk_ws;     // bf3_splitk_floats(M,N,K) floats
-    int prof_id;
-    float* row_stats;     // [M][bf3_stat_parts(M,N,K)][2]; written only when bf3_fuses_stats(M,N,K)
-};
-int bf3_stat_parts(int M, int N, int K);
-int bf3_pad(int k);
-size_t bf3_splitk_floats(int M, int N, int K);
-bool bf3_fuses_stats(int M, int N, int K);
-// float32 [R,C] (leading dimension ld) -> split form, as it is [R][2 bf3_pad(C)] and/or transposed
-// [C][2 bf3_pad(R)] (either may be NULL)
-hipError_t launch_split_bf16(const float* src, int R, int C, int ld, uint16_t* rowmajor, uint16_t* transposed,
-                             hipStream_t s);
-hipError_t launch_gemm_bf16x3(const Bf3Args& g, hipStream_t s);
-// logits -> d loss / d z directly in split form (both orientations) + per-chunk column sums for dc
-hipError_t launch_dz_split(const float* Z, const float* lse, const int32_t* y, const float* Y, float* part, int N,
-                           int O, int loss_kind, uint16_t* rowmajor, uint16_t* transposed, int* chunks_out,
-                           hipStream_t s);
 
 // ---------------------------------------------------------------------------------------
 // Recurrence (forward and reverse-time loops)
