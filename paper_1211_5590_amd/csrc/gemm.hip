@@ -40,6 +40,7 @@ namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
@@ -256,7 +257,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void gemm_kernel(GemmParams p)
     // block's products, from the second on (its last product has left the matrix core by then).
     f32x16 small[2];
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#define MMA(x, y, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, c, 0, 0, 0)
+    // operands exchanged: a block is held transposed (see the epilogue)
+#define MMA(x, y, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16(y, x, c, 0, 0, 0)
     auto block = [&](const bf16x8 (&a)[PARTS], const bf16x8 (&b)[PARTS], f32x16& c, f32x16& t, bool fold, f32x16& c0,
                      const f32x16& t0) {
         if constexpr (PARTS == 3) {
@@ -370,7 +372,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void gemm_kernel(GemmParams p)
     }
 #undef GEMM_FETCH
 
-    // Accumulator layout of a 32x32 block: lane -> column lane%32; register e -> row
+    // Accumulator layout of a 32x32 block: lane -> row lane%32; register e -> column
     // 8*(e/4) + 4*(lane/32) + e%4.
     const int r_first = m0 + wm * TM * 32, c_first = n0 + wn * TN * 32;
     float odd = 0.f;   // NaN if any result is not finite
@@ -395,7 +397,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void gemm_kernel(GemmParams p)
                         av = AT ? p.A[(size_t)(kbeg + k) * p.lda + r] : p.A[r * p.lda + kbeg + k];
                         bv = BT ? p.B[n * p.ldb + kbeg + k] : p.B[(size_t)(kbeg + k) * p.ldb + n];
                     }
-                    c = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, c, 0, 0, 0);
+                    c = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, av, c, 0, 0, 0);
                 }
 #pragma unroll
                 for (int ii = 0; ii < TM; ++ii)
@@ -408,51 +410,75 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void gemm_kernel(GemmParams p)
 
     float* Cout = p.C + (p.splits > 1 ? (size_t)blockIdx.z * p.M * p.ldc : 0);
     const bool final_out = p.splits == 1;
-    int col[TN];
-    float bias[TN];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        col[j] = c_first + 32 * j + lane % 32;
-        bias[j] = (final_out && p.bias_n && col[j] < p.N) ? p.bias_n[col[j]] : 0.f;
-    }
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
+    const int row_l = r_first + lane % 32, col_l = c_first + 4 * (lane / 32);
+    if (final_out && p.bias_n)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const int row = r_first + 32 * i + 8 * (e / 4) + 4 * (lane / 32) + e % 4;
-                if (row < p.M && col[j] < p.N) {
-                    float* dst = Cout + (size_t)row * p.ldc + col[j];
-                    float v = acc[i][j][e] + bias[j];
-                    if (final_out && p.beta) v += *dst;
-                    *dst = v;
-                }
+                const float bias = p.bias_n[min(col_l + 32 * j + 8 * (e / 4) + e % 4, p.N - 1)];
+#pragma unroll
+                for (int i = 0; i < TM; ++i) acc[i][j][e] += bias;
             }
 
+    // The result goes through a part of LDS of the wavefront's own, 32 rows at a time, so that a store
+    // request covers whole stretches of rows (TN * 128 bytes) and not 32 pieces of 16 bytes.
+    constexpr int ROW = TN * 32 + 4, CL = TN * 8, RS = 64 / CL;   // floats per row; lanes per row, rows per request
+    static_assert(NW * 32 * ROW * 4 <= (NW == 8 ? 3 : 2) * STAGE, "the staging fits the slab buffers");
+    if constexpr (NW != 8) lds_barrier();   // (the two groups of the other form have just met)
+    float* stage = reinterpret_cast<float*>(lds) + wave * 32 * ROW;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<float4*>(stage + (lane % 32) * ROW + 32 * j + 8 * q + 4 * (lane / 32)) =
+                    make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+#pragma unroll
+        for (int t = 0; t < 32 / RS; ++t) {
+            const int r = t * RS + lane / CL, row = r_first + 32 * i + r, col = c_first + (lane % CL) * 4;
+            const float4 x = *reinterpret_cast<const float4*>(stage + r * ROW + (lane % CL) * 4);
+            if (row >= p.M) continue;
+            float* dst = Cout + (size_t)row * p.ldc + col;
+            if (col + 3 < p.N) {
+                f32x4u v = {x.x, x.y, x.z, x.w};
+                if (final_out && p.beta) v += *reinterpret_cast<const f32x4u*>(dst);
+                *reinterpret_cast<f32x4u*>(dst) = v;
+            } else {
+                const float y[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (col + e < p.N) dst[e] = (final_out && p.beta) ? dst[e] + y[e] : y[e];
+            }
+        }
+    }
+
     // Fused row statistics of a log-sum-exp over the columns: every wavefront leaves, for each of
-    // its rows, the maximum of its TN * 32 columns and the sum of exponentials relative to it.
+    // its rows, the maximum of its TN * 32 columns and the sum of exponentials relative to it.  A lane
+    // holds half of a row's columns, the lane 32 further the other half.
     if constexpr (STATS) if (final_out) {
         const int nparts = p.tiles_n * WGN, part = tile_n * WGN + wn;
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < TM; ++i) {
+            float m = -INFINITY, sum = 0.f;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                float v[TN], m = -INFINITY, sum = 0.f;
+            for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    v[j] = acc[i][j][e] + bias[j];
-                    if (col[j] < p.N) m = fmaxf(m, v[j]);
-                }
-                m = max32(m);   // register-to-register lane exchanges: no LDS round trips in the chain
+                for (int e = 0; e < 16; ++e)
+                    if (col_l + 32 * j + 8 * (e / 4) + e % 4 < p.N) m = fmaxf(m, acc[i][j][e]);
+            const auto other = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+            m = fmaxf(__uint_as_float(other[0]), __uint_as_float(other[1]));
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    if (col[j] < p.N) sum += __expf(v[j] - m);
-                sum = sum32(sum);
-                const int row = r_first + 32 * i + 8 * (e / 4) + 4 * (lane / 32) + e % 4;
-                if (lane % 32 == 0 && row < p.M)
-                    *reinterpret_cast<float2*>(p.stats + ((size_t)row * nparts + part) * 2) = make_float2(m, sum);
-            }
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    if (col_l + 32 * j + 8 * (e / 4) + e % 4 < p.N) sum += __expf(acc[i][j][e] - m);
+            sum = swap32_sum(sum);
+            const int row = row_l + 32 * i;
+            if (lane < 32 && row < p.M)
+                *reinterpret_cast<float2*>(p.stats + ((size_t)row * nparts + part) * 2) = make_float2(m, sum);
+        }
     }
 }
 
@@ -624,7 +650,6 @@ size_t gemm_splitk_floats(int M, int N, int K, int parts) {
 // consecutive outputs (whatever row they fall in), the partials of the K slices added in slice order
 // (eight 16-byte requests in flight per thread), one pass over the partial buffer at the rate memory
 // delivers it.
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 __global__ __launch_bounds__(256) void splitk_reduce_flat_kernel(const float* __restrict__ part, float* __restrict__ C,
                                                                  const float* __restrict__ bias, size_t total, int N,
                                                                  int splits, int beta) {
