@@ -27,6 +27,10 @@
 //     the stores is needed.  The first look uses ordinary loads (lines this compute unit has never
 //     cached: they are served by the XCD's L2); a look that came too early has left stale lines in the
 //     first-level cache, so later looks use device-scope loads, which pass it.
+// A hidden size that is no multiple of 4 leaves rows (and the history's slots) at 4-byte alignment and
+// the last piece of a row ragged: that piece is fetched as the row's last four words, and its lane
+// shifts the words that belong to it into place (seven selects per step in the wavefronts that take
+// part; the loads and the waits are the same).
 // A workgroup takes its group from the XCD it finds itself on and its column slice from a per-XCD
 // counter, so all workgroups of a group share one L2 by construction whenever the 256 workgroups are
 // co-resident (cooperative launch, one workgroup per compute unit: checked before the launch).
@@ -51,6 +55,7 @@ namespace rnn {
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int XT = 512;            // threads: 8 wavefronts
 constexpr int RB = 4;              // batch rows per group
@@ -81,6 +86,25 @@ __device__ __forceinline__ void xcd_lds_barrier() {
 __device__ __forceinline__ bool fresh(float4 v) {
     return __float_as_uint(v.x) != kSentinel && __float_as_uint(v.y) != kSentinel &&
            __float_as_uint(v.z) != kSentinel && __float_as_uint(v.w) != kSentinel;
+}
+
+// the words of a row's last four that start `d` further along, zeros behind them
+__device__ __forceinline__ float4 shifted(float4 v, int d) {
+    return make_float4(d == 0 ? v.x : d == 1 ? v.y : d == 2 ? v.z : v.w, d == 0 ? v.y : d == 1 ? v.z : d == 2 ? v.w : 0.f,
+                       d == 0 ? v.z : d == 1 ? v.w : 0.f, d == 0 ? v.w : 0.f);
+}
+// p[0..3] at 4-byte alignment; words from `left` on do not exist and read as zero (left <= 0: none exist)
+__device__ __forceinline__ float4 piece(const float* p, int left) {
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (left >= 4) {
+        const f32x4u t = *reinterpret_cast<const f32x4u*>(p);
+        v = make_float4(t[0], t[1], t[2], t[3]);
+    } else {
+        if (left > 0) v.x = p[0];
+        if (left > 1) v.y = p[1];
+        if (left > 2) v.z = p[2];
+    }
+    return v;
 }
 
 // 64 matrix instructions: the four values of one state piece against 64 k of the matrix, block AB
@@ -147,8 +171,7 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const int k = kb + 64 * q + r4 + 4 * i, cc = c0 + c4;
-                const bool on = k < H && cc < H;                     // H % 4 == 0: a piece is inside or outside
-                v[i] = on ? *reinterpret_cast<const float4*>(a.Wh + (size_t)k * H + cc) : make_float4(0.f, 0.f, 0.f, 0.f);
+                v[i] = piece(a.Wh + (size_t)k * H + cc, k < H ? H - cc : 0);
             }
 #pragma unroll
             for (int i = 0; i < 16; ++i) *reinterpret_cast<float4*>(stg + (r4 + 4 * i) * 64 + c4) = v[i];
@@ -171,8 +194,7 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const int row = c0 + r4 + 4 * i, k = kb + 64 * q + k4;
-                const bool on = row < H && k < H;                    // H % 4 == 0: a piece is inside or outside
-                v[i] = on ? *reinterpret_cast<const float4*>(a.Wh + (size_t)row * H + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+                v[i] = piece(a.Wh + (size_t)row * H + k, row < H ? H - k : 0);
             }
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
@@ -189,13 +211,15 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
 
     // ---- the state pieces of this lane: row ri, columns kb + 64 q + 4 kg .. + 3; pieces outside
     //      the matrix (rows past the batch, columns past H) stay zero ---------------------------------
-    int p_off[NQ];
+    int p_off[NQ], p_shift[NQ];
     bool p_on[NQ];
+    const bool ragged = H % 4 != 0;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
         const int k = kb + 64 * q + 4 * kg;
         p_on[q] = ri < nrows && k < H;
-        p_off[q] = p_on[q] ? (b0 + ri) * H + k : b0 * H;       // clamped duplicates outside the matrix
+        p_off[q] = p_on[q] ? (b0 + ri) * H + min(k, H - 4) : b0 * H;   // clamped duplicates outside the matrix
+        p_shift[q] = p_on[q] ? max(k - (H - 4), 0) : 0;
     }
     float4 st[NQ];                         // the state of the coming step
 #pragma unroll
@@ -203,15 +227,16 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         if (p_on[q]) {
             if (!BWD) {
-                if (a.h0) v = *reinterpret_cast<const float4*>(a.h0 + p_off[q]);
+                if (a.h0) v = piece(a.h0 + p_off[q], 4);
             } else {
-                const float4 g = *reinterpret_cast<const float4*>(a.G + (size_t)(T - 1) * bh + p_off[q]);
-                const float4 h = *reinterpret_cast<const float4*>(a.h_all + (size_t)T * bh + p_off[q]);
+                const float4 g = piece(a.G + (size_t)(T - 1) * bh + p_off[q], 4);
+                const float4 h = piece(a.h_all + (size_t)T * bh + p_off[q], 4);
                 float4 c = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (a.dh_last) c = *reinterpret_cast<const float4*>(a.dh_last + p_off[q]);
+                if (a.dh_last) c = piece(a.dh_last + p_off[q], 4);
                 v.x = (g.x + c.x) * act_grad<ACT>(h.x); v.y = (g.y + c.y) * act_grad<ACT>(h.y);
                 v.z = (g.z + c.z) * act_grad<ACT>(h.z); v.w = (g.w + c.w) * act_grad<ACT>(h.w);
             }
+            v = shifted(v, p_shift[q]);
         }
         st[q] = v;
     }
@@ -299,7 +324,10 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
                 if (fresh(v[q])) need &= ~(1u << q);
         }
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) st[q] = (wanted & (1u << q)) ? v[q] : make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int q = 0; q < NQ; ++q) {
+            st[q] = (wanted & (1u << q)) ? v[q] : make_float4(0.f, 0.f, 0.f, 0.f);
+            if (ragged) st[q] = shifted(st[q], p_shift[q]);
+        }
     };
 
     float last_v = 0.f;
@@ -369,9 +397,12 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
     }
 }
 
-__global__ __launch_bounds__(256) void fill_sentinel_kernel(uint4* __restrict__ p, size_t n16) {
-    const uint4 s = make_uint4(kSentinel, kSentinel, kSentinel, kSentinel);
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (size_t)gridDim.x * blockDim.x) p[i] = s;
+__global__ __launch_bounds__(256) void fill_sentinel_kernel(float* __restrict__ p, size_t n) {
+    const float s = __uint_as_float(kSentinel);
+    const f32x4u s4 = {s, s, s, s};
+    const size_t n4 = n / 4, first = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (size_t i = first; i < n4; i += (size_t)gridDim.x * blockDim.x) *reinterpret_cast<f32x4u*>(p + 4 * i) = s4;
+    if (first < n % 4) p[4 * n4 + first] = s;
 }
 
 template <int ACT, bool BWD>
@@ -389,7 +420,7 @@ size_t xcd_lds_bytes() { return (size_t)8 * 64 * 65 * 4; }
 // 2.1 us per step, against 5.5 us per step for a launch per step, so the shortest sequences stay with
 // the latter (cross-over at H = 1024, batch 64: 8 to 10 steps).
 bool rec_xcd_supported(int H, int B, int T) {
-    return T >= 10 && B > 4 && B <= NGRP * RB && H > 256 && H <= NSLOT * CWD && H % 4 == 0;
+    return T >= 10 && B > 4 && B <= NGRP * RB && H > 256 && H <= NSLOT * CWD;
 }
 
 template <bool BWD>
@@ -435,10 +466,10 @@ hipError_t launch_rec_xcd(const RecXcdArgs& a, bool bwd, hipStream_t s) {
         if (e != hipSuccess) return e;
         float* first = bwd ? a.Delta : a.hist + bh;
         const size_t rows = bwd ? (size_t)(a.T - 1) : (size_t)a.T;
-        const size_t n16 = rows * bh / 4;         // H % 4 == 0
-        if (n16 > 0) {
-            const unsigned blocks = (unsigned)((n16 + 255) / 256 < 2048 ? (n16 + 255) / 256 : 2048);
-            hipLaunchKernelGGL(fill_sentinel_kernel, dim3(blocks), dim3(256), 0, s, reinterpret_cast<uint4*>(first), n16);
+        const size_t n = rows * bh, n4 = (n + 3) / 4;
+        if (n > 0) {
+            const unsigned blocks = (unsigned)((n4 + 255) / 256 < 2048 ? (n4 + 255) / 256 : 2048);
+            hipLaunchKernelGGL(fill_sentinel_kernel, dim3(blocks), dim3(256), 0, s, first, n);
             e = hipGetLastError();
             if (e != hipSuccess) return e;
         }

@@ -55,3 +55,18 @@ def test_the_one_launch_wide_loop_at_its_edges(H):
         r.step()
         assert rnn.rnn_workspace_status(r.dims, r.ws) == 0
         compare(r.results(), oracle.fwd_bptt(case, h0=case.get("h0"), dh_last=case.get("dh_last")))
+
+
+@pytest.mark.parametrize("H", (257, 258, 259, 511, 513, 650, 1021, 1023))
+def test_the_one_launch_wide_loop_at_hidden_sizes_that_are_no_multiple_of_4(H):
+    """Rows at 4-byte alignment and a ragged last piece of every row, in the first and in the second
+    K half of a wavefront, with rows missing from the last batch group."""
+    for n, (B, T) in enumerate(((5, 10), (63, 12), (18, 31))):
+        case = ri.make_case(in_dim=90, hidden=H, out_dim=70, seq_len=T, batch=B, act=n % 2, with_h0=n != 1,
+                            with_dh_last=n >= 1, wdist=("normal", 0.5 / np.sqrt(H)), bias_std=0.1, seed=9500 + 11 * H + n)
+        r = Runner(case)
+        print(f"H={H} B={B} T={T}", flush=True)
+        assert rnn.rnn_recurrence_variant(r.dims) == "xcd_mfma"
+        r.step()
+        assert rnn.rnn_workspace_status(r.dims, r.ws) == 0
+        compare(r.results(), oracle.fwd_bptt(case, h0=case.get("h0"), dh_last=case.get("dh_last")))
