@@ -118,7 +118,9 @@ Plan make_plan(const rnn_dims* d) {
     p.lse = take(N * 4);
     p.rowloss = take(N * 4);
     p.U = take((!s.tokens || s.B > 4) ? N * H * 4 : 0);  // hoisted input term (dense, or batched tokens)
-    p.G = take(N * H * 4);
+    // (also scratch of the token gradient once the reverse loop has read it)
+    const size_t g_floats = s.tokens && N > 32 && dwx_scratch_floats((int)N, s.H) > N * H ? dwx_scratch_floats((int)N, s.H) : N * H;
+    p.G = take(g_floats * 4);
     p.Delta = take(N * H * 4);
     p.WhT = take(H * H * 4);
     p.hring = take(2 * B * H * 4);
@@ -385,9 +387,9 @@ hipError_t run_backward_from_dz(const rnn_dims* d, const rnn_params* P, const vo
     RNN_TRY(launch_colsum_finish(part, Gr->db, chunks, H, beta, s));
     // dWx
     if (z.tokens) {
-        // the logits buffer is dead by now and serves as scratch for per-range partial rows
+        // G is dead by now and serves as scratch for per-range partial rows
         RNN_TRY(launch_dwx_tokens(static_cast<const int32_t*>(x), Delta, Gr->dWx, N, z.NVin, H, beta,
-                                  Z, (size_t)N * O, N > 32 ? at<int32_t>(ws, pl.seen) : nullptr, s));
+                                  N > 32 ? G : nullptr, N > 32 ? at<int32_t>(ws, pl.seen) : nullptr, s));
     } else {
         GemmArgs g{};
         g.A = Delta; g.B = static_cast<const float*>(x); g.C = Gr->dWx;

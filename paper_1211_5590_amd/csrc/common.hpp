@@ -19,6 +19,30 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
+// four floats at 4-byte alignment (16-byte requests need no more than that)
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 load4u(const float* p) {
+    const f32x4u t = *reinterpret_cast<const f32x4u*>(p);
+    return make_float4(t[0], t[1], t[2], t[3]);
+}
+// the elements of v that start `d` (0..3) further along, zeros behind them: a row's last four words,
+// moved to where its ragged last piece begins
+__device__ __forceinline__ float4 shifted(float4 v, int d) {
+    return make_float4(d == 0 ? v.x : d == 1 ? v.y : d == 2 ? v.z : v.w, d == 0 ? v.y : d == 1 ? v.z : d == 2 ? v.w : 0.f,
+                       d == 0 ? v.z : d == 1 ? v.w : 0.f, d == 0 ? v.w : 0.f);
+}
+// p[0 .. min(left, 4) - 1] = v
+__device__ __forceinline__ void store4u(float* p, float4 v, int left) {
+    if (left >= 4) {
+        const f32x4u t = {v.x, v.y, v.z, v.w};
+        *reinterpret_cast<f32x4u*>(p) = t;
+    } else {
+        if (left > 0) p[0] = v.x;
+        if (left > 1) p[1] = v.y;
+        if (left > 2) p[2] = v.z;
+    }
+}
+
 // Workgroup barrier that waits for this wavefront's LDS traffic only.  __syncthreads() also waits
 // for every outstanding global access (vmcnt(0)), which would expose the full memory latency of
 // requests that were issued on purpose several iterations ahead of their use.

@@ -208,11 +208,12 @@ hipError_t launch_gn_softmax_metric(const float* Z, float* RZ, int N, int O, flo
 
 // ---------------------------------------------------------------------------------------
 // Token-keyed gradient of the input matrix and id validation
-// scratch (>= scratch_floats floats) and slot_table (>= dwx_table_ints(N, NV) ints) enable the grouped form
+// scratch (dwx_scratch_floats(N, H) floats) and slot_table (dwx_table_ints(N, NV) ints), both or neither,
+// enable the grouped form
+size_t dwx_scratch_floats(int N, int H);
 size_t dwx_table_ints(int N, int NV);
 hipError_t launch_dwx_tokens(const int32_t* x, const float* Delta, float* dWx, int N, int NV,
-                             int H, int beta, float* scratch, size_t scratch_floats,
-                             int32_t* seen_flags, hipStream_t s);
+                             int H, int beta, float* scratch, int32_t* slot_table, hipStream_t s);
 hipError_t launch_check_tokens(const int32_t* ids, int64_t n, int32_t limit, int32_t* bad,
                                hipStream_t s);
 

@@ -3,17 +3,25 @@
 //
 // Batch rows are independent, so the batch is cut into tiles of 4 rows and every tile gets its
 // own workgroup that never talks to another one: no device-wide synchronisation exists in this
-// kernel, a step costs one LDS-only workgroup barrier.  The state tile (4 x H) lives in LDS,
-// double buffered; the weights (Wh^T forward, Wh reverse) stay in registers for the whole
-// launch as B operands of v_mfma_f32_4x4x1_16b_f32.  That instruction computes 16 independent
-// 4x4 outer products per issue at the same flop rate as the larger shapes, so a tile of only 4
-// batch rows already runs a SIMD at its full fp32 matrix rate, and a batch of 128 spreads over
-// 32 compute units instead of the 8 that 16-row tiles would fill.
+// kernel, a step costs one LDS-only workgroup barrier.  The per-step epilogue (input term +
+// activation, or output-layer term times the activation derivative) is fused, its operands are
+// requested two steps ahead, and the new state goes to both the history in HBM and LDS (the paper's
+// Scan keeps every state for the gradient loop: property 1; nothing per step happens on the host:
+// properties 4 and 5).
 //
-// The per-step epilogue (input term + activation, or output-layer term times the activation
-// derivative) is fused, its operands are requested two steps ahead, and the new state goes to
-// both the history in HBM and the other LDS buffer (the paper's Scan keeps every state for
-// the gradient loop: property 1; nothing per step happens on the host: properties 4 and 5).
+// What bounds it: the latency of one step, T times, on ceil(B/4) compute units; most of a step is matrix
+// instructions.  They run on v_mfma_f32_16x16x32_bf16 with float32 accumulation.  State and matrix are
+// split into three bf16 numbers each, which hold all 24 bits of a float32 (hi = bf16(x),
+// mid = bf16(x - hi), lo = bf16(x - hi - mid)).  The 16 rows of an instruction are the 4 batch rows times
+// (hi, mid, lo, zero), so one pass over the state per part of the matrix gives all nine products;
+// the row groups lie 16 lanes apart and are added by three register swaps, which also leave batch row g in
+// lane group g.  At 256 units that is 1536 clocks of matrix instructions per step where the float32
+// form (v_mfma_f32_4x4x1, 4 rows at the full float32 rate) took 2048, and an accumulator is rounded
+// about 6 times per 32 terms instead of 32 times.
+//
+// Infinities do not split (inf = inf + mid + lo has no mid): a workgroup whose matrix or state holds one
+// goes on with plain float32 products read from memory, so that results are float32's in that case too.
+// NaNs need nothing: they make the same results NaN in either form.
 //
 #include "common.hpp"
 #include "internal.hpp"
@@ -25,163 +33,232 @@ namespace rnn {
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+// two float32 -> three words of two bf16 each; an infinity stays in the first
+__device__ __forceinline__ void split3(float x, float y, unsigned (&w)[3]) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const f32x2 v = {x, y};
+        w[q] = __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+        if (q < 2) {
+            x -= __uint_as_float(w[q] << 16);
+            y -= __uint_as_float(w[q] & 0xffff0000u);
+        }
+    }
 }
+__device__ __forceinline__ bool is_inf(float x) { return (__float_as_uint(x) & 0x7fffffffu) >= 0x7f7f8000u && x == x; }   // or rounds to one in bf16
 
-// Lane layout.  A wavefront owns 32 output columns.  Lane l = 32*hf + 4*blk + i (hf 0..1, blk 0..7, i 0..3):
-// blocks blk and 8+blk both produce columns 4*blk .. 4*blk+3 of the 32, for two different k, so
-// lane l supplies the B value M[k_hf][col0 + l%32] and receives, in accumulator register r, the
-// partial sum over its half's k of row r at that column; the two halves are added with
-// v_permlane32_swap, after which the lower lanes hold rows 0,1 and the upper lanes rows 2,3.
-// Every block needs the A values h[i][k]; instead of loading each into all blocks, an A register
-// holds 16 different k (k = 64q + 32*hf + 4*blk + e in register 4q+e, one 16-byte LDS read per
-// q) and the instruction's broadcast field (cbsz = 3: each group of 8 blocks takes A from its
-// block abid) selects k = 64q + 32*hf + 4*abid + e.  A lane's weights are HP/2 registers,
-// resident for the whole launch; a workgroup is HP/32 wavefronts, two per SIMD at HP = 256.
-template <int ACT, bool BWD, int HP>
-__global__ __launch_bounds__(2 * HP) void rec_batch_mfma_kernel(RecMfmaArgs a) {
-    constexpr int NQ = HP / 64;    // 16-byte A reads per lane and step
-    constexpr int LDH = HP + 16;   // LDS row stride: the 4 rows of a read land 16 banks apart
-    constexpr int NT = 2 * HP;     // threads
+// NK = slabs of 32 hidden units (K of the product and, times two, column tiles of 16).  CT column
+// tiles per wavefront, NW wavefronts: one tile each (and so 1, 2 or 3 per SIMD) up to 192 units, beyond
+// that two, whose matrix fills the registers of two wavefronts per SIMD.  Lane l of a wavefront: matrix operand k = 32 c + 8 (l / 16) + 0..7
+// of column (16 wave + l % 16) CT + t in tile t (a lane's columns are adjacent); state operand the same
+// k of row l % 16; result: batch row l / 16 of its columns.
+constexpr int batch_waves(int NK) { return NK <= 2 ? 4 : NK <= 4 ? 8 : NK <= 6 ? 12 : 8; }
+template <int ACT, bool BWD, int NK>
+__global__ __launch_bounds__(64 * batch_waves(NK), batch_waves(NK) / 4) void rec_batch_mfma_kernel(RecMfmaArgs a) {
+    constexpr int NW = batch_waves(NK), CT = NK <= 6 ? 1 : 2, NT = NW * 64;
+    constexpr int HP = 32 * NK;
+    constexpr int LDK = HP + 8;    // bf16 per LDS row: consecutive rows lie 4 banks apart
     constexpr int R4 = 4;          // batch rows per workgroup
-    __shared__ __attribute__((aligned(16))) float hs[2][R4][LDH];
+    __shared__ __attribute__((aligned(16))) uint16_t hs[2][16][LDK];   // rows: part * 4 + batch row; the last four stay 0
+    __shared__ int s_inf;
 
     const int H = a.H, B = a.B, T = a.T;
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-    const int hf = lane / 32, blk = (lane % 32) / 4, ri = lane % 4;
-    const int col = wave * 32 + lane % 32, colc = min(col, H - 1);
+    const int rg = lane / 16;                                   // batch row of this lane's results
+    const int col = (wave * 16 + lane % 16) * CT;               // first of its CT columns
     const int b0 = blockIdx.x * R4;
     const size_t bh = (size_t)B * H;
 
-    // ---- resident weights: wreg[(8q+b)*4+e] = M[k][col], k = 64q + 32hf + 4b + e,
-    //      M = Wh^T (forward) or Wh (reverse) ------------------------------------------------
-    float wreg[HP / 2];
-#pragma unroll
-    for (int j = 0; j < HP / 2; ++j) {
-        const int k = 64 * (j / 32) + 32 * hf + (j % 32);
-        const int kc = min(k, H - 1);
-        wreg[j] = BWD ? a.Wh[(size_t)kc * H + colc] : a.Wh[(size_t)colc * H + kc];
-    }
-    // Zero the padding in a second pass, by multiplication: a select would make every load
-    // above conditional and serialise them behind a wait each.
-    const float colmask = col < H ? 1.f : 0.f;
-#pragma unroll
-    for (int j = 0; j < HP / 2; ++j) {
-        const int k = 64 * (j / 32) + 32 * hf + (j % 32);
-        wreg[j] *= k < H ? colmask : 0.f;
-    }
-
-    // ---- initial state tile ------------------------------------------------------------------
-    for (int i = tid; i < 2 * R4 * LDH; i += NT) (&hs[0][0][0])[i] = 0.f;
+    for (int i = tid; i < 2 * 16 * LDK / 2; i += NT) reinterpret_cast<unsigned*>(&hs[0][0][0])[i] = 0u;
+    if (tid == 0) s_inf = 0;
     __syncthreads();
-    for (int i = tid; i < R4 * HP; i += NT) {
-        const int m = i / HP, j = i % HP, row = b0 + m;
-        if (row >= B || j >= H) continue;
-        float v;
-        if (!BWD) {
-            v = a.h0 ? a.h0[(size_t)row * H + j] : 0.f;
-            a.hist[(size_t)row * H + j] = v;                       // slot 0
-        } else {
-            const size_t e = (size_t)(T - 1) * bh + (size_t)row * H + j;
-            const float c = a.dh_last ? a.dh_last[(size_t)row * H + j] : 0.f;
-            const float h = a.h_all[(size_t)T * bh + (size_t)row * H + j];
-            v = (a.G[e] + c) * act_grad<ACT>(h);
-            a.Delta[e] = v;
+
+    // ---- resident weights, M = Wh^T (forward) or Wh (reverse); zero outside the matrix ------------
+    bf16x8 w[CT][NK][3];
+    bool odd = false;
+#pragma unroll
+    for (int c = 0; c < NK; ++c)
+#pragma unroll
+        for (int t = 0; t < CT; ++t) {
+            __builtin_amdgcn_sched_barrier(0);   // a piece at a time: the registers belong to w
+            float x[8];
+            const int k0 = 32 * c + 8 * rg, n = col + t, nc = min(n, H - 1);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int kc = min(k0 + e, H - 1);
+                x[e] = BWD ? a.Wh[(size_t)kc * H + nc] : a.Wh[(size_t)nc * H + kc];
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                if (n >= H || k0 + e >= H) x[e] = 0.f;
+                odd = odd || is_inf(x[e]);
+            }
+            unsigned p[4][3];
+#pragma unroll
+            for (int h = 0; h < 4; ++h) split3(x[2 * h], x[2 * h + 1], p[h]);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                const u32x4 v = {p[0][q], p[1][q], p[2][q], p[3][q]};
+                w[t][c][q] = __builtin_bit_cast(bf16x8, v);
+            }
         }
-        hs[0][m][j] = v;
+
+    // the CT values of this lane go to state buffer `buf` as three rows of bf16
+    auto put = [&](int buf, const float (&v)[CT]) {
+        if (col >= HP) return;     // a wavefront without columns
+        unsigned p[3];
+        split3(v[0], CT > 1 ? v[CT - 1] : 0.f, p);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            uint16_t* d = &hs[buf][q * R4 + rg][col];
+            if (CT == 2) *reinterpret_cast<unsigned*>(d) = p[q];
+            else *d = (uint16_t)p[q];
+        }
+#pragma unroll
+        for (int t = 0; t < CT; ++t)
+            if (is_inf(v[t])) s_inf = 1;
+    };
+
+    // ---- initial state tile: slot 0 of the history / Delta[T-1] ------------------------------------
+    const int row = b0 + rg;
+    bool on[CT];
+    unsigned off[CT];              // bytes from the workgroup's first row, clamped: always valid to read
+    const size_t first = (size_t)b0 * H;
+#pragma unroll
+    for (int t = 0; t < CT; ++t) {
+        on[t] = row < B && col + t < H;
+        off[t] = (unsigned)(min(rg, B - 1 - b0) * H + min(col + t, H - 1)) * 4u;
     }
+    auto at = [&](auto* base, int t) -> decltype(*base)& {   // base: uniform, of row 0
+        return *reinterpret_cast<std::remove_reference_t<decltype(*base)>*>(
+            reinterpret_cast<std::conditional_t<std::is_const_v<std::remove_reference_t<decltype(*base)>>, const char, char>*>(base + first) + off[t]);
+    };
+    float last[CT];                // the state of the last step
+#pragma unroll
+    for (int t = 0; t < CT; ++t) {
+        last[t] = 0.f;
+        if (!on[t]) continue;
+        if (!BWD) {
+            if (a.h0) last[t] = at(a.h0, t);
+        } else {
+            const float c = a.dh_last ? at(a.dh_last, t) : 0.f;
+            last[t] = (at(a.G + (size_t)(T - 1) * bh, t) + c) * act_grad<ACT>(at(a.h_all + (size_t)T * bh, t));
+        }
+    }
+    put(0, last);
+    if (odd) s_inf = 1;            // (read after the barrier only)
     __syncthreads();
 
-    // Epilogue operands (rows 2hf, 2hf+1 of this lane's column), requested two steps ahead.
+    // Epilogue operands, requested two steps ahead.
     // forward: x0 = input term U[s]; reverse (t = T-2-s): x0 = G[t], x1 = h_t = h_all[t+1].
     const int nsteps = BWD ? T - 1 : T;
-    size_t rowoff[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) rowoff[i] = (size_t)min(b0 + 2 * hf + i, B - 1) * H + colc;
-    auto load_epi = [&](int s, float (&x0)[2], float (&x1)[2]) {
+    auto load_epi = [&](int s, float (&x0)[CT], float (&x1)[CT]) {
         const int sc = max(min(s, nsteps - 1), 0);   // clamped: always a valid step to read
-        const int t = BWD ? max(T - 2 - sc, 0) : sc;
-        const size_t base = (size_t)t * bh;
+        const size_t base = (size_t)(BWD ? max(T - 2 - sc, 0) : sc) * bh;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int t = 0; t < CT; ++t) {
             if (!BWD) {
-                x0[i] = a.U[base + rowoff[i]];
+                x0[t] = at(a.U + base, t);
             } else {
-                x0[i] = a.G[base + rowoff[i]];
-                x1[i] = a.h_all[base + bh + rowoff[i]];
+                x0[t] = at(a.G + base, t);
+                x1[t] = at(a.h_all + base + bh, t);
             }
         }
     };
-    float n0[2][2], n1[2][2];
+    float n0[2][CT], n1[2][CT];
 #pragma unroll
     for (int p = 0; p < 2; ++p)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) { n0[p][i] = 0.f; n1[p][i] = 0.f; }
+        for (int t = 0; t < CT; ++t) { n0[p][t] = 0.f; n1[p][t] = 0.f; }
     load_epi(0, n0[0], n1[0]);
     load_epi(1, n0[1], n1[1]);
 
-    // out[i] = sum_k h[2hf+i][k] * M[k][col] from state buffer CUR
-    auto product = [&](auto cur_c, float (&out)[2]) {
-        constexpr int CUR = decltype(cur_c)::value;
-        float areg[4 * NQ];
+    // out[t] = sum_k h[rg][k] M[k][col + t] from state buffer `cur`
+    auto product = [&](int cur, float (&out)[CT]) {
+        bf16x8 s[NK];
+        auto fetch = [&](int c) { s[c] = *reinterpret_cast<const bf16x8*>(&hs[cur][lane % 16][32 * c + 8 * rg]); };
+        f32x4 acc[CT][2];          // the matrix's hi part; its mid and lo parts
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const float4 v =
-                *reinterpret_cast<const float4*>(&hs[CUR][ri][64 * q + 32 * hf + 4 * blk]);
-            areg[4 * q] = v.x; areg[4 * q + 1] = v.y; areg[4 * q + 2] = v.z; areg[4 * q + 3] = v.w;
+        for (int t = 0; t < CT; ++t) acc[t][0] = acc[t][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        constexpr int AHEAD = NK < 3 ? NK : 3;      // pieces of the state in flight (registers are full)
+#pragma unroll
+        for (int c = 0; c < AHEAD; ++c) fetch(c);
+        const int inf = s_inf;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < NK; ++c) {
+#pragma unroll
+            for (int q = 2; q >= 0; --q)
+#pragma unroll
+                for (int t = 0; t < CT; ++t)
+                    acc[t][q ? 1 : 0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(s[c], w[t][c][q], acc[t][q ? 1 : 0], 0, 0, 0);
+            if (c + AHEAD < NK) fetch(c + AHEAD);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        f32x4 acc[4];
+        if (__builtin_amdgcn_readfirstlane(inf)) {   // plain float32, straight from memory
+            for (int t = 0; t < CT; ++t) {
+                float sum = 0.f;
+                const int n = min(col + t, H - 1);
+                for (int k = 0; k < H; ++k) {
+                    float h = 0.f;
+                    for (int q = 0; q < 3; ++q) {
+                        const float part = __uint_as_float((unsigned)hs[cur][q * R4 + rg][k] << 16);
+                        if (q == 0 || !is_inf(h)) h += part;
+                    }
+                    sum = fmaf(h, BWD ? a.Wh[(size_t)k * H + n] : a.Wh[(size_t)n * H + k], sum);
+                }
+                out[t] = sum;
+            }
+            return;
+        }
+        // lane group g, register e: row group g (part of the state) of batch row e.  Adding the groups
+        // and moving batch row g to lane group g is one swap of halves and one of 16-lane rows.
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#define RNN_MFMA4_BLOCK(Q, AB)                                                                   \
-    _Pragma("unroll") for (int e = 0; e < 4; ++e)                                                \
-        acc[e] = __builtin_amdgcn_mfma_f32_4x4x1f32(areg[4 * (Q) + e],                           \
-                                                    wreg[(8 * (Q) + (AB)) * 4 + e], acc[e], 3,   \
-                                                    (AB), 0);
-#define RNN_MFMA4_Q(Q)                                                                           \
-    RNN_MFMA4_BLOCK(Q, 0) RNN_MFMA4_BLOCK(Q, 1) RNN_MFMA4_BLOCK(Q, 2) RNN_MFMA4_BLOCK(Q, 3)      \
-    RNN_MFMA4_BLOCK(Q, 4) RNN_MFMA4_BLOCK(Q, 5) RNN_MFMA4_BLOCK(Q, 6) RNN_MFMA4_BLOCK(Q, 7)
-        RNN_MFMA4_Q(0)
-        if constexpr (NQ > 1) { RNN_MFMA4_Q(1) }
-        if constexpr (NQ > 2) { RNN_MFMA4_Q(2) RNN_MFMA4_Q(3) }
-#undef RNN_MFMA4_Q
-#undef RNN_MFMA4_BLOCK
-        const f32x4 part = (acc[0] + acc[1]) + (acc[2] + acc[3]);
-        // add the two k halves: rows 0,2 in one swap, rows 1,3 in the other
+        for (int t = 0; t < CT; ++t) {
+            const f32x4 v = acc[t][0] + acc[t][1];
+            float u[2];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(part[i]),
-                                                            __float_as_uint(part[i + 2]), false,
-                                                            false);
-            out[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+            for (int i = 0; i < 2; ++i) {
+                const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 2]), false, false);
+                u[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+            }
+            const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(u[0]), __float_as_uint(u[1]), false, false);
+            out[t] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
         }
     };
 
-    auto step = [&](int s, auto slot_c) {
-        constexpr int SLOT = decltype(slot_c)::value;   // s & 1: state buffer and operand slot
-        float acc[2];
-        product(slot_c, acc);
-
-        const int t = BWD ? T - 2 - s : s;
-        float* out = BWD ? a.Delta + (size_t)t * bh
+    auto store_state = [&](int s) {   // s = -1: the initial state
+        const int row_t = BWD ? T - 2 - s : s;
+        float* out = BWD ? a.Delta + (size_t)row_t * bh
                          : a.hist + (size_t)(a.ring ? ((s + 1) & 1) : (s + 1)) * bh;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int m = 2 * hf + i;
-            const float v = BWD ? (acc[i] + n0[SLOT][i]) * act_grad<ACT>(n1[SLOT][i])
-                                : activate<ACT>(acc[i] + n0[SLOT][i]);
-            if (col < H) {
-                hs[SLOT ^ 1][m][col] = v;
-                if (b0 + m < B) out[(size_t)(b0 + m) * H + col] = v;
-            }
+        for (int t = 0; t < CT; ++t)
+            if (on[t]) at(out, t) = last[t];
+    };
+    auto step = [&](int s, auto slot_c) {
+        constexpr int SLOT = decltype(slot_c)::value;   // s & 1: state buffer and operand slot
+        float acc[CT];
+        product(SLOT, acc);
+#pragma unroll
+        for (int t = 0; t < CT; ++t) {
+            const float v = BWD ? (acc[t] + n0[SLOT][t]) * act_grad<ACT>(n1[SLOT][t]) : activate<ACT>(acc[t] + n0[SLOT][t]);
+            last[t] = on[t] ? v : 0.f;
         }
+        put(SLOT ^ 1, last);
+        store_state(s);
         // The slot is free again: request the operands of step s + 2 into the same registers.
-        // Unconditional (the step index is clamped) so that the wait counts stay exact.
+        // Unconditional (the step index is clamped) so that the wait counts stay exact.  Both stay in
+        // front of the barrier, where they run beside the LDS writes: behind it they delay the next
+        // step's first products (128 units: 0.43 -> 0.48 us per step; 256: no gain).
         load_epi(s + 2, n0[SLOT], n1[SLOT]);
         lds_barrier();
     };
+    store_state(-1);
 
     // pairs of steps with no branch between them (exact wait counts), then the odd one out
     int s2 = 0;
@@ -191,24 +268,20 @@ __global__ __launch_bounds__(2 * HP) void rec_batch_mfma_kernel(RecMfmaArgs a) {
     }
     if (s2 < nsteps) step(s2, std::integral_constant<int, 0>{});
     __syncthreads();
-    const int cur = nsteps > 0 ? (nsteps & 1) : 0;
 
     if (!BWD) {
         if (a.h_last)
-            for (int i = tid; i < R4 * HP; i += NT) {
-                const int m = i / HP, j = i % HP;
-                if (b0 + m < B && j < H) a.h_last[(size_t)(b0 + m) * H + j] = hs[cur][m][j];
-            }
+#pragma unroll
+            for (int t = 0; t < CT; ++t)
+                if (on[t]) at(a.h_last, t) = last[t];            // T >= 1: the last step's value
         return;
     }
     if (a.dh0) {  // dh0 = delta_0 Wh: one more product, no epilogue
-        float acc[2];
-        if (cur == 0) product(std::integral_constant<int, 0>{}, acc);
-        else product(std::integral_constant<int, 1>{}, acc);
-        if (col < H)
+        float acc[CT];
+        product(nsteps > 0 ? (nsteps & 1) : 0, acc);
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-                if (b0 + 2 * hf + i < B) a.dh0[(size_t)(b0 + 2 * hf + i) * H + col] = acc[i];
+        for (int t = 0; t < CT; ++t)
+            if (on[t]) at(a.dh0, t) = acc[t];
     }
 }
 
@@ -223,11 +296,15 @@ __global__ __launch_bounds__(256) void gather_input_kernel(const int32_t* __rest
 }
 
 template <int ACT, bool BWD>
-hipError_t launch_hp(const RecMfmaArgs& a, hipStream_t s) {
-    dim3 grid((a.B + 3) / 4);
-    if (a.H <= 64) hipLaunchKernelGGL((rec_batch_mfma_kernel<ACT, BWD, 64>), grid, dim3(128), 0, s, a);
-    else if (a.H <= 128) hipLaunchKernelGGL((rec_batch_mfma_kernel<ACT, BWD, 128>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((rec_batch_mfma_kernel<ACT, BWD, 256>), grid, dim3(512), 0, s, a);
+hipError_t launch_nk(const RecMfmaArgs& a, hipStream_t s) {
+    const dim3 grid((a.B + 3) / 4);
+    switch ((a.H + 31) / 32) {
+#define RNN_NK(NK) \
+    case NK: hipLaunchKernelGGL((rec_batch_mfma_kernel<ACT, BWD, NK>), grid, dim3(64 * batch_waves(NK)), 0, s, a); break;
+        RNN_NK(1) RNN_NK(2) RNN_NK(3) RNN_NK(4) RNN_NK(5) RNN_NK(6) RNN_NK(7) RNN_NK(8)
+#undef RNN_NK
+        default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 
@@ -245,8 +322,8 @@ hipError_t launch_gather_input(const int32_t* x, const float* Wx, const float* b
 hipError_t launch_rec_batch_mfma(const RecMfmaArgs& a, bool bwd, hipStream_t s) {
     if (!rec_batch_mfma_supported(a.H, a.B)) return hipErrorInvalidValue;
     ProfileScope ps(bwd ? K_REC_BWD : K_REC_FWD, s);
-    if (!bwd) return a.act == 0 ? launch_hp<0, false>(a, s) : launch_hp<1, false>(a, s);
-    return a.act == 0 ? launch_hp<0, true>(a, s) : launch_hp<1, true>(a, s);
+    if (!bwd) return a.act == 0 ? launch_nk<0, false>(a, s) : launch_nk<1, false>(a, s);
+    return a.act == 0 ? launch_nk<0, true>(a, s) : launch_nk<1, true>(a, s);
 }
 
 }  // namespace rnn

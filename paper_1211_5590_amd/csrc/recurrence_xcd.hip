@@ -55,7 +55,6 @@ namespace rnn {
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int XT = 512;            // threads: 8 wavefronts
 constexpr int RB = 4;              // batch rows per group
@@ -88,17 +87,11 @@ __device__ __forceinline__ bool fresh(float4 v) {
            __float_as_uint(v.z) != kSentinel && __float_as_uint(v.w) != kSentinel;
 }
 
-// the words of a row's last four that start `d` further along, zeros behind them
-__device__ __forceinline__ float4 shifted(float4 v, int d) {
-    return make_float4(d == 0 ? v.x : d == 1 ? v.y : d == 2 ? v.z : v.w, d == 0 ? v.y : d == 1 ? v.z : d == 2 ? v.w : 0.f,
-                       d == 0 ? v.z : d == 1 ? v.w : 0.f, d == 0 ? v.w : 0.f);
-}
 // p[0..3] at 4-byte alignment; words from `left` on do not exist and read as zero (left <= 0: none exist)
 __device__ __forceinline__ float4 piece(const float* p, int left) {
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
     if (left >= 4) {
-        const f32x4u t = *reinterpret_cast<const f32x4u*>(p);
-        v = make_float4(t[0], t[1], t[2], t[3]);
+        v = load4u(p);
     } else {
         if (left > 0) v.x = p[0];
         if (left > 1) v.y = p[1];

@@ -10,7 +10,7 @@
 // A second kernel, one wavefront per vocabulary row, adds the token's partial rows in ascending
 // range order.  Delta is read once and every sum has a fixed order.
 //
-// Scan form (fallback when the scratch space is too small): every wavefront owns one
+// Scan form (a short id list): every wavefront owns one
 // vocabulary row and scans the whole id list for its token.
 #include "common.hpp"
 #include "internal.hpp"
@@ -72,13 +72,20 @@ __global__ __launch_bounds__(256) void dwx_tokens_kernel(const int32_t* __restri
     }
 }
 
+// four columns of a row from c on; SHORT: all of a row of fewer than four columns
+template <bool SHORT>
+__device__ __forceinline__ float4 columns(const float* __restrict__ row, int c, int H) {
+    if (!SHORT) return load4u(row + c);
+    return make_float4(row[0], H > 1 ? row[1] : 0.f, H > 2 ? row[2] : 0.f, 0.f);
+}
+
 constexpr int kGroupThreads = 512;
 constexpr int kRowsInFlight = 8;
 
 // One range of CL ids per workgroup: sort, group, sum.  part: compact partial rows
 // [range*CL + group][H]; slot[token][range] = group + 1, or -(n + 1) for a single occurrence at
 // row n, where the token occurs in the range (the table is zeroed before this kernel).
-template <int CL>
+template <int CL, bool SHORT>
 __global__ __launch_bounds__(kGroupThreads) void dwx_group_kernel(const int32_t* __restrict__ x,
                                                                   const float* __restrict__ Delta,
                                                                   float* __restrict__ part,
@@ -141,51 +148,30 @@ __global__ __launch_bounds__(kGroupThreads) void dwx_group_kernel(const int32_t*
             if (lane == 0) slot[(size_t)v * ranges + blockIdx.x] = -(base + (int)(unsigned)key[i0] + 1);
             continue;
         }
-        if ((H & 3) == 0) {
-            // 256 columns per pass as one float4 per lane, eight rows in flight, added in order
-            for (int c0 = 4 * lane; c0 < H; c0 += 4 * kWave) {
-                float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-                for (int i = i0; i < i1; i += kRowsInFlight) {
-                    float4 r[kRowsInFlight];
+        // 256 columns per pass, four per lane (at 4-byte alignment; the lane of a ragged end reads the
+        // row's last four), eight rows in flight, added in order
+        for (int c0 = 4 * lane; c0 < H; c0 += 4 * kWave) {
+            const int c = max(min(c0, H - 4), 0);
+            float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int i = i0; i < i1; i += kRowsInFlight) {
+                float4 r[kRowsInFlight];
 #pragma unroll
-                    for (int u = 0; u < kRowsInFlight; ++u) {
-                        const int ii = min(i + u, i1 - 1);
-                        r[u] = *reinterpret_cast<const float4*>(Delta + (size_t)(base + (int)(unsigned)key[ii]) * H + c0);
-                    }
+                for (int u = 0; u < kRowsInFlight; ++u)
+                    r[u] = columns<SHORT>(Delta + (size_t)(base + (int)(unsigned)key[min(i + u, i1 - 1)]) * H, c, H);
 #pragma unroll
-                    for (int u = 0; u < kRowsInFlight; ++u)
-                        if (i + u < i1) { acc.x += r[u].x; acc.y += r[u].y; acc.z += r[u].z; acc.w += r[u].w; }
-                }
-                *reinterpret_cast<float4*>(part + ((size_t)base + grp) * H + c0) = acc;
+                for (int u = 0; u < kRowsInFlight; ++u)
+                    if (i + u < i1) { acc.x += r[u].x; acc.y += r[u].y; acc.z += r[u].z; acc.w += r[u].w; }
             }
-        } else {
-            for (int c0 = 0; c0 < H; c0 += kColsPerPass) {
-                float acc[kQ];
-#pragma unroll
-                for (int q = 0; q < kQ; ++q) acc[q] = 0.f;
-                for (int i = i0; i < i1; ++i) {
-                    const float* row = Delta + (size_t)(base + (int)(unsigned)key[i]) * H;
-#pragma unroll
-                    for (int q = 0; q < kQ; ++q) {
-                        const int col = c0 + q * kWave + lane;
-                        if (col < H) acc[q] += row[col];
-                    }
-                }
-#pragma unroll
-                for (int q = 0; q < kQ; ++q) {
-                    const int col = c0 + q * kWave + lane;
-                    if (col < H) part[((size_t)base + grp) * H + col] = acc[q];
-                }
-            }
+            store4u(part + ((size_t)base + grp) * H + c0, shifted(acc, c0 - c), H - c0);
         }
         if (lane == 0) slot[(size_t)v * ranges + blockIdx.x] = grp + 1;
     }
 }
 
 // dWx[v] = sum over the ranges (ascending) of the token's partial rows; zero row if none.
-// One wavefront per (token, chunk of 256 columns) when rows are 16-byte aligned (VEC), else
-// per token with scalar columns; eight rows in flight, added in range order.
-template <bool VEC>
+// One wavefront per (token, chunk of 256 columns), four columns per lane as in dwx_group_kernel; eight
+// rows in flight, added in range order.
+template <bool SHORT>
 __global__ __launch_bounds__(256) void dwx_gather_kernel(const float* __restrict__ part,
                                                          const int32_t* __restrict__ slot,
                                                          const float* __restrict__ Delta,
@@ -195,75 +181,41 @@ __global__ __launch_bounds__(256) void dwx_gather_kernel(const float* __restrict
     const long long task = (long long)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
     const int v = (int)(task / col_chunks), chunk = (int)(task % col_chunks);
     if (v >= NV) return;
-    const int c0 = VEC ? chunk * 4 * kWave + 4 * lane : 0;
-    float4 acc4 = make_float4(0.f, 0.f, 0.f, 0.f);
-    float acc[kQ];
-#pragma unroll
-    for (int q = 0; q < kQ; ++q) acc[q] = 0.f;
+    const int c0 = chunk * 4 * kWave + 4 * lane, c = max(min(c0, H - 4), 0);
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     bool any = false;
-    for (int pass0 = 0; pass0 < (VEC ? 1 : (H + kColsPerPass - 1) / kColsPerPass); ++pass0) {
-        const int cs = pass0 * kColsPerPass;
-        if (!VEC) {
+    for (int r0 = 0; r0 < ranges; r0 += kWave) {     // 64 table entries per look
+        const int r = r0 + lane;
+        const int sl = r < ranges ? slot[(size_t)v * ranges + r] : 0;
+        unsigned long long mask = __ballot(sl != 0);
+        any = any || mask != 0;
+        while (mask) {
+            const float* rows[kRowsInFlight];
+            int cnt = 0;
 #pragma unroll
-            for (int q = 0; q < kQ; ++q) acc[q] = 0.f;
-        }
-        for (int r0 = 0; r0 < ranges; r0 += kWave) {     // 64 table entries per look
-            const int r = r0 + lane;
-            const int sl = r < ranges ? slot[(size_t)v * ranges + r] : 0;
-            unsigned long long mask = __ballot(sl != 0);
-            any = any || mask != 0;
-            while (mask) {
-                const float* rows[kRowsInFlight];
-                int cnt = 0;
-#pragma unroll
-                for (int u = 0; u < kRowsInFlight; ++u) {
-                    rows[u] = Delta;                       // placeholder, not added
-                    if (mask) {
-                        const int src = __ffsll((long long)mask) - 1;
-                        mask &= mask - 1;
-                        const int e = __shfl(sl, src, kWave);
-                        rows[u] = e > 0 ? part + ((size_t)(r0 + src) * CL + (e - 1)) * H
-                                        : Delta + (size_t)(-e - 1) * H;
-                        cnt = u + 1;
-                    }
-                }
-                if (VEC) {
-                    float4 t[kRowsInFlight];
-#pragma unroll
-                    for (int u = 0; u < kRowsInFlight; ++u)
-                        t[u] = c0 < H ? *reinterpret_cast<const float4*>(rows[u] + c0) : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-                    for (int u = 0; u < kRowsInFlight; ++u)
-                        if (u < cnt) { acc4.x += t[u].x; acc4.y += t[u].y; acc4.z += t[u].z; acc4.w += t[u].w; }
-                } else {
-                    for (int u = 0; u < cnt; ++u) {
-#pragma unroll
-                        for (int q = 0; q < kQ; ++q) {
-                            const int col = cs + q * kWave + lane;
-                            if (col < H) acc[q] += rows[u][col];
-                        }
-                    }
+            for (int u = 0; u < kRowsInFlight; ++u) {
+                rows[u] = Delta;                       // placeholder, not added
+                if (mask) {
+                    const int src = __ffsll((long long)mask) - 1;
+                    mask &= mask - 1;
+                    const int e = __shfl(sl, src, kWave);
+                    rows[u] = e > 0 ? part + ((size_t)(r0 + src) * CL + (e - 1)) * H
+                                    : Delta + (size_t)(-e - 1) * H;
+                    cnt = u + 1;
                 }
             }
-        }
-        if (beta && !any) return;         // accumulate mode leaves untouched rows alone
-        if (VEC) {
-            if (c0 < H) {
-                float4* dst = reinterpret_cast<float4*>(dWx + (size_t)v * H + c0);
-                if (beta) { const float4 o = *dst; acc4.x += o.x; acc4.y += o.y; acc4.z += o.z; acc4.w += o.w; }
-                *dst = acc4;
-            }
-        } else {
+            float4 t[kRowsInFlight];
 #pragma unroll
-            for (int q = 0; q < kQ; ++q) {
-                const int col = cs + q * kWave + lane;
-                if (col < H) {
-                    float* dst = dWx + (size_t)v * H + col;
-                    *dst = beta ? *dst + acc[q] : acc[q];
-                }
-            }
+            for (int u = 0; u < kRowsInFlight; ++u) t[u] = columns<SHORT>(rows[u], c, H);
+#pragma unroll
+            for (int u = 0; u < kRowsInFlight; ++u)
+                if (u < cnt) { acc.x += t[u].x; acc.y += t[u].y; acc.z += t[u].z; acc.w += t[u].w; }
         }
     }
+    if ((beta && !any) || c0 >= H) return;         // accumulate mode leaves untouched rows alone
+    float* dst = dWx + (size_t)v * H;
+    if (beta) { const float4 o = columns<SHORT>(dst, c, H); acc.x += o.x; acc.y += o.y; acc.z += o.z; acc.w += o.w; }
+    store4u(dst + c0, shifted(acc, c0 - c), H - c0);
 }
 
 __global__ void zero_table_kernel(int32_t* p, size_t n) {
@@ -298,15 +250,15 @@ int dwx_range_len(int N) {
     return cl;
 }
 int dwx_ranges(int N) { const int cl = dwx_range_len(N); return (N + cl - 1) / cl; }
+size_t dwx_scratch_floats(int N, int H) { return (size_t)dwx_ranges(N) * dwx_range_len(N) * H; }
 size_t dwx_table_ints(int N, int NV) { return (size_t)dwx_ranges(N) * NV; }
 
 hipError_t launch_dwx_tokens(const int32_t* x, const float* Delta, float* dWx, int N, int NV, int H,
-                             int beta, float* scratch, size_t scratch_floats, int32_t* slot_table,
-                             hipStream_t s) {
+                             int beta, float* scratch, int32_t* slot_table, hipStream_t s) {
     const int rows_per_block = 256 / kWave;
     const int blocks = (NV + rows_per_block - 1) / rows_per_block;
     const int cl = dwx_range_len(N), ranges = dwx_ranges(N);
-    const bool grouped = scratch && slot_table && (size_t)ranges * cl * H <= scratch_floats;
+    const bool grouped = scratch && slot_table;
     if (!grouped) {
         ProfileScope ps(K_DWX_TOKENS, s);
         hipLaunchKernelGGL(dwx_tokens_kernel, dim3(blocks), dim3(256), 0, s, x, Delta, dWx, N, NV, H, beta);
@@ -318,29 +270,30 @@ hipError_t launch_dwx_tokens(const int32_t* x, const float* Delta, float* dWx, i
         size_t zb = (n + 2047) / 2048;
         if (zb > 1024) zb = 1024;
         hipLaunchKernelGGL(zero_table_kernel, dim3((unsigned)zb), dim3(256), 0, s, slot_table, n);
+#define RNN_GROUP(CL)                                                                                    \
+    do {                                                                                                 \
+        if (H >= 4) hipLaunchKernelGGL((dwx_group_kernel<CL, false>), dim3(ranges), dim3(kGroupThreads), 0, s, x, Delta, scratch, slot_table, N, NV, H); \
+        else hipLaunchKernelGGL((dwx_group_kernel<CL, true>), dim3(ranges), dim3(kGroupThreads), 0, s, x, Delta, scratch, slot_table, N, NV, H);         \
+    } while (0)
         switch (cl) {
-            case 256: hipLaunchKernelGGL(dwx_group_kernel<256>, dim3(ranges), dim3(kGroupThreads), 0, s, x, Delta, scratch, slot_table, N, NV, H); break;
-            case 512: hipLaunchKernelGGL(dwx_group_kernel<512>, dim3(ranges), dim3(kGroupThreads), 0, s, x, Delta, scratch, slot_table, N, NV, H); break;
-            case 1024: hipLaunchKernelGGL(dwx_group_kernel<1024>, dim3(ranges), dim3(kGroupThreads), 0, s, x, Delta, scratch, slot_table, N, NV, H); break;
-            case 2048: hipLaunchKernelGGL(dwx_group_kernel<2048>, dim3(ranges), dim3(kGroupThreads), 0, s, x, Delta, scratch, slot_table, N, NV, H); break;
-            default: hipLaunchKernelGGL(dwx_group_kernel<4096>, dim3(ranges), dim3(kGroupThreads), 0, s, x, Delta, scratch, slot_table, N, NV, H); break;
+            case 256: RNN_GROUP(256); break;
+            case 512: RNN_GROUP(512); break;
+            case 1024: RNN_GROUP(1024); break;
+            case 2048: RNN_GROUP(2048); break;
+            default: RNN_GROUP(4096); break;
         }
+#undef RNN_GROUP
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     ProfileScope ps(K_DWX_TOKENS, s);
-    const bool vec = H % 4 == 0 && (reinterpret_cast<uintptr_t>(dWx) & 15u) == 0 &&
-                     (reinterpret_cast<uintptr_t>(Delta) & 15u) == 0 && (reinterpret_cast<uintptr_t>(scratch) & 15u) == 0;
-    if (vec) {
-        const int col_chunks = (H + 4 * kWave - 1) / (4 * kWave);
-        const long long tasks = (long long)NV * col_chunks;
-        const unsigned gb = (unsigned)((tasks + rows_per_block - 1) / rows_per_block);
-        hipLaunchKernelGGL(dwx_gather_kernel<true>, dim3(gb), dim3(256), 0, s, scratch, slot_table, Delta, dWx,
-                           NV, H, ranges, cl, beta, col_chunks);
-    } else {
-        hipLaunchKernelGGL(dwx_gather_kernel<false>, dim3(blocks), dim3(256), 0, s, scratch, slot_table, Delta,
-                           dWx, NV, H, ranges, cl, beta, 1);
-    }
+    const int col_chunks = (H + 4 * kWave - 1) / (4 * kWave);
+    const long long tasks = (long long)NV * col_chunks;
+    const unsigned gb = (unsigned)((tasks + rows_per_block - 1) / rows_per_block);
+    if (H >= 4) hipLaunchKernelGGL(dwx_gather_kernel<false>, dim3(gb), dim3(256), 0, s, scratch, slot_table, Delta, dWx,
+                                   NV, H, ranges, cl, beta, col_chunks);
+    else hipLaunchKernelGGL(dwx_gather_kernel<true>, dim3(gb), dim3(256), 0, s, scratch, slot_table, Delta, dWx,
+                            NV, H, ranges, cl, beta, col_chunks);
     return hipGetLastError();
 }
 

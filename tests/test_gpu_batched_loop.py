@@ -1,0 +1,52 @@
+"""The batched loop with register-resident weights at every number of 32-unit slabs it is built for, on
+both sides of every slab edge, with missing batch rows, both directions and activations, against the
+oracle; and infinities, which its three-way bf16 split cannot hold."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1211_5590_amd as rnn
+import rnn_inputs as ri
+from gpu_harness import Runner, compare
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("H", [1, 2, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 224, 225, 255, 256])
+def test_every_slab_count(H):
+    for n, (B, T) in enumerate(((5, 1), (8, 2), (7, 12))):
+        case = ri.make_case(40, H, 30, T, B, act=n % 2, with_h0=n != 1, with_dh_last=n >= 1,
+                            wdist=("normal", 0.7 / np.sqrt(H)), bias_std=0.1, seed=700 + 5 * H + n)
+        r = Runner(case)
+        assert rnn.rnn_recurrence_variant(r.dims) == "batch_mfma"
+        r.step()
+        compare(r.results(), oracle.fwd_bptt(case, h0=case.get("h0"), dh_last=case.get("dh_last")))
+
+
+@pytest.mark.parametrize("where", ["matrix", "state", "large"])
+def test_infinities_give_what_float32_gives(where):
+    H, B, T = 70, 6, 3
+    g = torch.Generator().manual_seed(1)
+    Wh = torch.rand(H, H, generator=g) * 0.2 - 0.1
+    h = torch.rand(B, H, generator=g) * 0.5 + 0.2
+    U = torch.rand(T, B, H, generator=g) - 0.5
+    if where == "matrix":
+        Wh[3, 5], Wh[9, 60] = float("inf"), float("-inf")
+    elif where == "state":
+        h[2, 7] = float("inf")
+        Wh[:, 7] = Wh[:, 7].abs() + 0.01
+    else:
+        Wh[4, 4] = 3.4e38                      # rounds to infinity in bf16
+    p = dict(Wx=torch.eye(H).cuda(), Wh=Wh.cuda(), b=torch.zeros(H).cuda(), V=torch.zeros(H, 2).cuda(), c=torch.zeros(2).cuda())
+    dims = rnn.Dims(H, H, 2, T, B, rnn.INPUT_DENSE, rnn.ACT_TANH, rnn.LOSS_LINEAR_MSE, 0)
+    ws = torch.empty(rnn.rnn_workspace_bytes(dims), dtype=torch.uint8, device="cuda")
+    rnn.rnn_workspace_init(dims, ws)
+    hist = torch.zeros(T + 1, B, H, device="cuda")
+    rnn.rnn_forward(dims, p, U.cuda(), h.cuda(), hist, None, ws)
+    got = hist.cpu()
+    for t in range(T):
+        ref = torch.tanh(got[t] @ Wh.t() + U[t])
+        assert torch.equal(torch.isnan(got[t + 1]), torch.isnan(ref)), t
+        fine = ~torch.isnan(ref)
+        assert float((got[t + 1][fine] - ref[fine]).abs().max()) < 1e-5

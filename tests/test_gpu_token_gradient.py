@@ -1,0 +1,27 @@
+"""Gradient of the token-indexed input matrix at the row widths where its four-columns-per-lane kernels
+change form (fewer than four columns, ragged ends, more than one 256-column chunk), with a vocabulary
+smaller and larger than the hidden size, overwriting and accumulating, against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1211_5590_amd as rnn
+import rnn_inputs as ri
+from gpu_harness import Runner, grad_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("H,NV", [(1, 50), (2, 9), (3, 300), (4, 70), (5, 40), (255, 60), (257, 30), (261, 900), (514, 20)])
+def test_token_gradient_at_this_row_width(H, NV):
+    case = ri.make_case(NV, H, NV, 21, 29, wdist=("normal", 0.5 / np.sqrt(H)), bias_std=0.1, seed=40 + H)
+    ref = oracle.fwd_bptt(case)
+    r = Runner(case)
+    r.step()
+    once = r.results()
+    grad_close("dWx", once["dWx"], ref["dWx"])
+    unseen = np.setdiff1d(np.arange(NV), np.unique(case["x"]))
+    assert not once["dWx"][unseen].any()
+    r.set_flags(rnn.FLAG_ACCUMULATE | rnn.FLAG_BPTT_RECOMPUTE)
+    r.bptt()
+    grad_close("2x dWx", r.results()["dWx"], 2.0 * ref["dWx"])
