@@ -332,8 +332,10 @@ int rnn_gauss_newton_vec(const rnn_dims *dims, const rnn_params *params, const r
  *
  * rnn_mlp_train runs n_batches consecutive batches in one call (the paper's function objects
  * offer the same as a repeat count, "several iterations at once"): nothing returns to the host
- * between batches, every batch is 2 n_hidden + 2 launches on hip_stream (one more with more than
- * 16 classes).
+ * between batches.  With at most one hidden layer (of at most 1024 units), 16 classes, 64 rows per batch
+ * and 896 inputs (a multiple of 4) up to 1024 batches are one launch, which keeps the model on chip and
+ * is cooperative with a hidden layer; otherwise every batch is 2 n_hidden + 2 launches on hip_stream (one
+ * more with more than 16 classes).
  *   dims     host struct; act = RNN_ACT_* of the hidden layers; flags: RNN_FLAG_SYNC only;
  *            n_hidden + 1 <= RNN_MLP_MAX_LAYERS; batch <= 1024 (else RNN_EUNSUPPORTED)
  *   params   host struct of device pointers, layer l = 0..n_hidden (input side first):

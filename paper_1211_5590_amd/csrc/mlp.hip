@@ -6,7 +6,8 @@
 //     W_l <- W_l - lr dloss/dW_l,  b_l <- b_l - lr dloss/db_l      after every batch.
 //
 // At these sizes a step moves a few megabytes of weights and computes almost nothing, so what it
-// costs is launches and memory round trips.  A step is 2 L + 2 launches (L hidden layers: L + 1
+// costs is launches and memory round trips.  With at most one hidden layer all batches of a call share
+// one launch (mlp_one_kernel below).  Otherwise a step is 2 L + 2 launches (L hidden layers: L + 1
 // forward, the last of them with the loss in its epilogue when there are at most 16 classes, L
 // backward, and ONE update of all layers, which also adds up the batch's loss), each
 // built like the batched recurrence's step kernel to pay one round trip: a workgroup owns a
@@ -316,6 +317,339 @@ __global__ __launch_bounds__(1024) void mlp_ce_kernel(float* __restrict__ Z, con
     }
 }
 
+// ---- all batches of a call in one launch: at most one hidden layer ------------------------------------
+//
+// What bounds the launches above at these sizes is the launches themselves (4 us each, 4 per batch with
+// one hidden layer).  Here the model stays in registers from batch to batch: workgroup p owns hidden units
+// 16p .. 16p+15 with their rows of W_1 (or, without a hidden layer, one workgroup owns the classes), its
+// eight wavefronts the blocks of 16 inputs w, w + 8, ...  A lane's registers hold W[n = lane % 16]
+// [k = 4 (lane / 16) + e] of a block, which is the operand v_mfma_f32_16x16x4_f32 wants for the forward
+// product (walking k in that order) and also the layout in which it leaves dW^T = X^T dZ: the update
+// is a subtraction in place.  Of W_2 a workgroup keeps its 16 columns.  The only thing workgroups
+// exchange per batch is logits: every workgroup publishes its share of them and either (few
+// words: P * batch * classes <= ONE_HOP) everyone adds up all shares and forms the same softmax, or the
+// rows are dealt to the workgroups, which add them up and publish dZ.  Words carry the batch's number
+// as their tag (tagged_store).  The shares alternate between two boxes: a workgroup can write share i+2
+// only when it has everyone's share i+1, which they publish after they have read share i.  Sums run in
+// a fixed order.
+//
+// Per batch, before -> now: 784-500-10 single examples 16.7 -> 5.5 us, 10 rows 18.1 -> 8.6, 60 rows 22.4 -> 19;
+// 784-10 single examples 8.1 -> 1.9 us, 60 rows 13.7 -> 12.6.
+constexpr int OT = 512, OW = OT / kWave, ONE_HOP = 2048, ONE_BATCHES = 1024;
+constexpr int ONE_SPINS = 1 << 26;   // a bound, not a time-out: the launch is cooperative
+
+struct MlpOneArgs {
+    const float* X; const int32_t* y;
+    float *W1, *b1, *W2, *b2;        // no hidden layer: W1, b1 are the output layer's
+    float* losses;                   // nullable
+    unsigned long long *zbox, *dbox; // [2][P][B * O] shares of the logits; [B][O + 1] dZ and row losses
+    int B, K, H, O, P, act, rows_per, n_batches;   // rows_per: rows a workgroup adds up (B: one hop)
+    float lr;
+};
+
+// K is covered by 8 * KB blocks of 16 inputs, the batch by TILES tiles of 16 rows.  TILES = 0: one example,
+// multiplied on the vector units (a matrix instruction would compute 16 rows for it).
+template <bool HID, int KB, int TILES>
+__global__ __launch_bounds__(OT, 2) void mlp_one_kernel(const MlpOneArgs a) {
+    constexpr bool SINGLE = TILES == 0;
+    constexpr int MT = SINGLE ? 1 : TILES, MR = SINGLE ? 1 : 16 * MT;
+    __shared__ float red[OW][4 * MT][kWave];
+    __shared__ float a_s[MR][17], dz_s[MR][17], d1_s[MR][17], w2_s[16][17], b1_s[16], b2_s[16], rowloss[64];
+    __shared__ float zp[ONE_HOP];
+    __shared__ int s_fail;
+    const int tid = threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int g = lane / 16, nn = lane % 16;
+    const int B = a.B, K = a.K, O = a.O, P = a.P, wg = blockIdx.x;
+    const int N1 = HID ? a.H : O, n0 = wg * 16, n1 = min(n0 + nn, N1 - 1);
+    const bool n_on = n0 + nn < N1;
+
+    float w[KB][4];
+#pragma unroll
+    for (int b = 0; b < KB; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int k = 16 * (wave + OW * b) + 4 * g + e;
+            const float v = a.W1[(size_t)n1 * K + min(k, K - 1)];
+            w[b][e] = n_on && k < K ? v : 0.f;
+        }
+    if (tid < 16) {
+        b1_s[tid] = n0 + tid < N1 ? a.b1[n0 + tid] : 0.f;
+        b2_s[tid] = HID && tid < O ? a.b2[tid] : 0.f;
+    }
+    if (HID && tid < 256) {
+        const int c = tid / 16, n = tid % 16;
+        w2_s[c][n] = c < O && n0 + n < a.H ? a.W2[(size_t)c * a.H + n0 + n] : 0.f;
+    }
+    if (tid == 0) s_fail = 0;
+
+    // The batch as the forward product reads it: row m = 16 mt + nn, inputs 4 g .. 4 g + 3 of each block;
+    // as the update reads it: row m = 4 u + g, input nn of each block.  Rows past the batch repeat its last
+    // one (their results are dropped, their dZ is zero).  A block past the end of a row reads the next row
+    // (past the batch: zeros, by the request's bound) and meets weights that are kept zero.  Buffer
+    // requests: one lane offset per row for all blocks, the block in the scalar base.
+    float4 xa[MT][KB];
+    unsigned row_a[MT], row_t[4 * MT];   // bytes
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) row_a[mt] = (unsigned)(min(16 * mt + nn, B - 1) * K + 4 * g) * 4u;
+#pragma unroll
+    for (int u = 0; u < 4 * MT; ++u) row_t[u] = (unsigned)(min(4 * u + g, B - 1) * K + nn) * 4u;
+    auto window = [&](int batch, int b) {
+        const int k = min(16 * (wave + OW * b), B * K);
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.X + (size_t)batch * B * K + k), 0, (B * K - k) * 4, 0x00020000);
+    };
+    auto load_rows = [&](int batch) {
+#pragma unroll
+        for (int b = 0; b < KB; ++b) {
+            const auto x = window(batch, b);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+                xa[mt][b] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(x, row_a[mt], 0, 0));
+        }
+    };
+    auto load_t = [&](int batch, int b, float (&v)[4 * MT]) {
+        const auto x = window(batch, b);
+#pragma unroll
+        for (int u = 0; u < 4 * MT; ++u) v[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(x, row_t[u], 0, 0));
+    };
+    // which words this thread writes and waits for: the same for every batch
+    const int r0 = HID ? (a.rows_per == B ? 0 : min(wg * a.rows_per, B)) : 0;
+    const int r1 = HID ? min(r0 + a.rows_per, B) : B, per = (r1 - r0) * O;
+    int zm[2], zc[2], zat[4], dm[4], dc[4];   // -1: no such word
+    if (HID) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) { const int v = tid + OT * u; zm[u] = v < B * O ? v / O : -1; zc[u] = v % O; }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int v = tid + OT * u;
+            zat[u] = v < per * P ? (v / per) * B * O + r0 * O + v % per : -1;
+            dm[u] = v < B * (O + 1) ? v / (O + 1) : -1;
+            dc[u] = v % (O + 1);
+        }
+    }
+    auto await = [&](const unsigned long long* box, const long long (&at)[4], unsigned tag, unsigned long long (&word)[4]) {
+        if (!wait4(box, at, tag, ONE_SPINS, word)) s_fail = 1;
+    };
+    load_rows(0);
+    __syncthreads();
+
+    for (int i = 0; i < a.n_batches; ++i) {
+        const unsigned tag = (unsigned)i + 1u;
+        // ---- forward product of this workgroup's 16 units ------------------------------------------
+        float4 xc[SINGLE ? KB : 1];    // the single example, for the update
+        if constexpr (SINGLE) {
+            float sum[2] = {0.f, 0.f};
+#pragma unroll
+            for (int b = 0; b < KB; ++b) {
+                const float4 v = xc[b] = xa[0][b];
+                sum[b & 1] = fmaf(v.x, w[b][0], sum[b & 1]); sum[b & 1] = fmaf(v.y, w[b][1], sum[b & 1]);
+                sum[b & 1] = fmaf(v.z, w[b][2], sum[b & 1]); sum[b & 1] = fmaf(v.w, w[b][3], sum[b & 1]);
+            }
+            const float all = swap32_sum(swap16_sum(sum[0] + sum[1]));
+            if (g == 0) red[wave][0][nn] = all;
+        } else {
+            f32x4 acc[MT];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int b = 0; b < KB; ++b)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) {
+                        const float4 v = xa[mt][b];
+                        acc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w, w[b][e], acc[mt], 0, 0, 0);
+                    }
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) red[wave][4 * mt + e][lane] = acc[mt][e];
+        }
+        // The update's operands: all of them now, where there are few, else block by block later; and
+        // the next batch's rows.  Both arrive while the workgroups exchange their shares.
+        constexpr bool EARLY = MT == 1;
+        float xt[EARLY ? KB : 2][4 * MT];
+        if (!SINGLE)
+#pragma unroll
+            for (int b = 0; b < (EARLY ? KB : 1); ++b) load_t(i, b, xt[b]);
+        if (MT < 4) load_rows(min(i + 1, a.n_batches - 1));   // (four tiles: no registers for both; see the end)
+        lds_barrier();
+        for (int v = tid; v < MR * 16; v += OT) {
+            const int q = v / kWave, l = v % kWave, m = 16 * (q / 4) + 4 * (l / 16) + q % 4, n = l % 16;
+            float sum = b1_s[n];
+#pragma unroll
+            for (int ww = 0; ww < OW; ++ww) sum += red[ww][q][l];
+            const bool on = m < B && n0 + n < N1;
+            if (HID) sum = a.act == RNN_ACT_SIGMOID ? sigmoidf_fast(sum) : tanhf_fast(sum);
+            a_s[m][n] = on ? sum : 0.f;
+        }
+        lds_barrier();
+        // ---- logits of rows [r0, r1), shares of all workgroups added in order ------------------------
+        if (HID) {
+            unsigned long long* zb = a.zbox + (size_t)(i & 1) * P * B * O;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (zm[u] < 0) continue;
+                float sum = 0.f;
+#pragma unroll
+                for (int n = 0; n < 16; ++n) sum = fmaf(a_s[zm[u]][n], w2_s[zc[u]][n], sum);
+                tagged_store(zb + (size_t)wg * B * O + tid + OT * u, tag, sum);
+            }
+            if (zat[0] >= 0) {
+                unsigned long long word[4];
+                await(zb, {zat[0], zat[1], zat[2], zat[3]}, tag, word);
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (zat[u] >= 0) zp[tid + OT * u] = tagged_value(word[u]);
+            }
+            lds_barrier();
+        }
+        // ---- softmax, loss and dZ of those rows: 16 lanes per row -------------------------------------
+        const int32_t* yb = a.y + (size_t)i * B;
+        for (int r = r0 + 4 * wave + g; r < r0 + ((r1 - r0 + 3) / 4) * 4; r += 4 * OW) {
+            const bool ok = r < r1 && nn < O;
+            float z = 0.f;
+            if (HID) {
+                z = b2_s[nn];
+                if (ok) {
+                    const float* q = zp + (r - r0) * O + nn;
+#pragma unroll 8
+                    for (int p = 0; p < P; ++p) z += q[p * per];
+                }
+            } else if (ok) {
+                z = a_s[r][nn];
+            }
+            const int yy = r < r1 ? yb[r] : -1;
+            const float mx = max16(ok ? z : -INFINITY);
+            const float lse = mx + __logf(sum16(ok ? __expf(z - mx) : 0.f));
+            const float loss = lse - sum16(ok && nn == yy ? z : 0.f);
+            const float d = ok ? (__expf(z - lse) - (nn == yy ? 1.f : 0.f)) * (1.0f / (float)B) : 0.f;
+            if (HID && a.rows_per != B) {
+                if (ok) tagged_store(a.dbox + (size_t)r * (O + 1) + nn, tag, d);
+                if (r < r1 && nn == 0) tagged_store(a.dbox + (size_t)r * (O + 1) + O, tag, loss);
+            } else if (r < r1) {
+                dz_s[r][nn] = d;
+                if (nn == 0) rowloss[r] = loss;
+            }
+        }
+        if (HID && a.rows_per != B) {
+            unsigned long long word[4];
+            if (dm[0] >= 0) {
+                long long at[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) at[u] = dm[u] < 0 ? -1 : tid + OT * u;
+                await(a.dbox, at, tag, word);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (dm[u] < 0) continue;
+                    if (dc[u] < O) dz_s[dm[u]][dc[u]] = tagged_value(word[u]);
+                    else rowloss[dm[u]] = tagged_value(word[u]);
+                }
+            }
+        }
+        // columns and rows that do not exist: zero (the products below run over whole tiles)
+        for (int v = tid; v < MR * 16; v += OT)
+            if (v / 16 >= B || v % 16 >= O) dz_s[v / 16][v % 16] = 0.f;
+        lds_barrier();
+        if (s_fail) {                // cannot happen while the workgroups are co-resident
+            if (wg == 0 && tid == 0 && a.losses)
+                for (int j = i; j < a.n_batches; ++j) a.losses[j] = __uint_as_float(0x7fc00000u);
+            return;
+        }
+        if (wg == 0 && wave == 0 && a.losses) {
+            const float sum = sum64(lane < B ? rowloss[lane] : 0.f);
+            if (lane == 0) a.losses[i] = sum / (float)B;
+        }
+        // ---- dZ of the hidden units -------------------------------------------------------------------
+        if (HID) {
+            for (int v = tid; v < MR * 16; v += OT) {
+                const int m = v / 16, n = v % 16;
+                float sum = 0.f;
+#pragma unroll
+                for (int c = 0; c < 16; ++c) sum = fmaf(dz_s[m][c], w2_s[c][n], sum);
+                const float h = a_s[m][n];
+                d1_s[m][n] = m < B && n0 + n < N1 ? sum * (a.act == RNN_ACT_SIGMOID ? act_grad<0>(h) : act_grad<1>(h)) : 0.f;
+            }
+            lds_barrier();
+        }
+        const float(*d1)[17] = HID ? d1_s : dz_s;
+        // ---- updates ----------------------------------------------------------------------------------
+#pragma unroll
+        for (int b = 0; b < KB; ++b) {
+            f32x4 dw = {0.f, 0.f, 0.f, 0.f};
+            if constexpr (SINGLE) {
+                const float d = d1[0][nn];
+                dw = (f32x4){xc[b].x * d, xc[b].y * d, xc[b].z * d, xc[b].w * d};
+            } else {
+                if (!EARLY && b + 1 < KB) load_t(i, b + 1, xt[(b + 1) & 1]);
+                if (!EARLY) __builtin_amdgcn_sched_barrier(0);       // one block ahead and no more
+#pragma unroll
+                for (int u = 0; u < 4 * MT; ++u)
+                    dw = __builtin_amdgcn_mfma_f32_16x16x4f32(xt[EARLY ? b : b & 1][u], d1[4 * u + g][nn], dw, 0, 0, 0);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[b][e] -= a.lr * dw[e];
+            if (16 * (wave + OW * b) + 16 > K)                   // the ragged last block: K % 4 == 0
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[b][e] = 16 * (wave + OW * b) + 4 * g < K ? w[b][e] : 0.f;
+        }
+        if (wave == OW - 1 || (HID && wave >= OW - 3)) {
+            if (wave == OW - 1) {            // b_1 (no hidden layer: b)
+                float sum = 0.f;
+                for (int m = g; m < MR; m += 4) sum += d1[m][nn];
+                sum = swap32_sum(swap16_sum(sum));
+                if (g == 0) b1_s[nn] -= a.lr * sum;
+            } else if (wave == OW - 2) {     // b_2: the same in every workgroup
+                float sum = 0.f;
+                for (int m = g; m < MR; m += 4) sum += dz_s[m][nn];
+                sum = swap32_sum(swap16_sum(sum));
+                if (g == 0) b2_s[nn] -= a.lr * sum;
+            } else {                         // W_2's columns: rows 4 g + e, column nn
+                f32x4 dw = {0.f, 0.f, 0.f, 0.f};
+                if constexpr (SINGLE) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) dw[e] = dz_s[0][4 * g + e] * a_s[0][nn];
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 4 * MT; ++u) dw = __builtin_amdgcn_mfma_f32_16x16x4f32(dz_s[4 * u + g][nn], a_s[4 * u + g][nn], dw, 0, 0, 0);
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w2_s[4 * g + e][nn] -= a.lr * dw[e];
+            }
+        }
+        if (MT == 4) load_rows(min(i + 1, a.n_batches - 1));
+        lds_barrier();
+    }
+#pragma unroll
+    for (int b = 0; b < KB; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int k = 16 * (wave + OW * b) + 4 * g + e;
+            if (n_on && k < K) a.W1[(size_t)n1 * K + k] = w[b][e];
+        }
+    if (tid < 16) {
+        if (n0 + tid < N1) a.b1[n0 + tid] = b1_s[tid];
+        if (HID && wg == 0 && tid < O) a.b2[tid] = b2_s[tid];
+    }
+    if (HID && tid < 256) {
+        const int c = tid / 16, n = tid % 16;
+        if (c < O && n0 + n < a.H) a.W2[(size_t)c * a.H + n0 + n] = w2_s[c][n];
+    }
+}
+
+// Shapes the one-launch kernel holds: rows of whole 16-byte pieces, 7 blocks of 16 inputs per wavefront, 64 rows, 16 classes, and no
+// more hidden units than 64 workgroups own (beyond that polling the shares costs what launches do).
+bool mlp_one_supported(const rnn_mlp_dims* d) {
+    return d->n_hidden <= 1 && d->out_dim <= 16 && d->batch <= 64 && d->in_dim % 4 == 0 && d->in_dim <= 896 && (d->n_hidden == 0 || d->hidden <= 1024);
+}
+int mlp_one_wgs(const rnn_mlp_dims* d) { return d->n_hidden ? (d->hidden + 15) / 16 : 1; }
+
+template <bool HID>
+const void* mlp_one_pick(int K, int B) {
+#define RNN_ONE(KB) (B == 1 ? (const void*)mlp_one_kernel<HID, KB, 0> : B <= 16 ? (const void*)mlp_one_kernel<HID, KB, 1> : B <= 32 ? (const void*)mlp_one_kernel<HID, KB, 2> : (const void*)mlp_one_kernel<HID, KB, 4>)
+    return K <= 256 ? RNN_ONE(2) : RNN_ONE(7);
+#undef RNN_ONE
+}
+
 struct Widths { int w[RNN_MLP_MAX_LAYERS + 2]; int layers; };
 
 bool mlp_dims_ok(const rnn_mlp_dims* d) {
@@ -342,7 +676,7 @@ inline size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 
 // workspace: activations of the hidden layers, logits / dZ of the output layer, two dZ buffers of
 // the hidden width
-struct MlpPlan { size_t act[RNN_MLP_MAX_LAYERS + 1], Z, dz[RNN_MLP_MAX_LAYERS], losspart, total; };
+struct MlpPlan { size_t act[RNN_MLP_MAX_LAYERS + 1], Z, dz[RNN_MLP_MAX_LAYERS], losspart, zbox, dbox, total; };
 
 MlpPlan mlp_plan(const rnn_mlp_dims* d) {
     const Widths w = widths_of(d);
@@ -354,6 +688,9 @@ MlpPlan mlp_plan(const rnn_mlp_dims* d) {
     // dZ of layer l's outputs, l < layers - 1 (the last layer's is Z itself, in place)
     for (int l = 0; l + 1 < w.layers; ++l) p.dz[l] = take((size_t)d->batch * w.w[l + 1] * 4);
     p.losspart = take((size_t)((d->batch + 15) / 16 + 1) * 4);   // + one word that takes the loss when the caller wants none
+    const bool boxes = d->n_hidden == 1 && mlp_one_supported(d);
+    p.zbox = take(boxes ? (size_t)2 * mlp_one_wgs(d) * d->batch * d->out_dim * 8 : 0);
+    p.dbox = take(boxes ? (size_t)d->batch * (d->out_dim + 1) * 8 : 0);
     p.total = off;
     return p;
 }
@@ -386,6 +723,42 @@ hipError_t launch_fwd_ce(const float* A, const float* W, const float* b, float* 
     return hipGetLastError();
 }
 
+// Are the workgroups of the one-launch kernel co-resident on the current device?
+bool mlp_one_ready(const void* fn, int wgs) {
+    int dev = 0, per_cu = 0, cus = 0;
+    return hipGetDevice(&dev) == hipSuccess &&
+           hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, OT, 0) == hipSuccess &&
+           hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && per_cu * cus >= wgs;
+}
+
+hipError_t run_mlp_one(const rnn_mlp_dims* d, const rnn_mlp_params* p, const float* X, const int32_t* y, int64_t n_batches,
+                       float lr, float* losses, char* ws, const MlpPlan& pl, const void* fn, hipStream_t s) {
+    MlpOneArgs a{};
+    const bool hid = d->n_hidden == 1;
+    a.W1 = p->W[0]; a.b1 = p->b[0]; a.W2 = hid ? p->W[1] : nullptr; a.b2 = hid ? p->b[1] : nullptr;
+    a.zbox = reinterpret_cast<unsigned long long*>(ws + pl.zbox);
+    a.dbox = reinterpret_cast<unsigned long long*>(ws + pl.dbox);
+    a.B = d->batch; a.K = d->in_dim; a.H = d->hidden; a.O = d->out_dim; a.P = mlp_one_wgs(d); a.act = d->act; a.lr = lr;
+    a.rows_per = !hid || a.P * a.B * a.O <= ONE_HOP ? a.B : (a.B + a.P - 1) / a.P;
+    for (int64_t i = 0; i < n_batches; i += ONE_BATCHES) {
+        a.X = X + (size_t)i * a.B * a.K;
+        a.y = y + (size_t)i * a.B;
+        a.losses = losses ? losses + i : nullptr;
+        a.n_batches = (int)(n_batches - i < ONE_BATCHES ? n_batches - i : ONE_BATCHES);
+        hipError_t e = hipSuccess;
+        if (hid) {   // cleared words are "not written yet"
+            ProfileScope ps(K_MISC, s);
+            e = launch_zero_words(reinterpret_cast<int32_t*>(ws + pl.zbox), (int)((pl.total - pl.zbox) / 4), s);
+            if (e != hipSuccess) return e;
+        }
+        ProfileScope ps(K_MLP_ONE, s);
+        void* args[] = {&a};
+        e = hid ? hipLaunchCooperativeKernel(fn, dim3(a.P), dim3(OT), args, 0, s) : hipLaunchKernel(fn, dim3(1), dim3(OT), args, 0, s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 }  // namespace
 }  // namespace rnn
 
@@ -415,6 +788,15 @@ int rnn_mlp_train(const rnn_mlp_dims* dims, const rnn_mlp_params* params, const 
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     char* ws = static_cast<char*>(workspace);
     const int B = dims->batch, L = w.layers;
+    if (n_batches > 0 && mlp_one_supported(dims)) {
+        const void* fn = dims->n_hidden ? mlp_one_pick<true>(dims->in_dim, B) : mlp_one_pick<false>(dims->in_dim, B);
+        if (!dims->n_hidden || mlp_one_ready(fn, mlp_one_wgs(dims))) {
+            if (run_mlp_one(dims, params, X, y, n_batches, lr, losses, ws, pl, fn, s) != hipSuccess) return RNN_EHIP;
+            if (dims->flags & RNN_FLAG_SYNC)
+                if (hipStreamSynchronize(s) != hipSuccess) return RNN_EHIP;
+            return RNN_OK;
+        }
+    }
     float* Z = reinterpret_cast<float*>(ws + pl.Z);
     // the one update launch of a batch: every layer's grid, one after another
     // at most 16 classes: the output layer's tile holds whole rows, its epilogue forms the loss and

@@ -29,7 +29,7 @@ const char* const kNames[K_COUNT] = {
     "rec_fwd", "rec_bwd", "ce_row_stats", "mse_row_loss", "loss_reduce", "dz",
     "colsum_partial", "colsum_finish", "dwx_tokens", "check_tokens",
     "skinny_logits", "skinny_back", "skinny_reverse", "misc", "train_stream", "window", "gn_metric",
-    "mlp_fwd", "mlp_ce", "mlp_bwd_data", "mlp_update"};
+    "mlp_fwd", "mlp_ce", "mlp_bwd_data", "mlp_update", "mlp_train"};
 }  // namespace
 
 void profile_before(int, hipStream_t s) {
