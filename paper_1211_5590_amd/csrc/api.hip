@@ -128,7 +128,9 @@ Plan make_plan(const rnn_dims* d) {
     p.part = take((size_t)colsum_chunks((int)N) * widest * 4);
     p.splitk = take(max_splitk_floats(s, output_parts(d)) * 4);
     p.scratch = take(256);
-    p.flags = take(4096 + 16 * B * H);   // state-exchange boxes of the multi-workgroup loops
+    // state-exchange boxes of the multi-workgroup loops
+    const size_t ring = rec_xcd_supported(s.H, s.B, s.T) ? rec_xcd_ring_bytes(s.H, s.B) : 0;
+    p.flags = take(4096 + (ring > 16 * B * H ? ring : 16 * B * H));
     const size_t strips = (size_t)skinny_strips(s.O);
     const bool small = N <= 32;
     p.statbox = take(small ? skinny_stat_box_bytes((int)N, s.O) : 0);
@@ -223,7 +225,8 @@ hipError_t run_forward(const rnn_dims* d, const rnn_params* P, const void* x, co
         RecXcdArgs m{};
         m.Wh = P->Wh; m.H = z.H; m.T = z.T; m.B = z.B; m.act = d->act;
         m.U = U; m.h0 = h0; m.hist = h_all; m.h_last = h_last;
-        m.counters = at<int32_t>(ws, pl.flags); m.status = at<int32_t>(ws, pl.scratch) + 1;
+        m.counters = at<int32_t>(ws, pl.flags); m.ring = at<float>(ws, pl.flags + 4096);
+        m.status = at<int32_t>(ws, pl.scratch) + 1;
         return launch_rec_xcd(m, false, s);
     }
     if (v.stepwise) return run_rec_fwd_stepwise(a, s);
@@ -315,7 +318,8 @@ hipError_t run_reverse_loop(const rnn_dims* d, const float* Wh, const float* WhT
         RecXcdArgs m{};
         m.Wh = Wh; m.H = H; m.T = z.T; m.B = z.B; m.act = d->act;
         m.G = G; m.h_all = h_all; m.dh_last = dh_last; m.Delta = Delta; m.dh0 = dh0;
-        m.counters = at<int32_t>(ws, pl.flags); m.status = at<int32_t>(ws, pl.scratch) + 1;
+        m.counters = at<int32_t>(ws, pl.flags); m.ring = at<float>(ws, pl.flags + 4096);
+        m.status = at<int32_t>(ws, pl.scratch) + 1;
         return launch_rec_xcd(m, true, s);
     }
     // the remaining families read the matrix transposed: one copy per call

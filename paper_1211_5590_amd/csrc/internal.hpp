@@ -123,7 +123,7 @@ hipError_t launch_gather_input(const int32_t* x, const float* Wx, const float* b
 hipError_t launch_rec_batch_mfma(const RecMfmaArgs& a, bool bwd, hipStream_t s);
 
 // Persistent batched loop for 256 < H <= 1024 (recurrence_xcd.hip): one batch group per XCD, the state
-// handed over through that XCD's L2.  Needs the full history (no ring) and the input term U.
+// handed over through that XCD's L2.  Needs the full history and the input term U.
 struct RecXcdArgs {
     const float* Wh;
     int H, T, B, act;
@@ -135,11 +135,12 @@ struct RecXcdArgs {
     // reverse
     const float* G; const float* h_all; const float* dh_last; float* Delta; float* dh0;
     int32_t* counters;    // 8 words of workspace (cleared by the launcher)
+    float* ring;          // rec_xcd_ring_bytes of workspace, 16-byte aligned (filled by the launcher)
     int32_t* status;      // device status word: set to 1 when a bounded wait expires
     int spin_limit;       // <= 0: default
-    int first_look_pause; // pauses of 64 clocks between the own tile's store and the first look (<= 0: default)
 };
 bool rec_xcd_supported(int H, int B, int T);                       // shape only (host)
+size_t rec_xcd_ring_bytes(int H, int B);
 bool rec_xcd_ready(int H, int act, bool bwd);               // and the current device can hold the grid at once
 hipError_t launch_rec_xcd(const RecXcdArgs& a, bool bwd, hipStream_t s);
 

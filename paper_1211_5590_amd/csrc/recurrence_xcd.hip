@@ -15,37 +15,39 @@
 // value of row l % 4 for the 16 k of its block l / 4, and receives rows 0..3 at column c0 + l.  The
 // 16-byte piece of the state a lane fetches from memory (row l % 4, four consecutive k) is exactly
 // what it feeds the instruction, so the state goes from the cache into the operand registers
-// without passing LDS.
+// without passing LDS.  A wavefront's share of K is an eighth of H in whole blocks of 16 (48 to 128),
+// and the instructions of blocks past it are left out.
 //
 // Inside a group the new state travels through the L2 cache its compute units share, with no flags,
-// no fences and no kernel boundaries:
-//   * the state IS the history: a workgroup stores its tile of h_all[t+1] (forward) or Delta[t]
-//     (reverse) with device-scope stores;
-//   * the rows a step will produce were filled with a bit pattern arithmetic never produces (an
-//     all-ones NaN) before the launch; every wavefront fetches the K slice its own product needs and
-//     repeats until no such word is left.  Every 4-byte value validates itself, so no ordering between
-//     the stores is needed.  The first look uses ordinary loads (lines this compute unit has never
-//     cached: they are served by the XCD's L2); a look that came too early has left stale lines in the
-//     first-level cache, so later looks use device-scope loads, which pass it.
-// A hidden size that is no multiple of 4 leaves rows (and the history's slots) at 4-byte alignment and
-// the last piece of a row ragged: that piece is fetched as the row's last four words, and its lane
-// shifts the words that belong to it into place (seven selects per step in the wavefronts that take
-// part; the loads and the waits are the same).
+// no fences and no kernel boundaries, in a ring of four states kept beside the history:
+//   * every word of a free slot holds a bit pattern arithmetic never produces (an all-ones NaN; a value
+//     that came in as one is published as another NaN); every wavefront fetches the K slice its own
+//     product needs and repeats until no such word is left.  Every 4-byte value validates itself, so
+//     no ordering between the stores of a step is needed;
+//   * a state is laid out as [k / 4][row][k % 4], the order of a wavefront's lanes: its fetch is one
+//     contiguous stretch.  (From rows as the history holds them, each quad of lanes would touch four
+//     cache lines: the exchange alone took 2050 clocks that way, 1350 this way);
+//   * the stores are workgroup-scope: they stop at the XCD's L2, where the group's readers look.  Device
+//     scope sends them on to memory first: 2600 to 3900 clocks for the exchange, by how early the
+//     readers look.  The looks are device-scope loads, which pass the first-level cache;
+//   * who publishes state s + 1 turns its share of state s - 1 back into a free slot (everybody has read
+//     that: state s is complete) and waits for that store with its next look at the ring, that is before
+//     it publishes state s + 2.  The slot is published again as state s + 3, which nobody looks for
+//     without having seen all of state s + 2: no look can find the words of the state before.
+// A hidden size that is no multiple of 4 has the rest of a row's last piece published as zeros.
 // A workgroup takes its group from the XCD it finds itself on and its column slice from a per-XCD
 // counter, so all workgroups of a group share one L2 by construction whenever the 256 workgroups are
 // co-resident (cooperative launch, one workgroup per compute unit: checked before the launch).
 // Every wait is bounded, and an expired wait sets the status word.
 //
-// Measured (H = 1024, batch 64, in-kernel clock): a step takes about 5300 clocks: 1150 for a
-// wavefront's 128 matrix instructions, 400 for the epilogue, and about 2000 between the request
-// for the new state and its arrival, which neither the bytes (4 or 8 rows per group), nor the scope
-// of the store, nor how long the request waits after the store, nor having the lines in the L2
-// before they are written changes; a request for rows written one step earlier returns in 400.
+// Measured (a loop of 256 steps, batch 64, H = 1024): 600 us with the state read from the history and
+// device-scope stores, 475 now; 100 steps at H = 513, batch 33: 207 -> 161, at H = 512, batch 64:
+// 158 -> 132.  A step at H = 1024 takes about 3900 clocks: 2050 for the matrix instructions of the
+// two wavefronts of a SIMD at the rate of float32, 550 from the last of them to the store, the rest for the
+// store and the look.
 #include "common.hpp"
 #include "internal.hpp"
 #include "prof.hpp"
-
-#include <stdlib.h>
 
 #include <mutex>
 #include <type_traits>
@@ -63,6 +65,7 @@ constexpr int NXCD = 8;            // XCDs: the layout this loop is built on
 constexpr int WG_PER_XCD = 32;     // compute units per XCD = workgroups per XCD
 constexpr int NSLOT = 16;          // workgroups per group
 constexpr int NGRP = 16;           // groups: x and x + 8 on XCD x
+constexpr int RSLOTS = 4;          // states the exchange ring holds
 constexpr unsigned kSentinel = 0xFFFFFFFFu;
 
 #ifdef RNN_REC_TRACE
@@ -79,8 +82,10 @@ __device__ long long g_xcd_trace[4 * 8];
 #define XT_FLUSH(bwd)
 #endif
 
-__device__ __forceinline__ void xcd_lds_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+// leaves the first-level cache and stays in the XCD's L2, where every reader of the word looks for it (a
+// device-scope store would go on to memory first: see above)
+__device__ __forceinline__ void ring_store(float* p, float v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 __device__ __forceinline__ bool fresh(float4 v) {
     return __float_as_uint(v.x) != kSentinel && __float_as_uint(v.y) != kSentinel &&
@@ -112,14 +117,19 @@ __device__ __forceinline__ void mfma_blocks(const float4 st, const float* __rest
      ...);
 }
 
+// words of one state in the exchange ring: 8 KW columns of the batch's groups of RB rows, as [k / 4][row][k % 4]
+// inside a group, the order in which a wavefront's lanes want them
+__host__ __device__ inline int ring_state(int B, int kw) { return (B + RB - 1) / RB * RB * 8 * kw; }
+
 // KW = k per wavefront (8 KW >= H)
 template <int ACT, bool BWD, int KW>
 __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
-    constexpr int NQ = KW / 64;            // 16-byte state pieces per lane and step
+    constexpr int NQ = (KW + 63) / 64;     // 16-byte state pieces per lane and step
+    constexpr int NB1 = (KW - 64) / 4;     // blocks of four k of the second piece
     extern __shared__ __attribute__((aligned(16))) float smem[];
     __shared__ int s_abort, s_grp, s_slot;
-    __shared__ __attribute__((aligned(16))) int s_stored[4];
-    float* part = smem;                    // [2][8 wavefronts][RB][CWD] partial tiles, by step parity
+    __shared__ int s_stored;                   // steps whose first row this workgroup has stored
+    float* part = smem;                    // [2][8 wavefronts][CWD][RB] partial tiles, by step parity
 
     const int H = a.H, B = a.B, T = a.T;
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
@@ -136,7 +146,7 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
         s_slot = n % NSLOT;
         s_abort = 0;
     }
-    if (tid < 4) s_stored[tid] = 0;
+    if (tid == 0) s_stored = 0;
     __syncthreads();
     const int grp = s_grp, slot = s_slot;
     const int b0 = grp * RB, c0 = slot * CWD;
@@ -146,7 +156,6 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
     }
     if (b0 >= B || c0 >= H) return;              // nothing to do here, and nobody waits for this workgroup
     const int nrows = min(RB, B - b0);
-    const int col = c0 + lane, colc = min(col, H - 1);
 
     // ---- resident weights: wreg[j] = M[kb + j][col], M = Wh^T (forward) or Wh (reverse); zero
     //      outside the matrix ----------------------------------------------------------------------
@@ -170,7 +179,7 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
             for (int i = 0; i < 16; ++i) *reinterpret_cast<float4*>(stg + (r4 + 4 * i) * 64 + c4) = v[i];
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the tile is this wavefront's own
 #pragma unroll
-            for (int j = 0; j < 64; ++j) wreg[64 * q + j] = stg[j * 64 + lane];
+            for (int j = 0; j < min(64, KW - 64 * q); ++j) wreg[64 * q + j] = stg[j * 64 + lane];
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
         __syncthreads();                                             // the partial tiles reuse this memory
@@ -196,24 +205,28 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
             }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the tile is this wavefront's own
 #pragma unroll
-            for (int j = 0; j < 64; ++j) wreg[64 * q + j] = stg[lane * PITCH + j];
+            for (int j = 0; j < min(64, KW - 64 * q); ++j) wreg[64 * q + j] = stg[lane * PITCH + j];
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
         __syncthreads();                                             // the partial tiles reuse this memory
     }
 
     // ---- the state pieces of this lane: row ri, columns kb + 64 q + 4 kg .. + 3; pieces outside
-    //      the matrix (rows past the batch, columns past H) stay zero ---------------------------------
+    //      the matrix (rows past the batch, columns past H) or another wavefront's stay zero ------------
     int p_off[NQ], p_shift[NQ];
     bool p_on[NQ];
-    const bool ragged = H % 4 != 0;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
         const int k = kb + 64 * q + 4 * kg;
-        p_on[q] = ri < nrows && k < H;
+        p_on[q] = ri < nrows && k < H && 64 * q + 4 * kg < KW;
         p_off[q] = p_on[q] ? (b0 + ri) * H + min(k, H - 4) : b0 * H;   // clamped duplicates outside the matrix
         p_shift[q] = p_on[q] ? max(k - (H - 4), 0) : 0;
     }
+    // the same pieces in the exchange ring: one contiguous stretch per wavefront and q
+    const int rstate = ring_state(B, KW);
+    int r_off[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) r_off[q] = p_on[q] ? b0 * 8 * KW + (kb + 64 * q) * RB + 4 * lane : b0 * 8 * KW + kb * RB;
     float4 st[NQ];                         // the state of the coming step
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
@@ -236,10 +249,14 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
 
     const int nsteps = BWD ? T - 1 : T;
 
-    // ---- epilogue lanes (wavefronts 0..3): wavefront w finishes row w, lane l column c0 + l ---------
-    const int em = wave, ec = c0 + lane;
-    const bool e_on = wave < RB && em < nrows && ec < H;
+    // ---- epilogue lanes (wavefronts 0..3): 16 columns of the tile per wavefront, in the ring's order, so
+    //      that a wavefront's share of the new state leaves as one stretch of 256 bytes -------------------
+    const int em = (lane >> 2) & 3, et = 16 * (wave & 3) + 4 * (lane >> 4) + (lane & 3), ec = c0 + et;
+    const bool e_on = wave < 4 && em < nrows && ec < H;
+    // the columns that fill the ragged last piece of a row are published as zeros
+    const bool e_pub = wave < 4 && em < nrows && ec < (H + 3) / 4 * 4;
     const size_t e_off = (size_t)min(b0 + em, B - 1) * H + min(ec, H - 1);
+    const int e_ring = b0 * 8 * KW + c0 * RB + 64 * (wave & 3) + lane;
     if (e_on) {    // slot 0 of the history (forward) / Delta[T-1] (reverse): the owner of a column stores it
         if (!BWD) {
             a.hist[e_off] = a.h0 ? a.h0[e_off] : 0.f;
@@ -263,7 +280,6 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
     float n0[2] = {0.f, 0.f}, n1[2] = {0.f, 0.f};
     if (wave < 4) {
         load_epi(0, n0[0], n1[0]);
-        load_epi(1, n0[1], n1[1]);
     }
 
     XT_DECL;
@@ -272,23 +288,21 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
         f32x4 acc[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[e] = (f32x4){0.f, 0.f, 0.f, 0.f};
-        mfma_blocks(st[0], wreg, acc, std::make_integer_sequence<int, 16>{});
-        if constexpr (NQ > 1) mfma_blocks(st[NQ - 1], wreg + 64 * (NQ - 1), acc, std::make_integer_sequence<int, 16>{});
+        mfma_blocks(st[0], wreg, acc, std::make_integer_sequence<int, (KW < 64 ? KW / 4 : 16)>{});
+        if constexpr (NQ > 1) mfma_blocks(st[NQ - 1], wreg + 64, acc, std::make_integer_sequence<int, NB1>{});
         return (acc[0] + acc[1]) + (acc[2] + acc[3]);
     };
     auto park_partial = [&](int par, const f32x4 p4) {
-        float* pp = part + (par * 8 + wave) * RB * CWD;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) pp[i * CWD + lane] = p4[i];
+        *reinterpret_cast<f32x4*>(part + (par * 8 + wave) * RB * CWD + RB * lane) = p4;
     };
     auto tile_sum = [&](int par) {            // epilogue lanes: the eight wavefronts' partial sums
-        const float* pp = part + par * 8 * RB * CWD + em * CWD + lane;
-        float v = 0.f;
+        const float* pp = part + par * 8 * RB * CWD + RB * et + em;
+        float v[8];
 #pragma unroll
-        for (int w = 0; w < 8; ++w) v += pp[w * RB * CWD];
-        return v;
+        for (int w = 0; w < 8; ++w) v[w] = pp[w * RB * CWD];
+        return ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
     };
-    // The lane's pieces of the rows at `src`, waiting until no "not written yet" word is left.
+    // The lane's pieces of the state at `src` in the ring, waiting until no "not written yet" word is left.
     auto collect = [&](const float* src) {
         float4 v[NQ];
         unsigned need = 0;
@@ -299,19 +313,11 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
             XT_COUNT(6, 1);
             if (spins > a.spin_limit) { s_abort = 1; break; }
             if (spins > 0) __builtin_amdgcn_s_sleep(2);
-            if constexpr (NQ == 2) {
-                if (spins == 0)
-                    asm volatile("global_load_dwordx4 %0, %2, off\n\tglobal_load_dwordx4 %1, %3, off\n\ts_waitcnt vmcnt(0)"
-                                 : "=&v"(v[0]), "=&v"(v[1]) : "v"(src + p_off[0]), "v"(src + p_off[1]) : "memory");
-                else
-                    asm volatile("global_load_dwordx4 %0, %2, off sc1\n\tglobal_load_dwordx4 %1, %3, off sc1\n\ts_waitcnt vmcnt(0)"
-                                 : "=&v"(v[0]), "=&v"(v[1]) : "v"(src + p_off[0]), "v"(src + p_off[1]) : "memory");
-            } else {
-                if (spins == 0)
-                    asm volatile("global_load_dwordx4 %0, %1, off\n\ts_waitcnt vmcnt(0)" : "=&v"(v[0]) : "v"(src + p_off[0]) : "memory");
-                else
-                    asm volatile("global_load_dwordx4 %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=&v"(v[0]) : "v"(src + p_off[0]) : "memory");
-            }
+            if constexpr (NQ == 2)
+                asm volatile("global_load_dwordx4 %0, %2, off sc1\n\tglobal_load_dwordx4 %1, %3, off sc1\n\ts_waitcnt vmcnt(0)"
+                             : "=&v"(v[0]), "=&v"(v[1]) : "v"(src + r_off[0]), "v"(src + r_off[1]) : "memory");
+            else
+                asm volatile("global_load_dwordx4 %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=&v"(v[0]) : "v"(src + r_off[0]) : "memory");
 #pragma unroll
             for (int q = 0; q < NQ; ++q)
                 if (fresh(v[q])) need &= ~(1u << q);
@@ -319,7 +325,6 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
             st[q] = (wanted & (1u << q)) ? v[q] : make_float4(0.f, 0.f, 0.f, 0.f);
-            if (ragged) st[q] = shifted(st[q], p_shift[q]);
         }
     };
 
@@ -330,33 +335,33 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
     auto step = [&](int s, auto slot_c, bool fetch_next) {
         constexpr int SLOT = decltype(slot_c)::value;   // s & 1: partial buffer and operand slot
         XTM(0);
+        if (wave < 4) load_epi(s + 1, n0[SLOT ^ 1], n1[SLOT ^ 1]);
         park_partial(SLOT, product());
         XTM(1);
-        xcd_lds_barrier();
+        lds_barrier();
         XTM(2);
         const int t = BWD ? T - 2 - s : s;
         float* dst = BWD ? a.Delta + (size_t)t * bh : a.hist + (size_t)(s + 1) * bh;
+        float* box = a.ring + (size_t)((s + 1) % RSLOTS) * rstate;
         if (wave < 4) {
             const float sum = tile_sum(SLOT);
-            const float v = BWD ? (sum + n0[SLOT]) * act_grad<ACT>(n1[SLOT]) : activate<ACT>(sum + n0[SLOT]);
-            if (e_on) __hip_atomic_store(dst + e_off, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            float v = BWD ? (sum + n0[SLOT]) * act_grad<ACT>(n1[SLOT]) : activate<ACT>(sum + n0[SLOT]);
+            if (__float_as_uint(v) == kSentinel) v = __uint_as_float(0x7FC00000u);   // a NaN that came in as all ones
+            if (e_pub) ring_store(box + e_ring, e_on ? v : 0.f);
+            if (tid == 0) s_stored = s + 1;
+            if (e_on) dst[e_off] = v;
+            if (e_pub) ring_store(a.ring + (size_t)((s + 3) % RSLOTS) * rstate + e_ring, __uint_as_float(kSentinel));
             last_v = v;
-            if (lane == 0) s_stored[wave] = s + 1;      // the tile is on its way
-            load_epi(s + 2, n0[SLOT], n1[SLOT]);        // the slot is free again (unconditional: exact wait counts)
         }
         XTM(3);
         if (fetch_next) {
-            // The other workgroups are in step with this one: look for their tiles a short pause after
-            // this workgroup's own tile has been stored (a look that comes before its data costs a
-            // second, slower one).
-            for (int spins = 0; spins < (1 << 16); ++spins) {
-                const int4 f = lds_peek4(s_stored);
-                if (f.x == s + 1 && f.y == s + 1 && f.z == s + 1 && f.w == s + 1) break;
-                __builtin_amdgcn_s_sleep(1);
-            }
-            for (int k = 0; k < a.first_look_pause; ++k) __builtin_amdgcn_s_sleep(1);
+            // The other workgroups are in step with this one.  The wavefronts that have just stored a row
+            // look at once; the others look when the first row is on its way (a look that comes long
+            // before its data costs a second, slower one).
+            if (wave >= 4)
+                for (int spins = 0; spins < (1 << 16) && lds_peek(&s_stored) != s + 1; ++spins) __builtin_amdgcn_s_sleep(1);
             XTM(4);
-            collect(dst);
+            collect(box);
         }
         XTM(5);
     };
@@ -390,18 +395,28 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
     }
 }
 
-__global__ __launch_bounds__(256) void fill_sentinel_kernel(float* __restrict__ p, size_t n) {
+// the exchange ring starts as sentinels (n4 pieces of 16 bytes), the slice counters at zero
+__global__ __launch_bounds__(256) void xcd_clear_kernel(float* __restrict__ ring, int n4, int32_t* __restrict__ counters) {
     const float s = __uint_as_float(kSentinel);
-    const f32x4u s4 = {s, s, s, s};
-    const size_t n4 = n / 4, first = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (size_t i = first; i < n4; i += (size_t)gridDim.x * blockDim.x) *reinterpret_cast<f32x4u*>(p + 4 * i) = s4;
-    if (first < n % 4) p[4 * n4 + first] = s;
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n4) reinterpret_cast<float4*>(ring)[i] = make_float4(s, s, s, s);
+    if (i < NXCD) counters[i] = 0;
 }
 
 template <int ACT, bool BWD>
 const void* pick_xcd_kernel(int kw) {
-    return kw == 64 ? (const void*)rec_xcd_kernel<ACT, BWD, 64> : (const void*)rec_xcd_kernel<ACT, BWD, 128>;
+    switch (kw) {
+        case 48: return (const void*)rec_xcd_kernel<ACT, BWD, 48>;
+        case 64: return (const void*)rec_xcd_kernel<ACT, BWD, 64>;
+        case 80: return (const void*)rec_xcd_kernel<ACT, BWD, 80>;
+        case 96: return (const void*)rec_xcd_kernel<ACT, BWD, 96>;
+        case 112: return (const void*)rec_xcd_kernel<ACT, BWD, 112>;
+        default: return (const void*)rec_xcd_kernel<ACT, BWD, 128>;
+    }
 }
+
+// k per wavefront: an eighth of H in whole blocks of 16
+int xcd_kw(int H) { return H <= 384 ? 48 : (H + 127) / 128 * 16; }
 
 // partial tiles of a step; the forward kernel first stages its matrix slice there
 size_t xcd_lds_bytes() { return (size_t)8 * 64 * 65 * 4; }
@@ -410,15 +425,17 @@ size_t xcd_lds_bytes() { return (size_t)8 * 64 * 65 * 4; }
 
 // Shapes the one-launch loop serves and is the faster choice for.  The launch has a fixed cost (a
 // cooperative launch, every workgroup loading its 256 KB of the matrix: about 28 us) and then takes
-// 2.1 us per step, against 5.5 us per step for a launch per step, so the shortest sequences stay with
-// the latter (cross-over at H = 1024, batch 64: 8 to 10 steps).
+// 1.8 us per step at H = 1024, against 5.5 us per step for a launch per step, so the shortest sequences
+// stay with the latter (cross-over at H = 1024, batch 64: 8 to 10 steps).
 bool rec_xcd_supported(int H, int B, int T) {
     return T >= 10 && B > 4 && B <= NGRP * RB && H > 256 && H <= NSLOT * CWD;
 }
 
+size_t rec_xcd_ring_bytes(int H, int B) { return (size_t)RSLOTS * ring_state(B, xcd_kw(H)) * 4; }
+
 template <bool BWD>
 const void* xcd_kernel_for(int H, int act) {
-    const int kw = H <= 512 ? 64 : 128;
+    const int kw = xcd_kw(H);
     return act == 0 ? pick_xcd_kernel<0, BWD>(kw) : pick_xcd_kernel<1, BWD>(kw);
 }
 
@@ -428,7 +445,7 @@ bool rec_xcd_ready(int H, int act, bool bwd) {
     const void* fn = bwd ? xcd_kernel_for<true>(H, act) : xcd_kernel_for<false>(H, act);
     const size_t lds = xcd_lds_bytes();
     struct Seen { const void* fn; int dev; bool ok; };
-    static Seen seen[16];
+    static Seen seen[64];
     static int n_seen = 0;
     static std::mutex mu;
     int dev = 0;
@@ -441,7 +458,7 @@ bool rec_xcd_ready(int H, int act, bool bwd) {
                     hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, XT, lds) == hipSuccess &&
                     hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
                     per_cu >= 1 && cus == NXCD * WG_PER_XCD;
-    if (n_seen < 16) seen[n_seen++] = Seen{fn, dev, ok};
+    if (n_seen < 64) seen[n_seen++] = Seen{fn, dev, ok};
     return ok;
 }
 
@@ -451,29 +468,16 @@ hipError_t launch_rec_xcd(const RecXcdArgs& a, bool bwd, hipStream_t s) {
     const void* fn = bwd ? xcd_kernel_for<true>(a.H, a.act) : xcd_kernel_for<false>(a.H, a.act);
     const size_t lds = xcd_lds_bytes();
 
-    // the rows the loop will produce start as sentinels; the slice counters start at zero
-    const size_t bh = (size_t)a.B * a.H;
     {
         ProfileScope ps(K_MISC, s);
-        hipError_t e = launch_zero_words(a.counters, NXCD, s);
+        const int n4 = RSLOTS * ring_state(a.B, xcd_kw(a.H)) / 4;
+        hipLaunchKernelGGL(xcd_clear_kernel, dim3((n4 + 255) / 256), dim3(256), 0, s, a.ring, n4, a.counters);
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        float* first = bwd ? a.Delta : a.hist + bh;
-        const size_t rows = bwd ? (size_t)(a.T - 1) : (size_t)a.T;
-        const size_t n = rows * bh, n4 = (n + 3) / 4;
-        if (n > 0) {
-            const unsigned blocks = (unsigned)((n4 + 255) / 256 < 2048 ? (n4 + 255) / 256 : 2048);
-            hipLaunchKernelGGL(fill_sentinel_kernel, dim3(blocks), dim3(256), 0, s, first, n);
-            e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
     }
     ProfileScope ps(bwd ? K_REC_BWD : K_REC_FWD, s);
     RecXcdArgs args = a;
     if (args.spin_limit <= 0) args.spin_limit = wait_limit();
-    if (args.first_look_pause <= 0) args.first_look_pause = 6;
-#ifdef RNN_REC_TRACE
-    if (const char* env = getenv("RNN_XCD_PAUSE")) args.first_look_pause = atoi(env);
-#endif
     void* kargs[] = {&args};
     return hipLaunchCooperativeKernel(fn, dim3(NXCD * WG_PER_XCD), dim3(XT), kargs, (unsigned)lds, s);
 }

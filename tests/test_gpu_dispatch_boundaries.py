@@ -4,6 +4,7 @@ several workgroups, batched matrix-core loop, the one-launch wide loop, one laun
 short windows, both activations, token and dense inputs, initial states and incoming gradients."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import paper_1211_5590_amd as rnn
@@ -70,3 +71,36 @@ def test_the_one_launch_wide_loop_at_hidden_sizes_that_are_no_multiple_of_4(H):
         r.step()
         assert rnn.rnn_workspace_status(r.dims, r.ws) == 0
         compare(r.results(), oracle.fwd_bptt(case, h0=case.get("h0"), dh_last=case.get("dh_last")))
+
+
+@pytest.mark.parametrize("H", (384, 385, 640, 641, 768, 769, 896, 897))
+def test_the_one_launch_wide_loop_where_a_wavefronts_share_of_the_matrix_changes(H):
+    """A wavefront takes an eighth of the hidden units in whole blocks of 16: the last and the first size of a
+    share, and the second piece of the state that only some lanes hold."""
+    for n, (B, T) in enumerate(((6, 10), (33, 17))):
+        case = ri.make_case(in_dim=90, hidden=H, out_dim=70, seq_len=T, batch=B, act=n % 2, with_h0=n == 0,
+                            with_dh_last=n == 1, wdist=("normal", 0.5 / np.sqrt(H)), bias_std=0.1, seed=9700 + 11 * H + n)
+        r = Runner(case)
+        print(f"H={H} B={B} T={T}", flush=True)
+        assert rnn.rnn_recurrence_variant(r.dims) == "xcd_mfma"
+        r.step()
+        assert rnn.rnn_workspace_status(r.dims, r.ws) == 0
+        compare(r.results(), oracle.fwd_bptt(case, h0=case.get("h0"), dh_last=case.get("dh_last")))
+
+
+def test_the_one_launch_wide_loop_hands_on_a_nan_of_any_bits():
+    """The loop marks words that are not there yet with one bit pattern of a NaN: a state that is that very
+    NaN has to arrive as a NaN in the row it belongs to, and nowhere else, and no wait may expire for it."""
+    case = ri.make_case(in_dim=90, hidden=300, out_dim=70, seq_len=12, batch=7, act=1, wdist=("normal", 0.03),
+                        bias_std=0.1, seed=97)
+    case["x"][:] = 1
+    case["x"][4, 2] = 3
+    bits = case["Wx"].view(np.uint32)
+    bits[3, 17] = 0xFFFFFFFF
+    r = Runner(case)
+    r.forward()
+    torch.cuda.synchronize()
+    assert rnn.rnn_workspace_status(r.dims, r.ws) == 0
+    bad = torch.isnan(r.h_all).cpu().numpy()
+    assert bad[5, 2, 17] and bad[5].sum() == 1
+    assert bad[6:, 2].all() and not np.delete(bad, 2, axis=1).any()
