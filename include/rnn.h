@@ -371,7 +371,8 @@ const char *rnn_strerror(int code);
  * reports and tests): "wg_resident" (one workgroup per sequence, weights in LDS),
  * "grid_resident" (several cooperating workgroups per sequence), "batch_mfma" (batched,
  * hidden <= 256: one persistent matrix-core workgroup per 4 batch rows, weights in registers),
- * "xcd_mfma" (batched, 256 < hidden <= 1024, batch <= 64, at least 10 steps, on
+ * "xcd_mfma" (256 < hidden <= 1024, batch <= 64, at least 10 steps - batch 1 to 4: at least 16,
+ * batch 1 and 2: hidden <= 640, and with the full history - on
  * a device of 8 x 32 compute units: one persistent launch, 16 groups of 4 batch rows, two groups
  * per XCD),
  * "step_mfma" (other batched sizes: one fused matrix-core launch per step) or "reference". */

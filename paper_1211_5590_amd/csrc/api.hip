@@ -33,6 +33,7 @@ struct Variant {
     RecResPlan fwd, bwd;  // plans of the two loops when resident
     bool grid;            // several workgroups per sequence, role-split form (recurrence_grid.hip)
     RecGridPlan gplan;
+    bool xcd;             // one launch over the XCDs where the device can hold it (recurrence_xcd.hip), before the others
 };
 
 struct Sizes {
@@ -96,6 +97,7 @@ Variant pick_variant(const rnn_dims* d) {
     if (!v.resident) {
         v.batch_mfma = rec_batch_mfma_supported(s.H, s.B);
         v.stepwise = !v.batch_mfma && s.B > 4;
+        v.xcd = v.stepwise && rec_xcd_supported(s.H, s.B, s.T);
         return v;
     }
     v.grid = (v.fwd.P > 1 || v.bwd.P > 1) && rec_grid_plan(s.H, s.B, &v.gplan);
@@ -105,6 +107,7 @@ Variant pick_variant(const rnn_dims* d) {
         v.skinny = true;
         v.bwd = fused;
     }
+    v.xcd = (v.fwd.P > 1 || v.bwd.P > 1) && !v.skinny && rec_xcd_supported(s.H, s.B, s.T);
     return v;
 }
 
@@ -201,6 +204,14 @@ hipError_t run_forward(const rnn_dims* d, const rnn_params* P, const void* x, co
         a.U = at<float>(ws, pl.U);
     }
     const Variant v = pick_variant(d);
+    if (v.xcd && h_all && rec_xcd_ready(z.H, d->act, false)) {
+        RecXcdArgs m{};
+        m.Wh = P->Wh; m.H = z.H; m.T = z.T; m.B = z.B; m.act = d->act;
+        m.x = a.x; m.Wx = P->Wx; m.b = P->b; m.U = a.U; m.h0 = h0; m.hist = h_all; m.h_last = h_last;
+        m.counters = at<int32_t>(ws, pl.flags); m.ring = at<float>(ws, pl.flags + 4096);
+        m.status = at<int32_t>(ws, pl.scratch) + 1;
+        return launch_rec_xcd(m, false, s);
+    }
     if (v.resident) {
         RecResArgs r{};
         r.Wh = P->Wh; r.H = z.H; r.T = z.T; r.B = z.B; r.act = d->act;
@@ -217,17 +228,6 @@ hipError_t run_forward(const rnn_dims* d, const rnn_params* P, const void* x, co
         m.Wh = P->Wh; m.H = z.H; m.T = z.T; m.B = z.B; m.act = d->act;
         m.U = U; m.h0 = h0; m.hist = a.hist; m.h_last = h_last; m.ring = a.ring;
         return launch_rec_batch_mfma(m, false, s);
-    }
-    if (v.stepwise && h_all && rec_xcd_supported(z.H, z.B, z.T) && rec_xcd_ready(z.H, d->act, false)) {
-        // one persistent launch for all steps (one batch group per XCD)
-        float* U = at<float>(ws, pl.U);
-        if (z.tokens) RNN_TRY(launch_gather_input(a.x, P->Wx, P->b, U, (int)z.N, z.H, s));
-        RecXcdArgs m{};
-        m.Wh = P->Wh; m.H = z.H; m.T = z.T; m.B = z.B; m.act = d->act;
-        m.U = U; m.h0 = h0; m.hist = h_all; m.h_last = h_last;
-        m.counters = at<int32_t>(ws, pl.flags); m.ring = at<float>(ws, pl.flags + 4096);
-        m.status = at<int32_t>(ws, pl.scratch) + 1;
-        return launch_rec_xcd(m, false, s);
     }
     if (v.stepwise) return run_rec_fwd_stepwise(a, s);
     return launch_rec_fwd_reference(a, s);
@@ -300,6 +300,14 @@ hipError_t run_reverse_loop(const rnn_dims* d, const float* Wh, const float* WhT
     if (v.skinny) {   // the plain plan of the resident loop
         if (!rec_resident_plan(z.H, z.B, z.T, true, false, 0, &v.bwd)) v.resident = false;
     }
+    if (v.xcd && rec_xcd_ready(z.H, d->act, true)) {
+        RecXcdArgs m{};
+        m.Wh = Wh; m.H = H; m.T = z.T; m.B = z.B; m.act = d->act;
+        m.G = G; m.h_all = h_all; m.dh_last = dh_last; m.Delta = Delta; m.dh0 = dh0;
+        m.counters = at<int32_t>(ws, pl.flags); m.ring = at<float>(ws, pl.flags + 4096);
+        m.status = at<int32_t>(ws, pl.scratch) + 1;
+        return launch_rec_xcd(m, true, s);
+    }
     if (v.resident) {
         RecResArgs r{};
         r.Wh = Wh; r.H = H; r.T = z.T; r.B = z.B; r.act = d->act;
@@ -313,14 +321,6 @@ hipError_t run_reverse_loop(const rnn_dims* d, const float* Wh, const float* WhT
         m.Wh = Wh; m.H = H; m.T = z.T; m.B = z.B; m.act = d->act;
         m.G = G; m.h_all = h_all; m.dh_last = dh_last; m.Delta = Delta; m.dh0 = dh0;
         return launch_rec_batch_mfma(m, true, s);
-    }
-    if (v.stepwise && rec_xcd_supported(z.H, z.B, z.T) && rec_xcd_ready(z.H, d->act, true)) {
-        RecXcdArgs m{};
-        m.Wh = Wh; m.H = H; m.T = z.T; m.B = z.B; m.act = d->act;
-        m.G = G; m.h_all = h_all; m.dh_last = dh_last; m.Delta = Delta; m.dh0 = dh0;
-        m.counters = at<int32_t>(ws, pl.flags); m.ring = at<float>(ws, pl.flags + 4096);
-        m.status = at<int32_t>(ws, pl.scratch) + 1;
-        return launch_rec_xcd(m, true, s);
     }
     // the remaining families read the matrix transposed: one copy per call
     const float* WhT = WhT_or_null;
@@ -680,8 +680,9 @@ const char* rnn_strerror(int code) {
 const char* rnn_recurrence_variant(const rnn_dims* dims) {
     if (!dims_valid(dims)) return "invalid";
     const Variant v = pick_variant(dims);
+    if (v.xcd) return "xcd_mfma";
     if (v.batch_mfma) return "batch_mfma";
-    if (v.stepwise) return rec_xcd_supported(dims->hidden, dims->batch, dims->seq_len) ? "xcd_mfma" : "step_mfma";
+    if (v.stepwise) return "step_mfma";
     if (!v.resident) return "reference";
     return (v.fwd.P == 1 && !v.grid) ? "wg_resident" : "grid_resident";
 }
@@ -690,8 +691,8 @@ int rnn_recurrence_workgroups(const rnn_dims* dims) {
     if (!dims_valid(dims)) return RNN_EINVAL;
     const Variant v = pick_variant(dims);
     const Sizes s = sizes_of(dims);
+    if (v.xcd) return ((s.B + 3) / 4) * ((s.H + 63) / 64);
     if (v.batch_mfma) return (s.B + 3) / 4;
-    if (v.stepwise && rec_xcd_supported(s.H, s.B, s.T)) return ((s.B + 3) / 4) * ((s.H + 63) / 64);
     if (v.stepwise) return ((s.H + 15) / 16) * ((s.B + 15) / 16);   // tiles of one step launch
     if (!v.resident) return s.B;
     if (v.grid) return v.gplan.P * s.B;

@@ -123,11 +123,13 @@ hipError_t launch_gather_input(const int32_t* x, const float* Wx, const float* b
 hipError_t launch_rec_batch_mfma(const RecMfmaArgs& a, bool bwd, hipStream_t s);
 
 // Persistent batched loop for 256 < H <= 1024 (recurrence_xcd.hip): one batch group per XCD, the state
-// handed over through that XCD's L2.  Needs the full history and the input term U.
+// handed over through that XCD's L2.  Needs the full history.
 struct RecXcdArgs {
     const float* Wh;
     int H, T, B, act;
     // forward
+    const int32_t* x;     // token ids [T,B] with Wx [NV,H] and b [H], or NULL with
+    const float* Wx; const float* b;
     const float* U;       // [T,B,H] input term including the bias
     const float* h0;      // nullable
     float* hist;          // [T+1,B,H]

@@ -1,5 +1,5 @@
-// Persistent batched time loop for hidden sizes whose matrix needs many compute units (batch > 4,
-// 256 < hidden <= 1024): ONE launch for all steps instead of one launch per step.
+// Persistent batched time loop for hidden sizes whose matrix needs many compute units (256 < hidden <= 1024,
+// batch up to 64): ONE launch for all steps instead of one launch per step.
 //
 // The paper's Scan keeps the loop inside one graph node so that nothing per step happens outside
 // compiled code (properties 4 and 5) and keeps every state (property 1); the per-step kernel
@@ -34,6 +34,8 @@
 //     that: state s is complete) and waits for that store with its next look at the ring, that is before
 //     it publishes state s + 2.  The slot is published again as state s + 3, which nobody looks for
 //     without having seen all of state s + 2: no look can find the words of the state before.
+// Token input takes its rows of Wx in the loop, a step ahead, instead of a gather launch that writes them
+// out for all steps and is read back (256 steps of 64 rows at H = 1024: 27 us).
 // A hidden size that is no multiple of 4 has the rest of a row's last piece published as zeros.
 // A workgroup takes its group from the XCD it finds itself on and its column slice from a per-XCD
 // counter, so all workgroups of a group share one L2 by construction whenever the 256 workgroups are
@@ -266,20 +268,32 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
             a.Delta[e] = (a.G[e] + c) * act_grad<ACT>(a.h_all[(size_t)T * bh + e_off]);
         }
     }
-    auto load_epi = [&](int s, float& x0, float& x1) {     // requested two steps ahead, clamped: always valid
-        const int sc = max(min(s, nsteps - 1), 0);
-        const int t = BWD ? max(T - 2 - sc, 0) : sc;
-        const size_t base = (size_t)t * bh;
-        if (!BWD) {
-            x0 = a.U[base + e_off];
-        } else {
+    // operands of the epilogue of step s, requested a step ahead (clamped: always valid).  Token input takes the
+    // row of Wx itself; the row's number is requested another step ahead.
+    auto step_of = [&](int s) { return max(min(s, nsteps - 1), 0); };
+    const float bias = !BWD && a.x && wave < 4 ? a.b[min(ec, H - 1)] : 0.f;
+    const int eb = min(b0 + em, B - 1);
+    int id = 0;                            // token of this lane's row at the step after the one last requested
+    auto load_id = [&](int s) {
+        if (!BWD && a.x) id = a.x[(size_t)step_of(s) * B + eb];
+    };
+    auto load_epi = [&](int s, float& x0, float& x1) {
+        const int sc = step_of(s);
+        const size_t base = (size_t)(BWD ? max(T - 2 - sc, 0) : sc) * bh;
+        if (BWD) {
             x0 = a.G[base + e_off];
             x1 = a.h_all[base + bh + e_off];
+        } else if (a.x) {
+            x0 = a.Wx[(size_t)id * H + min(ec, H - 1)];
+        } else {
+            x0 = a.U[base + e_off];
         }
     };
     float n0[2] = {0.f, 0.f}, n1[2] = {0.f, 0.f};
     if (wave < 4) {
+        load_id(0);
         load_epi(0, n0[0], n1[0]);
+        load_id(1);
     }
 
     XT_DECL;
@@ -335,7 +349,10 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
     auto step = [&](int s, auto slot_c, bool fetch_next) {
         constexpr int SLOT = decltype(slot_c)::value;   // s & 1: partial buffer and operand slot
         XTM(0);
-        if (wave < 4) load_epi(s + 1, n0[SLOT ^ 1], n1[SLOT ^ 1]);
+        if (wave < 4) {
+            load_epi(s + 1, n0[SLOT ^ 1], n1[SLOT ^ 1]);
+            load_id(s + 2);
+        }
         park_partial(SLOT, product());
         XTM(1);
         lds_barrier();
@@ -345,7 +362,7 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
         float* box = a.ring + (size_t)((s + 1) % RSLOTS) * rstate;
         if (wave < 4) {
             const float sum = tile_sum(SLOT);
-            float v = BWD ? (sum + n0[SLOT]) * act_grad<ACT>(n1[SLOT]) : activate<ACT>(sum + n0[SLOT]);
+            float v = BWD ? (sum + n0[SLOT]) * act_grad<ACT>(n1[SLOT]) : activate<ACT>(sum + (n0[SLOT] + bias));
             if (__float_as_uint(v) == kSentinel) v = __uint_as_float(0x7FC00000u);   // a NaN that came in as all ones
             if (e_pub) ring_store(box + e_ring, e_on ? v : 0.f);
             if (tid == 0) s_stored = s + 1;
@@ -427,8 +444,15 @@ size_t xcd_lds_bytes() { return (size_t)8 * 64 * 65 * 4; }
 // cooperative launch, every workgroup loading its 256 KB of the matrix: about 28 us) and then takes
 // 1.8 us per step at H = 1024, against 5.5 us per step for a launch per step, so the shortest sequences
 // stay with the latter (cross-over at H = 1024, batch 64: 8 to 10 steps).
+// Batch 1 to 4 has the loops that give every sequence its own workgroups.  Forward, loss and backward of
+// 100 steps with 1000 words, those against this one: H = 500, batch 1: 412 / 366 us, batch 4: 492 / 411;
+// H = 600, batch 2: 476 / 448; H = 700, batch 1: 456 / 450; but H = 1000, batch 1: 475 / 509 and H = 1024,
+// batch 2: 496 / 534 (a wavefront's matrix instructions cost the same for 1 row as for 4), while H = 1024,
+// batch 3, which has no room for 16 outputs per workgroup there, is 300 / 199 us per loop.  Of 10 steps
+// (H = 500: 149 / 142) the set-up is most.
 bool rec_xcd_supported(int H, int B, int T) {
-    return T >= 10 && B > 4 && B <= NGRP * RB && H > 256 && H <= NSLOT * CWD;
+    if (H <= 256 || H > NSLOT * CWD || B < 1 || B > NGRP * RB) return false;
+    return B > 4 ? T >= 10 : T >= 16 && (B > 2 || H <= 640);
 }
 
 size_t rec_xcd_ring_bytes(int H, int B) { return (size_t)RSLOTS * ring_state(B, xcd_kw(H)) * 4; }

@@ -104,3 +104,25 @@ def test_the_one_launch_wide_loop_hands_on_a_nan_of_any_bits():
     bad = torch.isnan(r.h_all).cpu().numpy()
     assert bad[5, 2, 17] and bad[5].sum() == 1
     assert bad[6:, 2].all() and not np.delete(bad, 2, axis=1).any()
+
+
+@pytest.mark.parametrize("H,B,T,want", ((257, 1, 16, True), (500, 1, 15, False), (513, 2, 33, True), (640, 1, 40, True),
+                                        (641, 1, 40, False), (641, 3, 17, True), (1024, 4, 16, True), (300, 1, 32, True)))
+def test_the_wide_loop_for_the_smallest_batches(H, B, T, want):
+    """Batch 1 to 4 on both sides of the rule that sends them to the one-launch wide loop, with token and with dense
+    input, and the forward pass without the history, which that loop does not serve."""
+    for kind in (0, 1):
+        case = ri.make_case(in_dim=92, hidden=H, out_dim=72, seq_len=T, batch=B, act=kind, input_kind=kind, with_h0=True,
+                            with_dh_last=kind == 0, wdist=("normal", 0.5 / np.sqrt(H)), bias_std=0.1, seed=9800 + 11 * H + kind)
+        r = Runner(case)
+        variant = rnn.rnn_recurrence_variant(r.dims)
+        print(f"H={H} B={B} T={T} input={kind} variant={variant}", flush=True)
+        assert (variant == "xcd_mfma") == want
+        r.step()
+        assert rnn.rnn_workspace_status(r.dims, r.ws) == 0
+        ref = oracle.fwd_bptt(case, h0=case.get("h0"), dh_last=case.get("dh_last"))
+        compare(r.results(), ref)
+        last = Runner(case, keep_history=False)
+        last.forward()
+        torch.cuda.synchronize()
+        assert np.max(np.abs(last.h_last.cpu().numpy() - ref["h_all"][-1])) <= 2e-5
