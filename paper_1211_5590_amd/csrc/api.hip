@@ -145,6 +145,8 @@ Plan make_plan(const rnn_dims* d) {
     const int parts = output_parts(d);
     p.lstat = take(s.ce && gemm_fuses_stats((int)N, s.O, s.H, parts)
                        ? N * (size_t)gemm_stat_parts((int)N, s.O, s.H, parts) * 8 : 0);
+    // a workspace sized without the flag stays too small for a call with it
+    if (d->flags & RNN_FLAG_BF16X3_OUTPUT) take(256);
     p.total = off;
     return p;
 }
