@@ -369,8 +369,8 @@ const char *rnn_strerror(int code);
 
 /* Name of the recurrence kernel family the dispatcher picks for these sizes (host-only; for
  * reports and tests): "wg_resident" (one workgroup per sequence, weights in LDS),
- * "grid_resident" (several cooperating workgroups per sequence), "batch_mfma" (batched,
- * hidden <= 256: one persistent matrix-core workgroup per 4 batch rows, weights in registers),
+ * "grid_resident" (several cooperating workgroups per sequence), "batch_mfma" (hidden <= 256,
+ * batch > 4, or batch 1 to 4 with hidden > 128 and at least 10 steps: one persistent matrix-core workgroup per 4 batch rows, weights in registers),
  * "xcd_mfma" (256 < hidden <= 1024, batch <= 64, at least 10 steps - batch 1 to 4: at least 16,
  * batch 1 and 2: hidden <= 640, and with the full history - on
  * a device of 8 x 32 compute units: one persistent launch, 16 groups of 4 batch rows, two groups

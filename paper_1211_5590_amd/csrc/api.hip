@@ -107,6 +107,12 @@ Variant pick_variant(const rnn_dims* d) {
         v.skinny = true;
         v.bwd = fused;
     }
+    // Batch 1 to 4 with more than 128 hidden units: the matrix no longer fits the registers of the loops above and
+    // a step is bound by reading it from LDS or by the exchange between workgroups.  The batched loop keeps it in
+    // registers split in three.  Forward, loss and backward of 100 steps, 1000 words, those against that: H = 150,
+    // batch 1: 415 / 197 us, H = 200: 387 / 284, H = 256: 401 / 297, batch 4: 423 / 321; of 12 steps, H = 256,
+    // batch 2: 154 / 108.  Of fewer than 10 steps the launches are most of it, and here it takes one more.
+    v.batch_mfma = s.T >= 10 && s.H > 128 && rec_batch_mfma_supported(s.H, s.B);
     v.xcd = (v.fwd.P > 1 || v.bwd.P > 1) && !v.skinny && rec_xcd_supported(s.H, s.B, s.T);
     return v;
 }
@@ -120,7 +126,7 @@ Plan make_plan(const rnn_dims* d) {
     p.Z = take(N * O * 4);
     p.lse = take(N * 4);
     p.rowloss = take(N * 4);
-    p.U = take((!s.tokens || s.B > 4) ? N * H * 4 : 0);  // hoisted input term (dense, or batched tokens)
+    p.U = take((!s.tokens || pick_variant(d).batch_mfma || s.B > 4) ? N * H * 4 : 0);  // hoisted input term (dense, or batched tokens)
     // (also scratch of the token gradient once the reverse loop has read it)
     const size_t g_floats = s.tokens && N > 32 && dwx_scratch_floats((int)N, s.H) > N * H ? dwx_scratch_floats((int)N, s.H) : N * H;
     p.G = take(g_floats * 4);
@@ -214,6 +220,14 @@ hipError_t run_forward(const rnn_dims* d, const rnn_params* P, const void* x, co
         m.status = at<int32_t>(ws, pl.scratch) + 1;
         return launch_rec_xcd(m, false, s);
     }
+    if (v.batch_mfma) {
+        float* U = at<float>(ws, pl.U);
+        if (z.tokens) RNN_TRY(launch_gather_input(a.x, P->Wx, P->b, U, (int)z.N, z.H, s));
+        RecMfmaArgs m{};
+        m.Wh = P->Wh; m.H = z.H; m.T = z.T; m.B = z.B; m.act = d->act;
+        m.U = U; m.h0 = h0; m.hist = a.hist; m.h_last = h_last; m.ring = a.ring;
+        return launch_rec_batch_mfma(m, false, s);
+    }
     if (v.resident) {
         RecResArgs r{};
         r.Wh = P->Wh; r.H = z.H; r.T = z.T; r.B = z.B; r.act = d->act;
@@ -222,14 +236,6 @@ hipError_t run_forward(const rnn_dims* d, const rnn_params* P, const void* x, co
         r.hist = a.hist; r.h_last = h_last; r.ring = a.ring;
         if (v.grid) return launch_rec_grid(r, v.gplan, false, s);
         return launch_rec_resident(r, v.fwd, false, s);
-    }
-    if (v.batch_mfma) {
-        float* U = at<float>(ws, pl.U);
-        if (z.tokens) RNN_TRY(launch_gather_input(a.x, P->Wx, P->b, U, (int)z.N, z.H, s));
-        RecMfmaArgs m{};
-        m.Wh = P->Wh; m.H = z.H; m.T = z.T; m.B = z.B; m.act = d->act;
-        m.U = U; m.h0 = h0; m.hist = a.hist; m.h_last = h_last; m.ring = a.ring;
-        return launch_rec_batch_mfma(m, false, s);
     }
     if (v.stepwise) return run_rec_fwd_stepwise(a, s);
     return launch_rec_fwd_reference(a, s);
@@ -310,6 +316,12 @@ hipError_t run_reverse_loop(const rnn_dims* d, const float* Wh, const float* WhT
         m.status = at<int32_t>(ws, pl.scratch) + 1;
         return launch_rec_xcd(m, true, s);
     }
+    if (v.batch_mfma) {
+        RecMfmaArgs m{};
+        m.Wh = Wh; m.H = H; m.T = z.T; m.B = z.B; m.act = d->act;
+        m.G = G; m.h_all = h_all; m.dh_last = dh_last; m.Delta = Delta; m.dh0 = dh0;
+        return launch_rec_batch_mfma(m, true, s);
+    }
     if (v.resident) {
         RecResArgs r{};
         r.Wh = Wh; r.H = H; r.T = z.T; r.B = z.B; r.act = d->act;
@@ -317,12 +329,6 @@ hipError_t run_reverse_loop(const rnn_dims* d, const float* Wh, const float* WhT
         r.G = G; r.h_all = h_all; r.dh_last = dh_last; r.Delta = Delta; r.dh0 = dh0;
         if (v.grid) return launch_rec_grid(r, v.gplan, true, s);
         return launch_rec_resident(r, v.bwd, true, s);
-    }
-    if (v.batch_mfma) {
-        RecMfmaArgs m{};
-        m.Wh = Wh; m.H = H; m.T = z.T; m.B = z.B; m.act = d->act;
-        m.G = G; m.h_all = h_all; m.dh_last = dh_last; m.Delta = Delta; m.dh0 = dh0;
-        return launch_rec_batch_mfma(m, true, s);
     }
     // the remaining families read the matrix transposed: one copy per call
     const float* WhT = WhT_or_null;

@@ -25,6 +25,18 @@ __device__ __forceinline__ float4 load4u(const float* p) {
     const f32x4u t = *reinterpret_cast<const f32x4u*>(p);
     return make_float4(t[0], t[1], t[2], t[3]);
 }
+// p[0..3] at 4-byte alignment; words from `left` on do not exist and read as zero (left <= 0: none exist)
+__device__ __forceinline__ float4 piece(const float* p, int left) {
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (left >= 4) {
+        v = load4u(p);
+    } else {
+        if (left > 0) v.x = p[0];
+        if (left > 1) v.y = p[1];
+        if (left > 2) v.z = p[2];
+    }
+    return v;
+}
 // the elements of v that start `d` (0..3) further along, zeros behind them: a row's last four words,
 // moved to where its ragged last piece begins
 __device__ __forceinline__ float4 shifted(float4 v, int d) {

@@ -104,7 +104,7 @@ hipError_t launch_rec_bwd_with_strips(RecResArgs a, const RecResPlan& pl, const 
 hipError_t run_rec_fwd_stepwise(const RecFwdArgs& a, hipStream_t s);
 hipError_t run_rec_bwd_stepwise(const RecBwdArgs& a, hipStream_t s);
 
-// Persistent batched loop with register-resident weights (recurrence_mfma.hip), H <= 256, B > 4.
+// Persistent batched loop with register-resident weights (recurrence_mfma.hip), H <= 256.
 struct RecMfmaArgs {
     const float* Wh;
     int H, T, B, act;

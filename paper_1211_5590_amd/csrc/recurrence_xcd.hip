@@ -94,19 +94,6 @@ __device__ __forceinline__ bool fresh(float4 v) {
            __float_as_uint(v.z) != kSentinel && __float_as_uint(v.w) != kSentinel;
 }
 
-// p[0..3] at 4-byte alignment; words from `left` on do not exist and read as zero (left <= 0: none exist)
-__device__ __forceinline__ float4 piece(const float* p, int left) {
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (left >= 4) {
-        v = load4u(p);
-    } else {
-        if (left > 0) v.x = p[0];
-        if (left > 1) v.y = p[1];
-        if (left > 2) v.z = p[2];
-    }
-    return v;
-}
-
 // 64 matrix instructions: the four values of one state piece against 64 k of the matrix, block AB
 // of the lanes supplying the state (abid) for k = 4 AB + e
 template <int... AB>

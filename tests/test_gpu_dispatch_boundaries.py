@@ -126,3 +126,26 @@ def test_the_wide_loop_for_the_smallest_batches(H, B, T, want):
         last.forward()
         torch.cuda.synchronize()
         assert np.max(np.abs(last.h_last.cpu().numpy() - ref["h_all"][-1])) <= 2e-5
+
+
+@pytest.mark.parametrize("H,T", ((1, 19), (3, 9), (8, 33), (9, 8), (16, 41), (17, 33), (32, 7), (33, 40), (64, 17), (65, 35),
+                                 (80, 9), (81, 33), (96, 24), (97, 33), (113, 40), (128, 33), (129, 10), (160, 40), (161, 33),
+                                 (192, 12), (193, 33), (255, 10), (256, 35)))
+def test_the_loops_of_the_smallest_batches_at_their_edges(H, T):
+    """Batch 1 to 4: every count of lanes and of pieces per lane of the one-workgroup loop, whole and ragged chunks of
+    its eight steps, and the batched loop above 128 hidden units; the forward pass also without the history, whose two
+    slots are then written in turn."""
+    for n, B in enumerate((1, 3)):
+        case = ri.make_case(in_dim=70, hidden=H, out_dim=68, seq_len=T, batch=B, act=n, with_h0=n == 0, with_dh_last=n == 1,
+                            wdist=("normal", 0.5 / np.sqrt(H)), bias_std=0.1, seed=9900 + 13 * H + n)
+        r = Runner(case)
+        print(f"H={H} B={B} T={T} variant={rnn.rnn_recurrence_variant(r.dims)}", flush=True)
+        assert (rnn.rnn_recurrence_variant(r.dims) == "batch_mfma") == (H > 128)
+        r.step()
+        assert rnn.rnn_workspace_status(r.dims, r.ws) == 0
+        ref = oracle.fwd_bptt(case, h0=case.get("h0"), dh_last=case.get("dh_last"))
+        compare(r.results(), ref)
+        last = Runner(case, keep_history=False)
+        last.forward()
+        torch.cuda.synchronize()
+        assert np.max(np.abs(last.h_last.cpu().numpy() - ref["h_all"][-1])) <= 2e-5
