@@ -72,3 +72,12 @@ def test_two_streams_and_a_captured_call_repeat_exactly():
         torch.cuda.synchronize()
         assert np.array_equal(s["losses"].cpu().numpy(), first["losses"])
         assert np.array_equal(s["W"][0].cpu().numpy(), first["W"][0])
+
+
+@pytest.mark.parametrize("I,H,L,O,B", ((1, 2, 2, 3, 1), (3, 5, 3, 2, 16), (63, 65, 2, 17, 17), (66, 255, 2, 10, 32), (257, 61, 3, 16, 33),
+                                       (64, 258, 2, 5, 64), (130, 67, 2, 10, 65)))
+def test_the_update_of_deep_classifiers_at_ragged_rows(I, H, L, O, B):
+    """Rows of the weights that end inside a lane's 16-byte piece, in every form the batch size picks."""
+    case = ri.make_mlp_case(I, H, L, O, B, n_batches=4, act=ri.ACT_TANH, bias_std=0.2, seed=I + H + B)
+    lr = min(0.05, 4.0 / I)
+    check(run_gpu(case, lr), mlp.train(case, lr), case)
