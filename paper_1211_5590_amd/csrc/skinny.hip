@@ -110,10 +110,10 @@ __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
             float e0 = 0.f, e1 = 0.f;
             if (n0 + r < N) {
                 const float z0 = red[r * CW + lane], z1 = red[r * CW + 64 + lane];
-                const float m = wave_max(fmaxf(z0, z1));
+                const float m = max64(fmaxf(z0, z1));
                 e0 = __expf(z0 - m);          // exp(-inf) = 0 for padding columns
                 e1 = __expf(z1 - m);
-                const float s = wave_sum(e0 + e1);
+                const float s = sum64(e0 + e1);
                 const int y = s_y[n0 + r] - blockIdx.x * CW;
                 const float zy = (y >= 0 && y < CW) ? red[r * CW + y] : 0.f;   // read before the overwrite
                 if (lane == 0) {
@@ -203,6 +203,8 @@ __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
     const unsigned epoch = a.epoch;
     // All words of a group of rows are requested at once (four per thread in flight), parked in
     // LDS, and merged from there: the waiting costs about one memory round trip in total.
+    int span = 1;                        // lanes that hold strips: a power of two
+    while (span < strips && span < kWave) span *= 2;
     float* stage = red;                  // NWV*NR*CW floats >= 2*strips (checked by the host)
     __shared__ float zys[32];
     const unsigned long long* zybox = a.stat_box + (size_t)N * strips * 2;
@@ -237,8 +239,7 @@ __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
                 const float* st = stage + ((size_t)(n - n_lo) * strips + g) * 2;
                 lse_merge(m, sum, st[0], st[1]);
             }
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) {
+            for (int off = span / 2; off > 0; off >>= 1) {      // lanes from `span` on hold nothing
                 const float m2 = __shfl_xor(m, off, kWave), s2 = __shfl_xor(sum, off, kWave);
                 lse_merge(m, sum, m2, s2);
             }
