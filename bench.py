@@ -283,14 +283,16 @@ def _roofline_entry(name, prof, case):
                     traffic=None, avg_us=us)
     nbytes, flops = work
     sec = us * 1e-6
-    if case.get("_bf16x3") and name in ("gemm_logits", "gemm_dV", "gemm_G"):
-        # hi/lo split operands: three bf16 matrix instructions per product term, so the matrix
-        # cores execute 3x the algorithmic flops; both rates are stated against the bf16 peak
+    if name.startswith("gemm_"):
+        # operands split into three bf16 numbers (two with the flag: the output layer's and the weight gradients'
+        # products): six (three) bf16 matrix instructions per product term; both rates against the bf16 peak
+        two = case.get("_bf16x3") and name in ("gemm_logits", "gemm_dV", "gemm_G", "gemm_dWh", "gemm_dWx")
+        terms = 3.0 if two else 6.0
         ach = flops / sec / 1e12
         return dict(kernel=name, bound="mfma", achieved=ach, peak=BF16_MFMA_PEAK_TFLOPS, unit="TFLOP/s",
                     frac=ach / BF16_MFMA_PEAK_TFLOPS, traffic=None, avg_us=us, algorithmic_flops=flops,
-                    dtype="bf16 hi/lo split, f32 accumulate", executed_flops=3.0 * flops,
-                    frac_executed=3.0 * ach / BF16_MFMA_PEAK_TFLOPS)
+                    dtype="bf16 %s split, f32 accumulate" % ("hi/lo" if two else "hi/mid/lo"), executed_flops=terms * flops,
+                    frac_executed=terms * ach / BF16_MFMA_PEAK_TFLOPS)
     if flops / nbytes >= RIDGE:   # above the ridge point: arithmetic bound
         ach = flops / sec / 1e12
         # the batch-1..4 loops multiply on the vector ALUs (same fp32 peak as the matrix cores)
