@@ -43,7 +43,8 @@
 // Every wait is bounded, and an expired wait sets the status word.
 //
 // Measured (a loop of 256 steps, batch 64, H = 1024): 600 us with the state read from the history and
-// device-scope stores, 475 now; 100 steps at H = 513, batch 33: 207 -> 161, at H = 512, batch 64:
+// device-scope stores, 475 now (1000 words; 540 right behind the large products of 10000 words, which
+// leave the chip at a lower clock); 100 steps at H = 513, batch 33: 207 -> 161, at H = 512, batch 64:
 // 158 -> 132.  A step at H = 1024 takes about 3900 clocks: 2050 for the matrix instructions of the
 // two wavefronts of a SIMD at the rate of float32, 550 from the last of them to the store, the rest for the
 // store and the look.
