@@ -1,5 +1,5 @@
 // Persistent batched time loop on the matrix cores with the recurrent matrix resident in
-// registers (hidden size <= 256, batch > 4).
+// registers (hidden size <= 256: batch above 4, and from 129 units on the smaller ones too).
 //
 // Batch rows are independent, so the batch is cut into tiles of 4 rows and every tile gets its
 // own workgroup that never talks to another one: no device-wide synchronisation exists in this
