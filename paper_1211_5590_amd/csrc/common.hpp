@@ -140,6 +140,10 @@ __device__ __forceinline__ float act_grad(float h) {
     return ACT == 0 ? h * (1.0f - h) : 1.0f - h * h;
 }
 
+// What the exponentials of a part are taken relative to: its maximum, but a finite number where that is -inf (every
+// class of the part is masked out; exp(-inf - -inf) would be NaN).  Such a part is the pair (-inf, 0).
+__device__ __forceinline__ float exp_base(float m) { return fmaxf(m, -3.402823466e38f); }
+
 // merge two (max, sum of exp relative to max) pairs of a log-sum-exp
 __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2) {
     const float mn = fmaxf(m, m2);

@@ -475,11 +475,12 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void gemm_kernel(GemmParams p)
                     if (col_l + 32 * j + 8 * (e / 4) + e % 4 < p.N) m = fmaxf(m, acc[i][j][e]);
             const auto other = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
             m = fmaxf(__uint_as_float(other[0]), __uint_as_float(other[1]));
+            const float base = exp_base(m);
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
                 for (int e = 0; e < 16; ++e)
-                    if (col_l + 32 * j + 8 * (e / 4) + e % 4 < p.N) sum += __expf(acc[i][j][e] - m);
+                    if (col_l + 32 * j + 8 * (e / 4) + e % 4 < p.N) sum += __expf(acc[i][j][e] - base);
             sum = swap32_sum(sum);
             const int row = row_l + 32 * i;
             if (lane < 32 && row < p.M)

@@ -34,7 +34,7 @@ __global__ __launch_bounds__(256) void ce_row_stats_kernel(const float* __restri
             s = s * __expf(m - v) + 1.f;  // exp(-inf) = 0 on the first element
             m = v;
         } else {
-            s += __expf(v - m);
+            s += __expf(v - exp_base(m));
         }
     }
 #pragma unroll
@@ -53,7 +53,7 @@ __global__ __launch_bounds__(256) void ce_row_stats_kernel(const float* __restri
     }
 }
 
-// One wavefront per row: merges the (max, sum exp) pairs the logits product left per 64-column
+// One wavefront per row: merges the (max, sum exp) pairs the logits product left per column
 // part, in a fixed order, into lse; rowloss = lse - z[y].
 __global__ __launch_bounds__(256) void ce_merge_stats_kernel(const float* __restrict__ stats, int parts,
                                                              const float* __restrict__ Z,

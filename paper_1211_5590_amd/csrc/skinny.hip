@@ -111,8 +111,9 @@ __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
             if (n0 + r < N) {
                 const float z0 = red[r * CW + lane], z1 = red[r * CW + 64 + lane];
                 const float m = max64(fmaxf(z0, z1));
-                e0 = __expf(z0 - m);          // exp(-inf) = 0 for padding columns
-                e1 = __expf(z1 - m);
+                const float base = exp_base(m);
+                e0 = __expf(z0 - base);       // exp(-inf) = 0 for padding columns
+                e1 = __expf(z1 - base);
                 const float s = sum64(e0 + e1);
                 const int y = s_y[n0 + r] - blockIdx.x * CW;
                 const float zy = (y >= 0 && y < CW) ? red[r * CW + y] : 0.f;   // read before the overwrite

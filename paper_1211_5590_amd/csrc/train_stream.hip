@@ -642,7 +642,7 @@ __device__ __forceinline__ void strip_body(const StreamArgs& a, const int g, flo
                 for (int wv = 0; wv < 8; ++wv) t8[wv] = ld4(tmax + wv * 16 + 4 * kg);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) yv[r] = s_y[min(n0 + 4 * kg + r, T - 1)];
-                float4 mm = t8[0];
+                float4 mm = make_float4(exp_base(t8[0].x), exp_base(t8[0].y), exp_base(t8[0].z), exp_base(t8[0].w));
 #pragma unroll
                 for (int wv = 1; wv < 8; ++wv) {
                     mm.x = fmaxf(mm.x, t8[wv].x); mm.y = fmaxf(mm.y, t8[wv].y);
