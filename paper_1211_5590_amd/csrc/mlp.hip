@@ -382,27 +382,30 @@ __global__ __launch_bounds__(OT, 2) void mlp_one_kernel(const MlpOneArgs a) {
     if (tid == 0) s_fail = 0;
 
     // The batch as the forward product reads it: row m = 16 mt + nn, inputs 4 g .. 4 g + 3 of each block;
-    // as the update reads it: row m = 4 u + g, input nn of each block.  Rows past the batch repeat its last
-    // one (their results are dropped, their dZ is zero).  A block past the end of a row reads the next row
-    // (past the batch: zeros, by the request's bound) and meets weights that are kept zero.  Buffer
-    // requests: one lane offset per row for all blocks, the block in the scalar base.
+    // as the update reads it: row m = 4 u + g, input nn of each block.  Buffer requests: one lane offset per
+    // row for all blocks, the block in the scalar base.  What does not exist reads as zero, by the request's
+    // bound: rows past the batch, blocks past the end of a row and, in the forward product, the pieces past
+    // it (an infinite input of the next row must not meet the zero weights there).  The update's requests
+    // may read into the next row: those columns of W are set to zero after it.
+    constexpr unsigned NONE = 0x80000000u;
     float4 xa[MT][KB];
     unsigned row_a[MT], row_t[4 * MT];   // bytes
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) row_a[mt] = (unsigned)(min(16 * mt + nn, B - 1) * K + 4 * g) * 4u;
+    for (int mt = 0; mt < MT; ++mt) row_a[mt] = SINGLE ? 16u * g : 16 * mt + nn < B ? (unsigned)((16 * mt + nn) * K + 4 * g) * 4u : NONE;
 #pragma unroll
-    for (int u = 0; u < 4 * MT; ++u) row_t[u] = (unsigned)(min(4 * u + g, B - 1) * K + nn) * 4u;
+    for (int u = 0; u < 4 * MT; ++u) row_t[u] = 4 * u + g < B ? (unsigned)((4 * u + g) * K + nn) * 4u : NONE;
     auto window = [&](int batch, int b) {
-        const int k = min(16 * (wave + OW * b), B * K);
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.X + (size_t)batch * B * K + k), 0, (B * K - k) * 4, 0x00020000);
+        const int k = 16 * (wave + OW * b);
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.X + (size_t)batch * B * K + min(k, K)), 0, k < K ? (B * K - k) * 4 : 0, 0x00020000);
     };
     auto load_rows = [&](int batch) {
 #pragma unroll
         for (int b = 0; b < KB; ++b) {
             const auto x = window(batch, b);
+            const bool in = SINGLE || 16 * (wave + OW * b) + 4 * g < K;
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
-                xa[mt][b] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(x, row_a[mt], 0, 0));
+                xa[mt][b] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(x, in ? row_a[mt] : NONE, 0, 0));
         }
     };
     auto load_t = [&](int batch, int b, float (&v)[4 * MT]) {

@@ -81,3 +81,22 @@ def test_the_update_of_deep_classifiers_at_ragged_rows(I, H, L, O, B):
     case = ri.make_mlp_case(I, H, L, O, B, n_batches=4, act=ri.ACT_TANH, bias_std=0.2, seed=I + H + B)
     lr = min(0.05, 4.0 / I)
     check(run_gpu(case, lr), mlp.train(case, lr), case)
+
+
+@pytest.mark.parametrize("I,H,B,m", ((784, 30, 10, 4), (20, 9, 3, 1), (784, 40, 33, 32), (260, 16, 60, 17), (36, 20, 17, 16)))
+def test_an_infinite_input_stays_in_its_own_example(I, H, B, m):
+    """Saturating hidden units keep the logits of an example with an infinite input finite: the batch's loss is finite,
+    and the step is not a number in the column of that input alone (0 times infinity), as in the oracle."""
+    for k in (0, I - 1):
+        case = ri.make_mlp_case(I, H, 1, 10, B, n_batches=1, act=ri.ACT_TANH, bias_std=0.2, seed=I + H + B)
+        case["X"][m, k] = np.inf
+        with np.errstate(invalid="ignore"):
+            ref = mlp.train(case, 0.05)
+        got = run_gpu(case, 0.05)
+        assert np.isfinite(ref["losses"]).all()
+        np.testing.assert_allclose(got["losses"], ref["losses"], rtol=1e-4)
+        for l in range(2):
+            nan = np.isnan(ref["W"][l])
+            assert l == 1 or (nan[:, k].all() and nan.sum() == H)
+            assert np.array_equal(np.isnan(got["W"][l]), nan)
+            assert np.abs(got["W"][l] - ref["W"][l])[~nan].max() <= 1e-4 * np.abs(ref["W"][l][~nan]).max()
