@@ -332,8 +332,10 @@ __global__ __launch_bounds__(1024) void mlp_ce_kernel(float* __restrict__ Z, con
 // only when it has everyone's share i+1, which they publish after they have read share i.  Sums run in
 // a fixed order.
 //
-// Per batch, before -> now: 784-500-10 single examples 16.7 -> 5.5 us, 10 rows 18.1 -> 8.6, 60 rows 22.4 -> 19;
-// 784-10 single examples 8.1 -> 1.9 us, 60 rows 13.7 -> 12.6.
+// Per batch, launches -> this (calls of 200 batches, inputs in the caches): 784-500-10 single examples 17.1 -> 4.9 us,
+// 10 rows 18.0 -> 8.1, 60 rows 22.3 -> 17.5; 784-10 single examples 9.1 -> 1.7 us, 10 rows 9.4 -> 3.4, 60 rows
+// 13.5 -> 11.9.  With the inputs coming from memory (calls of 400 batches): 60 rows of 784-500-10 22.9 -> 18.0, of 784-10
+// 14.5 -> 14.1.
 constexpr int OT = 512, OW = OT / kWave, ONE_HOP = 2048, ONE_BATCHES = 1024;
 constexpr int ONE_SPINS = 1 << 26;   // a bound, not a time-out: the launch is cooperative
 
@@ -638,8 +640,11 @@ __global__ __launch_bounds__(OT, 2) void mlp_one_kernel(const MlpOneArgs a) {
     }
 }
 
-// Shapes the one-launch kernel holds: rows of whole 16-byte pieces, 7 blocks of 16 inputs per wavefront, 64 rows, 16 classes, and no
-// more hidden units than 64 workgroups own (beyond that polling the shares costs what launches do).
+// Shapes the one-launch kernel holds: rows of whole 16-byte pieces, 7 blocks of 16 inputs per wavefront (the form of
+// four row tiles with a hidden layer takes all 256 registers and 48 bytes of scratch with 7), 64 rows, 16 classes, and no more
+// hidden units than 64 workgroups own (beyond that polling the shares costs what launches do).  Without a hidden layer
+// one workgroup does all the work, which still gains at the largest batch: 64 rows of 784 inputs 13.9 -> 12.0 us, from
+// memory 14.8 -> 14.5; of 896 inputs 14.8 -> 13.9, from memory 15.3 -> 15.4.
 bool mlp_one_supported(const rnn_mlp_dims* d) {
     return d->n_hidden <= 1 && d->out_dim <= 16 && d->batch <= 64 && d->in_dim % 4 == 0 && d->in_dim <= 896 && (d->n_hidden == 0 || d->hidden <= 1024);
 }

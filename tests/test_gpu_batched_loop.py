@@ -50,3 +50,48 @@ def test_infinities_give_what_float32_gives(where):
         assert torch.equal(torch.isnan(got[t + 1]), torch.isnan(ref)), t
         fine = ~torch.isnan(ref)
         assert float((got[t + 1][fine] - ref[fine]).abs().max()) < 1e-5
+
+
+@pytest.mark.parametrize("H", [30, 70, 250])
+def test_a_state_beyond_bf16s_range_against_weights_of_zero(H):
+    """3.4e38 is a float32 that rounds to infinity in bf16: times a weight of zero it adds nothing."""
+    B, T = 6, 5
+    big = 3.4e38
+    g = torch.Generator().manual_seed(2)
+    Wh = torch.rand(H, H, generator=g) * 0.2 - 0.1
+    Wh[:, 7] = 0.0
+    Wh[5, 7] = 1e-38                             # and one that leaves something of it
+    U = torch.rand(T, B, H, generator=g) - 0.5
+    p = dict(Wx=torch.eye(H).cuda(), Wh=Wh.cuda(), b=torch.zeros(H).cuda(), V=torch.zeros(H, 2).cuda(), c=torch.zeros(2).cuda())
+    dims = rnn.Dims(H, H, 2, T, B, rnn.INPUT_DENSE, rnn.ACT_TANH, rnn.LOSS_LINEAR_MSE, 0)
+    ws = torch.empty(rnn.rnn_workspace_bytes(dims), dtype=torch.uint8, device="cuda")
+    rnn.rnn_workspace_init(dims, ws)
+    h0 = torch.rand(B, H, generator=g) * 0.5
+    h0[2, 7], h0[4, 7] = big, -big
+    for last_only in (False, True):
+        hist = None if last_only else torch.zeros(T + 1, B, H, device="cuda")
+        last = torch.zeros(B, H, device="cuda")
+        rnn.rnn_forward(dims, p, U.cuda(), h0.cuda(), hist, last, ws)
+        h = h0.double()
+        for t in range(T):
+            h = torch.tanh(h @ Wh.double().t() + U[t].double())
+            if not last_only:
+                assert float((hist[t + 1].cpu().double() - h).abs().max()) < 2e-5, t
+        assert float((last.cpu().double() - h).abs().max()) < 2e-5
+    # reverse loop: states of zero (slope 1), the incoming gradient is the large number
+    Wh[7, :] = 0.0
+    Wh[7, 5] = 1e-38
+    p["Wh"] = Wh.cuda()
+    hist = torch.zeros(T + 1, B, H, device="cuda")
+    dh = torch.rand(B, H, generator=g)
+    dh[1, 7] = big
+    loss = torch.zeros(1, device="cuda")
+    grads = {"d" + k: torch.zeros_like(v) for k, v in p.items()}
+    dh0 = torch.zeros(B, H, device="cuda")
+    Y = torch.zeros(T, B, 2, device="cuda")
+    rnn.rnn_loss(dims, p, hist, Y, loss, ws)
+    rnn.rnn_bptt(dims, p, torch.zeros(T, B, H, device="cuda"), Y, hist, dh.cuda(), grads, dh0, ws)
+    d = dh.double()
+    for t in range(T):
+        d = d @ Wh.double()
+    assert float((dh0.cpu().double() - d).abs().max()) <= 1e-5 * float(d.abs().max())
