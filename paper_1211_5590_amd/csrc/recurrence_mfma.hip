@@ -19,10 +19,11 @@
 // form (v_mfma_f32_4x4x1, 4 rows at the full float32 rate) took 2048, and an accumulator is rounded
 // about 6 times per 32 terms instead of 32 times.
 //
-// Infinities do not split (inf = inf + mid + lo has no mid): a workgroup whose matrix or state holds one
-// goes on with plain float32 products read from memory, so that results are float32's in that case too.
+// Infinities do not split (inf = inf + mid + lo has no mid), nor does bf16 rounding of the largest float32 numbers
+// (from 0x7f7f8000 on hi rounds to infinity): a step whose state holds one, and every step where the matrix
+// does, takes plain float32 products of the matrix in memory instead, so that results are float32's in that case
+// too.
 // NaNs need nothing: they make the same results NaN in either form.
-//
 #include "common.hpp"
 #include "internal.hpp"
 #include "prof.hpp"
@@ -67,7 +68,11 @@ __global__ __launch_bounds__(64 * batch_waves(NK), batch_waves(NK) / 4) void rec
     __shared__ __attribute__((aligned(16))) uint16_t hs[2][16][LDK];   // rows: part * 4 + batch row; the last four stay 0
     constexpr bool TURN = !BWD && NK > 2;
     constexpr int PITCH = 36;      // floats per row of a wavefront's turning tile: 16-byte rows, spread over the banks
-    __shared__ int s_inf;
+    // s_inf[i]: number of the last state put into buffer i that holds a value that does not split.  States are numbered from 0
+    // and alternate between the buffers, so a step that finds its own state's number there knows, and every wavefront of
+    // it knows the same: the flag is set in front of the barrier that ends the step before and can next be set behind
+    // the one that ends this step.  s_odd: the matrix holds such a value.
+    __shared__ int s_inf[2], s_odd;
 
     const int H = a.H, B = a.B, T = a.T;
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
@@ -77,7 +82,7 @@ __global__ __launch_bounds__(64 * batch_waves(NK), batch_waves(NK) / 4) void rec
     const size_t bh = (size_t)B * H;
 
     for (int i = tid; i < 2 * 16 * LDK / 2; i += NT) reinterpret_cast<unsigned*>(&hs[0][0][0])[i] = 0u;
-    if (tid == 0) s_inf = 0;
+    if (tid == 0) s_inf[0] = s_inf[1] = -1, s_odd = 0;
     __syncthreads();
 
     // ---- resident weights, M = Wh^T (forward) or Wh (reverse); zero outside the matrix ------------
@@ -149,7 +154,7 @@ __global__ __launch_bounds__(64 * batch_waves(NK), batch_waves(NK) / 4) void rec
     }
 
     // the CT values of this lane go to state buffer `buf` as three rows of bf16
-    auto put = [&](int buf, const float (&v)[CT]) {
+    auto put = [&](int buf, int number, const float (&v)[CT]) {
         if (col >= HP) return;     // a wavefront without columns
         unsigned p[3];
         split3(v[0], CT > 1 ? v[CT - 1] : 0.f, p);
@@ -161,7 +166,7 @@ __global__ __launch_bounds__(64 * batch_waves(NK), batch_waves(NK) / 4) void rec
         }
 #pragma unroll
         for (int t = 0; t < CT; ++t)
-            if (is_inf(v[t])) s_inf = 1;
+            if (is_inf(v[t])) s_inf[buf] = number;
     };
 
     // ---- initial state tile: slot 0 of the history / Delta[T-1] ------------------------------------
@@ -190,9 +195,10 @@ __global__ __launch_bounds__(64 * batch_waves(NK), batch_waves(NK) / 4) void rec
             last[t] = (at(a.G + (size_t)(T - 1) * bh, t) + c) * act_grad<ACT>(at(a.h_all + (size_t)T * bh, t));
         }
     }
-    put(0, last);
-    if (odd) s_inf = 1;            // (read after the barrier only)
+    put(0, 0, last);
+    if (odd) s_odd = 1;            // (read after the barrier only)
     __syncthreads();
+    const bool odd_matrix = __builtin_amdgcn_readfirstlane(s_odd) != 0;
 
     // Epilogue operands, requested two steps ahead.
     // forward: x0 = input term U[s]; reverse (t = T-2-s): x0 = G[t], x1 = h_t = h_all[t+1].
@@ -218,8 +224,8 @@ __global__ __launch_bounds__(64 * batch_waves(NK), batch_waves(NK) / 4) void rec
     load_epi(0, n0[0], n1[0]);
     load_epi(1, n0[1], n1[1]);
 
-    // out[t] = sum_k h[rg][k] M[k][col + t] from state buffer `cur`
-    auto product = [&](int cur, float (&out)[CT]) {
+    // out[t] = sum_k h[rg][k] M[k][col + t] from state buffer `cur`, which holds state `number`
+    auto product = [&](int cur, int number, float (&out)[CT]) {
         bf16x8 s[NK];
         auto fetch = [&](int c) { s[c] = *reinterpret_cast<const bf16x8*>(&hs[cur][lane % 16][32 * c + 8 * rg]); };
         f32x4 acc[CT][2];          // the matrix's hi part; its mid and lo parts
@@ -228,7 +234,7 @@ __global__ __launch_bounds__(64 * batch_waves(NK), batch_waves(NK) / 4) void rec
         constexpr int AHEAD = NK < 3 ? NK : 3;      // pieces of the state in flight (registers are full)
 #pragma unroll
         for (int c = 0; c < AHEAD; ++c) fetch(c);
-        const int inf = s_inf;
+        const int inf = s_inf[cur];
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int c = 0; c < NK; ++c) {
@@ -240,7 +246,7 @@ __global__ __launch_bounds__(64 * batch_waves(NK), batch_waves(NK) / 4) void rec
             if (c + AHEAD < NK) fetch(c + AHEAD);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (__builtin_amdgcn_readfirstlane(inf)) {   // plain float32, straight from memory
+        if (odd_matrix || __builtin_amdgcn_readfirstlane(inf) == number) {   // plain float32, straight from memory
             for (int t = 0; t < CT; ++t) {
                 float sum = 0.f;
                 const int n = min(col + t, H - 1);
@@ -283,13 +289,13 @@ __global__ __launch_bounds__(64 * batch_waves(NK), batch_waves(NK) / 4) void rec
     auto step = [&](int s, auto slot_c) {
         constexpr int SLOT = decltype(slot_c)::value;   // s & 1: state buffer and operand slot
         float acc[CT];
-        product(SLOT, acc);
+        product(SLOT, s, acc);
 #pragma unroll
         for (int t = 0; t < CT; ++t) {
             const float v = BWD ? (acc[t] + n0[SLOT][t]) * act_grad<ACT>(n1[SLOT][t]) : activate<ACT>(acc[t] + n0[SLOT][t]);
             last[t] = on[t] ? v : 0.f;
         }
-        put(SLOT ^ 1, last);
+        put(SLOT ^ 1, s + 1, last);
         store_state(s);
         // The slot is free again: request the operands of step s + 2 into the same registers.
         // Unconditional (the step index is clamped) so that the wait counts stay exact.  Both stay in
@@ -318,7 +324,7 @@ __global__ __launch_bounds__(64 * batch_waves(NK), batch_waves(NK) / 4) void rec
     }
     if (a.dh0) {  // dh0 = delta_0 Wh: one more product, no epilogue
         float acc[CT];
-        product(nsteps > 0 ? (nsteps & 1) : 0, acc);
+        product(nsteps > 0 ? (nsteps & 1) : 0, max(nsteps, 0), acc);
 #pragma unroll
         for (int t = 0; t < CT; ++t)
             if (on[t]) at(a.dh0, t) = acc[t];

@@ -95,3 +95,31 @@ def test_a_state_beyond_bf16s_range_against_weights_of_zero(H):
     for t in range(T):
         d = d @ Wh.double()
     assert float((dh0.cpu().double() - d).abs().max()) <= 1e-5 * float(d.abs().max())
+
+
+@pytest.mark.parametrize("H", [70, 256])
+def test_an_infinity_of_one_state_costs_that_step_only(H):
+    """The steps that take float32 products from memory are those whose state holds the infinity: one, as tanh is finite.
+    (512 steps of the ordinary form are 15 of such a step, so a factor of 3 is far from both outcomes.)"""
+    B, T = 8, 512
+    g = torch.Generator(device="cuda").manual_seed(4)
+    rand = lambda *s: torch.rand(*s, generator=g, device="cuda") - 0.5   # noqa: E731
+    p = dict(Wx=rand(H, 8), Wh=rand(H, H) * 0.2, b=rand(H), V=rand(H, 2), c=rand(2))
+    dims = rnn.Dims(8, H, 2, T, B, rnn.INPUT_DENSE, rnn.ACT_TANH, rnn.LOSS_LINEAR_MSE, 0)
+    ws = torch.empty(rnn.rnn_workspace_bytes(dims), dtype=torch.uint8, device="cuda")
+    rnn.rnn_workspace_init(dims, ws)
+    X, h0, hist = rand(T, B, 8), rand(B, H), torch.zeros(T + 1, B, H, device="cuda")
+    t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+
+    def best():
+        times = []
+        for _ in range(6):
+            t0.record()
+            rnn.rnn_forward(dims, p, X, h0, hist, None, ws)
+            t1.record()
+            torch.cuda.synchronize()
+            times.append(t0.elapsed_time(t1))
+        return min(times)
+    finite = best()
+    h0[1, 3] = float("inf")
+    assert best() < 3.0 * finite
