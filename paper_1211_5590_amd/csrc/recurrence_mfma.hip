@@ -21,8 +21,8 @@
 //
 // Infinities do not split (inf = inf + mid + lo has no mid), nor does bf16 rounding of the largest float32 numbers
 // (from 0x7f7f8000 on hi rounds to infinity): a step whose state holds one, and every step where the matrix
-// does, takes plain float32 products of the matrix in memory instead, so that results are float32's in that case
-// too.
+// does, takes plain float32 products of state and matrix in memory instead, so that results are float32's in that
+// case too.
 // NaNs need nothing: they make the same results NaN in either form.
 #include "common.hpp"
 #include "internal.hpp"
@@ -51,7 +51,9 @@ __device__ __forceinline__ void split3(float x, float y, unsigned (&w)[3]) {
         }
     }
 }
-__device__ __forceinline__ bool is_inf(float x) { return (__float_as_uint(x) & 0x7fffffffu) >= 0x7f7f8000u && x == x; }   // or rounds to one in bf16
+// a number of at least this magnitude (float32 bits) is an infinity or rounds to one in bf16
+constexpr unsigned NO_SPLIT = 0x7f7f8000u;
+__device__ __forceinline__ bool at_least(float x, unsigned limit) { return (__float_as_uint(x) & 0x7fffffffu) >= limit && x == x; }
 
 // NK = slabs of 32 hidden units (K of the product and, times two, column tiles of 16).  CT column
 // tiles per wavefront, NW wavefronts: one tile each (and so 1, 2 or 3 per SIMD) up to 192 units, beyond
@@ -68,10 +70,10 @@ __global__ __launch_bounds__(64 * batch_waves(NK), batch_waves(NK) / 4) void rec
     __shared__ __attribute__((aligned(16))) uint16_t hs[2][16][LDK];   // rows: part * 4 + batch row; the last four stay 0
     constexpr bool TURN = !BWD && NK > 2;
     constexpr int PITCH = 36;      // floats per row of a wavefront's turning tile: 16-byte rows, spread over the banks
-    // s_inf[i]: number of the last state put into buffer i that holds a value that does not split.  States are numbered from 0
-    // and alternate between the buffers, so a step that finds its own state's number there knows, and every wavefront of
-    // it knows the same: the flag is set in front of the barrier that ends the step before and can next be set behind
-    // the one that ends this step.  s_odd: the matrix holds such a value.
+    // s_inf[i]: number of the last state put into buffer i that does not go through the matrix cores.  States are
+    // numbered from 0 and alternate between the buffers, so a step that finds its own state's number there knows, and every
+    // wavefront of it knows the same: the mark is set in front of the barrier that ends the step before and can
+    // next be set behind the one that ends this step.
     __shared__ int s_inf[2], s_odd;
 
     const int H = a.H, B = a.B, T = a.T;
@@ -91,7 +93,7 @@ __global__ __launch_bounds__(64 * batch_waves(NK), batch_waves(NK) / 4) void rec
     auto keep = [&](int c, int t, const float (&x)[8]) {
         unsigned p[4][3];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) odd = odd || is_inf(x[e]);
+        for (int e = 0; e < 8; ++e) odd = odd || at_least(x[e], NO_SPLIT);
 #pragma unroll
         for (int h = 0; h < 4; ++h) split3(x[2 * h], x[2 * h + 1], p[h]);
 #pragma unroll
@@ -153,6 +155,7 @@ __global__ __launch_bounds__(64 * batch_waves(NK), batch_waves(NK) / 4) void rec
             }
     }
 
+    unsigned limit = NO_SPLIT;     // 0 if the matrix holds such a number: then every state is marked
     // the CT values of this lane go to state buffer `buf` as three rows of bf16
     auto put = [&](int buf, int number, const float (&v)[CT]) {
         if (col >= HP) return;     // a wavefront without columns
@@ -166,7 +169,7 @@ __global__ __launch_bounds__(64 * batch_waves(NK), batch_waves(NK) / 4) void rec
         }
 #pragma unroll
         for (int t = 0; t < CT; ++t)
-            if (is_inf(v[t])) s_inf[buf] = number;
+            if (at_least(v[t], limit)) s_inf[buf] = number;
     };
 
     // ---- initial state tile: slot 0 of the history / Delta[T-1] ------------------------------------
@@ -196,9 +199,9 @@ __global__ __launch_bounds__(64 * batch_waves(NK), batch_waves(NK) / 4) void rec
         }
     }
     put(0, 0, last);
-    if (odd) s_odd = 1;            // (read after the barrier only)
+    if (odd) { s_odd = 1; s_inf[0] = 0; }     // (read after the barrier only)
     __syncthreads();
-    const bool odd_matrix = __builtin_amdgcn_readfirstlane(s_odd) != 0;
+    limit = __builtin_amdgcn_readfirstlane(s_odd) ? 0u : NO_SPLIT;
 
     // Epilogue operands, requested two steps ahead.
     // forward: x0 = input term U[s]; reverse (t = T-2-s): x0 = G[t], x1 = h_t = h_all[t+1].
@@ -246,22 +249,6 @@ __global__ __launch_bounds__(64 * batch_waves(NK), batch_waves(NK) / 4) void rec
             if (c + AHEAD < NK) fetch(c + AHEAD);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (odd_matrix || __builtin_amdgcn_readfirstlane(inf) == number) {   // plain float32, straight from memory
-            for (int t = 0; t < CT; ++t) {
-                float sum = 0.f;
-                const int n = min(col + t, H - 1);
-                for (int k = 0; k < H; ++k) {
-                    float h = 0.f;
-                    for (int q = 0; q < 3; ++q) {
-                        const float part = __uint_as_float((unsigned)hs[cur][q * R4 + rg][k] << 16);
-                        if (q == 0 || !is_inf(h)) h += part;
-                    }
-                    sum = fmaf(h, BWD ? a.Wh[(size_t)k * H + n] : a.Wh[(size_t)n * H + k], sum);
-                }
-                out[t] = sum;
-            }
-            return;
-        }
         // lane group g, register e: row group g (part of the state) of batch row e.  Adding the groups
         // and moving batch row g to lane group g is one swap of halves and one of 16-lane rows.
 #pragma unroll
@@ -275,6 +262,22 @@ __global__ __launch_bounds__(64 * batch_waves(NK), batch_waves(NK) / 4) void rec
             }
             const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(u[0]), __float_as_uint(u[1]), false, false);
             out[t] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        }
+        if (__builtin_amdgcn_readfirstlane(inf) == number) [[unlikely]] {   // plain float32, straight from memory
+            // The parts cannot tell a number that rounds to infinity from an infinity, so the state is read from where
+            // store_state has put it.  All wavefronts of the workgroup are here, each waits for its own stores.
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            lds_barrier();
+            const float* h = (BWD ? a.Delta + (size_t)(T - 1 - number) * bh : a.hist + (size_t)(a.ring ? number & 1 : number) * bh) +
+                             (size_t)min(b0 + rg, B - 1) * H;
+            for (int t = 0; t < CT; ++t) {
+                float sum = 0.f;
+                const int n = min(col + t, H - 1);
+                for (int k = 0; k < H; ++k)
+                    sum = fmaf(__hip_atomic_load(h + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                               BWD ? a.Wh[(size_t)k * H + n] : a.Wh[(size_t)n * H + k], sum);
+                out[t] = sum;
+            }
         }
     };
 
@@ -308,6 +311,9 @@ __global__ __launch_bounds__(64 * batch_waves(NK), batch_waves(NK) / 4) void rec
 
     // pairs of steps with no branch between them (exact wait counts), then the odd one out
     int s2 = 0;
+    // Where the loop lies against 64 bytes moves a step by up to 4 % (256 units, 1024 steps, forward and reverse: 1025 + 1034 us
+    // here, 1040 + 1038 left to chance); this place is the best for 200 and 256 units and costs the smaller ones nothing.
+    asm volatile(".p2align 6\n\t.fill 4, 4, 0xbf800000");   // s_nop 0
     for (; s2 + 1 < nsteps; s2 += 2) {
         step(s2, std::integral_constant<int, 0>{});
         step(s2 + 1, std::integral_constant<int, 1>{});
