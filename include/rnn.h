@@ -74,7 +74,8 @@ extern "C" {
  * (error per product term below 2^-16 relative; parameters, results and everything else stay
  * float32).  Without it the same products split every operand into three bf16 numbers, which hold all
  * 24 bits, and take six products: float32 accuracy.  Set it on rnn_workspace_bytes, rnn_loss and
- * rnn_bptt alike.  Ignored where the column-strip kernels of a short single
+ * rnn_bptt alike; rnn_forward, rnn_workspace_init and rnn_workspace_status take a workspace sized with it
+ * whether it is set in their dims or not (every other flag leaves the size and the layout alone).  Ignored where the column-strip kernels of a short single
  * sequence serve the output layer; rnn_gauss_newton_vec takes it too (its five output-layer
  * products); rejected by rnn_window and rnn_train_stream. */
 #define RNN_FLAG_BF16X3_OUTPUT 16u

@@ -72,19 +72,19 @@ Sizes sizes_of(const rnn_dims* d) {
 // bf16 numbers an operand of the output layer's and the weight gradients' products is split into
 int output_parts(const rnn_dims* d) { return (d->flags & RNN_FLAG_BF16X3_OUTPUT) ? 2 : 3; }
 
-size_t max_splitk_floats(const Sizes& s, int parts) {
+size_t max_splitk_floats(const Sizes& s) {
     const int N = (int)s.N, H = s.H, O = s.O, D = s.NVin;
     size_t m = 0;
     auto take = [&](size_t v) { if (v > m) m = v; };
-    take(gemm_splitk_floats(N, O, H, parts));   // Z = Hs V
-    take(gemm_splitk_floats(H, O, N, parts));   // dV = Hs^T dZ
-    take(gemm_splitk_floats(N, H, O, parts));   // G = dZ V^T
-    take(gemm_splitk_floats(H, H, N, parts));   // dWh = Delta^T Hprev
-    take(gemm_splitk_floats(s.B, H, H)); // dh0 = delta_0 Wh (stepwise recurrence)
-    if (!s.tokens) {
-        take(gemm_splitk_floats(N, H, D));  // U = X Wx^T
-        take(gemm_splitk_floats(H, D, N, parts));  // dWx = Delta^T X
+    for (int parts = 2; parts <= 3; ++parts) {
+        take(gemm_splitk_floats(N, O, H, parts));   // Z = Hs V
+        take(gemm_splitk_floats(H, O, N, parts));   // dV = Hs^T dZ
+        take(gemm_splitk_floats(N, H, O, parts));   // G = dZ V^T
+        take(gemm_splitk_floats(H, H, N, parts));   // dWh = Delta^T Hprev
+        if (!s.tokens) take(gemm_splitk_floats(H, D, N, parts));  // dWx = Delta^T X
     }
+    take(gemm_splitk_floats(s.B, H, H)); // dh0 = delta_0 Wh (stepwise recurrence)
+    if (!s.tokens) take(gemm_splitk_floats(N, H, D));  // U = X Wx^T
     return m;
 }
 
@@ -117,8 +117,12 @@ Variant pick_variant(const rnn_dims* d) {
     return v;
 }
 
+// One layout whatever the flags: the calls of a window may differ in them (rnn_forward is not asked for the flag of the
+// split products), and the status word and the exchange words have to lie in the same place for all of them.
 Plan make_plan(const rnn_dims* d) {
     const Sizes s = sizes_of(d);
+    rnn_dims plain = *d;
+    plain.flags = 0;
     const size_t N = (size_t)s.N, H = (size_t)s.H, O = (size_t)s.O, B = (size_t)s.B;
     Plan p;
     size_t off = 0;
@@ -126,7 +130,7 @@ Plan make_plan(const rnn_dims* d) {
     p.Z = take(N * O * 4);
     p.lse = take(N * 4);
     p.rowloss = take(N * 4);
-    p.U = take((!s.tokens || pick_variant(d).batch_mfma || s.B > 4) ? N * H * 4 : 0);  // hoisted input term (dense, or batched tokens)
+    p.U = take((!s.tokens || pick_variant(&plain).batch_mfma || s.B > 4) ? N * H * 4 : 0);  // hoisted input term (dense, or batched tokens)
     // (also scratch of the token gradient once the reverse loop has read it)
     const size_t g_floats = s.tokens && N > 32 && dwx_scratch_floats((int)N, s.H) > N * H ? dwx_scratch_floats((int)N, s.H) : N * H;
     p.G = take(g_floats * 4);
@@ -135,7 +139,7 @@ Plan make_plan(const rnn_dims* d) {
     p.hring = take(2 * B * H * 4);
     const size_t widest = O > H ? O : H;
     p.part = take((size_t)colsum_chunks((int)N) * widest * 4);
-    p.splitk = take(max_splitk_floats(s, output_parts(d)) * 4);
+    p.splitk = take(max_splitk_floats(s) * 4);
     p.scratch = take(256);
     // state-exchange boxes of the multi-workgroup loops
     const size_t ring = rec_xcd_supported(s.H, s.B, s.T) ? rec_xcd_ring_bytes(s.H, s.B) : 0;
@@ -148,10 +152,15 @@ Plan make_plan(const rnn_dims* d) {
     p.vy = take(small ? N * H * 4 : 0);
     p.seen = take(s.tokens && N > 32 ? dwx_table_ints((int)N, s.NVin) * 4 : 0);
     // row statistics the logits product leaves per column part (fused log-sum-exp)
-    const int parts = output_parts(d);
-    p.lstat = take(s.ce && gemm_fuses_stats((int)N, s.O, s.H, parts)
-                       ? N * (size_t)gemm_stat_parts((int)N, s.O, s.H, parts) * 8 : 0);
-    // a workspace sized without the flag stays too small for a call with it
+    size_t stat_parts = 0;
+    for (int parts = 2; s.ce && parts <= 3; ++parts)
+        if (gemm_fuses_stats((int)N, s.O, s.H, parts)) {
+            const size_t n = (size_t)gemm_stat_parts((int)N, s.O, s.H, parts);
+            if (n > stat_parts) stat_parts = n;
+        }
+    p.lstat = take(N * stat_parts * 8);
+    // A size asked for with the split-product flag is larger than one without it and serves both kinds of call; a call with
+    // the flag refuses a workspace sized without.
     if (d->flags & RNN_FLAG_BF16X3_OUTPUT) take(256);
     p.total = off;
     return p;

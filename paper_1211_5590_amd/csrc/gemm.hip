@@ -601,9 +601,9 @@ GemmPlan search_plan(int M, int N, int K, int parts) {
 // sizes it has met last.
 GemmPlan plan_gemm(int M, int N, int K, int parts) {
     struct Entry { int M, N, K, parts; GemmPlan plan; };
-    static thread_local Entry seen[32];
+    static thread_local Entry seen[128];
     const unsigned h = (unsigned)M * 0x9e3779b1u ^ (unsigned)N * 0x85ebca6bu ^ (unsigned)K * 0xc2b2ae35u ^ (unsigned)parts;
-    Entry& e = seen[(h ^ h >> 15) & 31u];
+    Entry& e = seen[(h ^ h >> 15) & 127u];
     if (e.M != M || e.N != N || e.K != K || e.parts != parts) e = {M, N, K, parts, search_plan(M, N, K, parts)};
     return e.plan;
 }

@@ -196,3 +196,22 @@ def test_measure_ceilings_rejects_bad_arguments_without_a_gpu():
     assert L.rnn_measure_ceilings(fake, 1 << 30, None, None) == -1
     assert L.rnn_measure_ceilings(fake, (128 << 20) - 1, res, None) == -1     # scratch too short
     assert L.rnn_measure_ceilings(fake + 8, 1 << 30, res, None) == -1       # misaligned
+
+
+def test_one_workspace_serves_calls_with_and_without_the_flags():
+    """The calls of a window share a workspace and need not set the same flags: a size asked for with the split-product
+    flag serves calls without it, and no other flag changes the size.  Sizes over the whole range, and some at which the
+    products' plans with and without the split-product flag differ most."""
+    import random
+    rng = random.Random(5)
+    log = lambda lo, hi: int(round(lo * (hi / lo) ** rng.random()))   # noqa: E731
+    sizes = [(305, 260, 36, 8), (9973, 650, 70, 33), (6200, 1023, 161, 11), (2421, 679, 34, 35), (300, 200, 36, 2)]
+    sizes += [(log(8, 12000), log(4, 1100), log(1, 300), log(1, 70)) for _ in range(600)]
+    for nv, H, T, B in sizes:
+        for kind in (0, 1):
+            d = dict(in_dim=nv if kind == 0 else min(nv, 200), hidden=H, out_dim=nv, seq_len=T, batch=B, input_kind=kind)
+            plain = rnn.rnn_workspace_bytes(good_dims(**d))
+            flag = rnn.rnn_workspace_bytes(good_dims(**d, flags=rnn.FLAG_BF16X3_OUTPUT))
+            assert flag > plain, d
+            for other in (rnn.FLAG_ACCUMULATE, rnn.FLAG_SYNC, rnn.FLAG_BPTT_RECOMPUTE, rnn.FLAG_REFERENCE_KERNELS):
+                assert rnn.rnn_workspace_bytes(good_dims(**d, flags=other)) == plain, (d, other)

@@ -72,3 +72,24 @@ def test_split_products_stay_close_to_the_float32_path_and_repeat_exactly():
         assert np.array_equal(a[k], b[k]), k
         scale = np.abs(f32[k]).max()
         assert np.abs(a[k] - f32[k]).max() <= 5e-5 * scale, (k, np.abs(a[k] - f32[k]).max() / scale)
+
+
+# vocabulary, hidden, steps, batch: sizes at which the products with the flag cut K otherwise than those without
+@pytest.mark.parametrize("NV,H,T,B", [(305, 260, 36, 8), (2421, 679, 34, 35), (300, 200, 36, 2), (40, 24, 9, 1)])
+@pytest.mark.parametrize("forward_flags", [0, rnn.FLAG_REFERENCE_KERNELS], ids=["plain", "reference_kernels"])
+def test_a_forward_call_without_the_flag_on_a_workspace_sized_with_it(NV, H, T, B, forward_flags):
+    """The header asks for the flag on rnn_workspace_bytes, rnn_loss and rnn_bptt, not on rnn_forward: that call takes
+    the workspace, and leaves the status word and what the others exchange in it alone."""
+    case = ri.make_case(NV, H, NV, T, B, wdist=("normal", 0.3 / np.sqrt(H)), bias_std=0.1, with_h0=True, seed=40 + H)
+    ref = oracle.fwd_bptt(case, h0=case["h0"])
+    r = Runner(case, BF3)
+    for _ in range(2):
+        r.set_flags(forward_flags)
+        r.forward()
+        assert rnn.rnn_workspace_status(r.dims, r.ws) == 0
+        r.set_flags(BF3)
+        assert rnn.rnn_workspace_status(r.dims, r.ws) == 0
+        r.loss_()
+        r.bptt()
+        assert rnn.rnn_workspace_status(r.dims, r.ws) == 0
+        compare(r.results(), ref)
