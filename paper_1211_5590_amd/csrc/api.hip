@@ -130,7 +130,8 @@ Plan make_plan(const rnn_dims* d) {
     p.Z = take(N * O * 4);
     p.lse = take(N * 4);
     p.rowloss = take(N * 4);
-    p.U = take((!s.tokens || pick_variant(&plain).batch_mfma || s.B > 4) ? N * H * 4 : 0);  // hoisted input term (dense, or batched tokens)
+    // hoisted input term: dense input, or the rows of Wx gathered for the batched loop (the other loops fetch theirs)
+    p.U = take(!s.tokens || pick_variant(&plain).batch_mfma ? N * H * 4 : 0);
     // (also scratch of the token gradient once the reverse loop has read it)
     const size_t g_floats = s.tokens && N > 32 && dwx_scratch_floats((int)N, s.H) > N * H ? dwx_scratch_floats((int)N, s.H) : N * H;
     p.G = take(g_floats * 4);

@@ -109,12 +109,6 @@ __device__ __forceinline__ float max16(float v) {
     v = fmaxf(v, dpp<0x141>(v)); v = fmaxf(v, dpp<0x140>(v));
     return v;
 }
-__device__ __forceinline__ float max32(float v) {
-    v = max16(v);
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 
 __device__ __forceinline__ float sigmoidf_fast(float a) {

@@ -215,3 +215,11 @@ def test_one_workspace_serves_calls_with_and_without_the_flags():
             assert flag > plain, d
             for other in (rnn.FLAG_ACCUMULATE, rnn.FLAG_SYNC, rnn.FLAG_BPTT_RECOMPUTE, rnn.FLAG_REFERENCE_KERNELS):
                 assert rnn.rnn_workspace_bytes(good_dims(**d, flags=other)) == plain, (d, other)
+
+
+def test_token_input_of_a_wide_layer_reserves_no_input_term():
+    """Its loops fetch the rows of Wx themselves: T B H floats less than dense input, whose projection is kept."""
+    T, B, H = 256, 64, 1024
+    d = dict(in_dim=64, hidden=H, out_dim=64, seq_len=T, batch=B)
+    tokens, dense = (rnn.rnn_workspace_bytes(good_dims(**d, input_kind=k)) for k in (0, 1))
+    assert dense - tokens >= 0.9 * T * B * H * 4
