@@ -40,8 +40,6 @@
 
 #include <math.h>
 
-#include <atomic>
-
 namespace rnn {
 namespace {
 
@@ -613,14 +611,8 @@ hipError_t launch_form(const GemmParams& p, hipStream_t s) {
     constexpr int NW = WGM * WGN;
     constexpr size_t smem = (NW == 8 ? 3 : 2) * (size_t)(Operand<WGM * TM * 32, BK, !AT, NW, PARTS>::BYTES + Operand<WGN * TN * 32, BK, BT, NW, PARTS>::BYTES);
     auto* kernel = &gemm_kernel<WGM, WGN, TM, TN, BK, PF, MINW, PARTS, AT, BT, STATS>;
-    if (smem > 65536) {   // per kernel form and process: allow more than 64 KB of dynamic LDS
-        static std::atomic<bool> raised{false};
-        if (!raised.load(std::memory_order_acquire)) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-            if (e != hipSuccess) return e;
-            raised.store(true, std::memory_order_release);
-        }
-    }
+    const hipError_t e = allow_lds(reinterpret_cast<const void*>(kernel), smem);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3(p.tiles_m * p.tiles_n, 1, p.splits), dim3(NW * 64), smem, s, p);
     return hipGetLastError();
 }

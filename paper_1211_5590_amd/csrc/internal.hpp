@@ -146,6 +146,8 @@ size_t rec_xcd_ring_bytes(int H, int B);
 bool rec_xcd_ready(int H, int act, bool bwd);               // and the current device can hold the grid at once
 hipError_t launch_rec_xcd(const RecXcdArgs& a, bool bwd, hipStream_t s);
 
+// before a launch of `fn` with that much dynamic LDS on the current device (lds_limit.hip)
+hipError_t allow_lds(const void* fn, size_t bytes);
 hipError_t launch_zero_words(int32_t* p, int n, hipStream_t s);
 // polls a bounded wait between workgroups makes before it gives up (host state, rnn_set_wait_limit)
 int wait_limit();

@@ -658,13 +658,8 @@ hipError_t launch_rec_bwd_with_strips(RecResArgs a, const RecResPlan& pl, const 
                                 : (const void*)rec_bwd_with_strips_kernel<1>;
     size_t smem = pl.smem;
     if (skinny::back_smem(a.H) > smem) smem = skinny::back_smem(a.H);
-    static size_t allowed[2] = {0, 0};
-    const int slot = a.act == 0 ? 0 : 1;
-    if (smem > 64 * 1024 && smem > allowed[slot]) {
-        hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        if (e != hipSuccess) return e;
-        allowed[slot] = smem;
-    }
+    const hipError_t e = allow_lds(fn, smem);
+    if (e != hipSuccess) return e;
     ProfileScope ps(K_REC_BWD, s);
     const dim3 grid(1 + skinny_strips(k.O)), block(kThreads);
     if (a.act == 0) hipLaunchKernelGGL((rec_bwd_with_strips_kernel<0>), grid, block, smem, s, a, k);
@@ -729,13 +724,8 @@ hipError_t launch_rec_resident(RecResArgs a, const RecResPlan& pl, bool bwd, hip
     const void* fn;
     if (!bwd) fn = a.act == 0 ? (const void*)rec_resident_kernel<0, false> : (const void*)rec_resident_kernel<1, false>;
     else fn = a.act == 0 ? (const void*)rec_resident_kernel<0, true> : (const void*)rec_resident_kernel<1, true>;
-    static size_t allowed[4] = {0, 0, 0, 0};
-    const int slot = (bwd ? 2 : 0) + (a.act == 0 ? 0 : 1);
-    if (pl.smem > 64 * 1024 && pl.smem > allowed[slot]) {
-        hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.smem);
-        if (e != hipSuccess) return e;
-        allowed[slot] = pl.smem;
-    }
+    const hipError_t e = allow_lds(fn, pl.smem);
+    if (e != hipSuccess) return e;
     ProfileScope ps(bwd ? K_REC_BWD : K_REC_FWD, s);
     dim3 grid(pl.P, a.B), block(kThreads);
     a.xcd_pack = 0;

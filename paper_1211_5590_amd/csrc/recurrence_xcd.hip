@@ -466,7 +466,7 @@ bool rec_xcd_ready(int H, int act, bool bwd) {
     for (int i = 0; i < n_seen; ++i)
         if (seen[i].fn == fn && seen[i].dev == dev) return seen[i].ok;
     int per_cu = 0, cus = 0;
-    const bool ok = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess &&
+    const bool ok = allow_lds(fn, lds) == hipSuccess &&
                     hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, XT, lds) == hipSuccess &&
                     hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
                     per_cu >= 1 && cus == NXCD * WG_PER_XCD;

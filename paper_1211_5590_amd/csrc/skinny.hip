@@ -277,14 +277,8 @@ bool skinny_supported(int N, int H, int O) {
 }
 
 hipError_t launch_skinny_logits(const SkinnyArgs& a, hipStream_t s) {
-    static size_t allowed = 0;
-    if (logits_smem(a.H) > 64 * 1024 && logits_smem(a.H) > allowed) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(skinny_logits_kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)logits_smem(a.H));
-        if (e != hipSuccess) return e;
-        allowed = logits_smem(a.H);
-    }
+    const hipError_t e = allow_lds(reinterpret_cast<const void*>(skinny_logits_kernel), logits_smem(a.H));
+    if (e != hipSuccess) return e;
     ProfileScope ps(K_SKINNY_LOGITS, s);
     hipLaunchKernelGGL(skinny_logits_kernel, dim3(skinny_strips(a.O)), dim3(NTH), logits_smem(a.H), s, a);
     return hipGetLastError();

@@ -1296,19 +1296,6 @@ void bind_boxes(StreamArgs& a, void* workspace, const StreamPlan& pl) {
     a.spin_limit = wait_limit();
 }
 
-// dynamic LDS above 64 KB has to be allowed once per kernel
-hipError_t allow_lds(const void* fn, size_t bytes) {
-    static const void* seen[32];
-    static size_t seen_bytes[32];
-    static int n_seen = 0;
-    if (bytes <= 64 * 1024) return hipSuccess;
-    for (int i = 0; i < n_seen; ++i)
-        if (seen[i] == fn && seen_bytes[i] >= bytes) return hipSuccess;
-    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    if (e == hipSuccess && n_seen < 32) { seen[n_seen] = fn; seen_bytes[n_seen] = bytes; ++n_seen; }
-    return e;
-}
-
 // Can `blocks` workgroups of this kernel be resident at once on the current device?  The
 // one-window kernels wait for each other inside the launch, so a plain launch is only used when
 // the whole grid fits the chip by itself; otherwise the launch is cooperative (the runtime then
