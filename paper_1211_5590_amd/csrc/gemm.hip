@@ -81,7 +81,10 @@ __device__ __forceinline__ void split_pair(float x, float y, unsigned (&w)[PARTS
 // request); else at src[k*ld + r] (a lane fetches 8 k of one row, 64 consecutive rows per request).
 // Every address is a base that is uniform over the wavefront plus a small lane offset.  Rows past the
 // end repeat the last one; what they give is never stored.
-template <int R, int BK, bool KCONTIG, int NW, int PARTS>
+// WIDE: leading dimensions whose offsets do not fit 32 bits (a vocabulary of tens of millions); every lane
+// has an address of its own.
+constexpr int LD_MAX = 1 << 26;   // 15 rows of that are the last offset below 2^32 bytes
+template <int R, int BK, bool KCONTIG, int NW, int PARTS, bool WIDE>
 struct Operand {
     static constexpr int UNIT = KCONTIG ? 4 : 8;                       // elements per unit
     static constexpr int U = R * BK / UNIT / (NW * 64);                // units per thread
@@ -91,7 +94,7 @@ struct Operand {
     static constexpr int PLANE = CHUNK * (BK / 8);                     // bytes of one part
     static constexpr int BYTES = PLANE * PARTS;
 
-    const float* base[U];   // uniform
+    const float* base[U];   // uniform (WIDE: the lane's own)
     unsigned voff[U];       // lane offset, bytes
     int koff[U];            // first k of the unit inside a slab
     int lds[U];             // byte offset of the unit inside a part's plane
@@ -115,6 +118,12 @@ struct Operand {
                 koff[u] = kq * 8;
                 lds[u] = kq * CHUNK + r * 16;
             }
+            if (WIDE) {
+                const int row = KCONTIG ? g * RPI + lane / LPR : (g % GR) * 64 + lane;
+                const size_t r = (size_t)min(r0 + row, rlim - 1), k = (size_t)(kbeg + koff[u]);
+                base[u] = KCONTIG ? src + r * ld + (size_t)kbeg : src + k * ld + r;
+                voff[u] = KCONTIG ? (unsigned)koff[u] * 4u : 0u;
+            }
         }
     }
     // Buffer requests: the uniform part of an address stays in scalar registers.
@@ -126,7 +135,14 @@ struct Operand {
     __device__ __forceinline__ void load(float (&x)[U][UNIT], int ld, int k) const {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (KCONTIG) {
+            if constexpr (WIDE && KCONTIG) {
+                const f32x4u t = *reinterpret_cast<const f32x4u*>(base[u] + koff[u] + k);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[u][e] = t[e];
+            } else if constexpr (WIDE) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) x[u][e % UNIT] = base[u][(size_t)(k + e) * ld];
+            } else if (KCONTIG) {
                 const f32x4 t = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(window(base[u] + k), voff[u], 0, 0));
 #pragma unroll
                 for (int e = 0; e < 4; ++e) x[u][e] = t[e];
@@ -187,11 +203,11 @@ __device__ __forceinline__ void tile_coords(int bid, int tiles_m, int tiles_n, i
 }
 
 // WGM x WGN wavefronts, each TM x TN blocks of 32x32; AT: A is [K,M]; BT: B is [N,K]
-template <int WGM, int WGN, int TM, int TN, int BK, int PF, int MINW, int PARTS, bool AT, bool BT, bool STATS>
+template <int WGM, int WGN, int TM, int TN, int BK, int PF, int MINW, int PARTS, bool AT, bool BT, bool STATS, bool WIDE>
 __global__ __launch_bounds__(WGM* WGN * 64, MINW) void gemm_kernel(GemmParams p) {
     constexpr int NW = WGM * WGN, BM = WGM * TM * 32, BN = WGN * TN * 32;
-    typedef Operand<BM, BK, !AT, NW, PARTS> OpA;
-    typedef Operand<BN, BK, BT, NW, PARTS> OpB;
+    typedef Operand<BM, BK, !AT, NW, PARTS, WIDE> OpA;
+    typedef Operand<BN, BK, BT, NW, PARTS, WIDE> OpB;
     constexpr int STAGE = OpA::BYTES + OpB::BYTES;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];   // [2 or 3][STAGE]
 
@@ -542,22 +558,6 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
     }
 }
 
-// Leading dimensions beyond the 32-bit offsets of the tiled kernel's requests (a vocabulary of tens of
-// millions): one output per thread.
-constexpr int LD_MAX = 1 << 26;
-__global__ __launch_bounds__(256) void gemm_wide_kernel(GemmParams p, int a_t, int b_t) {
-    const size_t total = (size_t)p.M * p.N;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-        const size_t m = i / p.N, n = i % p.N;
-        float s = 0.f;
-        for (int k = 0; k < p.K; ++k)
-            s = fmaf(a_t ? p.A[(size_t)k * p.lda + m] : p.A[m * p.lda + k], b_t ? p.B[n * p.ldb + k] : p.B[(size_t)k * p.ldb + n], s);
-        if (p.bias_n) s += p.bias_n[n];
-        float* dst = p.C + m * p.ldc + n;
-        *dst = p.beta ? *dst + s : s;
-    }
-}
-
 struct GemmPlan { int tile, splits, kchunk; };
 
 // Tile and K cut of a product: the pair with the least estimated time.  The estimate is, per round of
@@ -577,8 +577,20 @@ GemmPlan search_plan(int M, int N, int K, int parts) {
     const double out = 4.0 * M * (double)N;
     GemmPlan best{};
     double t_best = 1e300;
+    if (K > 1 << 23) {
+        // Sums of many millions of terms: a matrix instruction's accumulator drifts by about 2^-32 of itself per 16 terms
+        // of one sign, so the length of a cut's sum, not the time, decides: at most 2^15 terms, as far as the partials
+        // fit.  (67 million terms of one sign, cut 256 ways: 2.8e-6 off, cut 2049 ways: 1.6e-7, in float32 matrix
+        // instructions cut 1024 ways: 4.4e-7.)
+        const double tiles = (double)((M - 1) / 64 + 1) * (double)((N - 1) / 64 + 1);
+        const double most = fmin(fmin(65536.0 / tiles, 4e9 / out), 32768.0), want = ceil(K / 32768.0);
+        const long cut = (long)fmax(1.0, fmin(want, most)), slabs = ((long)K + 31) / 32, per = (slabs + cut - 1) / cut;
+        return {64, (int)((slabs + per - 1) / per), (int)(per * 32)};
+    }
+    const bool wide = N > LD_MAX || K > LD_MAX;     // a leading dimension may be: the 64 x 64 tile has that form
     for (const Form& f : forms[parts == 2 ? 0 : 1]) {
-        const double tiles = (double)((M + f.tile - 1) / f.tile) * (double)((N + f.tile - 1) / f.tile);
+        if (wide && f.tile != 64) continue;
+        const double tiles = (double)((M - 1) / f.tile + 1) * (double)((N - 1) / f.tile + 1);
         const long slabs = ((long)K + f.bk - 1) / f.bk;
         for (const int cut : cuts) {
             if (cut > 1 && (2 * cut > slabs || tiles * cut > 65536.0 || cut * out > 4e9)) break;   // at least two slabs per cut
@@ -606,11 +618,11 @@ GemmPlan plan_gemm(int M, int N, int K, int parts) {
     return e.plan;
 }
 
-template <int WGM, int WGN, int TM, int TN, int BK, int PF, int MINW, int PARTS, bool AT, bool BT, bool STATS>
+template <int WGM, int WGN, int TM, int TN, int BK, int PF, int MINW, int PARTS, bool AT, bool BT, bool STATS, bool WIDE = false>
 hipError_t launch_form(const GemmParams& p, hipStream_t s) {
     constexpr int NW = WGM * WGN;
-    constexpr size_t smem = (NW == 8 ? 3 : 2) * (size_t)(Operand<WGM * TM * 32, BK, !AT, NW, PARTS>::BYTES + Operand<WGN * TN * 32, BK, BT, NW, PARTS>::BYTES);
-    auto* kernel = &gemm_kernel<WGM, WGN, TM, TN, BK, PF, MINW, PARTS, AT, BT, STATS>;
+    constexpr size_t smem = (NW == 8 ? 3 : 2) * (size_t)(Operand<WGM * TM * 32, BK, !AT, NW, PARTS, WIDE>::BYTES + Operand<WGN * TN * 32, BK, BT, NW, PARTS, WIDE>::BYTES);
+    auto* kernel = &gemm_kernel<WGM, WGN, TM, TN, BK, PF, MINW, PARTS, AT, BT, STATS, WIDE>;
     const hipError_t e = allow_lds(reinterpret_cast<const void*>(kernel), smem);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3(p.tiles_m * p.tiles_n, 1, p.splits), dim3(NW * 64), smem, s, p);
@@ -626,6 +638,12 @@ hipError_t launch_tile(int tile, const GemmParams& p, hipStream_t s) {
 
 template <int PARTS>
 hipError_t launch_layout(int tile, bool a_t, bool b_t, const GemmParams& p, hipStream_t s) {
+    if (p.lda > LD_MAX || p.ldb > LD_MAX) {
+        if (tile != 64 || p.stats) return hipErrorInvalidValue;   // (neither comes out of a plan of such sizes)
+        if (a_t) return launch_form<2, 2, 1, 1, 32, 2, 2, PARTS, true, false, false, true>(p, s);
+        if (b_t) return launch_form<2, 2, 1, 1, 32, 2, 2, PARTS, false, true, false, true>(p, s);
+        return launch_form<2, 2, 1, 1, 32, 2, 2, PARTS, false, false, false, true>(p, s);
+    }
     if (p.stats) return launch_tile<PARTS, false, false, true>(tile, p, s);
     if (a_t) return launch_tile<PARTS, true, false, false>(tile, p, s);
     if (b_t) return launch_tile<PARTS, false, true, false>(tile, p, s);
@@ -636,7 +654,7 @@ hipError_t launch_layout(int tile, bool a_t, bool b_t, const GemmParams& p, hipS
 
 int gemm_stat_parts(int M, int N, int K, int parts) {
     const GemmPlan pl = plan_gemm(M, N, K, parts);
-    return (N + pl.tile - 1) / pl.tile * (pl.tile == 64 ? 2 : pl.tile / 64);
+    return ((N - 1) / pl.tile + 1) * (pl.tile == 64 ? 2 : pl.tile / 64);
 }
 bool gemm_fuses_stats(int M, int N, int K, int parts) { return N <= LD_MAX && K <= LD_MAX && plan_gemm(M, N, K, parts).splits == 1; }
 
@@ -718,14 +736,8 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
     p.stats = pl.splits == 1 ? g.row_stats : nullptr;
     if (p.stats && (g.a_t || g.b_t)) return hipErrorInvalidValue;   // only the output projection carries them
     p.kchunk = pl.kchunk; p.beta = g.beta; p.splits = pl.splits;
-    p.tiles_m = (g.M + pl.tile - 1) / pl.tile;
-    p.tiles_n = (g.N + pl.tile - 1) / pl.tile;
-    if (g.lda > LD_MAX || g.ldb > LD_MAX) {
-        p.C = g.C; p.ldc = g.ldc;
-        ProfileScope ps(g.prof_id, s);
-        hipLaunchKernelGGL(gemm_wide_kernel, dim3(4096), dim3(256), 0, s, p, g.a_t ? 1 : 0, g.b_t ? 1 : 0);
-        return hipGetLastError();
-    }
+    p.tiles_m = (g.M - 1) / pl.tile + 1;
+    p.tiles_n = (g.N - 1) / pl.tile + 1;
     if (pl.splits > 1) { p.C = g.splitk_ws; p.ldc = g.N; } else { p.C = g.C; p.ldc = g.ldc; }
     {
         ProfileScope ps(g.prof_id, s);
