@@ -15,8 +15,11 @@
 // bf16 matrix rate is 16 times the float32 one, so six products still leave a factor of 2.6.
 // RNN_FLAG_BF16X3_OUTPUT's products leave lo away: hi hi + hi mid + mid hi (PARTS = 2).
 // Operands that hold infinities or NaNs, or so large that hi rounds to infinity, give a result
-// that is not finite; a wavefront that sees one computes its part of the tile again with
-// v_mfma_f32_32x32x2_f32 straight from memory, so such inputs give what float32 gives.
+// that is not finite.  A workgroup that sees one looks its operands over for NaNs, which make the same results NaN
+// in either form, and computes its tile again with v_mfma_f32_32x32x2_f32 if that does not explain all it sees,
+// so such inputs give what float32 gives.  (256 steps, batch 64, 1024 units, 10000 classes with a NaN in one initial state, the
+// whole step: 7.8 ms, 6.6 without it; recomputed wavefront by wavefront from memory, as it was, 61.  The loss
+// alone with an infinite row of V, where every tile is computed again: 4.5 ms, 1.8 without, as it was 15.7.)
 //
 // Where the split is made.  Operands stay float32 in memory, in either orientation and at any
 // 4-byte aligned address; a thread splits what it has fetched on the way to LDS, 5.5 vector
@@ -168,6 +171,29 @@ struct Operand {
                 if (in) x[u][e] = KCONTIG ? at(base[u] + k + e, voff[u]) : at(base[u] + (size_t)(k + e) * ld, voff[u]);
             }
     }
+    // the unit's row of the tile
+    __device__ __forceinline__ static int row(int u, int wave, int lane) {
+        const int g = u * NW + wave;
+        return KCONTIG ? g * RPI + lane / LPR : (g % GR) * 64 + lane;
+    }
+    // marks the rows that hold a NaN
+    __device__ __forceinline__ static void mark(const float (&x)[U][UNIT], int* nan, int wave, int lane) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            bool any = false;
+#pragma unroll
+            for (int e = 0; e < UNIT; ++e) any = any || x[u][e] != x[u][e];
+            if (any) nan[row(u, wave, lane)] = 1;
+        }
+    }
+    // the slab as float32, [k][row]
+    static constexpr int PITCH = R + 4;
+    __device__ __forceinline__ void park_whole(const float (&x)[U][UNIT], float* tile, int wave, int lane) const {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < UNIT; ++e) tile[(koff[u] + e) * PITCH + row(u, wave, lane)] = x[u][e];
+    }
     __device__ __forceinline__ void park(const float (&x)[U][UNIT], unsigned char* tile) const {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -210,6 +236,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void gemm_kernel(GemmParams p)
     typedef Operand<BN, BK, BT, NW, PARTS, WIDE> OpB;
     constexpr int STAGE = OpA::BYTES + OpB::BYTES;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];   // [2 or 3][STAGE]
+    __shared__ int s_odd, s_again;
 
     const int lane = threadIdx.x % 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     const int wm = wave / WGN, wn = wave % WGN;
@@ -245,6 +272,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void gemm_kernel(GemmParams p)
     }
     oa.park(xa[0], lds);
     ob.park(xb[0], lds + OpA::BYTES);
+    if (threadIdx.x == 0) s_odd = s_again = 0;
     // requests past the end repeat the last slab, which nobody reads; with one slab there may be no
     // whole one to repeat
 #define GEMM_FETCH(slot, slab)                                     \
@@ -402,28 +430,74 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void gemm_kernel(GemmParams p)
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) odd = fmaf(acc[i][j][e], 0.f, odd);
-    if (__any(odd != odd)) {
-        for (int i = 0; i < TM; ++i) {
-            for (int j = 0; j < TN; ++j) {
-                f32x16 c;
+    if (__any(odd != odd)) s_odd = 1;
+    lds_barrier();                      // (also: nobody reads the slabs any more)
+    if (__builtin_amdgcn_readfirstlane(s_odd)) {
+        float ya[OpA::U][OpA::UNIT], yb[OpB::U][OpB::UNIT];
+        auto fetch = [&](int slab) {
+            if (left && slab == 0) {
+                oa.load_tail(ya, p.lda, whole * BK, left);
+                ob.load_tail(yb, p.ldb, whole * BK, left);
+            } else {
+                oa.load(ya, p.lda, shift + slab * BK);
+                ob.load(yb, p.ldb, shift + slab * BK);
+            }
+        };
+        int *nan_a = reinterpret_cast<int*>(lds), *nan_b = nan_a + BM;
+        for (int i = threadIdx.x; i < BM + BN; i += NW * 64) nan_a[i] = 0;
+        lds_barrier();
+        for (int s = 0; s < nk; ++s) {
+            fetch(s);
+            OpA::mark(ya, nan_a, wave, lane);
+            OpB::mark(yb, nan_b, wave, lane);
+        }
+        lds_barrier();
+        bool again = false;
 #pragma unroll
-                for (int e = 0; e < 16; ++e) c[e] = 0.f;
-                const size_t r = (size_t)min(r_first + 32 * i + lane % 32, p.M - 1);
-                const size_t n = (size_t)min(c_first + 32 * j + lane % 32, p.N - 1);
-                for (int k0 = 0; k0 < klen; k0 += 2) {
-                    const int k = k0 + lane / 32;
-                    float av = 0.f, bv = 0.f;
-                    if (k < klen) {
-                        av = AT ? p.A[(size_t)(kbeg + k) * p.lda + r] : p.A[r * p.lda + kbeg + k];
-                        bv = BT ? p.B[n * p.ldb + kbeg + k] : p.B[(size_t)(kbeg + k) * p.ldb + n];
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int4 nb = *reinterpret_cast<const int4*>(nan_b + wn * TN * 32 + 32 * j + 8 * q + 4 * (lane / 32));
+#pragma unroll
+                for (int i = 0; i < TM; ++i) {
+                    const int na = nan_a[wm * TM * 32 + 32 * i + lane % 32];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int n = e == 0 ? nb.x : e == 1 ? nb.y : e == 2 ? nb.z : nb.w;
+                        again = again || (!(fabsf(acc[i][j][4 * q + e]) <= 3.402823466e38f) && !na && !n);
                     }
-                    c = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, av, c, 0, 0, 0);
                 }
+            }
+        if (__any(again)) s_again = 1;
+        lds_barrier();
+        if (__builtin_amdgcn_readfirstlane(s_again)) {
+            float *ta = reinterpret_cast<float*>(lds), *tb = ta + BK * OpA::PITCH;
+            static_assert(BK * (OpA::PITCH + OpB::PITCH) * 4 <= 2 * STAGE, "a float32 slab fits the slab buffers");
 #pragma unroll
-                for (int ii = 0; ii < TM; ++ii)
+            for (int i = 0; i < TM; ++i)
 #pragma unroll
-                    for (int jj = 0; jj < TN; ++jj)
-                        if (ii == i && jj == j) acc[ii][jj] = c;
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+            fetch(0);
+            for (int s = 0; s < nk; ++s) {
+                oa.park_whole(ya, ta, wave, lane);
+                ob.park_whole(yb, tb, wave, lane);
+                lds_barrier();
+                if (s + 1 < nk) fetch(s + 1);
+#pragma unroll 2
+                for (int k = 0; k < BK; k += 2) {
+                    float av[TM], bv[TN];
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) av[i] = ta[(k + lane / 32) * OpA::PITCH + wm * TM * 32 + 32 * i + lane % 32];
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) bv[j] = tb[(k + lane / 32) * OpB::PITCH + wn * TN * 32 + 32 * j + lane % 32];
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv[j], av[i], acc[i][j], 0, 0, 0);
+                }
+                lds_barrier();
             }
         }
     }
@@ -445,7 +519,6 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void gemm_kernel(GemmParams p)
     // request covers whole stretches of rows (TN * 128 bytes) and not 32 pieces of 16 bytes.
     constexpr int ROW = TN * 32 + 4, CL = TN * 8, RS = 64 / CL;   // floats per row; lanes per row, rows per request
     static_assert(NW * 32 * ROW * 4 <= (NW == 8 ? 3 : 2) * STAGE, "the staging fits the slab buffers");
-    if constexpr (NW != 8) lds_barrier();   // (the two groups of the other form have just met)
     float* stage = reinterpret_cast<float*>(lds) + wave * 32 * ROW;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
