@@ -6,7 +6,8 @@
 //
 // Arithmetic.  A float32 number is the sum of three bf16 numbers, x = hi + mid + lo with
 // hi = bf16(x), mid = bf16(x - hi), lo = bf16(x - hi - mid) (8 significand bits each, round to
-// nearest: nothing of the 24 bits is lost), and a product term a b is taken as the six products
+// nearest: nothing of the 24 bits is lost down to about 1e-33, where lo becomes too small for bf16; a smaller
+// operand is off by up to 2^-134: a product of numbers of 1e-35 by 3e-6 of itself), and a product term a b is taken as the six products
 // hi lo + lo hi + mid mid + hi mid + mid hi + hi hi in float32 accumulators; the three dropped ones
 // are below 2^-24 |a b|.  Measured against 64 bits over sums of 128 to 16384 terms (random sign, equal
 // sign, nearly cancelling) the result is 0.3 to 0.75 times as far off as v_mfma_f32_16x16x4_f32 over

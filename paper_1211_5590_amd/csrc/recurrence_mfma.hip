@@ -12,7 +12,7 @@
 // What bounds it: the latency of one step, T times, on ceil(B/4) compute units; most of a step is matrix
 // instructions.  They run on v_mfma_f32_16x16x32_bf16 with float32 accumulation.  State and matrix are
 // split into three bf16 numbers each, which hold all 24 bits of a float32 (hi = bf16(x),
-// mid = bf16(x - hi), lo = bf16(x - hi - mid)).  The 16 rows of an instruction are the 4 batch rows times
+// mid = bf16(x - hi), lo = bf16(x - hi - mid); below about 1e-33 they are off by up to 2^-134).  The 16 rows of an instruction are the 4 batch rows times
 // (hi, mid, lo, zero), so one pass over the state per part of the matrix gives all nine products;
 // the row groups lie 16 lanes apart and are added by three register swaps, which also leave batch row g in
 // lane group g.  At 256 units that is 1536 clocks of matrix instructions per step where the float32
