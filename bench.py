@@ -228,6 +228,7 @@ def algorithmic_work(kernel, c):
 
 
 RIDGE = FP32_MFMA_PEAK_TFLOPS * 1e12 / (HBM_PEAK_GBS * 1e9)   # flop per byte
+BATCH_MFMA_TERMS = 9.0   # bf16 products per term of the batched loop: (hi, mid, lo) of the state times those of the matrix
 
 
 def on_chip_roofline(name, us, c):
@@ -235,7 +236,8 @@ def on_chip_roofline(name, us, c):
     own ceiling is the on-chip rate of the compute units they occupy (one workgroup per unit).
     Weights resident in LDS/registers and used once per step (batch rows do not share a
     workgroup): LDS read bandwidth of those units against T*B*H*H*4 bytes per launch.
-    Matrix-core loops: the fp32 MFMA rate of those units against 2*rows*H*H flop per launch."""
+    Matrix-core loops: the MFMA rate of those units against 2*rows*H*H flop per launch -- the
+    bf16 rate and nine products per term for the loop that splits its operands in three."""
     if name not in ("rec_fwd", "rec_bwd"):
         return None
     T, B, H = c["seq_len"], c["batch"], c["hidden"]
@@ -252,8 +254,13 @@ def on_chip_roofline(name, us, c):
                     on_chip_bytes=nbytes)
     rows = B if variant == "step_mfma" else T * B      # one launch = one step, or all of them
     flops = 2.0 * rows * H * H
-    peak = FP32_MFMA_PEAK_TFLOPS * n_cu / N_CU
     ach = flops / sec / 1e12
+    if variant == "batch_mfma":
+        peak = BF16_MFMA_PEAK_TFLOPS * n_cu / N_CU
+        return dict(bound="mfma", n_cu=n_cu, achieved=ach, peak=peak, unit="TFLOP/s", frac=ach / peak, flops=flops,
+                    dtype="bf16 hi/mid/lo split, f32 accumulate", executed_flops=BATCH_MFMA_TERMS * flops,
+                    frac_executed=BATCH_MFMA_TERMS * ach / peak)
+    peak = FP32_MFMA_PEAK_TFLOPS * n_cu / N_CU
     return dict(bound="mfma", n_cu=n_cu, achieved=ach, peak=peak, unit="TFLOP/s", frac=ach / peak,
                 flops=flops)
 
@@ -283,17 +290,19 @@ def _roofline_entry(name, prof, case):
                     traffic=None, avg_us=us)
     nbytes, flops = work
     sec = us * 1e-6
-    if name.startswith("gemm_"):
-        # operands split into three bf16 numbers (two with the flag: the output layer's and the weight gradients'
-        # products): six (three) bf16 matrix instructions per product term; both rates against the bf16 peak
-        two = case.get("_bf16x3") and name in ("gemm_logits", "gemm_dV", "gemm_G", "gemm_dWh", "gemm_dWx")
-        terms = 3.0 if two else 6.0
+    # operands split into three bf16 numbers (two with the flag: the output layer's and the weight gradients'
+    # products): six (three) bf16 matrix instructions per product term, nine in the batched loop; rates against the bf16
+    # peak, unless the bytes take longer at the rate of memory than those instructions at that peak
+    two = case.get("_bf16x3") and name in ("gemm_logits", "gemm_dV", "gemm_G", "gemm_dWh", "gemm_dWx")
+    terms = (3.0 if two else 6.0) if name.startswith("gemm_") else \
+        BATCH_MFMA_TERMS if name in ("rec_fwd", "rec_bwd") and case.get("_variant") == "batch_mfma" else 0.0
+    if terms and terms * flops / BF16_MFMA_PEAK_TFLOPS / 1e12 >= nbytes / HBM_PEAK_GBS / 1e9:
         ach = flops / sec / 1e12
         return dict(kernel=name, bound="mfma", achieved=ach, peak=BF16_MFMA_PEAK_TFLOPS, unit="TFLOP/s",
                     frac=ach / BF16_MFMA_PEAK_TFLOPS, traffic=None, avg_us=us, algorithmic_flops=flops,
                     dtype="bf16 %s split, f32 accumulate" % ("hi/lo" if two else "hi/mid/lo"), executed_flops=terms * flops,
                     frac_executed=terms * ach / BF16_MFMA_PEAK_TFLOPS)
-    if flops / nbytes >= RIDGE:   # above the ridge point: arithmetic bound
+    if not terms and flops / nbytes >= RIDGE:   # above the ridge point: arithmetic bound
         ach = flops / sec / 1e12
         # the batch-1..4 loops multiply on the vector ALUs (same fp32 peak as the matrix cores)
         valu = name in ("rec_fwd", "rec_bwd") and case.get("_variant") in ("wg_resident", "grid_resident")
@@ -452,6 +461,14 @@ def train_stream_leg(windows, reps=3, lr=0.1):
     }
 
 
+def mlp_launches(n_hidden, n_batches):
+    """Launches of one rnn_mlp_train call at the benchmark's sizes: one per 1024 batches with at most one hidden layer, and with
+    one another that clears the words its workgroups exchange; else 2 n_hidden + 2 per batch."""
+    if n_hidden > 1:
+        return n_batches * (2 * n_hidden + 2)
+    return -(-n_batches // 1024) * (1 + n_hidden)
+
+
 def mlp_leg(n_batches=400, lr=0.01):
     """The paper's neural-network training benchmark shapes (784 inputs, 10 classes; logistic
     regression, 1 x 500 and 3 x 1000 hidden units; batches of 1, 10, 60) through rnn_mlp_train:
@@ -484,7 +501,7 @@ def mlp_leg(n_batches=400, lr=0.01):
             n_params = sum(w.numel() + v.numel() for w, v in zip(W, b))
             entry = dict(examples_per_s=n_batches * batch / wall, us_per_batch=1e6 * wall / n_batches,
                          gpu_event_us_per_batch=1e3 * e0.elapsed_time(e1) / n_batches,
-                         launches_per_batch=2 * case["n_hidden"] + 2 if case["n_hidden"] > 1 else 1.0 / n_batches, parameters=n_params,
+                         launches_per_batch=mlp_launches(case["n_hidden"], n_batches) / n_batches, parameters=n_params,
                          loss_first=float(losses[0]), loss_last=float(losses[-1]))
             if name == "MLP3" and batch == 60:
                 rnn.rnn_profile_begin(1 << 16)
