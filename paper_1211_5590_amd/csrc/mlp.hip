@@ -389,11 +389,17 @@ __global__ __launch_bounds__(OT, 2) void mlp_one_kernel(const MlpOneArgs a) {
     // bound: rows past the batch, blocks past the end of a row and, in the forward product, the pieces past
     // it (an infinite input of the next row must not meet the zero weights there).  The update's requests
     // may read into the next row: those columns of W are set to zero after it.
+    // With two tiles of rows those past the batch repeat its last one in the forward product (nothing takes
+    // their results) and whole blocks are asked for without the check of their pieces: 784-126-10, 21 rows 9.44 ->
+    // 9.23 us per batch, 784-10 6.25 -> 5.70; with one tile that costs 3 % and with four 5.
     constexpr unsigned NONE = 0x80000000u;
     float4 xa[MT][KB];
     unsigned row_a[MT], row_t[4 * MT];   // bytes
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) row_a[mt] = SINGLE ? 16u * g : 16 * mt + nn < B ? (unsigned)((16 * mt + nn) * K + 4 * g) * 4u : NONE;
+    for (int mt = 0; mt < MT; ++mt) {
+        const int m = 16 * mt + nn;
+        row_a[mt] = SINGLE ? 16u * g : m < B || MT == 2 ? (unsigned)(min(m, B - 1) * K + 4 * g) * 4u : NONE;
+    }
 #pragma unroll
     for (int u = 0; u < 4 * MT; ++u) row_t[u] = 4 * u + g < B ? (unsigned)((4 * u + g) * K + nn) * 4u : NONE;
     auto window = [&](int batch, int b) {
@@ -401,6 +407,16 @@ __global__ __launch_bounds__(OT, 2) void mlp_one_kernel(const MlpOneArgs a) {
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.X + (size_t)batch * B * K + min(k, K)), 0, k < K ? (B * K - k) * 4 : 0, 0x00020000);
     };
     auto load_rows = [&](int batch) {
+        if (MT == 2 && K % 16 == 0) {
+#pragma unroll
+            for (int b = 0; b < KB; ++b) {
+                const auto x = window(batch, b);
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    xa[mt][b] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(x, row_a[mt], 0, 0));
+            }
+            return;
+        }
 #pragma unroll
         for (int b = 0; b < KB; ++b) {
             const auto x = window(batch, b);

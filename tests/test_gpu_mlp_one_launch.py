@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 # in_dim, hidden (0: none), classes, batch
 SIZES = [(4, 0, 1, 1), (16, 0, 16, 2), (256, 0, 10, 16), (260, 0, 10, 17), (896, 0, 10, 64), (900, 0, 10, 64),
          (8, 1, 2, 1), (20, 16, 3, 2), (128, 17, 16, 33), (784, 33, 10, 1), (784, 100, 10, 32), (132, 500, 10, 64),
-         (64, 1024, 16, 64), (64, 1025, 10, 3), (252, 40, 16, 65), (784, 1000, 10, 1), (784, 300, 7, 9)]
+         (784, 0, 10, 21), (784, 126, 10, 21), (64, 1024, 16, 64), (64, 1025, 10, 3), (252, 40, 16, 65), (784, 1000, 10, 1), (784, 300, 7, 9)]
 
 
 @pytest.mark.parametrize("I,H,O,B", SIZES)
@@ -83,7 +83,8 @@ def test_the_update_of_deep_classifiers_at_ragged_rows(I, H, L, O, B):
     check(run_gpu(case, lr), mlp.train(case, lr), case)
 
 
-@pytest.mark.parametrize("I,H,B,m", ((784, 30, 10, 4), (20, 9, 3, 1), (784, 40, 33, 32), (260, 16, 60, 17), (36, 20, 17, 16)))
+@pytest.mark.parametrize("I,H,B,m", ((784, 30, 10, 4), (20, 9, 3, 1), (784, 40, 33, 32), (260, 16, 60, 17), (36, 20, 17, 16),
+                                     (784, 33, 21, 20), (256, 17, 32, 7)))
 def test_an_infinite_input_stays_in_its_own_example(I, H, B, m):
     """Saturating hidden units keep the logits of an example with an infinite input finite: the batch's loss is finite,
     and the step is not a number in the column of that input alone (0 times infinity), as in the oracle."""
