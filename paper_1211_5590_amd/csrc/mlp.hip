@@ -391,7 +391,7 @@ __global__ __launch_bounds__(OT, 2) void mlp_one_kernel(const MlpOneArgs a) {
     // may read into the next row: those columns of W are set to zero after it.
     // With two tiles of rows those past the batch repeat its last one in the forward product (nothing takes
     // their results) and whole blocks are asked for without the check of their pieces: 784-126-10, 21 rows 9.44 ->
-    // 9.23 us per batch, 784-10 6.25 -> 5.70; with one tile that costs 3 % and with four 5.
+    // 9.21 us per batch, 784-10 6.25 -> 5.65; with one tile that costs 3 % and with four 5.
     constexpr unsigned NONE = 0x80000000u;
     float4 xa[MT][KB];
     unsigned row_a[MT], row_t[4 * MT];   // bytes
