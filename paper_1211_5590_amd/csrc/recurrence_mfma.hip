@@ -55,6 +55,14 @@ __device__ __forceinline__ void split3(float x, float y, unsigned (&w)[3]) {
 constexpr unsigned NO_SPLIT = 0x7f7f8000u;
 __device__ __forceinline__ bool at_least(float x, unsigned limit) { return (__float_as_uint(x) & 0x7fffffffu) >= limit && x == x; }
 
+// Where the loop lies against 32 bytes moves a step by up to 4 %, so it starts on a line of 64 and this many words of
+// s_nop after it, the fastest of 0, 2, 4 and 6 for the form (512 steps, 8 rows, measured at a size of each NK: 168 units,
+// tanh, forward 347 us with none and 360 with four; 200 units, tanh, reverse 527 with four and 549 with none).
+constexpr int loop_fill(int act, bool bwd, int nk) {
+    const char* const words = act == 0 ? (bwd ? "20664200" : "00000000") : (bwd ? "06464644" : "40404000");
+    return words[nk - 1] - '0';
+}
+
 // NK = slabs of 32 hidden units (K of the product and, times two, column tiles of 16).  CT column
 // tiles per wavefront, NW wavefronts: one tile each (and so 1, 2 or 3 per SIMD) up to 192 units, beyond
 // that two, whose matrix fills the registers of two wavefronts per SIMD.  Lane l of a wavefront: matrix operand k = 32 c + 8 (l / 16) + 0..7
@@ -311,9 +319,8 @@ __global__ __launch_bounds__(64 * batch_waves(NK), batch_waves(NK) / 4) void rec
 
     // pairs of steps with no branch between them (exact wait counts), then the odd one out
     int s2 = 0;
-    // Where the loop lies against 64 bytes moves a step by up to 4 % (256 units, 1024 steps, forward and reverse: 1025 + 1034 us
-    // here, 1040 + 1038 left to chance); this place is the best for 200 and 256 units and costs the smaller ones nothing.
-    asm volatile(".p2align 6\n\t.fill 4, 4, 0xbf800000");   // s_nop 0
+    // (loop_fill: s_nop 0)
+    asm volatile(".p2align 6\n\t.fill %0, 4, 0xbf800000" ::"i"(loop_fill(ACT, BWD, NK)));
     for (; s2 + 1 < nsteps; s2 += 2) {
         step(s2, std::integral_constant<int, 0>{});
         step(s2 + 1, std::integral_constant<int, 1>{});
