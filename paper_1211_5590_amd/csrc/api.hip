@@ -123,7 +123,7 @@ Variant pick_variant(const rnn_dims* d) {
     }
     // Batch 1 to 4 with more than 128 hidden units: the matrix no longer fits the registers of the loops above and
     // a step is bound by reading it from LDS or by the exchange between workgroups.  The batched loop keeps it in
-    // registers split in 16-bit parts.  Forward, loss and backward of 100 steps, 1000 words, those against that: H = 150,
+    // registers split in three.  Forward, loss and backward of 100 steps, 1000 words, those against that: H = 150,
     // batch 1: 415 / 197 us, H = 200: 387 / 284, H = 256: 401 / 297, batch 4: 423 / 321; of 12 steps, H = 256,
     // batch 2: 154 / 108.  Of fewer than 10 steps the launches are most of it, and here it takes one more.
     v.batch_mfma = s.T >= 10 && s.H > 128 && rec_batch_mfma_supported(s.H, s.B);
