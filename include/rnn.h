@@ -72,10 +72,10 @@ extern "C" {
  * (and dWh = Delta^T H_prev, dense-input dWx = Delta^T X) run on the bf16 matrix cores with float32 accumulation, every float32
  * operand split into two bf16 numbers (hi + lo) and each product taken as hi*hi + hi*lo + lo*hi
  * (error per product term below 2^-16 relative; parameters, results and everything else stay
- * float32).  Products too small for the tiles of that form take the one that is used without the flag: sums
- * of 448 terms and more on two f16 numbers per operand, scaled by powers of two, shorter ones on three bf16
- * numbers; float32 accuracy either way (three bf16 numbers: an operand below about 1e-33 is off by up to
- * 2^-134, the smallest bf16 step).  Set it on rnn_workspace_bytes, rnn_loss and
+ * float32).  Without it the same products split every operand into three bf16 numbers, which hold all
+ * 24 bits, and take six products: float32 accuracy, whatever the sizes of the numbers beside each other (an
+ * operand below about 1e-33 is off by up to 2^-134, the smallest bf16 step).  Products too small for the tiles of the
+ * two-number form take three with the flag as well.  Set it on rnn_workspace_bytes, rnn_loss and
  * rnn_bptt alike; rnn_forward, rnn_workspace_init and rnn_workspace_status take a workspace sized with it
  * whether it is set in their dims or not (every other flag leaves the size and the layout alone).  Ignored where the column-strip kernels of a short single
  * sequence serve the output layer; rnn_gauss_newton_vec takes it too (its five output-layer

@@ -5,7 +5,6 @@
 #include "../../include/rnn.h"
 
 #include <atomic>
-#include <cmath>
 
 #include "internal.hpp"
 #include "prof.hpp"
@@ -70,32 +69,19 @@ Sizes sizes_of(const rnn_dims* d) {
     return s;
 }
 
-// Powers of two the operands of the products are taken times (GemmArgs): states are at most 1, weights and directions
-// lie around 0.1, a dense input may be a count; dZ is at most 1/N, the errors in front of the loop and in it a fraction
-// of the weights of that.
-constexpr int kStateExp = 14, kWeightExp = 10, kInputExp = 6;
-int floor_log2(double v) { int e = 0; frexp(v, &e); return e - 1; }
-int clamp_exp(int e) { return e < -126 ? -126 : e > 126 ? 126 : e; }
-// the output layer's and the weight gradients' products on 16 bits of every operand
-bool two_part(const rnn_dims* d) { return (d->flags & RNN_FLAG_BF16X3_OUTPUT) != 0; }
-
-struct GradExp { int dz, delta; };
-GradExp grad_exp(const rnn_dims* d) {
-    const double N = (double)d->seq_len * d->batch, O = d->out_dim;
-    if (d->loss_kind == RNN_LOSS_SOFTMAX_CE) return {clamp_exp(15 + floor_log2(N)), clamp_exp(10 + floor_log2(N))};
-    return {clamp_exp(10 + floor_log2(N * O)), clamp_exp(10 + floor_log2(N * O))};
-}
+// bf16 numbers an operand of the output layer's and the weight gradients' products is split into
+int output_parts(const rnn_dims* d) { return (d->flags & RNN_FLAG_BF16X3_OUTPUT) ? 2 : 3; }
 
 size_t max_splitk_floats(const Sizes& s) {
     const int N = (int)s.N, H = s.H, O = s.O, D = s.NVin;
     size_t m = 0;
     auto take = [&](size_t v) { if (v > m) m = v; };
-    for (const bool two : {false, true}) {
-        take(gemm_splitk_floats(N, O, H, two));   // Z = Hs V
-        take(gemm_splitk_floats(H, O, N, two));   // dV = Hs^T dZ
-        take(gemm_splitk_floats(N, H, O, two));   // G = dZ V^T
-        take(gemm_splitk_floats(H, H, N, two));   // dWh = Delta^T Hprev
-        if (!s.tokens) take(gemm_splitk_floats(H, D, N, two));  // dWx = Delta^T X
+    for (int parts = 2; parts <= 3; ++parts) {
+        take(gemm_splitk_floats(N, O, H, parts));   // Z = Hs V
+        take(gemm_splitk_floats(H, O, N, parts));   // dV = Hs^T dZ
+        take(gemm_splitk_floats(N, H, O, parts));   // G = dZ V^T
+        take(gemm_splitk_floats(H, H, N, parts));   // dWh = Delta^T Hprev
+        if (!s.tokens) take(gemm_splitk_floats(H, D, N, parts));  // dWx = Delta^T X
     }
     take(gemm_splitk_floats(s.B, H, H)); // dh0 = delta_0 Wh (stepwise recurrence)
     if (!s.tokens) take(gemm_splitk_floats(N, H, D));  // U = X Wx^T
@@ -168,9 +154,9 @@ Plan make_plan(const rnn_dims* d) {
     p.seen = take(s.tokens && N > 32 ? dwx_table_ints((int)N, s.NVin) * 4 : 0);
     // row statistics the logits product leaves per column part (fused log-sum-exp)
     size_t stat_parts = 0;
-    for (const bool two : {false, true})
-        if (s.ce && gemm_fuses_stats((int)N, s.O, s.H, two)) {
-            const size_t n = (size_t)gemm_stat_parts((int)N, s.O, s.H, two);
+    for (int parts = 2; s.ce && parts <= 3; ++parts)
+        if (gemm_fuses_stats((int)N, s.O, s.H, parts)) {
+            const size_t n = (size_t)gemm_stat_parts((int)N, s.O, s.H, parts);
             if (n > stat_parts) stat_parts = n;
         }
     p.lstat = take(N * stat_parts * 8);
@@ -229,7 +215,7 @@ hipError_t run_forward(const rnn_dims* d, const rnn_params* P, const void* x, co
         g.A = static_cast<const float*>(x); g.B = P->Wx; g.C = at<float>(ws, pl.U);
         g.M = (int)z.N; g.N = z.H; g.K = z.NVin;
         g.lda = z.NVin; g.ldb = z.NVin; g.ldc = z.H;
-        g.a_t = false; g.b_t = true; g.bias_n = P->b; g.beta = 0; g.prof_id = K_GEMM_U; g.a_exp = kInputExp; g.b_exp = kWeightExp;
+        g.a_t = false; g.b_t = true; g.bias_n = P->b; g.beta = 0; g.prof_id = K_GEMM_U;
         g.splitk_ws = at<float>(ws, pl.splitk);
         RNN_TRY(launch_gemm(g, s));
         a.x = nullptr;
@@ -295,17 +281,17 @@ hipError_t run_loss(const rnn_dims* d, const rnn_params* P, const float* h_all, 
     g.B = P->V; g.C = Z;
     g.M = N; g.N = z.O; g.K = z.H;
     g.lda = z.H; g.ldb = z.O; g.ldc = z.O;
-    g.a_t = false; g.b_t = false; g.bias_n = P->c; g.beta = 0; g.prof_id = K_GEMM_LOGITS; g.a_exp = kStateExp; g.b_exp = kWeightExp;
+    g.a_t = false; g.b_t = false; g.bias_n = P->c; g.beta = 0; g.prof_id = K_GEMM_LOGITS;
     g.splitk_ws = at<float>(ws, pl.splitk);
+    g.parts = output_parts(d);
     // softmax-CE: the product's epilogue leaves (max, sum exp) per row and column part, so the
     // logits are not read again for the log-sum-exp
-    g.two_part = two_part(d);
-    const bool fused = z.ce && gemm_fuses_stats(N, z.O, z.H, g.two_part);
+    const bool fused = z.ce && gemm_fuses_stats(N, z.O, z.H, g.parts);
     g.row_stats = fused ? at<float>(ws, pl.lstat) : nullptr;
     RNN_TRY(launch_gemm(g, s));
     float* rowloss = at<float>(ws, pl.rowloss);
     if (fused) {
-        RNN_TRY(launch_ce_merge_stats(g.row_stats, gemm_stat_parts(N, z.O, z.H, g.two_part), Z, static_cast<const int32_t*>(targets),
+        RNN_TRY(launch_ce_merge_stats(g.row_stats, gemm_stat_parts(N, z.O, z.H, g.parts), Z, static_cast<const int32_t*>(targets),
                                       at<float>(ws, pl.lse), rowloss, N, z.O, s));
         return launch_loss_reduce(rowloss, N, 1.0f / (float)N, loss, s);
     }
@@ -325,7 +311,7 @@ hipError_t run_loss(const rnn_dims* d, const rnn_params* P, const float* h_all, 
 // rows with the two exchanged.
 hipError_t run_reverse_loop(const rnn_dims* d, const float* Wh, const float* WhT_or_null, float* WhT_ws,
                             const float* G, const float* h_all, const float* dh_last, float* Delta,
-                            float* dh0, int delta_exp, void* ws, const Plan& pl, hipStream_t s) {
+                            float* dh0, void* ws, const Plan& pl, hipStream_t s) {
     const Sizes z = sizes_of(d);
     const int H = z.H;
     Variant v = pick_variant(d);
@@ -364,7 +350,7 @@ hipError_t run_reverse_loop(const rnn_dims* d, const float* Wh, const float* WhT
         RecBwdArgs a{};
         a.Wh = Wh; a.WhT = WhT; a.G = G; a.h_all = h_all; a.dh_last = dh_last;
         a.Delta = Delta; a.dh0 = dh0; a.splitk_ws = at<float>(ws, pl.splitk);
-        a.H = H; a.T = z.T; a.B = z.B; a.act = d->act; a.delta_exp = delta_exp; a.wh_exp = kWeightExp;
+        a.H = H; a.T = z.T; a.B = z.B; a.act = d->act;
         return run_rec_bwd_stepwise(a, s);
     }
     RecBwdArgs a{};
@@ -377,7 +363,7 @@ hipError_t run_reverse_loop(const rnn_dims* d, const float* Wh, const float* WhT
 // Everything of backpropagation that follows d loss / d z (held in the logits buffer of the
 // workspace): dV, G, the reverse loop, dWh, db, dWx.  dc is the caller's.
 hipError_t run_backward_from_dz(const rnn_dims* d, const rnn_params* P, const void* x, const float* h_all,
-                                const float* dh_last, const rnn_grads* Gr, float* dh0, GradExp ge, void* ws,
+                                const float* dh_last, const rnn_grads* Gr, float* dh0, void* ws,
                                 const Plan& pl, hipStream_t s) {
     const Sizes z = sizes_of(d);
     const int N = (int)z.N, H = z.H, O = z.O;
@@ -389,14 +375,14 @@ hipError_t run_backward_from_dz(const rnn_dims* d, const rnn_params* P, const vo
     float* Delta = at<float>(ws, pl.Delta);
     const float* Hs = h_all + (size_t)z.B * H;  // h_t rows
     const int chunks = colsum_chunks(N);
-    const bool two = two_part(d);
+    const int parts = output_parts(d);
     // dV = Hs^T dZ
     {
         GemmArgs g{};
         g.A = Hs; g.B = Z; g.C = Gr->dV;
         g.M = H; g.N = O; g.K = N;
         g.lda = H; g.ldb = O; g.ldc = O;
-        g.a_t = true; g.b_t = false; g.beta = beta; g.splitk_ws = splitk; g.two_part = two; g.prof_id = K_GEMM_DV; g.a_exp = kStateExp; g.b_exp = ge.dz;
+        g.a_t = true; g.b_t = false; g.beta = beta; g.splitk_ws = splitk; g.parts = parts; g.prof_id = K_GEMM_DV;
         RNN_TRY(launch_gemm(g, s));
     }
     // G = dZ V^T
@@ -405,17 +391,17 @@ hipError_t run_backward_from_dz(const rnn_dims* d, const rnn_params* P, const vo
         g.A = Z; g.B = P->V; g.C = G;
         g.M = N; g.N = H; g.K = O;
         g.lda = O; g.ldb = O; g.ldc = H;
-        g.a_t = false; g.b_t = true; g.beta = 0; g.splitk_ws = splitk; g.two_part = two; g.prof_id = K_GEMM_G; g.a_exp = ge.dz; g.b_exp = kWeightExp;
+        g.a_t = false; g.b_t = true; g.beta = 0; g.splitk_ws = splitk; g.parts = parts; g.prof_id = K_GEMM_G;
         RNN_TRY(launch_gemm(g, s));
     }
-    RNN_TRY(run_reverse_loop(d, P->Wh, nullptr, at<float>(ws, pl.WhT), G, h_all, dh_last, Delta, dh0, ge.delta, ws, pl, s));
+    RNN_TRY(run_reverse_loop(d, P->Wh, nullptr, at<float>(ws, pl.WhT), G, h_all, dh_last, Delta, dh0, ws, pl, s));
     // dWh = Delta^T Hprev  (Hprev rows = h_all[0:T])
     {
         GemmArgs g{};
         g.A = Delta; g.B = h_all; g.C = Gr->dWh;
         g.M = H; g.N = H; g.K = N;
         g.lda = H; g.ldb = H; g.ldc = H;
-        g.a_t = true; g.b_t = false; g.beta = beta; g.splitk_ws = splitk; g.two_part = two; g.prof_id = K_GEMM_DWH; g.a_exp = ge.delta; g.b_exp = kStateExp;
+        g.a_t = true; g.b_t = false; g.beta = beta; g.splitk_ws = splitk; g.parts = parts; g.prof_id = K_GEMM_DWH;
         RNN_TRY(launch_gemm(g, s));
     }
     // db = column sums of Delta
@@ -431,7 +417,7 @@ hipError_t run_backward_from_dz(const rnn_dims* d, const rnn_params* P, const vo
         g.A = Delta; g.B = static_cast<const float*>(x); g.C = Gr->dWx;
         g.M = H; g.N = z.NVin; g.K = N;
         g.lda = H; g.ldb = z.NVin; g.ldc = z.NVin;
-        g.a_t = true; g.b_t = false; g.beta = beta; g.splitk_ws = splitk; g.two_part = two; g.prof_id = K_GEMM_DWX; g.a_exp = ge.delta; g.b_exp = kInputExp;
+        g.a_t = true; g.b_t = false; g.beta = beta; g.splitk_ws = splitk; g.parts = parts; g.prof_id = K_GEMM_DWX;
         RNN_TRY(launch_gemm(g, s));
     }
     return hipSuccess;
@@ -475,7 +461,7 @@ hipError_t run_bptt(const rnn_dims* d, const rnn_params* P, const void* x, const
                       z.ce ? nullptr : static_cast<const float*>(targets), part, N, O,
                       d->loss_kind, s));
     RNN_TRY(launch_colsum_finish(part, Gr->dc, chunks, O, beta, s));
-    return run_backward_from_dz(d, P, x, h_all, dh_last, Gr, dh0, grad_exp(d), ws, pl, s);
+    return run_backward_from_dz(d, P, x, h_all, dh_last, Gr, dh0, ws, pl, s);
 }
 
 // Extra regions of the Gauss-Newton-vector product behind the ordinary plan.
@@ -526,11 +512,12 @@ hipError_t run_gauss_newton(const rnn_dims* d, const rnn_params* P, const rnn_pa
     const float* Hs = h_all + BH;
     const bool ce_metric = metric == RNN_GN_METRIC_LOSS && z.ce;
 
+    const int parts = output_parts(d);
     if (ce_metric) {   // logits of the current parameters, for the softmax in the metric
         GemmArgs g{};
         g.A = Hs; g.B = P->V; g.C = Zl;
         g.M = N; g.N = O; g.K = H; g.lda = H; g.ldb = O; g.ldc = O;
-        g.a_t = false; g.b_t = false; g.bias_n = P->c; g.beta = 0; g.two_part = two_part(d); g.prof_id = K_GEMM_LOGITS; g.a_exp = kStateExp; g.b_exp = kWeightExp;
+        g.a_t = false; g.b_t = false; g.bias_n = P->c; g.beta = 0; g.parts = parts; g.prof_id = K_GEMM_LOGITS;
         g.splitk_ws = splitk;
         RNN_TRY(launch_gemm(g, s));
     }
@@ -538,7 +525,7 @@ hipError_t run_gauss_newton(const rnn_dims* d, const rnn_params* P, const rnn_pa
         GemmArgs g{};
         g.A = h_all; g.B = Ga->Wh; g.C = C;
         g.M = N; g.N = H; g.K = H; g.lda = H; g.ldb = H; g.ldc = H;
-        g.a_t = false; g.b_t = true; g.bias_n = Ga->b; g.beta = 0; g.prof_id = K_GEMM_U; g.a_exp = kStateExp; g.b_exp = kWeightExp;
+        g.a_t = false; g.b_t = true; g.bias_n = Ga->b; g.beta = 0; g.prof_id = K_GEMM_U;
         g.splitk_ws = at<float>(ws, gp.splitk_c);
         RNN_TRY(launch_gemm(g, s));
     }
@@ -548,24 +535,24 @@ hipError_t run_gauss_newton(const rnn_dims* d, const rnn_params* P, const rnn_pa
         GemmArgs g{};
         g.A = static_cast<const float*>(x); g.B = Ga->Wx; g.C = C;
         g.M = N; g.N = H; g.K = z.NVin; g.lda = z.NVin; g.ldb = z.NVin; g.ldc = H;
-        g.a_t = false; g.b_t = true; g.beta = 1; g.prof_id = K_GEMM_U; g.a_exp = kInputExp; g.b_exp = kWeightExp; g.splitk_ws = splitk;
+        g.a_t = false; g.b_t = true; g.beta = 1; g.prof_id = K_GEMM_U; g.splitk_ws = splitk;
         RNN_TRY(launch_gemm(g, s));
     }
     // time-reversed rows: Crev[t] = C[T-1-t], hrev[t+1] = h_{T-1-t}
     RNN_TRY(launch_reverse_rows(C, Crev, z.T, (int)BH, s));
     RNN_TRY(launch_reverse_rows(Hs, hrev + BH, z.T, (int)BH, s));
     RNN_TRY(launch_transpose(P->Wh, WhT, H, H, s));
-    RNN_TRY(run_reverse_loop(d, WhT, P->Wh, nullptr, Crev, hrev, nullptr, Rhrev, nullptr, 0, ws, pl, s));
+    RNN_TRY(run_reverse_loop(d, WhT, P->Wh, nullptr, Crev, hrev, nullptr, Rhrev, nullptr, ws, pl, s));
     RNN_TRY(launch_reverse_rows(Rhrev, Rh, z.T, (int)BH, s));
     {   // R z = Rh V + gc
         GemmArgs g{};
         g.A = Rh; g.B = P->V; g.C = U;
         g.M = N; g.N = O; g.K = H; g.lda = H; g.ldb = O; g.ldc = O;
-        g.a_t = false; g.b_t = false; g.bias_n = Ga->c; g.beta = 0; g.two_part = two_part(d); g.prof_id = K_GEMM_LOGITS; g.a_exp = kWeightExp; g.b_exp = kWeightExp;
+        g.a_t = false; g.b_t = false; g.bias_n = Ga->c; g.beta = 0; g.parts = parts; g.prof_id = K_GEMM_LOGITS;
         g.splitk_ws = splitk;
         RNN_TRY(launch_gemm(g, s));
         // ... + Hs gV
-        g.A = Hs; g.B = Ga->V; g.bias_n = nullptr; g.beta = 1; g.a_exp = kStateExp;
+        g.A = Hs; g.B = Ga->V; g.bias_n = nullptr; g.beta = 1;
         RNN_TRY(launch_gemm(g, s));
     }
     if (Rz_out)
@@ -577,8 +564,7 @@ hipError_t run_gauss_newton(const rnn_dims* d, const rnn_params* P, const rnn_pa
     // Gc = column sums of u, then the rest of backpropagation
     RNN_TRY(launch_colsum_partial(U, at<float>(ws, pl.part), N, O, s));
     RNN_TRY(launch_colsum_finish(at<float>(ws, pl.part), Out->dc, colsum_chunks(N), O, beta, s));
-    return run_backward_from_dz(d, P, x, h_all, nullptr, Out, nullptr, metric == RNN_GN_METRIC_LOSS ? grad_exp(d) : GradExp{kWeightExp, kWeightExp},
-                                ws, pl, s);
+    return run_backward_from_dz(d, P, x, h_all, nullptr, Out, nullptr, ws, pl, s);
 }
 
 bool params_ok(const rnn_params* P) {

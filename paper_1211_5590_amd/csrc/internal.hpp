@@ -25,15 +25,11 @@ struct GemmArgs {
     // nullable: [M][gemm_stat_parts()][2] receives, per row and per column part of the final
     // result, (max, sum of exp relative to that max); written only when gemm_fuses_stats()
     float* row_stats;
-    // Sums of many terms: the operands are taken times 2^a_exp and 2^b_exp (-126 .. 126) on their way to the matrix cores.
-    // Results do not depend on it; a tile one of whose rows of op(A) or columns of op(B) then has its largest number
-    // outside [2^-8, 65504) is computed twice.
-    int a_exp, b_exp;
-    bool two_part = false;   // 16 bits of every operand are enough (RNN_FLAG_BF16X3_OUTPUT)
+    int parts = 3;        // bf16 numbers a float32 operand is split into: 3 keeps all of it, 2 its first 16 bits
 };
-size_t gemm_splitk_floats(int M, int N, int K, bool two_part = false);
-int gemm_stat_parts(int M, int N, int K, bool two_part = false);
-bool gemm_fuses_stats(int M, int N, int K, bool two_part = false);
+size_t gemm_splitk_floats(int M, int N, int K, int parts = 3);
+int gemm_stat_parts(int M, int N, int K, int parts = 3);
+bool gemm_fuses_stats(int M, int N, int K, int parts = 3);
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 
 // C[m,n] = (beta ? C : 0) + sum over splits of part[s][m][n] + bias_n[n], fixed order
@@ -63,7 +59,6 @@ struct RecBwdArgs {
     float* dh0;           // nullable [B,H]
     int H, T, B, act;
     float* splitk_ws;     // split-K scratch for the dh0 product (stepwise path)
-    int delta_exp, wh_exp;   // what Delta and Wh are taken times there (see GemmArgs)
 };
 // Resident-weight persistent loops (recurrence.hip).  One struct serves both directions.
 struct RecResArgs {

@@ -1,10 +1,10 @@
-"""The products on two f16 parts (sums of 448 terms and more): rows and columns of every magnitude, at tile edges and
-remainders of K, through dV = H^T dZ of a one-step call whose dZ is known exactly (V = c = 0, squared error:
-dZ = -2 Y / (N O), N O a power of two or the quotient formed the same way), against float64.
+"""The products of three bf16 parts on rows and columns of every magnitude, at tile edges and remainders of K, through
+dV = H^T dZ of a one-step call whose dZ is known exactly (V = c = 0, squared error: dZ = -2 Y / (N O), N O a power of two or
+the quotient formed the same way), against float64.
 
-Bound: a number is held to 2^-23 of itself or 2^-28 of the largest of its row, the product of the two lower parts is below
-2^-22 of the whole, and a sum of K terms is rounded about K/8 times: |error| <= (2^-21 + 2^-27 r + sqrt(K/8) 2^-24) sum |a b|, with r the
-ratio of K max|a| max|b| to sum |a b|, at most 64 here; the test allows 2 (sqrt(K/8) + 16) 2^-24 sum |a b|."""
+Bound: a number keeps its 24 bits whatever lies beside it, the dropped product terms are below 2^-24 of the whole, and
+a sum of K terms is rounded about K/8 times: |error| <= (2^-23 + sqrt(K/8) 2^-24) sum |a b|; the test allows
+2 (sqrt(K/8) + 16) 2^-24 sum |a b|."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +14,7 @@ import paper_1211_5590_amd as rnn
 pytestmark = pytest.mark.gpu
 
 SIZES = [(448, 5, 3), (450, 63, 65), (479, 64, 129), (700, 200, 257), (1025, 900, 2000), (2100, 1000, 3001)]   # rows, hidden, outputs
-KINDS = ["plain", "low_rows", "high_rows", "mixed", "zeros", "far"]
+KINDS = ["plain", "low_rows", "high_rows", "mixed", "zeros", "far", "edge"]
 
 
 def operands(kind, N, H, O):
@@ -39,13 +39,16 @@ def operands(kind, N, H, O):
     elif kind == "far":      # one number of a row dwarfs the rest, and what it meets is as small
         h[N // 2, H - 1] = 3e30
         Y[N // 2] *= 1e-30
+    elif kind == "edge":     # small rows whose largest number meets a zero, the rest of them 2^26 times smaller
+        h *= 2.0 ** -48
+        h[N // 2] = 2.0 ** -22 * (1.0 + h[N // 2].abs() * 2.0 ** 47)
+        Y[N // 2] = 0.0
     return h, Y
 
 
-@pytest.mark.parametrize("kind", KINDS)
-@pytest.mark.parametrize("N,H,O", SIZES)
-def test_rows_and_columns_of_any_magnitude(N, H, O, kind):
-    h1, Y = operands(kind, N, H, O)
+def output_gradient(h1, Y):
+    """dV of the call, and the dZ it is formed from in float64"""
+    (N, H), O = h1.shape, Y.shape[1]
     p = dict(Wx=torch.zeros(H, 2), Wh=torch.zeros(H, H), b=torch.zeros(H), V=torch.zeros(H, O), c=torch.zeros(O))
     p = {k: v.cuda() for k, v in p.items()}
     dims = rnn.Dims(2, H, O, 1, N, rnn.INPUT_DENSE, rnn.ACT_TANH, rnn.LOSS_LINEAR_MSE, 0)
@@ -58,8 +61,40 @@ def test_rows_and_columns_of_any_magnitude(N, H, O, kind):
     rnn.rnn_loss(dims, p, h, Y.view(1, N, O), loss, ws)
     rnn.rnn_bptt(dims, p, X, Y.view(1, N, O), h, None, grads, None, ws)
     scale = torch.tensor(2.0 / (N * O), dtype=torch.float32, device="cuda")
-    dZ = ((0.0 - Y) * scale).double()
+    return grads["dV"].double(), ((0.0 - Y) * scale).double()
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("N,H,O", SIZES)
+def test_rows_and_columns_of_any_magnitude(N, H, O, kind):
+    h1, Y = operands(kind, N, H, O)
+    got, dZ = output_gradient(h1, Y)
     ref, mag = h1.double().t() @ dZ, h1.double().abs().t() @ dZ.abs()
     bound = 2.0 * (np.sqrt(N / 8.0) + 16.0) * 2.0 ** -24 * mag + 1e-37
-    worst = float(((grads["dV"].double() - ref).abs() / bound).max())
+    worst = float(((got - ref).abs() / bound).max())
     assert worst <= 1.0, worst
+
+
+@pytest.mark.parametrize("N,H,O", SIZES)
+def test_a_term_by_itself_is_a_float32_product(N, H, O):
+    """One term per sum: the three dropped products are below 2^-24 |a b| together, the matrix core cuts the sum of the other six to
+    24 bits (2^-23 of itself if it does not round to nearest) and the five small ones among them, 2^-7 of it, five times more
+    (below 2^-27): 1.5 + 2^-4 units of 2^-23 |a b|."""
+    h1, Y = operands("plain", N, H, O)
+    h1 *= (torch.arange(N, device="cuda")[:, None] % H == torch.arange(H, device="cuda")[None, :]) * (torch.arange(N, device="cuda")[:, None] < H)
+    got, dZ = output_gradient(h1, Y)
+    ref = h1.double().t() @ dZ
+    worst = float(((got - ref).abs() / (ref.abs() * 2.0 ** -23 * 1.5625 + 1e-37)).max())
+    assert worst <= 1.0, worst
+
+
+@pytest.mark.parametrize("N,H,O", SIZES[-2:])
+def test_errors_do_not_lean_one_way(N, H, O):
+    """Sums over many results (a bias gradient, say) add up what the errors have in common.  The matrix core cuts a sum of 16
+    terms towards minus infinity, 2^-25 of its size on the mean; half of them are summed with their signs turned, which leaves at most
+    one such sum per cut of K: with up to four cuts of 1025 terms or more 4 sqrt(16 / 1025) 2^-25 = 2^-26 of a result's size."""
+    h1, Y = operands("plain", N, H, O)
+    got, dZ = output_gradient(h1, Y)
+    ref = h1.double().t() @ dZ
+    size = ref.norm() / ref.numel() ** 0.5
+    assert float((got - ref).mean().abs() / size) <= 2.0 ** -26
