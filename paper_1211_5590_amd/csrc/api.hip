@@ -293,16 +293,16 @@ hipError_t run_loss(const rnn_dims* d, const rnn_params* P, const float* h_all, 
     if (fused) {
         RNN_TRY(launch_ce_merge_stats(g.row_stats, gemm_stat_parts(N, z.O, z.H, g.parts), Z, static_cast<const int32_t*>(targets),
                                       at<float>(ws, pl.lse), rowloss, N, z.O, s));
-        return launch_loss_reduce(rowloss, N, 1.0f / (float)N, loss, s);
+        return launch_loss_reduce(rowloss, N, 1.0 / (double)N, loss, s);
     }
     if (z.ce) {
         RNN_TRY(launch_ce_row_stats(Z, static_cast<const int32_t*>(targets), at<float>(ws, pl.lse),
                                     rowloss, N, z.O, s));
-        return launch_loss_reduce(rowloss, N, 1.0f / (float)N, loss, s);
+        return launch_loss_reduce(rowloss, N, 1.0 / (double)N, loss, s);
     }
     int n_partial = 0;
     RNN_TRY(launch_mse_partial(Z, static_cast<const float*>(targets), rowloss, N, z.O, &n_partial, s));
-    return launch_loss_reduce(rowloss, n_partial, (float)(1.0 / ((double)N * (double)z.O)), loss, s);
+    return launch_loss_reduce(rowloss, n_partial, 1.0 / ((double)N * (double)z.O), loss, s);
 }
 
 // Reverse-time loop delta_t = (G_t + Wh^T delta_{t+1}) * act'(h_t) with the kernel family that

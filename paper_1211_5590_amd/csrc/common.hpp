@@ -111,6 +111,10 @@ __device__ __forceinline__ float max16(float v) {
 }
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 
+// e^x with log2 e in two parts.  In one float32 it is 1.3e-8 of itself too small, which makes every e^x of a softmax over
+// 10000 classes (x around -9) 1.2e-7 too large: next to nothing in one number, but it adds up over a sum of them.
+__device__ __forceinline__ float exp_exact(float x) { return __builtin_amdgcn_exp2f(fmaf(x, 1.44269502f, x * 1.92596299e-8f)); }
+
 __device__ __forceinline__ float sigmoidf_fast(float a) {
     // 1/(1+e^-a); e^-a overflows to +inf for a < -88 and the reciprocal then gives 0.
     return fast_rcp(1.0f + __expf(-a));

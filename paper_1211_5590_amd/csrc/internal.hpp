@@ -165,7 +165,7 @@ hipError_t launch_ce_merge_stats(const float* stats, int parts, const float* Z, 
 // squared-error partial sums over the flat [N*O] arrays: *n_partial (<= N) floats in `partial`
 hipError_t launch_mse_partial(const float* Z, const float* Y, float* partial, int N, int O,
                               int* n_partial, hipStream_t s);
-hipError_t launch_loss_reduce(const float* rowloss, int N, float scale, float* loss, hipStream_t s);
+hipError_t launch_loss_reduce(const float* rowloss, int N, double scale, float* loss, hipStream_t s);
 // Z -> dZ in place, plus per-row-chunk column sums into part[chunks][O]
 int colsum_chunks(int N);
 hipError_t launch_dz(float* Z, const float* lse, const int32_t* y, const float* Y, float* part,

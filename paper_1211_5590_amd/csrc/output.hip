@@ -19,6 +19,16 @@ __host__ __device__ inline int rows_per_chunk(int N) {
     return few > most ? few : most;
 }
 
+__device__ __forceinline__ double wave_sum64(double s) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, kWave);
+    return s;
+}
+
+// Log-sum-exp of a row, rounded once.  (logf of sums in the thousands is 3e-7 too small on the mean, which makes every probability
+// of every row that much too large.)
+__device__ __forceinline__ double lse_of(float m, float s) { return (double)m + log((double)s); }
+
 // One workgroup per row: lse = m + log(sum exp(z - m)), rowloss = lse - z[y].
 __global__ __launch_bounds__(256) void ce_row_stats_kernel(const float* __restrict__ Z,
                                                            const int32_t* __restrict__ y,
@@ -31,10 +41,10 @@ __global__ __launch_bounds__(256) void ce_row_stats_kernel(const float* __restri
     for (int k = tid; k < O; k += blockDim.x) {
         const float v = z[k];
         if (v > m) {
-            s = s * __expf(m - v) + 1.f;  // exp(-inf) = 0 on the first element
+            s = s * exp_exact(m - v) + 1.f;  // exp(-inf) = 0 on the first element
             m = v;
         } else {
-            s += __expf(v - exp_base(m));
+            s += exp_exact(v - exp_base(m));
         }
     }
 #pragma unroll
@@ -47,9 +57,9 @@ __global__ __launch_bounds__(256) void ce_row_stats_kernel(const float* __restri
     if (tid == 0) {
         float M = sm[0], S = ss[0];
         for (int w = 1; w < 4; ++w) lse_merge(M, S, sm[w], ss[w]);
-        const float l = M + logf(S);
-        lse[n] = l;
-        rowloss[n] = l - z[y[n]];
+        const double l = lse_of(M, S);
+        lse[n] = (float)l;
+        rowloss[n] = (float)(l - z[y[n]]);
     }
 }
 
@@ -75,9 +85,9 @@ __global__ __launch_bounds__(256) void ce_merge_stats_kernel(const float* __rest
         lse_merge(m, s, m2, s2);
     }
     if (lane == 0) {
-        const float l = m + logf(s);
-        lse[n] = l;
-        rowloss[n] = l - Z[(size_t)n * O + y[n]];
+        const double l = lse_of(m, s);
+        lse[n] = (float)l;
+        rowloss[n] = (float)(l - Z[(size_t)n * O + y[n]]);
     }
 }
 
@@ -88,12 +98,12 @@ __global__ __launch_bounds__(256) void mse_partial_kernel(const float* __restric
                                                           const float* __restrict__ Y,
                                                           float* __restrict__ partial,
                                                           size_t total, size_t per_block) {
-    __shared__ float ss[4];
+    __shared__ double ss[4];
     constexpr int U = 4;
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const size_t begin = (size_t)blockIdx.x * per_block;
     const size_t end = begin + per_block < total ? begin + per_block : total;
-    float s = 0.f;
+    double s = 0.0;
     for (size_t i0 = begin + (size_t)tid * VEC; i0 < end; i0 += (size_t)256 * VEC * U) {
         float z[U][VEC], t[U][VEC];
 #pragma unroll
@@ -116,30 +126,30 @@ __global__ __launch_bounds__(256) void mse_partial_kernel(const float* __restric
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int v = 0; v < VEC; ++v) {
-                const float e = z[u][v] - t[u][v];
-                s = fmaf(e, e, s);
+                const double e = z[u][v] - t[u][v];
+                s = fma(e, e, s);
             }
     }
-    s = wave_sum(s);
+    s = wave_sum64(s);
     if (lane == 0) ss[wave] = s;
     __syncthreads();
-    if (tid == 0) partial[blockIdx.x] = (ss[0] + ss[1]) + (ss[2] + ss[3]);
+    if (tid == 0) partial[blockIdx.x] = (float)((ss[0] + ss[1]) + (ss[2] + ss[3]));
 }
 
-// loss = scale * sum rowloss (single workgroup, fixed order)
+// loss = scale * sum rowloss (single workgroup, fixed order; in 64 bits, so that the mean is rounded once)
 __global__ __launch_bounds__(1024) void loss_reduce_kernel(const float* __restrict__ rowloss, int N,
-                                                           float scale, float* __restrict__ loss) {
-    __shared__ float ss[16];
+                                                           double scale, float* __restrict__ loss) {
+    __shared__ double ss[16];
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-    float s = 0.f;
+    double s = 0.0;
     for (int n = tid; n < N; n += blockDim.x) s += rowloss[n];
-    s = wave_sum(s);
+    s = wave_sum64(s);
     if (lane == 0) ss[wave] = s;
     __syncthreads();
     if (tid == 0) {
-        float t = 0.f;
+        double t = 0.0;
         for (int w = 0; w < 16; ++w) t += ss[w];
-        *loss = t * scale;
+        *loss = (float)(t * scale);
     }
 }
 
@@ -224,7 +234,7 @@ __global__ __launch_bounds__(256) void dz_kernel(float* __restrict__ Z, const fl
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) {
                     if (LOSS == 0) {
-                        d[v] = __expf(z[u][v] - l[u]);
+                        d[v] = exp_exact(z[u][v] - l[u]);
                         if (yy[u] == col + v) d[v] -= 1.f;
                         d[v] *= scale;
                     } else {
@@ -347,7 +357,7 @@ hipError_t launch_mse_partial(const float* Z, const float* Y, float* partial, in
     return hipGetLastError();
 }
 
-hipError_t launch_loss_reduce(const float* rowloss, int N, float scale, float* loss, hipStream_t s) {
+hipError_t launch_loss_reduce(const float* rowloss, int N, double scale, float* loss, hipStream_t s) {
     ProfileScope ps(K_LOSS_REDUCE, s);
     hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(1024), 0, s, rowloss, N, scale, loss);
     return hipGetLastError();
