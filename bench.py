@@ -200,7 +200,7 @@ def algorithmic_work(kernel, c):
         "gemm_U": (f * (N * I + H * I + N * H), 2.0 * N * H * I),           # U = X Wx^T + b
         "gemm_dWx": (f * (N * H + N * I + H * I), 2.0 * N * H * I),         # dWx = Delta^T X
         # element-wise / row-wise passes over the logits
-        "ce_row_stats": (f * N * O, 3.0 * N * O),
+        "ce_row_stats": None,      # over the logits, or over what their product has left of them
         "mse_row_loss": (2 * f * N * O, 3.0 * N * O),
         "dz": ((3 if not c["loss_kind"] == 0 else 2) * f * N * O, 3.0 * N * O),
         "dwx_tokens": (f * (N * H + I * H), 1.0 * N * H),
@@ -282,17 +282,6 @@ def roofline_entry(name, prof, case):
     return r
 
 
-F16_TERMS, F16_K = 3.0, 448
-
-
-def matrix_work(name, c, terms, flops, sec):
-    """What the matrix cores execute for a product, and the share of their rate that is."""
-    N = c["seq_len"] * c["batch"]
-    K = {"gemm_logits": c["hidden"], "gemm_G": c["out_dim"], "gemm_U": c["in_dim"], "gemm_dh0": c["hidden"]}.get(name, N)
-    done = (F16_TERMS if name.startswith("gemm_") and K >= F16_K else terms) * flops
-    return dict(matrix_flops=done, frac_matrix=done / sec / 1e12 / BF16_MFMA_PEAK_TFLOPS)
-
-
 def _roofline_entry(name, prof, case):
     work = algorithmic_work(name, case)
     us = prof[name]["avg_us"]
@@ -303,9 +292,7 @@ def _roofline_entry(name, prof, case):
     sec = us * 1e-6
     # operands split into three bf16 numbers (two with the flag: the output layer's and the weight gradients'
     # products): six (three) bf16 matrix instructions per product term, nine in the batched loop; rates against the bf16
-    # peak, unless the bytes take longer at the rate of memory than those instructions at that peak.  That form is the
-    # yardstick of `executed_flops`; sums of 448 terms and more run on two f16 parts, three instructions per term at the
-    # same rate: `matrix_flops` is what the kernel executes.
+    # peak, unless the bytes take longer at the rate of memory than those instructions at that peak
     two = case.get("_bf16x3") and name in ("gemm_logits", "gemm_dV", "gemm_G", "gemm_dWh", "gemm_dWx")
     terms = (3.0 if two else 6.0) if name.startswith("gemm_") else \
         BATCH_MFMA_TERMS if name in ("rec_fwd", "rec_bwd") and case.get("_variant") == "batch_mfma" else 0.0
@@ -314,7 +301,7 @@ def _roofline_entry(name, prof, case):
         return dict(kernel=name, bound="mfma", achieved=ach, peak=BF16_MFMA_PEAK_TFLOPS, unit="TFLOP/s",
                     frac=ach / BF16_MFMA_PEAK_TFLOPS, traffic=None, avg_us=us, algorithmic_flops=flops,
                     dtype="bf16 %s split, f32 accumulate" % ("hi/lo" if two else "hi/mid/lo"), executed_flops=terms * flops,
-                    frac_executed=terms * ach / BF16_MFMA_PEAK_TFLOPS, **matrix_work(name, case, terms, flops, sec))
+                    frac_executed=terms * ach / BF16_MFMA_PEAK_TFLOPS)
     if not terms and flops / nbytes >= RIDGE:   # above the ridge point: arithmetic bound
         ach = flops / sec / 1e12
         # the batch-1..4 loops multiply on the vector ALUs (same fp32 peak as the matrix cores)
@@ -339,16 +326,26 @@ def roofline_of(prof, case):
             t = json.load(fh).get(case.get("_name", ""), {}).get(name)
         if t:
             r["traffic"] = t["bytes_per_launch"]
-            r["traffic_source"] = ("profiles/hbm_traffic.json: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this "
-                                   "command, scaled by a 64 MiB copy; committed, not measured in this run")
+            r["traffic_source"] = "profiles/hbm_traffic.json (counters; not of this run)"
     except (OSError, ValueError):
         pass
     return r
 
 
+# The line has to stay short (see line()): of the kernels beside the dominant one it says only these.
+ROOFLINE_COLUMNS = ("kernel", "bound", "avg_us", "frac", "frac_executed", "frac_measured")
+
+
 def all_rooflines(prof, case):
-    return [roofline_entry(k, prof, case) for k in sorted(prof, key=lambda k: -prof[k]["total_ms"])
+    """Every kernel with known work, longest first: rows of ROOFLINE_COLUMNS under a row that names them."""
+    rows = [roofline_entry(k, prof, case) for k in sorted(prof, key=lambda k: -prof[k]["total_ms"])
             if algorithmic_work(k, case) is not None]
+    return [list(ROOFLINE_COLUMNS)] + [[r.get(c) for c in ROOFLINE_COLUMNS] for r in rows]
+
+
+def kernel_times(prof):
+    """{kernel: [launches, us each]}, longest first"""
+    return {k: [prof[k]["launches"], prof[k]["avg_us"]] for k in sorted(prof, key=lambda k: -prof[k]["total_ms"])}
 
 
 def cpu_baseline(name, budget_s, one_thread_row=True):
@@ -466,11 +463,7 @@ def train_stream_leg(windows, reps=3, lr=0.1):
                      "peak": peak, "unit": "TFLOP/s", "frac": flops / sec / 1e12 / peak,
                      "traffic": traffic, "n_cu": n_cu, "avg_us": 1e6 * sec,
                      "algorithmic_flops": flops, **measured,
-                     "note": "one launch per stream; the model stays on chip (memory sees the ids, "
-                             "the touched rows of Wx, the losses and the tagged words the workgroups "
-                             "exchange), so the ceiling stated is the matrix rate of the occupied "
-                             "compute units; the launch is bound by the latency of its dependent steps "
-                             "and exchanges"},
+                     "note": "one launch, the model on chip: held against the matrix rate of its units"},
     }
 
 
@@ -527,7 +520,7 @@ def mlp_leg(n_batches=400, lr=0.01):
                 rnn.rnn_profile_begin(1 << 16)
                 rnn.rnn_mlp_train(dims, pr, None, X, y, 50, lr, losses, ws)
                 prof = rnn.rnn_profile_end()
-                entry["kernels"] = {k: dict(launches=c, avg_us_raw=round(1e3 * ms / c, 3)) for k, (c, ms) in sorted(prof.items())}
+                entry["kernels"] = {k: [c, 1e3 * ms / c] for k, (c, ms) in sorted(prof.items())}
                 # the update pass reads and rewrites every weight once: 8 bytes per parameter
                 upd = prof.get("mlp_update")
                 if upd:
@@ -540,7 +533,7 @@ def mlp_leg(n_batches=400, lr=0.01):
                                                  "frac_measured": nbytes / (us * 1e-6) / 1e9
                                                  / max(MEASURED["hbm_read_GBps"], MEASURED["hbm_copy_GBps"])}
                                                 if MEASURED else {}),
-                                             note="one launch per batch updates all layers; event bracket not removed")
+                                             note="all layers; event bracket not removed")
             out[f"{name}_batch{batch}"] = entry
     return out
 
@@ -595,7 +588,7 @@ def gauss_newton_leg(names=("C3", "C4", "C5"), reps=5, flags=0):
         prof = rnn.rnn_profile_end()
         top = sorted(prof.items(), key=lambda kv: -kv[1][1])[:6]
         out[name] = dict(ms_per_product=ms, tokens_per_s=w.tokens_per_step / (ms * 1e-3),
-                         kernels={k: dict(launches=c, total_ms_raw=round(t, 4)) for k, (c, t) in top})
+                         kernels={k: [c, 1e3 * t / c] for k, (c, t) in top})
         del w, gws, res, g
         torch.cuda.empty_cache()
     return out
@@ -633,6 +626,11 @@ def sig(x, digits=5):
     return x
 
 
+def line(out):
+    """The line that is printed.  Its reader keeps about 20000 characters, so floats are rounded and nothing is spaced out: about 12000."""
+    return json.dumps(sig(out), separators=(",", ":"))
+
+
 def run_config(name, flags, windows=None, three_calls=False, steps=None, warm=None, all_kernels=False):
     """Time one configuration and profile one more step of it per kernel."""
     import torch
@@ -652,8 +650,7 @@ def run_config(name, flags, windows=None, three_calls=False, steps=None, warm=No
                entry_points="rnn_window" if w.fused else "rnn_forward,rnn_loss,rnn_bptt",
                recurrence_variant=rnn.rnn_recurrence_variant(w.dims),
                describe=describe(w.case), roofline=roofline_of(prof, w.case),
-               kernels={k: dict(launches=v["launches"], avg_us=round(v["avg_us"], 3),
-                                total_ms=round(v["total_ms"], 4)) for k, v in sorted(prof.items())},
+               kernels=kernel_times(prof),
                bracket_us=w.bracket_us)
     if all_kernels:
         res["rooflines_all_kernels"] = all_rooflines(prof, w.case)
@@ -784,11 +781,11 @@ def main():
         if "C4" in gn:
             out["gauss_newton_vec"]["C4_bf16x3_output"] = gauss_newton_leg(["C4"], flags=rnn.FLAG_BF16X3_OUTPUT)["C4"]
     out["device"] = device_facts(torch)
-    out["measured_ceilings"] = dict(MEASURED, note="saturating kernels of the library itself on this GPU: "
-                                    "device-memory copy (read + written bytes) and read (the larger is the HBM ceiling), 32x32x2 f32 and 32x32x16 bf16 "
-                                    "matrix products, 16-byte LDS reads; frac_measured in the roofline entries "
-                                    "is stated against these, frac against the published peaks")
-    print(json.dumps(sig(out)))
+    # saturating kernels of the library itself on this GPU: device-memory copy (read + written bytes) and read (the larger is the
+    # HBM ceiling), 32x32x2 f32 and 32x32x16 bf16 matrix products, 16-byte LDS reads; frac_measured in the roofline
+    # entries is stated against these, frac against the published peaks
+    out["measured_ceilings"] = MEASURED
+    print(line(out))
 
 
 if __name__ == "__main__":

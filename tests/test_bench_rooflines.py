@@ -43,3 +43,15 @@ def test_launches_of_a_classifier_call():
     assert bench.mlp_launches(1, 1025) == 4 and bench.mlp_launches(3, 10) == 80
 
 
+def test_the_line_stays_short():
+    """A line of 20000 characters was not read.  Seven configurations with the kernels of the largest, their rooflines once."""
+    names = ("gemm_logits", "gemm_dV", "gemm_G", "gemm_dWh", "gemm_dWx", "splitk_reduce", "rec_fwd", "rec_bwd", "ce_row_stats", "loss_reduce", "dz",
+             "colsum_partial", "colsum_finish", "dwx_tokens", "misc", "mse_row_loss", "transpose")
+    prof = {k: dict(launches=2, avg_us=1234.56789 / (i + 1), total_ms=2.46913578 / (i + 1)) for i, k in enumerate(names)}
+    c = case(_name="C4")
+    roofline = dict(bench.roofline_of(prof, c), peak_measured=2417.512345, frac_measured=0.533791234)
+    r = dict(tokens_per_s=2641512.345, timesteps_per_s=41273.612, ms_per_step=6.2025123, entry_points="rnn_forward,rnn_loss,rnn_bptt",
+             recurrence_variant="xcd_mfma", roofline=roofline, kernels=bench.kernel_times(prof))
+    out = dict(kernels=r["kernels"], rooflines_all_kernels=bench.all_rooflines(prof, c),
+               per_config={str(n): bench.per_config_entry(r) for n in range(7)})
+    assert len(bench.line(out)) < 10000, len(bench.line(out))
