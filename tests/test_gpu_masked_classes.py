@@ -53,6 +53,7 @@ def buffers(p, T, B, H):
 FORMS = {
     "tile_64": (68, 160, 36, 7),
     "tile_64_many_classes": (1024, 1024, 40, 8),
+    "tile_64_uncut_many_classes": (340, 1024, 40, 8),
     "tile_128": (200, 10000, 35, 20),
     "tile_256": (260, 4096, 64, 64),
     "k_cut": (1024, 260, 11, 6),
