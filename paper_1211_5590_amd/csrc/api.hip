@@ -222,7 +222,7 @@ hipError_t run_forward(const rnn_dims* d, const rnn_params* P, const void* x, co
         a.U = at<float>(ws, pl.U);
     }
     const Variant v = pick_variant(d);
-    if (v.xcd && h_all && rec_xcd_ready(z.H, d->act, false)) {
+    if (v.xcd && h_all && rec_xcd_ready(z.H, z.B, d->act, false)) {
         RecXcdArgs m{};
         m.Wh = P->Wh; m.H = z.H; m.T = z.T; m.B = z.B; m.act = d->act;
         m.x = a.x; m.Wx = P->Wx; m.b = P->b; m.U = a.U; m.h0 = h0; m.hist = h_all; m.h_last = h_last;
@@ -318,7 +318,7 @@ hipError_t run_reverse_loop(const rnn_dims* d, const float* Wh, const float* WhT
     if (v.skinny) {   // the plain plan of the resident loop
         if (!rec_resident_plan(z.H, z.B, z.T, true, false, 0, &v.bwd)) v.resident = false;
     }
-    if (v.xcd && rec_xcd_ready(z.H, d->act, true)) {
+    if (v.xcd && rec_xcd_ready(z.H, z.B, d->act, true)) {
         RecXcdArgs m{};
         m.Wh = Wh; m.H = H; m.T = z.T; m.B = z.B; m.act = d->act;
         m.G = G; m.h_all = h_all; m.dh_last = dh_last; m.Delta = Delta; m.dh0 = dh0;

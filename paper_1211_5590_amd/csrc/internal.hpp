@@ -140,10 +140,11 @@ struct RecXcdArgs {
     float* ring;          // rec_xcd_ring_bytes of workspace, 16-byte aligned (filled by the launcher)
     int32_t* status;      // device status word: set to 1 when a bounded wait expires
     int spin_limit;       // <= 0: default
+    int slots;            // workgroups of a group (filled in by the launcher)
 };
 bool rec_xcd_supported(int H, int B, int T);                       // shape only (host)
 size_t rec_xcd_ring_bytes(int H, int B);
-bool rec_xcd_ready(int H, int act, bool bwd);               // and the current device can hold the grid at once
+bool rec_xcd_ready(int H, int B, int act, bool bwd);             // and the current device can hold the grid at once
 hipError_t launch_rec_xcd(const RecXcdArgs& a, bool bwd, hipStream_t s);
 
 // before a launch of `fn` with that much dynamic LDS on the current device (lds_limit.hip)

@@ -4,15 +4,18 @@
 // The paper's Scan keeps the loop inside one graph node so that nothing per step happens outside
 // compiled code (properties 4 and 5) and keeps every state (property 1); the per-step kernel
 // boundary of recurrence_step.hip costs more than the step's arithmetic.  Here the chip's layout
-// does the work instead: batch rows are independent, so the batch is cut into 16 groups of up to 4
-// rows, two groups per XCD (groups x and x + 8 on XCD x), and 16 of the 32 compute units of an XCD
-// share one group's recurrence.  Every workgroup holds 64 output columns of the matrix (all K) in
-// registers for the whole launch and produces, per step, the 4 x 64 tile of the new state on the
+// does the work instead: batch rows are independent, so the batch is cut into up to 16 groups of up to 4
+// rows, groups x and x + 8 on XCD x, and the 32 compute units of an XCD share its one group's recurrence, or
+// 16 each of its two groups' (batch above 32).  Every workgroup holds 16, 32 or 64 output columns of the matrix (all K) in
+// registers for the whole launch, as few as cover H, and produces, per step, its tile of the new state on the
 // matrix cores; the eight wavefronts split K and meet in LDS.  Groups never talk to each other.
 //
-// Matrix instruction: v_mfma_f32_4x4x1 with the state broadcast over all 16 column blocks
-// (cbsz = 4): lane l supplies the matrix value M[k][c0 + l] of one k per instruction and the state
-// value of row l % 4 for the 16 k of its block l / 4, and receives rows 0..3 at column c0 + l.  The
+// Matrix instruction: v_mfma_f32_4x4x1, 16 blocks of 4 rows by 4 columns.  With 64 columns per workgroup the state is broadcast
+// over all 16 blocks (cbsz = 4): lane l supplies the matrix value M[k][c0 + l] of one k per instruction and the state
+// value of row l % 4 for the 16 k of its block l / 4, and receives rows 0..3 at column c0 + l.  With 32 or 16 columns the
+// lanes are two or four parts that each have all columns and a part of the k (cbsz = 3 or 2: the state is broadcast
+// within a part), so a step takes half or a quarter of the instructions, and a lane a half or a quarter of the registers.
+// The parts are added up after the wavefronts' tiles have met.  The
 // 16-byte piece of the state a lane fetches from memory (row l % 4, four consecutive k) is exactly
 // what it feeds the instruction, so the state goes from the cache into the operand registers
 // without passing LDS.  A wavefront's share of K is an eighth of H in whole blocks of 16 (48 to 128),
@@ -45,9 +48,11 @@
 // Measured (a loop of 256 steps, batch 64, H = 1024): 600 us with the state read from the history and
 // device-scope stores, 475 now (1000 words; 540 right behind the large products of 10000 words, which
 // leave the chip at a lower clock); 100 steps at H = 513, batch 33: 207 -> 161, at H = 512, batch 64:
-// 158 -> 132.  A step at H = 1024 takes about 3900 clocks: 2050 for the matrix instructions of the
+// 158 -> 132.  A step at H = 1024, batch 64 takes about 3900 clocks: 2050 for the matrix instructions of the
 // two wavefronts of a SIMD at the rate of float32, 550 from the last of them to the store, the rest for the
-// store and the look.
+// store and the look.  With fewer columns the instructions are less of it (100 steps, us of a forward loop with 64, 32, 16
+// columns): H = 500, batch 1: 134, 113, 110; H = 513, batch 19: 165, 136; H = 1024, batch 32: 200, 154;
+// H = 400, batch 40: 137, 117; H = 300, batch 20: 122, 110, 109.
 #include "common.hpp"
 #include "internal.hpp"
 #include "prof.hpp"
@@ -63,11 +68,10 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int XT = 512;            // threads: 8 wavefronts
 constexpr int RB = 4;              // batch rows per group
-constexpr int CWD = 64;            // output columns per workgroup
 constexpr int NXCD = 8;            // XCDs: the layout this loop is built on
 constexpr int WG_PER_XCD = 32;     // compute units per XCD = workgroups per XCD
-constexpr int NSLOT = 16;          // workgroups per group
-constexpr int NGRP = 16;           // groups: x and x + 8 on XCD x
+constexpr int NGRP = 16;           // groups at most: x and x + 8 on XCD x
+constexpr int H_MAX = 1024;
 constexpr int RSLOTS = 4;          // states the exchange ring holds
 constexpr unsigned kSentinel = 0xFFFFFFFFu;
 
@@ -95,15 +99,16 @@ __device__ __forceinline__ bool fresh(float4 v) {
            __float_as_uint(v.z) != kSentinel && __float_as_uint(v.w) != kSentinel;
 }
 
-// 64 matrix instructions: the four values of one state piece against 64 k of the matrix, block AB
-// of the lanes supplying the state (abid) for k = 4 AB + e
-template <int... AB>
+// the four values of one state piece against the matrix: every 64 / S lanes have the state of block AB of their own 16 / S
+// (abid), k = 4 AB + e of their share of the piece
+template <int S, int... AB>
 __device__ __forceinline__ void mfma_blocks(const float4 st, const float* __restrict__ w, f32x4 (&acc)[4],
                                             std::integer_sequence<int, AB...>) {
-    ((acc[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(st.x, w[4 * AB + 0], acc[0], 4, AB, 0),
-      acc[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(st.y, w[4 * AB + 1], acc[1], 4, AB, 0),
-      acc[2] = __builtin_amdgcn_mfma_f32_4x4x1f32(st.z, w[4 * AB + 2], acc[2], 4, AB, 0),
-      acc[3] = __builtin_amdgcn_mfma_f32_4x4x1f32(st.w, w[4 * AB + 3], acc[3], 4, AB, 0)),
+    constexpr int CB = S == 1 ? 4 : S == 2 ? 3 : 2;
+    ((acc[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(st.x, w[4 * AB + 0], acc[0], CB, AB, 0),
+      acc[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(st.y, w[4 * AB + 1], acc[1], CB, AB, 0),
+      acc[2] = __builtin_amdgcn_mfma_f32_4x4x1f32(st.z, w[4 * AB + 2], acc[2], CB, AB, 0),
+      acc[3] = __builtin_amdgcn_mfma_f32_4x4x1f32(st.w, w[4 * AB + 3], acc[3], CB, AB, 0)),
      ...);
 }
 
@@ -111,19 +116,20 @@ __device__ __forceinline__ void mfma_blocks(const float4 st, const float* __rest
 // inside a group, the order in which a wavefront's lanes want them
 __host__ __device__ inline int ring_state(int B, int kw) { return (B + RB - 1) / RB * RB * 8 * kw; }
 
-// KW = k per wavefront (8 KW >= H)
-template <int ACT, bool BWD, int KW>
+// KW = k per wavefront (8 KW >= H), CWD = output columns per workgroup
+template <int ACT, bool BWD, int KW, int CWD>
 __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
     constexpr int NQ = (KW + 63) / 64;     // 16-byte state pieces per lane and step
-    constexpr int NB1 = (KW - 64) / 4;     // blocks of four k of the second piece
+    constexpr int S = 64 / CWD;            // k per instruction, in as many parts of a wavefront's lanes
+    constexpr int N0 = KW < 64 ? KW : 64, N1 = KW - N0;   // k of the two pieces
     extern __shared__ __attribute__((aligned(16))) float smem[];
     __shared__ int s_abort, s_grp, s_slot;
     __shared__ int s_stored;                   // steps whose first row this workgroup has stored
-    float* part = smem;                    // [2][8 wavefronts][CWD][RB] partial tiles, by step parity
+    float* part = smem;                    // [2][8 wavefronts][S][CWD][RB] partial tiles, by step parity
 
     const int H = a.H, B = a.B, T = a.T;
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-    const int ri = lane % 4, kg = lane / 4;
+    const int ri = lane % 4;
     const size_t bh = (size_t)B * H;
 
     // ---- which group and which column slice: by the XCD this workgroup runs on ------------------
@@ -132,8 +138,8 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
         asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(id));
         const int xcc = (int)(id & 0xf);
         const int n = xcc < NXCD ? atomicAdd(a.counters + xcc, 1) : WG_PER_XCD;
-        s_grp = n < WG_PER_XCD ? xcc + NXCD * (n / NSLOT) : NGRP;
-        s_slot = n % NSLOT;
+        s_grp = n < WG_PER_XCD ? xcc + NXCD * (n / a.slots) : NGRP;
+        s_slot = n % a.slots;
         s_abort = 0;
     }
     if (tid == 0) s_stored = 0;
@@ -147,76 +153,85 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
     if (b0 >= B || c0 >= H) return;              // nothing to do here, and nobody waits for this workgroup
     const int nrows = min(RB, B - b0);
 
-    // ---- resident weights: wreg[j] = M[kb + j][col], M = Wh^T (forward) or Wh (reverse); zero
-    //      outside the matrix ----------------------------------------------------------------------
+    // ---- resident weights: wreg[64 / S * q + j] = M[k][c0 + lane % CWD], k = kb + 64 q + nq / S * (lane / CWD) + j with nq
+    //      the k of piece q; M = Wh^T (forward) or Wh (reverse); zero outside the matrix ----------------
     const int kb = KW * wave;
-    float wreg[KW];
+    const int part_k = lane / CWD, part_c = lane % CWD;   // this lane's part of every piece's k, and its column
+    float wreg[KW / S];
     if (BWD) {
         // M[k][col] = Wh[k][col]: a lane's values lie along a column of Wh.  Fetched as 16-byte pieces
-        // along the rows (a request covers four k of 256 bytes) into a wavefront-private LDS tile
-        // [64 k][64 columns], 64 k at a time, from which every lane takes its column.
+        // along the rows into a wavefront-private LDS tile [64 k][CWD columns], 64 k at a time, from which
+        // every lane takes its column.
         float* stg = smem + wave * 64 * 65;
-        const int r4 = lane >> 4, c4 = 4 * (lane & 15);
+        constexpr int RP = 256 / CWD;             // rows per request
+        const int r4 = lane / (CWD / 4), c4 = 4 * (lane % (CWD / 4));
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-            float4 v[16];
+            constexpr int NV = 64 / RP;
+            const int nq = q ? N1 : N0;
+            float4 v[NV];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int k = kb + 64 * q + r4 + 4 * i, cc = c0 + c4;
+            for (int i = 0; i < NV; ++i) {
+                const int k = kb + 64 * q + r4 + RP * i, cc = c0 + c4;
                 v[i] = piece(a.Wh + (size_t)k * H + cc, k < H ? H - cc : 0);
             }
 #pragma unroll
-            for (int i = 0; i < 16; ++i) *reinterpret_cast<float4*>(stg + (r4 + 4 * i) * 64 + c4) = v[i];
+            for (int i = 0; i < NV; ++i) *reinterpret_cast<float4*>(stg + (r4 + RP * i) * CWD + c4) = v[i];
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the tile is this wavefront's own
 #pragma unroll
-            for (int j = 0; j < min(64, KW - 64 * q); ++j) wreg[64 * q + j] = stg[j * 64 + lane];
+            for (int j = 0; j < nq / S; ++j) wreg[64 / S * q + j] = stg[(nq / S * part_k + j) * CWD + part_c];
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
         __syncthreads();                                             // the partial tiles reuse this memory
     } else {
         // M[k][col] = Wh[col][k]: a lane's values lie along a row of Wh.  Fetched as 16-byte pieces
         // along the rows (a request covers four rows of 256 bytes) and turned through a
-        // wavefront-private LDS tile [64 columns][64 k], 64 k at a time.
+        // wavefront-private LDS tile [CWD columns][64 k], 64 k at a time.
         constexpr int PITCH = 65;                 // odd: the transposed reads fall into distinct banks
         float* stg = smem + wave * 64 * PITCH;
         const int r4 = lane >> 4, k4 = 4 * (lane & 15);
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-            float4 v[16];
+            constexpr int NV = CWD / 4;
+            const int nq = q ? N1 : N0;
+            float4 v[NV];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
+            for (int i = 0; i < NV; ++i) {
                 const int row = c0 + r4 + 4 * i, k = kb + 64 * q + k4;
                 v[i] = piece(a.Wh + (size_t)row * H + k, row < H ? H - k : 0);
             }
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
+            for (int i = 0; i < NV; ++i) {
                 float* d = stg + (r4 + 4 * i) * PITCH + k4;
                 d[0] = v[i].x; d[1] = v[i].y; d[2] = v[i].z; d[3] = v[i].w;
             }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the tile is this wavefront's own
 #pragma unroll
-            for (int j = 0; j < min(64, KW - 64 * q); ++j) wreg[64 * q + j] = stg[lane * PITCH + j];
+            for (int j = 0; j < nq / S; ++j) wreg[64 / S * q + j] = stg[part_c * PITCH + nq / S * part_k + j];
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
         __syncthreads();                                             // the partial tiles reuse this memory
     }
 
-    // ---- the state pieces of this lane: row ri, columns kb + 64 q + 4 kg .. + 3; pieces outside
-    //      the matrix (rows past the batch, columns past H) or another wavefront's stay zero ------------
-    int p_off[NQ], p_shift[NQ];
+    // ---- the state pieces of this lane: row ri, four columns from p_k on; pieces outside the matrix (rows past
+    //      the batch, columns past H) or another wavefront's stay zero.  The 16 / S blocks of a part of the lanes hold the part's
+    //      k in order; a piece of fewer than 64 k leaves the last blocks of every part unused ------------
+    const int block = (lane / 4) % (16 / S);
+    int p_k[NQ], p_off[NQ], p_shift[NQ];
     bool p_on[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-        const int k = kb + 64 * q + 4 * kg;
-        p_on[q] = ri < nrows && k < H && 64 * q + 4 * kg < KW;
+        const int nq = q ? N1 : N0, k = kb + 64 * q + nq / S * part_k + 4 * block;
+        p_k[q] = k;
+        p_on[q] = ri < nrows && k < H && 4 * block < nq / S;
         p_off[q] = p_on[q] ? (b0 + ri) * H + min(k, H - 4) : b0 * H;   // clamped duplicates outside the matrix
         p_shift[q] = p_on[q] ? max(k - (H - 4), 0) : 0;
     }
-    // the same pieces in the exchange ring: one contiguous stretch per wavefront and q
+    // the same pieces in the exchange ring: one contiguous stretch per wavefront and q (per part of it, where nq < 64)
     const int rstate = ring_state(B, KW);
     int r_off[NQ];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) r_off[q] = p_on[q] ? b0 * 8 * KW + (kb + 64 * q) * RB + 4 * lane : b0 * 8 * KW + kb * RB;
+    for (int q = 0; q < NQ; ++q) r_off[q] = p_on[q] ? b0 * 8 * KW + p_k[q] * RB + 4 * ri : b0 * 8 * KW + kb * RB;
     float4 st[NQ];                         // the state of the coming step
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
@@ -239,14 +254,16 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
 
     const int nsteps = BWD ? T - 1 : T;
 
-    // ---- epilogue lanes (wavefronts 0..3): 16 columns of the tile per wavefront, in the ring's order, so
-    //      that a wavefront's share of the new state leaves as one stretch of 256 bytes -------------------
-    const int em = (lane >> 2) & 3, et = 16 * (wave & 3) + 4 * (lane >> 4) + (lane & 3), ec = c0 + et;
-    const bool e_on = wave < 4 && em < nrows && ec < H;
+    // ---- epilogue lanes (wavefronts 0..3): CWD / 4 columns of the tile per wavefront, in the ring's order, so
+    //      that a wavefront's share of the new state leaves as one stretch of 4 CWD bytes.  The S parts of an element
+    //      are summed by lanes 64 / S apart; the first of them stores the element ------------------------
+    const int ej = lane % (64 / S), ep = lane / (64 / S);
+    const int em = (ej >> 2) & 3, et = CWD / 4 * (wave & 3) + 4 * (ej >> 4) + (ej & 3), ec = c0 + et;
+    const bool e_on = wave < 4 && ep == 0 && em < nrows && ec < H;
     // the columns that fill the ragged last piece of a row are published as zeros
-    const bool e_pub = wave < 4 && em < nrows && ec < (H + 3) / 4 * 4;
+    const bool e_pub = wave < 4 && ep == 0 && em < nrows && ec < (H + 3) / 4 * 4;
     const size_t e_off = (size_t)min(b0 + em, B - 1) * H + min(ec, H - 1);
-    const int e_ring = b0 * 8 * KW + c0 * RB + 64 * (wave & 3) + lane;
+    const int e_ring = b0 * 8 * KW + c0 * RB + 64 / S * (wave & 3) + ej;
     if (e_on) {    // slot 0 of the history (forward) / Delta[T-1] (reverse): the owner of a column stores it
         if (!BWD) {
             a.hist[e_off] = a.h0 ? a.h0[e_off] : 0.f;
@@ -285,24 +302,27 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
     }
 
     XT_DECL;
-    // partial tile of this wavefront's K slice: element i = row i at column c0 + lane
+    // partial tile of this wavefront's K slice: element i = row i at column c0 + lane % CWD, of this lane's part of K
     auto product = [&]() {
         f32x4 acc[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[e] = (f32x4){0.f, 0.f, 0.f, 0.f};
-        mfma_blocks(st[0], wreg, acc, std::make_integer_sequence<int, (KW < 64 ? KW / 4 : 16)>{});
-        if constexpr (NQ > 1) mfma_blocks(st[NQ - 1], wreg + 64, acc, std::make_integer_sequence<int, NB1>{});
+        mfma_blocks<S>(st[0], wreg, acc, std::make_integer_sequence<int, N0 / S / 4>{});
+        if constexpr (NQ > 1) mfma_blocks<S>(st[NQ - 1], wreg + 64 / S, acc, std::make_integer_sequence<int, N1 / S / 4>{});
         return (acc[0] + acc[1]) + (acc[2] + acc[3]);
     };
     auto park_partial = [&](int par, const f32x4 p4) {
-        *reinterpret_cast<f32x4*>(part + (par * 8 + wave) * RB * CWD + RB * lane) = p4;
+        *reinterpret_cast<f32x4*>(part + (par * 8 + wave) * RB * 64 + RB * lane) = p4;
     };
-    auto tile_sum = [&](int par) {            // epilogue lanes: the eight wavefronts' partial sums
-        const float* pp = part + par * 8 * RB * CWD + RB * et + em;
+    auto tile_sum = [&](int par) {            // epilogue lanes: the eight wavefronts' partial sums, then the S parts'
+        const float* pp = part + par * 8 * RB * 64 + RB * (CWD * ep + et) + em;
         float v[8];
 #pragma unroll
-        for (int w = 0; w < 8; ++w) v[w] = pp[w * RB * CWD];
-        return ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+        for (int w = 0; w < 8; ++w) v[w] = pp[w * RB * 64];
+        float sum = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+        if constexpr (S == 4) sum = swap16_sum(sum);
+        if constexpr (S >= 2) sum = swap32_sum(sum);
+        return sum;
     };
     // The lane's pieces of the state at `src` in the ring, waiting until no "not written yet" word is left.
     auto collect = [&](const float* src) {
@@ -408,20 +428,30 @@ __global__ __launch_bounds__(256) void xcd_clear_kernel(float* __restrict__ ring
     if (i < NXCD) counters[i] = 0;
 }
 
-template <int ACT, bool BWD>
-const void* pick_xcd_kernel(int kw) {
-    switch (kw) {
-        case 48: return (const void*)rec_xcd_kernel<ACT, BWD, 48>;
-        case 64: return (const void*)rec_xcd_kernel<ACT, BWD, 64>;
-        case 80: return (const void*)rec_xcd_kernel<ACT, BWD, 80>;
-        case 96: return (const void*)rec_xcd_kernel<ACT, BWD, 96>;
-        case 112: return (const void*)rec_xcd_kernel<ACT, BWD, 112>;
-        default: return (const void*)rec_xcd_kernel<ACT, BWD, 128>;
-    }
-}
-
 // k per wavefront: an eighth of H in whole blocks of 16
 int xcd_kw(int H) { return H <= 384 ? 48 : (H + 127) / 128 * 16; }
+
+// Workgroups of a group and their columns.  Up to 32 rows are one group per XCD, which then has all 32 compute units, and the
+// fewer columns a workgroup has the fewer matrix instructions a step takes (measured: see the top).
+int xcd_slots(int B) { return B > NXCD * RB ? WG_PER_XCD / 2 : WG_PER_XCD; }
+int xcd_columns(int H, int B) {
+    const int per = (H + xcd_slots(B) - 1) / xcd_slots(B);
+    return per <= 16 ? 16 : per <= 32 ? 32 : 64;
+}
+
+template <int ACT, bool BWD>
+const void* pick_xcd_kernel(int kw, int cwd) {
+#define RNN_XCD(KW) (cwd == 32 ? (const void*)rec_xcd_kernel<ACT, BWD, KW, 32> : (const void*)rec_xcd_kernel<ACT, BWD, KW, 64>)
+    switch (kw) {
+        case 48: return cwd == 16 ? (const void*)rec_xcd_kernel<ACT, BWD, 48, 16> : RNN_XCD(48);
+        case 64: return cwd == 16 ? (const void*)rec_xcd_kernel<ACT, BWD, 64, 16> : RNN_XCD(64);
+        case 80: return RNN_XCD(80);
+        case 96: return RNN_XCD(96);
+        case 112: return RNN_XCD(112);
+        default: return RNN_XCD(128);
+    }
+#undef RNN_XCD
+}
 
 // partial tiles of a step; the forward kernel first stages its matrix slice there
 size_t xcd_lds_bytes() { return (size_t)8 * 64 * 65 * 4; }
@@ -439,25 +469,25 @@ size_t xcd_lds_bytes() { return (size_t)8 * 64 * 65 * 4; }
 // batch 3, which has no room for 16 outputs per workgroup there, is 300 / 199 us per loop.  Of 10 steps
 // (H = 500: 149 / 142) the set-up is most.
 bool rec_xcd_supported(int H, int B, int T) {
-    if (H <= 256 || H > NSLOT * CWD || B < 1 || B > NGRP * RB) return false;
+    if (H <= 256 || H > H_MAX || B < 1 || B > NGRP * RB) return false;
     return B > 4 ? T >= 10 : T >= 16 && (B > 2 || H <= 640);
 }
 
 size_t rec_xcd_ring_bytes(int H, int B) { return (size_t)RSLOTS * ring_state(B, xcd_kw(H)) * 4; }
 
 template <bool BWD>
-const void* xcd_kernel_for(int H, int act) {
-    const int kw = xcd_kw(H);
-    return act == 0 ? pick_xcd_kernel<0, BWD>(kw) : pick_xcd_kernel<1, BWD>(kw);
+const void* xcd_kernel_for(int H, int B, int act) {
+    const int kw = xcd_kw(H), cwd = xcd_columns(H, B);
+    return act == 0 ? pick_xcd_kernel<0, BWD>(kw, cwd) : pick_xcd_kernel<1, BWD>(kw, cwd);
 }
 
 // Can all 256 workgroups be resident at once on the current device (one per compute unit)?  Asked
 // once per kernel and device; also raises the kernel's LDS limit.
-bool rec_xcd_ready(int H, int act, bool bwd) {
-    const void* fn = bwd ? xcd_kernel_for<true>(H, act) : xcd_kernel_for<false>(H, act);
+bool rec_xcd_ready(int H, int B, int act, bool bwd) {
+    const void* fn = bwd ? xcd_kernel_for<true>(H, B, act) : xcd_kernel_for<false>(H, B, act);
     const size_t lds = xcd_lds_bytes();
     struct Seen { const void* fn; int dev; bool ok; };
-    static Seen seen[64];
+    static Seen seen[512];
     static int n_seen = 0;
     static std::mutex mu;
     int dev = 0;
@@ -470,14 +500,14 @@ bool rec_xcd_ready(int H, int act, bool bwd) {
                     hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, XT, lds) == hipSuccess &&
                     hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
                     per_cu >= 1 && cus == NXCD * WG_PER_XCD;
-    if (n_seen < 64) seen[n_seen++] = Seen{fn, dev, ok};
+    if (n_seen < 512) seen[n_seen++] = Seen{fn, dev, ok};
     return ok;
 }
 
 hipError_t launch_rec_xcd(const RecXcdArgs& a, bool bwd, hipStream_t s) {
     if (!rec_xcd_supported(a.H, a.B, a.T)) return hipErrorInvalidValue;
-    if (!rec_xcd_ready(a.H, a.act, bwd)) return hipErrorNotSupported;
-    const void* fn = bwd ? xcd_kernel_for<true>(a.H, a.act) : xcd_kernel_for<false>(a.H, a.act);
+    if (!rec_xcd_ready(a.H, a.B, a.act, bwd)) return hipErrorNotSupported;
+    const void* fn = bwd ? xcd_kernel_for<true>(a.H, a.B, a.act) : xcd_kernel_for<false>(a.H, a.B, a.act);
     const size_t lds = xcd_lds_bytes();
 
     {
@@ -490,6 +520,7 @@ hipError_t launch_rec_xcd(const RecXcdArgs& a, bool bwd, hipStream_t s) {
     ProfileScope ps(bwd ? K_REC_BWD : K_REC_FWD, s);
     RecXcdArgs args = a;
     if (args.spin_limit <= 0) args.spin_limit = wait_limit();
+    args.slots = xcd_slots(a.B);
     void* kargs[] = {&args};
     return hipLaunchCooperativeKernel(fn, dim3(NXCD * WG_PER_XCD), dim3(XT), kargs, (unsigned)lds, s);
 }

@@ -149,3 +149,16 @@ def test_the_loops_of_the_smallest_batches_at_their_edges(H, T):
         last.forward()
         torch.cuda.synchronize()
         assert np.max(np.abs(last.h_last.cpu().numpy() - ref["h_all"][-1])) <= 2e-5
+
+
+@pytest.mark.parametrize("H,B", ((512, 32), (512, 33), (513, 32), (513, 33), (1024, 32), (1024, 33), (300, 1), (384, 35)))
+def test_the_one_launch_wide_loop_where_the_columns_of_a_workgroup_change(H, B):
+    """16, 32 or 64 columns per workgroup: the last and the first size of each, with one and with two groups per die."""
+    case = ri.make_case(in_dim=90, hidden=H, out_dim=70, seq_len=16, batch=B, act=H % 2, with_h0=True, with_dh_last=True,
+                        wdist=("normal", 0.5 / np.sqrt(H)), bias_std=0.1, seed=9900 + 11 * H + B)
+    r = Runner(case)
+    print(f"H={H} B={B}", flush=True)
+    assert rnn.rnn_recurrence_variant(r.dims) == "xcd_mfma"
+    r.step()
+    assert rnn.rnn_workspace_status(r.dims, r.ws) == 0
+    compare(r.results(), oracle.fwd_bptt(case, h0=case.get("h0"), dh_last=case.get("dh_last")))
