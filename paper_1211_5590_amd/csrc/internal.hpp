@@ -136,17 +136,19 @@ struct RecXcdArgs {
     float* h_last;        // nullable
     // reverse
     const float* G; const float* h_all; const float* dh_last; float* Delta; float* dh0;
-    int32_t* counters;    // 8 words of workspace (cleared by the launcher)
+    int32_t* counters;    // 24 words of workspace (cleared by the launcher)
     float* ring;          // rec_xcd_ring_bytes of workspace, 16-byte aligned (filled by the launcher)
     int32_t* status;      // device status word: set to 1 when a bounded wait expires
     int spin_limit;       // <= 0: default
-    int slots;            // workgroups of a group (filled in by the launcher)
+    int slots, patience;  // workgroups of a group; 10 ns they wait for each other to come (filled in by the launcher)
 };
 bool rec_xcd_supported(int H, int B, int T);                       // shape only (host)
 size_t rec_xcd_ring_bytes(int H, int B);
 bool rec_xcd_ready(int H, int B, int act, bool bwd);             // and the current device can hold the grid at once
 hipError_t launch_rec_xcd(const RecXcdArgs& a, bool bwd, hipStream_t s);
 
+// Launch of a kernel whose workgroups wait for each other: it takes turns with others of its kind on the device (gang.hip)
+hipError_t launch_gang(const void* fn, dim3 grid, dim3 block, void** args, size_t lds, hipStream_t s);
 // before a launch of `fn` with that much dynamic LDS on the current device (lds_limit.hip)
 hipError_t allow_lds(const void* fn, size_t bytes);
 hipError_t launch_zero_words(int32_t* p, int n, hipStream_t s);

@@ -42,8 +42,11 @@
 // A hidden size that is no multiple of 4 has the rest of a row's last piece published as zeros.
 // A workgroup takes its group from the XCD it finds itself on and its column slice from a per-XCD
 // counter, so all workgroups of a group share one L2 by construction whenever the 256 workgroups are
-// co-resident (cooperative launch, one workgroup per compute unit: checked before the launch).
-// Every wait is bounded, and an expired wait sets the status word.
+// co-resident (one workgroup per compute unit: checked before the launch).  The launch is not cooperative but takes turns with
+// others of its kind (gang.hip).  Where other work keeps a part of a group off the chip for longer than the loop would
+// take on one workgroup, one of those that did come runs it by itself and the others leave, so the launch ends with right
+// results whatever else the GPU does (run_alone below).
+// Every wait is bounded, and an expired wait for a state sets the status word.
 //
 // Measured (a loop of 256 steps, batch 64, H = 1024): 600 us with the state read from the history and
 // device-scope stores, 475 now (1000 words; 540 right behind the large products of 10000 words, which
@@ -56,6 +59,8 @@
 #include "common.hpp"
 #include "internal.hpp"
 #include "prof.hpp"
+
+#include <math.h>
 
 #include <mutex>
 #include <type_traits>
@@ -74,6 +79,9 @@ constexpr int NGRP = 16;           // groups at most: x and x + 8 on XCD x
 constexpr int H_MAX = 1024;
 constexpr int RSLOTS = 4;          // states the exchange ring holds
 constexpr unsigned kSentinel = 0xFFFFFFFFu;
+constexpr int ROLL_CLOSED = 1 << 16;
+// what a workgroup does in its group: not known yet, its own columns, nothing, everything
+constexpr int PART_OPEN = 0, PART_ONE = 1, PART_NONE = 2, PART_ALL = 3;
 
 #ifdef RNN_REC_TRACE
 __device__ long long g_xcd_trace[4 * 8];
@@ -116,6 +124,90 @@ __device__ __forceinline__ void mfma_blocks(const float4 st, const float* __rest
 // inside a group, the order in which a wavefront's lanes want them
 __host__ __device__ inline int ring_state(int B, int kw) { return (B + RB - 1) / RB * RB * 8 * kw; }
 
+// The whole recurrence of one group on one workgroup, the matrix read from the caches every step: for a group of which not all
+// workgroups came.  sm: 2 RB ceil4(H) floats.
+template <int ACT, bool BWD>
+__device__ __forceinline__ void run_alone(const RecXcdArgs& a, int b0, int nrows, float* sm) {
+    const int H = a.H, T = a.T, HP = (H + 3) / 4 * 4, tid = threadIdx.x;
+    const size_t bh = (size_t)a.B * H;
+    float *cur = sm, *nxt = sm + RB * HP;
+    __syncthreads();
+    for (int e = tid; e < RB * HP; e += XT) {
+        const int r = e / HP, c = e - r * HP;
+        float v = 0.f;
+        if (r < nrows && c < H) {
+            const size_t off = (size_t)(b0 + r) * H + c;
+            if (!BWD) {
+                v = a.h0 ? a.h0[off] : 0.f;
+                a.hist[off] = v;
+            } else {
+                const size_t i = (size_t)(T - 1) * bh + off;
+                v = (a.G[i] + (a.dh_last ? a.dh_last[off] : 0.f)) * act_grad<ACT>(a.h_all[(size_t)T * bh + off]);
+                a.Delta[i] = v;
+            }
+        }
+        cur[e] = v;
+        nxt[e] = 0.f;
+    }
+    __syncthreads();
+    const int nsteps = BWD ? T - 1 : T;
+#pragma unroll 1
+    for (int s = 0; s < nsteps + (BWD && a.dh0 ? 1 : 0); ++s) {
+#pragma unroll 1
+        for (int col = tid; col < H; col += XT) {
+            float acc[RB][4];
+#pragma unroll
+            for (int r = 0; r < RB; ++r)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[r][e] = 0.f;
+#pragma unroll 2
+            for (int k = 0; k < HP; k += 4) {
+                float w[4];
+                if (BWD) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) w[e] = k + e < H ? a.Wh[(size_t)(k + e) * H + col] : 0.f;
+                } else {
+                    const float4 p = piece(a.Wh + (size_t)col * H + k, H - k);
+                    w[0] = p.x; w[1] = p.y; w[2] = p.z; w[3] = p.w;
+                }
+#pragma unroll
+                for (int r = 0; r < RB; ++r) {
+                    const float4 x = *reinterpret_cast<const float4*>(cur + r * HP + k);
+                    acc[r][0] = fmaf(x.x, w[0], acc[r][0]);
+                    acc[r][1] = fmaf(x.y, w[1], acc[r][1]);
+                    acc[r][2] = fmaf(x.z, w[2], acc[r][2]);
+                    acc[r][3] = fmaf(x.w, w[3], acc[r][3]);
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < RB; ++r) {
+                if (r >= nrows) continue;
+                const float sum = (acc[r][0] + acc[r][1]) + (acc[r][2] + acc[r][3]);
+                const size_t off = (size_t)(b0 + r) * H + col;
+                float v;
+                if (s == nsteps) {                       // reverse: the gradient of the initial state
+                    a.dh0[off] = sum;
+                    continue;
+                }
+                if (BWD) {
+                    const size_t i = (size_t)(T - 2 - s) * bh + off;
+                    v = (sum + a.G[i]) * act_grad<ACT>(a.h_all[i + bh]);
+                    a.Delta[i] = v;
+                } else {
+                    const size_t n = (size_t)s * a.B + b0 + r;
+                    const float u = a.x ? a.Wx[(size_t)a.x[n] * H + col] + a.b[col] : a.U[n * H + col];
+                    v = activate<ACT>(sum + u);
+                    a.hist[(size_t)(s + 1) * bh + off] = v;
+                    if (a.h_last && s == nsteps - 1) a.h_last[off] = v;
+                }
+                nxt[r * HP + col] = v;
+            }
+        }
+        __syncthreads();
+        float* t = cur; cur = nxt; nxt = t;
+    }
+}
+
 // KW = k per wavefront (8 KW >= H), CWD = output columns per workgroup
 template <int ACT, bool BWD, int KW, int CWD>
 __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
@@ -123,7 +215,7 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
     constexpr int S = 64 / CWD;            // k per instruction, in as many parts of a wavefront's lanes
     constexpr int N0 = KW < 64 ? KW : 64, N1 = KW - N0;   // k of the two pieces
     extern __shared__ __attribute__((aligned(16))) float smem[];
-    __shared__ int s_abort, s_grp, s_slot;
+    __shared__ int s_abort, s_grp, s_slot, s_part;
     __shared__ int s_stored;                   // steps whose first row this workgroup has stored
     float* part = smem;                    // [2][8 wavefronts][S][CWD][RB] partial tiles, by step parity
 
@@ -141,8 +233,8 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
         s_grp = n < WG_PER_XCD ? xcc + NXCD * (n / a.slots) : NGRP;
         s_slot = n % a.slots;
         s_abort = 0;
+        s_stored = 0;
     }
-    if (tid == 0) s_stored = 0;
     __syncthreads();
     const int grp = s_grp, slot = s_slot;
     const int b0 = grp * RB, c0 = slot * CWD;
@@ -152,6 +244,31 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
     }
     if (b0 >= B || c0 >= H) return;              // nothing to do here, and nobody waits for this workgroup
     const int nrows = min(RB, B - b0);
+
+    // ---- the group's roll: how many of its workgroups have come; ROLL_CLOSED once one of them has stopped waiting for the rest
+    const int whole = (H + CWD - 1) / CWD;
+    int* roll = a.counters + NXCD + grp;
+    long long came = 0;
+    auto settle = [&]() {                        // thread 0: what this workgroup does
+        for (int polls = 1;; ++polls) {
+            int w = __hip_atomic_load(roll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (w == whole) return PART_ONE;
+            if (w & ROLL_CLOSED) return PART_NONE;
+            if (polls >= a.spin_limit || wall_clock64() - came > a.patience) {
+                if (__hip_atomic_compare_exchange_strong(roll, &w, w | ROLL_CLOSED, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT))
+                    return PART_ALL;
+                continue;                        // somebody came, or closed it, at this moment
+            }
+            __builtin_amdgcn_s_sleep(8);
+        }
+    };
+    if (tid == 0) {
+        came = wall_clock64();
+        const int before = atomicAdd(roll, 1);
+        // (a bound of one poll is used up on arrival: the first to come does everything)
+        s_part = a.spin_limit <= 1 ? before == 0 ? PART_ALL : PART_NONE : before & ROLL_CLOSED ? PART_NONE : PART_OPEN;
+    }
 
     // ---- resident weights: wreg[64 / S * q + j] = M[k][c0 + lane % CWD], k = kb + 64 q + nq / S * (lane / CWD) + j with nq
     //      the k of piece q; M = Wh^T (forward) or Wh (reverse); zero outside the matrix ----------------
@@ -182,7 +299,6 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
             for (int j = 0; j < nq / S; ++j) wreg[64 / S * q + j] = stg[(nq / S * part_k + j) * CWD + part_c];
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
-        __syncthreads();                                             // the partial tiles reuse this memory
     } else {
         // M[k][col] = Wh[col][k]: a lane's values lie along a row of Wh.  Fetched as 16-byte pieces
         // along the rows (a request covers four rows of 256 bytes) and turned through a
@@ -210,7 +326,15 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
             for (int j = 0; j < nq / S; ++j) wreg[64 / S * q + j] = stg[part_c * PITCH + nq / S * part_k + j];
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
-        __syncthreads();                                             // the partial tiles reuse this memory
+    }
+
+    // by now the others have come, or something else holds their compute units
+    if (tid == 0 && s_part == PART_OPEN) s_part = settle();
+    __syncthreads();
+    const int mine = s_part;
+    if (mine != PART_ONE) {
+        if (mine == PART_ALL) run_alone<ACT, BWD>(a, b0, nrows, smem);
+        return;
     }
 
     // ---- the state pieces of this lane: row ri, four columns from p_k on; pieces outside the matrix (rows past
@@ -420,12 +544,12 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
     }
 }
 
-// the exchange ring starts as sentinels (n4 pieces of 16 bytes), the slice counters at zero
+// the exchange ring starts as sentinels (n4 pieces of 16 bytes), the slice counters and the rolls at zero
 __global__ __launch_bounds__(256) void xcd_clear_kernel(float* __restrict__ ring, int n4, int32_t* __restrict__ counters) {
     const float s = __uint_as_float(kSentinel);
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < n4) reinterpret_cast<float4*>(ring)[i] = make_float4(s, s, s, s);
-    if (i < NXCD) counters[i] = 0;
+    if (i < NXCD + NGRP) counters[i] = 0;
 }
 
 // k per wavefront: an eighth of H in whole blocks of 16
@@ -458,10 +582,10 @@ size_t xcd_lds_bytes() { return (size_t)8 * 64 * 65 * 4; }
 
 }  // namespace
 
-// Shapes the one-launch loop serves and is the faster choice for.  The launch has a fixed cost (a
-// cooperative launch, every workgroup loading its 256 KB of the matrix: about 28 us) and then takes
-// 1.8 us per step at H = 1024, against 5.5 us per step for a launch per step, so the shortest sequences
-// stay with the latter (cross-over at H = 1024, batch 64: 8 to 10 steps).
+// Shapes the one-launch loop serves and is the faster choice for.  The launch has a fixed cost (the ring's clearing and
+// every workgroup loading its part of the matrix: 10 us at H = 300, 18 at H = 1024, batch 64; 10 us more when it was
+// cooperative) and then takes 0.8 to 1.8 us per step, against 5.5 us per step at H = 1024 for a launch per step, so the shortest
+// sequences stay with the latter (cross-over at H = 1024, batch 64, with the cooperative launch: 8 to 10 steps).
 // Batch 1 to 4 has the loops that give every sequence its own workgroups.  Forward, loss and backward of
 // 100 steps with 1000 words, those against this one: H = 500, batch 1: 412 / 366 us, batch 4: 492 / 411;
 // H = 600, batch 2: 476 / 448; H = 700, batch 1: 456 / 450; but H = 1000, batch 1: 475 / 509 and H = 1024,
@@ -521,8 +645,12 @@ hipError_t launch_rec_xcd(const RecXcdArgs& a, bool bwd, hipStream_t s) {
     RecXcdArgs args = a;
     if (args.spin_limit <= 0) args.spin_limit = wait_limit();
     args.slots = xcd_slots(a.B);
+    // As long as one workgroup would take by itself: waiting costs at most as much again.  (100 steps at H = 300, 500, 700 and 1024:
+    // 1.5, 2.3, 6.5 and 13.2 ms)
+    const double alone_us = a.T * (5.0 + 125.0 * a.H / H_MAX * a.H / H_MAX);
+    args.patience = (int)(100.0 * fmin(fmax(alone_us, 200.0), 2e6));
     void* kargs[] = {&args};
-    return hipLaunchCooperativeKernel(fn, dim3(NXCD * WG_PER_XCD), dim3(XT), kargs, (unsigned)lds, s);
+    return launch_gang(fn, dim3(NXCD * WG_PER_XCD), dim3(XT), kargs, lds, s);
 }
 
 }  // namespace rnn
