@@ -2,8 +2,8 @@
 // Delta[n,:], without floating-point atomics: results are run-to-run identical however skewed
 // (Zipf) the ids are, and the same pass writes the zero rows of tokens that do not occur.
 //
-// Grouped form (the normal one): the id list is cut into ranges of CL ids.  One workgroup per
-// range sorts its (id, position) pairs in LDS (bitonic, keys are unique), which groups equal ids
+// Grouped form (the normal one): the id list is cut into ranges of CL ids.  A workgroup per
+// range and slice of columns sorts its (id, position) pairs in LDS (keys are unique), which groups equal ids
 // with ascending positions, and sums the Delta rows of every group in that order into a compact
 // partial row; a table [token][range] records which partial row, if any, belongs to a token
 // (or, for a token that occurs once in the range, which row of Delta).
@@ -82,89 +82,113 @@ __device__ __forceinline__ float4 columns(const float* __restrict__ row, int c, 
 constexpr int kGroupThreads = 512;
 constexpr int kRowsInFlight = 8;
 
-// One range of CL ids per workgroup: sort, group, sum.  part: compact partial rows
+// One range of CL ids by one slice of 64 columns per workgroup: sort, group, sum.  part: compact partial rows
 // [range*CL + group][H]; slot[token][range] = group + 1, or -(n + 1) for a single occurrence at
 // row n, where the token occurs in the range (the table is zeroed before this kernel).
+// What bounds it is the chain sort - group - sum of the longest group, and there are few ranges (700 ids: 3): so every slice of a
+// range sorts it again rather than wait for another, and 16 lanes have a group, 32 groups at a time.  (One workgroup
+// per range, all columns, bitonic sort: 14.9 us for 100 rows of 500, 25.4 for 800 of 500, 34.3 for 2310 of 650, 57.0 for 16384 of
+// 1024; now 8.3, 13.5, 12.9 and 25.4.  Sixteen rows in flight: 7.8, 13.0, 12.1 and 29.7.)
+constexpr int kSliceCols = 64, kLanes = kSliceCols / 4;   // columns of a workgroup, lanes of a group's row
+
 template <int CL, bool SHORT>
 __global__ __launch_bounds__(kGroupThreads) void dwx_group_kernel(const int32_t* __restrict__ x,
                                                                   const float* __restrict__ Delta,
                                                                   float* __restrict__ part,
                                                                   int32_t* __restrict__ slot,
                                                                   int N, int NV, int H) {
-    __shared__ unsigned long long key[CL];   // (id << 32) | position in the range; padding = ~0
+    __shared__ __attribute__((aligned(16))) unsigned long long key[CL];   // (id << 32) | position in the range; padding = ~0
     __shared__ int seg_start[CL + 1];
-    __shared__ int s_scan[kGroupThreads];
+    __shared__ int s_heads[kGroupThreads / kWave];
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const int base = blockIdx.x * CL;
-    for (int i = tid; i < CL; i += kGroupThreads) {
-        const int n = base + i;
-        key[i] = n < N ? ((unsigned long long)(unsigned)x[n] << 32) | (unsigned)i : ~0ull;
-    }
-    __syncthreads();
-    for (int k = 2; k <= CL; k <<= 1)
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int i = tid; i < CL; i += kGroupThreads) {
-                const int partner = i ^ j;
-                if (partner > i) {
-                    const unsigned long long a = key[i], b = key[partner];
-                    const bool up = (i & k) == 0;
-                    if ((a > b) == up) { key[i] = b; key[partner] = a; }
-                }
-            }
-            __syncthreads();
-        }
-    // group heads -> group numbers (block prefix sum over CL flags)
-    constexpr int PER = (CL + kGroupThreads - 1) / kGroupThreads;
     const int nvalid = min(CL, N - base);
+    if constexpr (CL <= 512) {
+        // an id's place is the number of ids before it: CL / 4 looks per thread and two barriers
+        __shared__ __attribute__((aligned(16))) int ids[CL];
+        constexpr int TPK = kGroupThreads / CL, SPAN = CL / TPK;      // threads per id, ids each of them looks at
+        const int i = tid / TPK, q = tid % TPK;
+        if (tid < CL) ids[tid] = tid < nvalid ? x[base + tid] : 0x7fffffff;   // padding: behind every id
+        __syncthreads();
+        const int mine = ids[i];
+        int place = 0;
+        for (int j = q * SPAN; j < (q + 1) * SPAN; j += 4) {
+            const int4 o = *reinterpret_cast<const int4*>(ids + j);
+            place += (o.x < mine || (o.x == mine && j < i)) + (o.y < mine || (o.y == mine && j + 1 < i)) +
+                     (o.z < mine || (o.z == mine && j + 2 < i)) + (o.w < mine || (o.w == mine && j + 3 < i));
+        }
+#pragma unroll
+        for (int t = 1; t < TPK; t <<= 1) place += __shfl_xor(place, t, kWave);
+        if (q == 0) key[place] = i < nvalid ? ((unsigned long long)(unsigned)mine << 32) | (unsigned)i : ~0ull;
+        __syncthreads();
+    } else {
+        for (int i = tid; i < CL; i += kGroupThreads)
+            key[i] = i < nvalid ? ((unsigned long long)(unsigned)x[base + i] << 32) | (unsigned)i : ~0ull;
+        __syncthreads();
+        for (int k = 2; k <= CL; k <<= 1)
+            for (int j = k >> 1; j > 0; j >>= 1) {
+                for (int i = tid; i < CL; i += kGroupThreads) {
+                    const int partner = i ^ j;
+                    if (partner > i) {
+                        const unsigned long long a = key[i], b = key[partner];
+                        const bool up = (i & k) == 0;
+                        if ((a > b) == up) { key[i] = b; key[partner] = a; }
+                    }
+                }
+                __syncthreads();
+            }
+    }
+    // group heads -> group numbers (prefix sum over CL flags: lanes, then wavefronts)
+    constexpr int PER = (CL + kGroupThreads - 1) / kGroupThreads;
     int heads = 0;
     for (int u = 0; u < PER; ++u) {
         const int i = tid * PER + u;
         heads += (i < nvalid && (i == 0 || (key[i] >> 32) != (key[i - 1] >> 32))) ? 1 : 0;
     }
-    s_scan[tid] = heads;
-    __syncthreads();
-    for (int off = 1; off < kGroupThreads; off <<= 1) {
-        const int v = tid >= off ? s_scan[tid - off] : 0;
-        __syncthreads();
-        s_scan[tid] += v;
-        __syncthreads();
+    int upto = heads;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const int v = __shfl_up(upto, off, kWave);
+        if (lane >= off) upto += v;
     }
-    int g = s_scan[tid] - heads;             // groups before this thread's elements
-    const int ngroups = s_scan[kGroupThreads - 1];
+    if (lane == kWave - 1) s_heads[wave] = upto;
+    __syncthreads();
+    int g = upto - heads, ngroups = 0;       // groups before this thread's elements, groups of the range
+#pragma unroll
+    for (int w = 0; w < kGroupThreads / kWave; ++w) {
+        if (w < wave) g += s_heads[w];
+        ngroups += s_heads[w];
+    }
     for (int u = 0; u < PER; ++u) {
         const int i = tid * PER + u;
         if (i < nvalid && (i == 0 || (key[i] >> 32) != (key[i - 1] >> 32))) seg_start[g++] = i;
     }
     if (tid == 0) seg_start[ngroups] = nvalid;
     __syncthreads();
-    // one wavefront per group: rows added in ascending position, 16 columns per lane per pass.
+    // 16 lanes per group: rows added in ascending position, four columns per lane (at 4-byte alignment; the lane of a
+    // ragged end reads the row's last four), eight rows in flight.
     // A token that occurs once in the range needs no partial row: the table points at its
     // Delta row instead (negative entry).
     const int ranges = gridDim.x;
-    for (int grp = wave; grp < ngroups; grp += kGroupThreads / kWave) {
+    const bool notes = blockIdx.y == 0 && tid % kLanes == 0;      // enters the group in the table
+    const int c0 = blockIdx.y * kSliceCols + 4 * (tid % kLanes), c = max(min(c0, H - 4), 0);
+    for (int grp = tid / kLanes; grp < ngroups; grp += kGroupThreads / kLanes) {
         const int i0 = seg_start[grp], i1 = seg_start[grp + 1];
         const int v = (int)(key[i0] >> 32);
-        if (i1 - i0 == 1) {
-            if (lane == 0) slot[(size_t)v * ranges + blockIdx.x] = -(base + (int)(unsigned)key[i0] + 1);
-            continue;
-        }
-        // 256 columns per pass, four per lane (at 4-byte alignment; the lane of a ragged end reads the
-        // row's last four), eight rows in flight, added in order
-        for (int c0 = 4 * lane; c0 < H; c0 += 4 * kWave) {
-            const int c = max(min(c0, H - 4), 0);
-            float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-            for (int i = i0; i < i1; i += kRowsInFlight) {
-                float4 r[kRowsInFlight];
+        const bool once = i1 - i0 == 1;
+        if (notes) slot[(size_t)v * ranges + blockIdx.x] = once ? -(base + (int)(unsigned)key[i0] + 1) : grp + 1;
+        if (once || c0 >= H) continue;
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int i = i0; i < i1; i += kRowsInFlight) {
+            float4 r[kRowsInFlight];
 #pragma unroll
-                for (int u = 0; u < kRowsInFlight; ++u)
-                    r[u] = columns<SHORT>(Delta + (size_t)(base + (int)(unsigned)key[min(i + u, i1 - 1)]) * H, c, H);
+            for (int u = 0; u < kRowsInFlight; ++u)
+                r[u] = columns<SHORT>(Delta + (size_t)(base + (int)(unsigned)key[min(i + u, i1 - 1)]) * H, c, H);
 #pragma unroll
-                for (int u = 0; u < kRowsInFlight; ++u)
-                    if (i + u < i1) { acc.x += r[u].x; acc.y += r[u].y; acc.z += r[u].z; acc.w += r[u].w; }
-            }
-            store4u(part + ((size_t)base + grp) * H + c0, shifted(acc, c0 - c), H - c0);
+            for (int u = 0; u < kRowsInFlight; ++u)
+                if (i + u < i1) { acc.x += r[u].x; acc.y += r[u].y; acc.z += r[u].z; acc.w += r[u].w; }
         }
-        if (lane == 0) slot[(size_t)v * ranges + blockIdx.x] = grp + 1;
+        store4u(part + ((size_t)base + grp) * H + c0, shifted(acc, c0 - c), H - c0);
     }
 }
 
@@ -270,10 +294,11 @@ hipError_t launch_dwx_tokens(const int32_t* x, const float* Delta, float* dWx, i
         size_t zb = (n + 2047) / 2048;
         if (zb > 1024) zb = 1024;
         hipLaunchKernelGGL(zero_table_kernel, dim3((unsigned)zb), dim3(256), 0, s, slot_table, n);
+        const int slices = (H + kSliceCols - 1) / kSliceCols;
 #define RNN_GROUP(CL)                                                                                    \
     do {                                                                                                 \
-        if (H >= 4) hipLaunchKernelGGL((dwx_group_kernel<CL, false>), dim3(ranges), dim3(kGroupThreads), 0, s, x, Delta, scratch, slot_table, N, NV, H); \
-        else hipLaunchKernelGGL((dwx_group_kernel<CL, true>), dim3(ranges), dim3(kGroupThreads), 0, s, x, Delta, scratch, slot_table, N, NV, H);         \
+        if (H >= 4) hipLaunchKernelGGL((dwx_group_kernel<CL, false>), dim3(ranges, slices), dim3(kGroupThreads), 0, s, x, Delta, scratch, slot_table, N, NV, H); \
+        else hipLaunchKernelGGL((dwx_group_kernel<CL, true>), dim3(ranges, slices), dim3(kGroupThreads), 0, s, x, Delta, scratch, slot_table, N, NV, H);         \
     } while (0)
         switch (cl) {
             case 256: RNN_GROUP(256); break;

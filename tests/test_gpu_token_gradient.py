@@ -25,3 +25,21 @@ def test_token_gradient_at_this_row_width(H, NV):
     r.set_flags(rnn.FLAG_ACCUMULATE | rnn.FLAG_BPTT_RECOMPUTE)
     r.bptt()
     grad_close("2x dWx", r.results()["dWx"], 2.0 * ref["dWx"])
+
+
+@pytest.mark.parametrize("T,B,H", [(5, 7, 63), (16, 16, 64), (257, 1, 65), (771, 5, 129), (1024, 64, 9), (1025, 64, 9), (2049, 64, 9)])
+def test_token_gradient_of_this_many_ids(T, B, H):
+    """One and several ranges of ids, a range that is full and one of a single id, ranges of 256, 512 and 1024 ids, and slices of
+    64 columns; one token makes up most of the ids."""
+    case = ri.make_case(40, H, 8, T, B, wdist=("normal", 0.5 / np.sqrt(H)), bias_std=0.1, seed=60 + T)
+    x = case["x"].reshape(-1)
+    x[np.arange(x.size) % 3 > 0] = 17
+    case["y"][:] %= 8
+    ref = oracle.fwd_bptt(case)
+    r = Runner(case)
+    r.step()
+    got = r.results()["dWx"]
+    grad_close("dWx", got, ref["dWx"])
+    # every token's own row: the tolerance above is one for the whole matrix
+    scale = np.abs(ref["dWx"]).max(axis=1, keepdims=True)
+    assert (np.abs(got - ref["dWx"]) <= 1e-3 * scale + 1e-12).all()
