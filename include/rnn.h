@@ -375,8 +375,9 @@ const char *rnn_strerror(int code);
  * "grid_resident" (several cooperating workgroups per sequence), "batch_mfma" (hidden <= 256,
  * batch > 4, or batch 1 to 4 with hidden > 128 and at least 10 steps: one persistent matrix-core workgroup per 4 batch rows, weights in registers),
  * "xcd_mfma" (256 < hidden <= 1024, batch <= 64, at least 10 steps - batch 1 to 4: at least 16,
- * batch 1 and 2: hidden <= 640, and with the full history - on
- * a device of 8 x 32 compute units: one persistent launch, 16 groups of 4 batch rows, two groups
+ * batch 1 and 2: hidden <= 640 -, or 192 < hidden <= 256, batch <= 128, at least 64 steps - 33 of tokens with
+ * batch > 4 -, and with the full history, on
+ * a device of 8 x 32 compute units: one persistent launch, groups of 4 batch rows, one to four
  * per XCD),
  * "step_mfma" (other batched sizes: one fused matrix-core launch per step) or "reference". */
 const char *rnn_recurrence_variant(const rnn_dims *dims);

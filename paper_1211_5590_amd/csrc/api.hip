@@ -97,7 +97,7 @@ Variant pick_variant(const rnn_dims* d) {
     if (!v.resident) {
         v.batch_mfma = rec_batch_mfma_supported(s.H, s.B);
         v.stepwise = !v.batch_mfma && s.B > 4;
-        v.xcd = v.stepwise && rec_xcd_supported(s.H, s.B, s.T);
+        v.xcd = (v.stepwise || v.batch_mfma) && rec_xcd_supported(s.H, s.B, s.T, s.tokens);
         return v;
     }
     v.grid = (v.fwd.P > 1 || v.bwd.P > 1) && rec_grid_plan(s.H, s.B, &v.gplan);
@@ -113,7 +113,7 @@ Variant pick_variant(const rnn_dims* d) {
     // batch 1: 415 / 197 us, H = 200: 387 / 284, H = 256: 401 / 297, batch 4: 423 / 321; of 12 steps, H = 256,
     // batch 2: 154 / 108.  Of fewer than 10 steps the launches are most of it, and here it takes one more.
     v.batch_mfma = s.T >= 10 && s.H > 128 && rec_batch_mfma_supported(s.H, s.B);
-    v.xcd = (v.fwd.P > 1 || v.bwd.P > 1) && !v.skinny && rec_xcd_supported(s.H, s.B, s.T);
+    v.xcd = (v.fwd.P > 1 || v.bwd.P > 1) && !v.skinny && rec_xcd_supported(s.H, s.B, s.T, s.tokens);
     return v;
 }
 
@@ -143,7 +143,7 @@ Plan make_plan(const rnn_dims* d) {
     p.splitk = take(max_splitk_floats(s) * 4);
     p.scratch = take(256);
     // state-exchange boxes of the multi-workgroup loops
-    const size_t ring = rec_xcd_supported(s.H, s.B, s.T) ? rec_xcd_ring_bytes(s.H, s.B) : 0;
+    const size_t ring = rec_xcd_supported(s.H, s.B, s.T, s.tokens) ? rec_xcd_ring_bytes(s.H, s.B) : 0;
     p.flags = take(4096 + (ring > 16 * B * H ? ring : 16 * B * H));
     const size_t strips = (size_t)skinny_strips(s.O);
     const bool small = N <= 32;
@@ -709,7 +709,7 @@ int rnn_recurrence_workgroups(const rnn_dims* dims) {
     if (!dims_valid(dims)) return RNN_EINVAL;
     const Variant v = pick_variant(dims);
     const Sizes s = sizes_of(dims);
-    if (v.xcd) return ((s.B + 3) / 4) * ((s.H + 63) / 64);
+    if (v.xcd) return rec_xcd_workgroups(s.H, s.B);
     if (v.batch_mfma) return (s.B + 3) / 4;
     if (v.stepwise) return ((s.H + 15) / 16) * ((s.B + 15) / 16);   // tiles of one step launch
     if (!v.resident) return s.B;

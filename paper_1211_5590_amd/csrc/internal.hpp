@@ -122,7 +122,7 @@ hipError_t launch_gather_input(const int32_t* x, const float* Wx, const float* b
                                int H, hipStream_t s);
 hipError_t launch_rec_batch_mfma(const RecMfmaArgs& a, bool bwd, hipStream_t s);
 
-// Persistent batched loop for 256 < H <= 1024 (recurrence_xcd.hip): one batch group per XCD, the state
+// Persistent batched loop for 192 < H <= 1024 (recurrence_xcd.hip): one to four batch groups per XCD, the state
 // handed over through that XCD's L2.  Needs the full history.
 struct RecXcdArgs {
     const float* Wh;
@@ -136,13 +136,14 @@ struct RecXcdArgs {
     float* h_last;        // nullable
     // reverse
     const float* G; const float* h_all; const float* dh_last; float* Delta; float* dh0;
-    int32_t* counters;    // 24 words of workspace (cleared by the launcher)
+    int32_t* counters;    // 40 words of workspace (cleared by the launcher)
     float* ring;          // rec_xcd_ring_bytes of workspace, 16-byte aligned (filled by the launcher)
     int32_t* status;      // device status word: set to 1 when a bounded wait expires
     int spin_limit;       // <= 0: default
     int slots, patience;  // workgroups of a group; 10 ns they wait for each other to come (filled in by the launcher)
 };
-bool rec_xcd_supported(int H, int B, int T);                       // shape only (host)
+bool rec_xcd_supported(int H, int B, int T, bool tokens);          // shape only (host)
+int rec_xcd_workgroups(int H, int B);
 size_t rec_xcd_ring_bytes(int H, int B);
 bool rec_xcd_ready(int H, int B, int act, bool bwd);             // and the current device can hold the grid at once
 hipError_t launch_rec_xcd(const RecXcdArgs& a, bool bwd, hipStream_t s);

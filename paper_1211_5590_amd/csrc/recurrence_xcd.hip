@@ -1,12 +1,12 @@
-// Persistent batched time loop for hidden sizes whose matrix needs many compute units (256 < hidden <= 1024,
-// batch up to 64): ONE launch for all steps instead of one launch per step.
+// Persistent batched time loop for hidden sizes whose matrix needs many compute units (256 < hidden <= 1024, batch up to 64), or
+// that take longer on one (193 to 256 units, batch up to 128, sequences that are not short): ONE launch for all steps instead of one launch per step.
 //
 // The paper's Scan keeps the loop inside one graph node so that nothing per step happens outside
 // compiled code (properties 4 and 5) and keeps every state (property 1); the per-step kernel
 // boundary of recurrence_step.hip costs more than the step's arithmetic.  Here the chip's layout
-// does the work instead: batch rows are independent, so the batch is cut into up to 16 groups of up to 4
-// rows, groups x and x + 8 on XCD x, and the 32 compute units of an XCD share its one group's recurrence, or
-// 16 each of its two groups' (batch above 32).  Every workgroup holds 16, 32 or 64 output columns of the matrix (all K) in
+// does the work instead: batch rows are independent, so the batch is cut into up to 32 groups of up to 4
+// rows, groups x, x + 8, x + 16 and x + 24 on XCD x, and the 32 compute units of an XCD share its one group's recurrence, or
+// have 16, 10 or 8 for each of its two, three or four groups' (batch above 32, 64 and 96).  Every workgroup holds 16, 32 or 64 output columns of the matrix (all K) in
 // registers for the whole launch, as few as cover H, and produces, per step, its tile of the new state on the
 // matrix cores; the eight wavefronts split K and meet in LDS.  Groups never talk to each other.
 //
@@ -18,7 +18,7 @@
 // The parts are added up after the wavefronts' tiles have met.  The
 // 16-byte piece of the state a lane fetches from memory (row l % 4, four consecutive k) is exactly
 // what it feeds the instruction, so the state goes from the cache into the operand registers
-// without passing LDS.  A wavefront's share of K is an eighth of H in whole blocks of 16 (48 to 128),
+// without passing LDS.  A wavefront's share of K is an eighth of H in whole blocks of 16 (32 to 128),
 // and the instructions of blocks past it are left out.
 //
 // Inside a group the new state travels through the L2 cache its compute units share, with no flags,
@@ -37,6 +37,10 @@
 //     that: state s is complete) and waits for that store with its next look at the ring, that is before
 //     it publishes state s + 2.  The slot is published again as state s + 3, which nobody looks for
 //     without having seen all of state s + 2: no look can find the words of the state before.
+// With 16 columns a ninth wavefront, the carrier, fetches the operands of the epilogues and stores the new states' rows: a look waits
+// for every request of its wavefront, so the wavefronts of the product make none but to the ring (500 units, batch 1: 0.91 ->
+// 0.83 us a step, 256 units, batch 32: 0.83 -> 0.73).  With 32 columns that costs the reverse loop more than it gains (1.16 -> 1.22 at
+// 513 units, 1.47 -> 1.65 at 1024), with 64 the registers do not suffice.
 // Token input takes its rows of Wx in the loop, a step ahead, instead of a gather launch that writes them
 // out for all steps and is read back (256 steps of 64 rows at H = 1024: 27 us).
 // A hidden size that is no multiple of 4 has the rest of a row's last piece published as zeros.
@@ -71,11 +75,15 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int XT = 512;            // threads: 8 wavefronts
+constexpr int NW = 8;              // wavefronts of the product
+constexpr int AHEAD = 4;           // steps the carrier requests in advance
+// 16 columns: a ninth wavefront fetches the operands and stores the rows
+__host__ __device__ constexpr bool has_carrier(int cwd) { return cwd == 16; }
+__host__ __device__ constexpr int threads_of(int cwd) { return 64 * (NW + (has_carrier(cwd) ? 1 : 0)); }
 constexpr int RB = 4;              // batch rows per group
 constexpr int NXCD = 8;            // XCDs: the layout this loop is built on
 constexpr int WG_PER_XCD = 32;     // compute units per XCD = workgroups per XCD
-constexpr int NGRP = 16;           // groups at most: x and x + 8 on XCD x
+constexpr int NGRP = 32;           // groups at most: x, x + 8, x + 16 and x + 24 on XCD x
 constexpr int H_MAX = 1024;
 constexpr int RSLOTS = 4;          // states the exchange ring holds
 constexpr unsigned kSentinel = 0xFFFFFFFFu;
@@ -126,7 +134,7 @@ __host__ __device__ inline int ring_state(int B, int kw) { return (B + RB - 1) /
 
 // The whole recurrence of one group on one workgroup, the matrix read from the caches every step: for a group of which not all
 // workgroups came.  sm: 2 RB ceil4(H) floats.
-template <int ACT, bool BWD>
+template <int ACT, bool BWD, int XT>
 __device__ __forceinline__ void run_alone(const RecXcdArgs& a, int b0, int nrows, float* sm) {
     const int H = a.H, T = a.T, HP = (H + 3) / 4 * 4, tid = threadIdx.x;
     const size_t bh = (size_t)a.B * H;
@@ -210,17 +218,20 @@ __device__ __forceinline__ void run_alone(const RecXcdArgs& a, int b0, int nrows
 
 // KW = k per wavefront (8 KW >= H), CWD = output columns per workgroup
 template <int ACT, bool BWD, int KW, int CWD>
-__global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
+__global__ __launch_bounds__(threads_of(CWD)) void rec_xcd_kernel(RecXcdArgs a) {
+    constexpr bool CARRY = has_carrier(CWD);
     constexpr int NQ = (KW + 63) / 64;     // 16-byte state pieces per lane and step
     constexpr int S = 64 / CWD;            // k per instruction, in as many parts of a wavefront's lanes
     constexpr int N0 = KW < 64 ? KW : 64, N1 = KW - N0;   // k of the two pieces
     extern __shared__ __attribute__((aligned(16))) float smem[];
     __shared__ int s_abort, s_grp, s_slot, s_part;
     __shared__ int s_stored;                   // steps whose first row this workgroup has stored
-    float* part = smem;                    // [2][8 wavefronts][S][CWD][RB] partial tiles, by step parity
+    // what the carrier hands to the epilogues and takes from them, by step parity: input term or G, slope, new state
+    __shared__ float s_in[2][CARRY ? RB * CWD : 1], s_slope[2][CARRY && BWD ? RB * CWD : 1], s_out[2][CARRY ? RB * CWD : 1];
+    float* part = smem;                    // [2][NW][S][CWD][RB] partial tiles, by step parity
 
     const int H = a.H, B = a.B, T = a.T;
-    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    const int tid = threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int ri = lane % 4;
     const size_t bh = (size_t)B * H;
 
@@ -272,6 +283,99 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
 
     // ---- resident weights: wreg[64 / S * q + j] = M[k][c0 + lane % CWD], k = kb + 64 q + nq / S * (lane / CWD) + j with nq
     //      the k of piece q; M = Wh^T (forward) or Wh (reverse); zero outside the matrix ----------------
+    const int nsteps = BWD ? T - 1 : T;
+
+    // ---- the carrier (wavefront NW) ---------------------------------------------------------------
+    // It fetches the operands of the epilogues AHEAD steps early and stores the new states' rows.  A look at the ring waits for every
+    // request of its wavefront, also for an operand of the next step that comes from memory and for a stored row: the
+    // wavefronts of the product make no request but the look and the stores to the ring.
+    // In the interval before barrier s it puts the operands of step s in place, whose epilogue follows that barrier, and stores the
+    // state of step s - 2, whose epilogue was before the barrier before.
+    if constexpr (CARRY) if (wave == NW) {
+        constexpr int NL = RB * CWD / kWave;
+        size_t off[NL];
+        int place[NL], cc[NL], cb[NL];
+        bool on[NL];
+        float bias[NL], x0[AHEAD][NL], x1[AHEAD][NL];
+        int id[AHEAD][NL];
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const int e = lane + kWave * i, row = e / CWD, col = e % CWD;
+            cb[i] = min(b0 + row, B - 1);
+            cc[i] = min(c0 + col, H - 1);
+            off[i] = (size_t)cb[i] * H + cc[i];
+            place[i] = 16 * (col / 4) + 4 * row + col % 4;
+            on[i] = row < nrows && c0 + col < H;
+            bias[i] = !BWD && a.x ? a.b[cc[i]] : 0.f;
+        }
+        auto carry = [&](auto tokens_c) __attribute__((always_inline)) {
+            constexpr bool TOK = decltype(tokens_c)::value;
+            // (requests past the last step repeat it)
+            auto want_id = [&](int s, int (&v)[NL]) __attribute__((always_inline)) {
+#pragma unroll
+                for (int i = 0; i < NL; ++i)
+                    if (TOK) v[i] = a.x[(size_t)min(s, nsteps - 1) * B + cb[i]];
+            };
+            auto want = [&](int s, const int (&v)[NL], float (&p)[NL], float (&q)[NL]) __attribute__((always_inline)) {
+                const int sc = min(s, nsteps - 1);
+                const size_t base = (size_t)(BWD ? T - 2 - sc : sc) * bh;
+#pragma unroll
+                for (int i = 0; i < NL; ++i) {
+                    p[i] = TOK ? a.Wx[(size_t)v[i] * H + cc[i]] : BWD ? a.G[base + off[i]] : a.U[base + off[i]];
+                    if (BWD) q[i] = a.h_all[base + bh + off[i]];
+                }
+            };
+            auto keep = [&](int s) __attribute__((always_inline)) {
+                float* dst = BWD ? a.Delta + (ptrdiff_t)(T - 2 - s) * (ptrdiff_t)bh : a.hist + (ptrdiff_t)(s + 1) * (ptrdiff_t)bh;
+#pragma unroll
+                for (int i = 0; i < NL; ++i) {
+                    const float v = s_out[s & 1][place[i]];
+                    if (on[i] && s >= 0) dst[off[i]] = v;
+                }
+            };
+            // one interval; the step's parity and its slot of the requests are those of u
+            auto interval = [&](int u, int s) __attribute__((always_inline)) {
+#pragma unroll
+                for (int i = 0; i < NL; ++i) {
+                    s_in[u & 1][place[i]] = TOK ? x0[u][i] + bias[i] : x0[u][i];
+                    if (BWD) s_slope[u & 1][place[i]] = act_grad<ACT>(x1[u][i]);
+                }
+                want(s + AHEAD, id[u], x0[u], x1[u]);
+                want_id(s + 2 * AHEAD, id[u]);
+                keep(s - 2);
+                lds_barrier();
+            };
+            if (nsteps > 0) {
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u) want_id(u, id[u]);
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u) want(u, id[u], x0[u], x1[u]);
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u) want_id(AHEAD + u, id[u]);
+            }
+            __syncthreads();                                         // (the matrix is in registers, and the group's roll is settled)
+            if (s_part != PART_ONE) return;
+            // (no branch inside the loop: the compiler then counts the requests in flight and waits for the oldest only)
+            int s0 = 0;
+            for (; s0 + AHEAD <= nsteps && !s_abort; s0 += AHEAD) {
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u) interval(u, s0 + u);
+            }
+#pragma unroll
+            for (int u = 0; u < AHEAD - 1; ++u)
+                if (s0 + u < nsteps && !s_abort) interval(u, s0 + u);
+            keep(nsteps - 2);
+            __syncthreads();
+            if (s_abort) return;
+            keep(nsteps - 1);
+            if (BWD && a.dh0) __syncthreads();
+        };
+        if (!BWD && a.x) carry(std::true_type{});
+        else carry(std::false_type{});
+        if (s_part == PART_ALL) run_alone<ACT, BWD, threads_of(CWD)>(a, b0, nrows, smem);
+        return;
+    }
+
     const int kb = KW * wave;
     const int part_k = lane / CWD, part_c = lane % CWD;   // this lane's part of every piece's k, and its column
     float wreg[KW / S];
@@ -282,10 +386,8 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
         float* stg = smem + wave * 64 * 65;
         constexpr int RP = 256 / CWD;             // rows per request
         const int r4 = lane / (CWD / 4), c4 = 4 * (lane % (CWD / 4));
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            constexpr int NV = 64 / RP;
-            const int nq = q ? N1 : N0;
+        auto stage = [&](auto piece_c) __attribute__((always_inline)) {
+            constexpr int q = decltype(piece_c)::value, nq = q ? N1 : N0, NV = 64 / RP;
             float4 v[NV];
 #pragma unroll
             for (int i = 0; i < NV; ++i) {
@@ -298,7 +400,9 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
 #pragma unroll
             for (int j = 0; j < nq / S; ++j) wreg[64 / S * q + j] = stg[(nq / S * part_k + j) * CWD + part_c];
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        }
+        };
+        stage(std::integral_constant<int, 0>{});
+        if constexpr (NQ > 1) stage(std::integral_constant<int, 1>{});
     } else {
         // M[k][col] = Wh[col][k]: a lane's values lie along a row of Wh.  Fetched as 16-byte pieces
         // along the rows (a request covers four rows of 256 bytes) and turned through a
@@ -306,10 +410,8 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
         constexpr int PITCH = 65;                 // odd: the transposed reads fall into distinct banks
         float* stg = smem + wave * 64 * PITCH;
         const int r4 = lane >> 4, k4 = 4 * (lane & 15);
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            constexpr int NV = CWD / 4;
-            const int nq = q ? N1 : N0;
+        auto stage = [&](auto piece_c) __attribute__((always_inline)) {
+            constexpr int q = decltype(piece_c)::value, nq = q ? N1 : N0, NV = CWD / 4;
             float4 v[NV];
 #pragma unroll
             for (int i = 0; i < NV; ++i) {
@@ -325,7 +427,9 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
 #pragma unroll
             for (int j = 0; j < nq / S; ++j) wreg[64 / S * q + j] = stg[part_c * PITCH + nq / S * part_k + j];
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        }
+        };
+        stage(std::integral_constant<int, 0>{});
+        if constexpr (NQ > 1) stage(std::integral_constant<int, 1>{});
     }
 
     // by now the others have come, or something else holds their compute units
@@ -333,7 +437,7 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
     __syncthreads();
     const int mine = s_part;
     if (mine != PART_ONE) {
-        if (mine == PART_ALL) run_alone<ACT, BWD>(a, b0, nrows, smem);
+        if (mine == PART_ALL) run_alone<ACT, BWD, threads_of(CWD)>(a, b0, nrows, smem);
         return;
     }
 
@@ -376,8 +480,6 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
         st[q] = v;
     }
 
-    const int nsteps = BWD ? T - 1 : T;
-
     // ---- epilogue lanes (wavefronts 0..3): CWD / 4 columns of the tile per wavefront, in the ring's order, so
     //      that a wavefront's share of the new state leaves as one stretch of 4 CWD bytes.  The S parts of an element
     //      are summed by lanes 64 / S apart; the first of them stores the element ------------------------
@@ -397,7 +499,8 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
             a.Delta[e] = (a.G[e] + c) * act_grad<ACT>(a.h_all[(size_t)T * bh + e_off]);
         }
     }
-    // operands of the epilogue of step s, requested a step ahead (clamped: always valid).  Token input takes the
+    const int e_at = 64 / S * (wave & 3) + ej;     // this lane's element in the tiles of the carrier
+    // Without a carrier: operands of the epilogue of step s, requested a step ahead (clamped: always valid).  Token input takes the
     // row of Wx itself; the row's number is requested another step ahead.
     auto step_of = [&](int s) { return max(min(s, nsteps - 1), 0); };
     const float bias = !BWD && a.x && wave < 4 ? a.b[min(ec, H - 1)] : 0.f;
@@ -419,7 +522,7 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
         }
     };
     float n0[2] = {0.f, 0.f}, n1[2] = {0.f, 0.f};
-    if (wave < 4) {
+    if (!CARRY && wave < 4) {
         load_id(0);
         load_epi(0, n0[0], n1[0]);
         load_id(1);
@@ -427,7 +530,7 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
 
     XT_DECL;
     // partial tile of this wavefront's K slice: element i = row i at column c0 + lane % CWD, of this lane's part of K
-    auto product = [&]() {
+    auto product = [&]() __attribute__((always_inline)) {
         f32x4 acc[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[e] = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -435,10 +538,10 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
         if constexpr (NQ > 1) mfma_blocks<S>(st[NQ - 1], wreg + 64 / S, acc, std::make_integer_sequence<int, N1 / S / 4>{});
         return (acc[0] + acc[1]) + (acc[2] + acc[3]);
     };
-    auto park_partial = [&](int par, const f32x4 p4) {
+    auto park_partial = [&](int par, const f32x4 p4) __attribute__((always_inline)) {
         *reinterpret_cast<f32x4*>(part + (par * 8 + wave) * RB * 64 + RB * lane) = p4;
     };
-    auto tile_sum = [&](int par) {            // epilogue lanes: the eight wavefronts' partial sums, then the S parts'
+    auto tile_sum = [&](int par) __attribute__((always_inline)) {            // epilogue lanes: the eight wavefronts' partial sums, then the S parts'
         const float* pp = part + par * 8 * RB * 64 + RB * (CWD * ep + et) + em;
         float v[8];
 #pragma unroll
@@ -449,7 +552,7 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
         return sum;
     };
     // The lane's pieces of the state at `src` in the ring, waiting until no "not written yet" word is left.
-    auto collect = [&](const float* src) {
+    auto collect = [&](const float* src) __attribute__((always_inline)) {
         float4 v[NQ];
         unsigned need = 0;
 #pragma unroll
@@ -478,10 +581,10 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
     // One workgroup barrier per step (the partial tiles are complete); the partial buffers alternate by
     // step parity, and no wavefront can be more than one step ahead of the epilogue of its own
     // workgroup, because every later tile of the group needs that epilogue's output.
-    auto step = [&](int s, auto slot_c, bool fetch_next) {
+    auto step = [&](int s, auto slot_c, bool fetch_next) __attribute__((always_inline)) {
         constexpr int SLOT = decltype(slot_c)::value;   // s & 1: partial buffer and operand slot
         XTM(0);
-        if (wave < 4) {
+        if (!CARRY && wave < 4) {
             load_epi(s + 1, n0[SLOT ^ 1], n1[SLOT ^ 1]);
             load_id(s + 2);
         }
@@ -493,12 +596,18 @@ __global__ __launch_bounds__(XT) void rec_xcd_kernel(RecXcdArgs a) {
         float* dst = BWD ? a.Delta + (size_t)t * bh : a.hist + (size_t)(s + 1) * bh;
         float* box = a.ring + (size_t)((s + 1) % RSLOTS) * rstate;
         if (wave < 4) {
+            const float in = CARRY ? s_in[SLOT][e_at] : BWD ? n0[SLOT] : n0[SLOT] + bias;
+            const float slope = !BWD ? 0.f : CARRY ? s_slope[SLOT][e_at] : act_grad<ACT>(n1[SLOT]);
             const float sum = tile_sum(SLOT);
-            float v = BWD ? (sum + n0[SLOT]) * act_grad<ACT>(n1[SLOT]) : activate<ACT>(sum + (n0[SLOT] + bias));
+            float v = BWD ? (sum + in) * slope : activate<ACT>(sum + in);
             if (__float_as_uint(v) == kSentinel) v = __uint_as_float(0x7FC00000u);   // a NaN that came in as all ones
             if (e_pub) ring_store(box + e_ring, e_on ? v : 0.f);
             if (tid == 0) s_stored = s + 1;
-            if (e_on) dst[e_off] = v;
+            if (CARRY) {
+                if (ep == 0) s_out[SLOT][e_at] = v;
+            } else if (e_on) {
+                dst[e_off] = v;
+            }
             if (e_pub) ring_store(a.ring + (size_t)((s + 3) % RSLOTS) * rstate + e_ring, __uint_as_float(kSentinel));
             last_v = v;
         }
@@ -553,11 +662,11 @@ __global__ __launch_bounds__(256) void xcd_clear_kernel(float* __restrict__ ring
 }
 
 // k per wavefront: an eighth of H in whole blocks of 16
-int xcd_kw(int H) { return H <= 384 ? 48 : (H + 127) / 128 * 16; }
+int xcd_kw(int H) { return H <= 256 ? 32 : (H + 127) / 128 * 16; }
 
-// Workgroups of a group and their columns.  Up to 32 rows are one group per XCD, which then has all 32 compute units, and the
+// Workgroups of a group and their columns.  Up to 32 rows are one group per XCD, which then has all 32 compute units; the
 // fewer columns a workgroup has the fewer matrix instructions a step takes (measured: see the top).
-int xcd_slots(int B) { return B > NXCD * RB ? WG_PER_XCD / 2 : WG_PER_XCD; }
+int xcd_slots(int B) { return WG_PER_XCD / ((B + NXCD * RB - 1) / (NXCD * RB)); }
 int xcd_columns(int H, int B) {
     const int per = (H + xcd_slots(B) - 1) / xcd_slots(B);
     return per <= 16 ? 16 : per <= 32 ? 32 : 64;
@@ -565,16 +674,11 @@ int xcd_columns(int H, int B) {
 
 template <int ACT, bool BWD>
 const void* pick_xcd_kernel(int kw, int cwd) {
-#define RNN_XCD(KW) (cwd == 32 ? (const void*)rec_xcd_kernel<ACT, BWD, KW, 32> : (const void*)rec_xcd_kernel<ACT, BWD, KW, 64>)
-    switch (kw) {
-        case 48: return cwd == 16 ? (const void*)rec_xcd_kernel<ACT, BWD, 48, 16> : RNN_XCD(48);
-        case 64: return cwd == 16 ? (const void*)rec_xcd_kernel<ACT, BWD, 64, 16> : RNN_XCD(64);
-        case 80: return RNN_XCD(80);
-        case 96: return RNN_XCD(96);
-        case 112: return RNN_XCD(112);
-        default: return RNN_XCD(128);
-    }
+#define RNN_XCD(KW, CWD) if (kw == KW && cwd == CWD) return (const void*)rec_xcd_kernel<ACT, BWD, KW, CWD>
+    RNN_XCD(32, 16); RNN_XCD(48, 16); RNN_XCD(64, 16); RNN_XCD(32, 32); RNN_XCD(48, 32); RNN_XCD(64, 32); RNN_XCD(80, 32);
+    RNN_XCD(96, 32); RNN_XCD(112, 32); RNN_XCD(128, 32); RNN_XCD(80, 64); RNN_XCD(96, 64); RNN_XCD(112, 64); RNN_XCD(128, 64);
 #undef RNN_XCD
+    return nullptr;
 }
 
 // partial tiles of a step; the forward kernel first stages its matrix slice there
@@ -592,9 +696,23 @@ size_t xcd_lds_bytes() { return (size_t)8 * 64 * 65 * 4; }
 // batch 2: 496 / 534 (a wavefront's matrix instructions cost the same for 1 row as for 4), while H = 1024,
 // batch 3, which has no room for 16 outputs per workgroup there, is 300 / 199 us per loop.  Of 10 steps
 // (H = 500: 149 / 142) the set-up is most.
-bool rec_xcd_supported(int H, int B, int T) {
-    if (H <= 256 || H > H_MAX || B < 1 || B > NGRP * RB) return false;
+// 193 to 256 units fit one workgroup per 4 rows (recurrence_mfma.hip), whose step is bound by its matrix instructions: 0.97 us
+// at H = 256 and 0.90 at H = 200, here 0.73 to 0.85 (16 columns, batch up to 64: 0.73); up to 192 units 0.63 there, here
+// 0.77 to 0.84.  35 steps of tokens, H = 200, batch 20, with the gathered input term there and the ring's clearing here: 46 and
+// 38 us there, 37 and 36 here; dense input has no rows to gather.  Where the arrays of a long sequence do not fit the chip's last-level
+// cache (256 MB) a step takes longer here, since a look at the ring waits behind its compute unit's requests to memory: H = 256,
+// batch 128, forward + reverse: 800 steps 0.79 + 0.91, 1600 steps 0.89 + 1.01, 3200 steps 0.96 + 1.03; batch 32, 12800 steps 0.86 +
+// 0.97; there 0.97 + 0.98 whatever the size.
+bool rec_xcd_supported(int H, int B, int T, bool tokens) {
+    if (H <= 192 || H > H_MAX || B < 1 || B > (H <= 256 ? 128 : 64)) return false;
+    if (H <= 256) return T >= (tokens && B > 4 ? 33 : 64) && (B <= NXCD * RB || (long long)T * B * H <= 1 << 26);
     return B > 4 ? T >= 10 : T >= 16 && (B > 2 || H <= 640);
+}
+
+// compute units the loop of these sizes keeps busy
+int rec_xcd_workgroups(int H, int B) {
+    const int c = xcd_columns(H, B);
+    return (B + RB - 1) / RB * ((H + c - 1) / c);
 }
 
 size_t rec_xcd_ring_bytes(int H, int B) { return (size_t)RSLOTS * ring_state(B, xcd_kw(H)) * 4; }
@@ -621,7 +739,7 @@ bool rec_xcd_ready(int H, int B, int act, bool bwd) {
         if (seen[i].fn == fn && seen[i].dev == dev) return seen[i].ok;
     int per_cu = 0, cus = 0;
     const bool ok = allow_lds(fn, lds) == hipSuccess &&
-                    hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, XT, lds) == hipSuccess &&
+                    hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads_of(xcd_columns(H, B)), lds) == hipSuccess &&
                     hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
                     per_cu >= 1 && cus == NXCD * WG_PER_XCD;
     if (n_seen < 512) seen[n_seen++] = Seen{fn, dev, ok};
@@ -629,7 +747,7 @@ bool rec_xcd_ready(int H, int B, int act, bool bwd) {
 }
 
 hipError_t launch_rec_xcd(const RecXcdArgs& a, bool bwd, hipStream_t s) {
-    if (!rec_xcd_supported(a.H, a.B, a.T)) return hipErrorInvalidValue;
+    if (a.H > H_MAX || a.B < 1 || a.B > NGRP * RB || (a.H + 63) / 64 > xcd_slots(a.B)) return hipErrorInvalidValue;
     if (!rec_xcd_ready(a.H, a.B, a.act, bwd)) return hipErrorNotSupported;
     const void* fn = bwd ? xcd_kernel_for<true>(a.H, a.B, a.act) : xcd_kernel_for<false>(a.H, a.B, a.act);
     const size_t lds = xcd_lds_bytes();
@@ -650,7 +768,7 @@ hipError_t launch_rec_xcd(const RecXcdArgs& a, bool bwd, hipStream_t s) {
     const double alone_us = a.T * (5.0 + 125.0 * a.H / H_MAX * a.H / H_MAX);
     args.patience = (int)(100.0 * fmin(fmax(alone_us, 200.0), 2e6));
     void* kargs[] = {&args};
-    return launch_gang(fn, dim3(NXCD * WG_PER_XCD), dim3(XT), kargs, lds, s);
+    return launch_gang(fn, dim3(NXCD * WG_PER_XCD), dim3(threads_of(xcd_columns(a.H, a.B))), kargs, lds, s);
 }
 
 }  // namespace rnn

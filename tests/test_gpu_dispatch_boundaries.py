@@ -162,3 +162,24 @@ def test_the_one_launch_wide_loop_where_the_columns_of_a_workgroup_change(H, B):
     r.step()
     assert rnn.rnn_workspace_status(r.dims, r.ws) == 0
     compare(r.results(), oracle.fwd_bptt(case, h0=case.get("h0"), dh_last=case.get("dh_last")))
+
+
+@pytest.mark.parametrize("H", (192, 193, 200, 255, 256))
+def test_the_one_launch_wide_loop_below_257_units(H):
+    """Both sides of the rule that sends 193 to 256 units there, one to four groups per die, tokens and dense input, and the
+    forward pass without the history, which that loop does not serve."""
+    for n, (B, T, kind, want) in enumerate(((5, 33, 0, True), (33, 32, 0, False), (65, 64, 1, True), (97, 33, 0, True), (128, 63, 1, False),
+                                            (128, 64, 1, True), (1, 64, 0, True), (4, 64, 1, True), (4, 63, 0, False), (129, 64, 0, False))):
+        case = ri.make_case(in_dim=60, hidden=H, out_dim=40, seq_len=T, batch=B, act=n % 2, input_kind=kind, with_h0=n % 3 == 0,
+                            with_dh_last=n % 2 == 0, wdist=("normal", 0.5 / np.sqrt(H)), bias_std=0.1, seed=9950 + 11 * H + n)
+        r = Runner(case)
+        print(f"H={H} B={B} T={T} input={kind}", flush=True)
+        assert (rnn.rnn_recurrence_variant(r.dims) == "xcd_mfma") == (want and H > 192)
+        r.step()
+        assert rnn.rnn_workspace_status(r.dims, r.ws) == 0
+        ref = oracle.fwd_bptt(case, h0=case.get("h0"), dh_last=case.get("dh_last"))
+        compare(r.results(), ref)
+        last = Runner(case, keep_history=False)
+        last.forward()
+        torch.cuda.synchronize()
+        assert np.max(np.abs(last.h_last.cpu().numpy() - ref["h_all"][-1])) <= 2e-5

@@ -19,7 +19,8 @@ def make(H, B, T, kind, seed=0):
                         with_dh_last=kind == 1, wdist=("normal", 0.5 / np.sqrt(H)), bias_std=0.1, seed=7100 + 11 * H + B + seed)
 
 
-@pytest.mark.parametrize("H,B,T", ((257, 5, 10), (301, 1, 16), (512, 33, 11), (515, 64, 12), (1023, 6, 10), (1024, 61, 10)))
+@pytest.mark.parametrize("H,B,T", ((257, 5, 10), (301, 1, 16), (512, 33, 11), (515, 64, 12), (1023, 6, 10), (1024, 61, 10),
+                                   (255, 127, 64)))
 @pytest.mark.parametrize("kind", (0, 1))
 def test_one_workgroup_runs_a_group_whose_others_are_missing(H, B, T, kind):
     case = make(H, B, T, kind)
