@@ -139,3 +139,22 @@ def test_gauss_newton_vec_at_configuration_size(name, overrides, flags):
     r.forward()
     got = r.gauss_newton(gamma, rnn.GN_METRIC_LOSS)
     check(got, r.Rz.cpu().numpy(), _config_refs[name])
+
+
+@pytest.mark.parametrize("O", [1, 2, 3, 5, 2047, 2048, 2049, 6145, 10243, 16384, 16387])
+def test_metric_of_this_many_classes(O):
+    """The softmax metric's kernel: fewer classes than a piece, ragged rows, every count of pieces a thread keeps, and rows that
+    are read again."""
+    case = ri.make_case(30, 7, O, 3, 4, act=1, wdist=("normal", 0.3), bias_std=0.5, seed=300 + O)
+    case["y"][:] %= O
+    gamma = ri.make_direction(case, 11)
+    r = GnRunner(case)
+    r.forward()
+    got = r.gauss_newton(gamma, rnn.GN_METRIC_LOSS)
+    ref = oracle.gauss_newton_vec(case, gamma, metric=0, want_Rz=True)
+    grad_close("Rz", r.Rz.cpu().numpy(), ref["Rz"])
+    for k in PNAMES:
+        if O == 1:                                           # a softmax over one class: the product is zero
+            assert np.abs(got["d" + k]).max() <= 1e-6
+        else:
+            grad_close("G" + k, got["d" + k], ref["G" + k])
