@@ -138,8 +138,7 @@ Plan make_plan(const rnn_dims* d) {
     p.Delta = take(N * H * 4);
     p.WhT = take(H * H * 4);
     p.hring = take(2 * B * H * 4);
-    const size_t widest = O > H ? O : H;
-    p.part = take((size_t)colsum_chunks((int)N) * widest * 4);
+    p.part = take((size_t)colsum_chunks((int)N) * (O + H) * 4);      // column sums of dZ, then of Delta
     p.splitk = take(max_splitk_floats(s) * 4);
     p.scratch = take(256);
     // state-exchange boxes of the multi-workgroup loops
@@ -197,6 +196,24 @@ int finish(const rnn_dims* d, hipStream_t s, hipError_t e) {
 
 // ---- stages ------------------------------------------------------------------------------
 
+// the wide loop's arguments that are the same in every call with these dims
+RecXcdArgs xcd_args(const rnn_dims* d, void* ws, const Plan& pl) {
+    const Sizes z = sizes_of(d);
+    RecXcdArgs m{};
+    m.H = z.H; m.T = z.T; m.B = z.B; m.act = d->act;
+    m.counters = at<int32_t>(ws, pl.flags); m.ring = at<float>(ws, pl.flags + 4096);
+    m.status = at<int32_t>(ws, pl.scratch) + 1;
+    return m;
+}
+
+// what an earlier kernel can set on the side for run_reverse_loop; false (and nothing to set) if its loop needs nothing
+bool reverse_fills(const rnn_dims* d, void* ws, const Plan& pl, FillJob* ring, FillJob* counters) {
+    *ring = *counters = FillJob{};
+    if (!pick_variant(d).xcd || !rec_xcd_ready(d->hidden, d->batch, d->act, true)) return false;
+    rec_xcd_fills(xcd_args(d, ws, pl), ring, counters);
+    return true;
+}
+
 hipError_t run_forward(const rnn_dims* d, const rnn_params* P, const void* x, const float* h0,
                        float* h_all, float* h_last, void* ws, const Plan& pl, hipStream_t s) {
     const Sizes z = sizes_of(d);
@@ -223,11 +240,9 @@ hipError_t run_forward(const rnn_dims* d, const rnn_params* P, const void* x, co
     }
     const Variant v = pick_variant(d);
     if (v.xcd && h_all && rec_xcd_ready(z.H, z.B, d->act, false)) {
-        RecXcdArgs m{};
-        m.Wh = P->Wh; m.H = z.H; m.T = z.T; m.B = z.B; m.act = d->act;
+        RecXcdArgs m = xcd_args(d, ws, pl);
+        m.Wh = P->Wh;
         m.x = a.x; m.Wx = P->Wx; m.b = P->b; m.U = a.U; m.h0 = h0; m.hist = h_all; m.h_last = h_last;
-        m.counters = at<int32_t>(ws, pl.flags); m.ring = at<float>(ws, pl.flags + 4096);
-        m.status = at<int32_t>(ws, pl.scratch) + 1;
         return launch_rec_xcd(m, false, s);
     }
     if (v.batch_mfma) {
@@ -308,10 +323,10 @@ hipError_t run_loss(const rnn_dims* d, const rnn_params* P, const float* h_all, 
 // Reverse-time loop delta_t = (G_t + Wh^T delta_{t+1}) * act'(h_t) with the kernel family that
 // serves these sizes (never the fused short-sequence form).  Wh and its transposed copy are
 // passed explicitly: the R-operator's forward sweep is the same recurrence run on time-reversed
-// rows with the two exchanged.
+// rows with the two exchanged.  cleared: an earlier kernel has set the exchange words (reverse_fills).
 hipError_t run_reverse_loop(const rnn_dims* d, const float* Wh, const float* WhT_or_null, float* WhT_ws,
                             const float* G, const float* h_all, const float* dh_last, float* Delta,
-                            float* dh0, void* ws, const Plan& pl, hipStream_t s) {
+                            float* dh0, void* ws, const Plan& pl, bool cleared, hipStream_t s) {
     const Sizes z = sizes_of(d);
     const int H = z.H;
     Variant v = pick_variant(d);
@@ -319,11 +334,9 @@ hipError_t run_reverse_loop(const rnn_dims* d, const float* Wh, const float* WhT
         if (!rec_resident_plan(z.H, z.B, z.T, true, false, 0, &v.bwd)) v.resident = false;
     }
     if (v.xcd && rec_xcd_ready(z.H, z.B, d->act, true)) {
-        RecXcdArgs m{};
-        m.Wh = Wh; m.H = H; m.T = z.T; m.B = z.B; m.act = d->act;
+        RecXcdArgs m = xcd_args(d, ws, pl);
+        m.Wh = Wh; m.cleared = cleared;
         m.G = G; m.h_all = h_all; m.dh_last = dh_last; m.Delta = Delta; m.dh0 = dh0;
-        m.counters = at<int32_t>(ws, pl.flags); m.ring = at<float>(ws, pl.flags + 4096);
-        m.status = at<int32_t>(ws, pl.scratch) + 1;
         return launch_rec_xcd(m, true, s);
     }
     if (v.batch_mfma) {
@@ -361,10 +374,10 @@ hipError_t run_reverse_loop(const rnn_dims* d, const float* Wh, const float* WhT
 }
 
 // Everything of backpropagation that follows d loss / d z (held in the logits buffer of the
-// workspace): dV, G, the reverse loop, dWh, db, dWx.  dc is the caller's.
+// workspace), whose columns' sums per chunk are in the front of `part`: dV, G, the reverse loop, dWh, db, dc, dWx.
 hipError_t run_backward_from_dz(const rnn_dims* d, const rnn_params* P, const void* x, const float* h_all,
                                 const float* dh_last, const rnn_grads* Gr, float* dh0, void* ws,
-                                const Plan& pl, hipStream_t s) {
+                                const Plan& pl, bool cleared, hipStream_t s) {
     const Sizes z = sizes_of(d);
     const int N = (int)z.N, H = z.H, O = z.O;
     const int beta = (d->flags & RNN_FLAG_ACCUMULATE) ? 1 : 0;
@@ -394,7 +407,7 @@ hipError_t run_backward_from_dz(const rnn_dims* d, const rnn_params* P, const vo
         g.a_t = false; g.b_t = true; g.beta = 0; g.splitk_ws = splitk; g.parts = parts; g.prof_id = K_GEMM_G;
         RNN_TRY(launch_gemm(g, s));
     }
-    RNN_TRY(run_reverse_loop(d, P->Wh, nullptr, at<float>(ws, pl.WhT), G, h_all, dh_last, Delta, dh0, ws, pl, s));
+    RNN_TRY(run_reverse_loop(d, P->Wh, nullptr, at<float>(ws, pl.WhT), G, h_all, dh_last, Delta, dh0, ws, pl, cleared, s));
     // dWh = Delta^T Hprev  (Hprev rows = h_all[0:T])
     {
         GemmArgs g{};
@@ -405,13 +418,21 @@ hipError_t run_backward_from_dz(const rnn_dims* d, const rnn_params* P, const vo
         RNN_TRY(launch_gemm(g, s));
     }
     // db = column sums of Delta
-    RNN_TRY(launch_colsum_partial(Delta, part, N, H, s));
-    RNN_TRY(launch_colsum_finish(part, Gr->db, chunks, H, beta, s));
+    float* part_h = part + (size_t)chunks * O;
+    if (z.tokens && N > 32) {
+        // dWx in the grouped form; its table is zeroed and both column sums are finished on the side of its launches.
+        // G is dead by now and serves as scratch for per-range partial rows
+        int32_t* table = at<int32_t>(ws, pl.seen);
+        RNN_TRY(launch_colsum_partial(Delta, part_h, N, H, FillJob{table, dwx_table_ints(N, z.NVin), 0}, s));
+        return launch_dwx_tokens_grouped(static_cast<const int32_t*>(x), Delta, Gr->dWx, N, z.NVin, H, beta, G, table,
+                                         colsum_job(part, Gr->dc, chunks, O, beta), colsum_job(part_h, Gr->db, chunks, H, beta), s);
+    }
+    RNN_TRY(launch_colsum_finish(part, Gr->dc, chunks, O, beta, s));
+    RNN_TRY(launch_colsum_partial(Delta, part_h, N, H, FillJob{}, s));
+    RNN_TRY(launch_colsum_finish(part_h, Gr->db, chunks, H, beta, s));
     // dWx
     if (z.tokens) {
-        // G is dead by now and serves as scratch for per-range partial rows
-        RNN_TRY(launch_dwx_tokens(static_cast<const int32_t*>(x), Delta, Gr->dWx, N, z.NVin, H, beta,
-                                  N > 32 ? G : nullptr, N > 32 ? at<int32_t>(ws, pl.seen) : nullptr, s));
+        RNN_TRY(launch_dwx_tokens(static_cast<const int32_t*>(x), Delta, Gr->dWx, N, z.NVin, H, beta, s));
     } else {
         GemmArgs g{};
         g.A = Delta; g.B = static_cast<const float*>(x); g.C = Gr->dWx;
@@ -433,7 +454,6 @@ hipError_t run_bptt(const rnn_dims* d, const rnn_params* P, const void* x, const
     float* part = at<float>(ws, pl.part);
     float* G = at<float>(ws, pl.G);
     float* Delta = at<float>(ws, pl.Delta);
-    const int chunks = colsum_chunks(N);
     const Variant v = pick_variant(d);
 
     RecResArgs r{};
@@ -456,12 +476,13 @@ hipError_t run_bptt(const rnn_dims* d, const rnn_params* P, const void* x, const
         return launch_rec_bwd_with_strips(r, v.bwd, k, s);
     }
 
-    // logits -> d loss / d logits (in place) and dc
+    // logits -> d loss / d logits (in place) and their columns' sums per chunk
+    FillJob ring, counters;
+    const bool cleared = reverse_fills(d, ws, pl, &ring, &counters);
     RNN_TRY(launch_dz(Z, at<float>(ws, pl.lse), z.ce ? static_cast<const int32_t*>(targets) : nullptr,
                       z.ce ? nullptr : static_cast<const float*>(targets), part, N, O,
-                      d->loss_kind, s));
-    RNN_TRY(launch_colsum_finish(part, Gr->dc, chunks, O, beta, s));
-    return run_backward_from_dz(d, P, x, h_all, dh_last, Gr, dh0, ws, pl, s);
+                      d->loss_kind, ring, counters, s));
+    return run_backward_from_dz(d, P, x, h_all, dh_last, Gr, dh0, ws, pl, cleared, s);
 }
 
 // Extra regions of the Gauss-Newton-vector product behind the ordinary plan.
@@ -499,7 +520,6 @@ hipError_t run_gauss_newton(const rnn_dims* d, const rnn_params* P, const rnn_pa
     const Sizes z = sizes_of(d);
     const int N = (int)z.N, H = z.H, O = z.O;
     const size_t BH = (size_t)z.B * H;
-    const int beta = (d->flags & RNN_FLAG_ACCUMULATE) ? 1 : 0;
     float* U = at<float>(ws, pl.Z);          // R z, then u = M R z (what backpropagation reads)
     float* Zl = at<float>(ws, gp.logits);
     float* C = at<float>(ws, pl.Delta);
@@ -529,9 +549,7 @@ hipError_t run_gauss_newton(const rnn_dims* d, const rnn_params* P, const rnn_pa
         g.splitk_ws = at<float>(ws, gp.splitk_c);
         RNN_TRY(launch_gemm(g, s));
     }
-    if (z.tokens) {
-        RNN_TRY(launch_gather_add(static_cast<const int32_t*>(x), Ga->Wx, C, N, H, s));
-    } else {   // C += X gWx^T
+    if (!z.tokens) {   // C += X gWx^T (tokens: the rows are gathered below)
         GemmArgs g{};
         g.A = static_cast<const float*>(x); g.B = Ga->Wx; g.C = C;
         g.M = N; g.N = H; g.K = z.NVin; g.lda = z.NVin; g.ldb = z.NVin; g.ldc = H;
@@ -539,10 +557,11 @@ hipError_t run_gauss_newton(const rnn_dims* d, const rnn_params* P, const rnn_pa
         RNN_TRY(launch_gemm(g, s));
     }
     // time-reversed rows: Crev[t] = C[T-1-t], hrev[t+1] = h_{T-1-t}
-    RNN_TRY(launch_reverse_rows(C, Crev, z.T, (int)BH, s));
-    RNN_TRY(launch_reverse_rows(Hs, hrev + BH, z.T, (int)BH, s));
-    RNN_TRY(launch_transpose(P->Wh, WhT, H, H, s));
-    RNN_TRY(run_reverse_loop(d, WhT, P->Wh, nullptr, Crev, hrev, nullptr, Rhrev, nullptr, ws, pl, s));
+    FillJob ring, counters;
+    const bool cleared = reverse_fills(d, ws, pl, &ring, &counters);
+    RNN_TRY(launch_gn_prepare(z.tokens ? static_cast<const int32_t*>(x) : nullptr, Ga->Wx, C, Hs, P->Wh, Crev, hrev + BH, WhT,
+                              z.T, z.B, H, ring, counters, s));
+    RNN_TRY(run_reverse_loop(d, WhT, P->Wh, nullptr, Crev, hrev, nullptr, Rhrev, nullptr, ws, pl, cleared, s));
     RNN_TRY(launch_reverse_rows(Rhrev, Rh, z.T, (int)BH, s));
     {   // R z = Rh V + gc
         GemmArgs g{};
@@ -561,10 +580,9 @@ hipError_t run_gauss_newton(const rnn_dims* d, const rnn_params* P, const rnn_pa
         RNN_TRY(launch_gn_softmax_metric(Zl, U, N, O, 1.0f / (float)N, s));
     else if (metric == RNN_GN_METRIC_LOSS)
         RNN_TRY(launch_scale(U, (size_t)N * O, (float)(2.0 / ((double)N * (double)O)), s));
-    // Gc = column sums of u, then the rest of backpropagation
-    RNN_TRY(launch_colsum_partial(U, at<float>(ws, pl.part), N, O, s));
-    RNN_TRY(launch_colsum_finish(at<float>(ws, pl.part), Out->dc, colsum_chunks(N), O, beta, s));
-    return run_backward_from_dz(d, P, x, h_all, nullptr, Out, nullptr, ws, pl, s);
+    // column sums of u for Gc, then the rest of backpropagation
+    RNN_TRY(launch_colsum_partial(U, at<float>(ws, pl.part), N, O, FillJob{}, s));
+    return run_backward_from_dz(d, P, x, h_all, nullptr, Out, nullptr, ws, pl, false, s);
 }
 
 bool params_ok(const rnn_params* P) {

@@ -199,6 +199,11 @@ __device__ __forceinline__ bool tagged_wait(const unsigned long long* p, unsigne
 }
 
 
+// words [0, n) = v, by block `bid` of `nb` with `threads` threads each: a fill that rides on another kernel
+__device__ __forceinline__ void fill_share(int32_t* p, size_t n, int32_t v, size_t bid, size_t nb, int threads) {
+    for (size_t i = bid * threads + threadIdx.x; i < n; i += nb * threads) p[i] = v;
+}
+
 // Every requested word is "used" here, also the clamped duplicates a batch requests past the end
 // of its range: a load whose result is never read stays pending in the compiler's bookkeeping,
 // and the wait it later inserts before reusing the register (in some unrelated loop) would also

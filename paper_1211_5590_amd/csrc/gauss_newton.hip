@@ -18,12 +18,38 @@ __global__ __launch_bounds__(256) void reverse_rows_kernel(const float* __restri
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < row; i += gridDim.x * blockDim.x) d[i] = s[i];
 }
 
-// C[n][:] += M[x[n]][:]
-__global__ __launch_bounds__(256) void gather_add_kernel(const int32_t* __restrict__ x, const float* __restrict__ M,
-                                                         float* __restrict__ C, int H) {
-    const int n = blockIdx.x;
-    const float* row = M + (size_t)x[n] * H;
-    for (int j = threadIdx.x; j < H; j += blockDim.x) C[(size_t)n * H + j] += row[j];
+// What the R-operator's sweep needs before its loop, in one launch of 256 threads per workgroup: the first T B workgroups turn a row
+// of C (with the row of M that its token picks) and one of Hs round in time, the next transpose a 32 x 32 tile of Wh each, and all
+// fill a share of the loop's exchange words.  (Four launches before, 3 us each.)
+struct GnPrepare {
+    const int32_t* x; const float* M;          // x NULL: no gathered rows
+    const float *C, *Hs, *Wh;
+    float *Crev, *hrev, *WhT;
+    int T, B, H;
+    FillJob ring, counters;
+};
+__global__ __launch_bounds__(256) void gn_prepare_kernel(GnPrepare a) {
+    const int H = a.H, N = a.T * a.B, tid = threadIdx.x;
+    fill_share(a.ring.p, a.ring.n, a.ring.v, blockIdx.x, gridDim.x, 256);
+    fill_share(a.counters.p, a.counters.n, a.counters.v, blockIdx.x, gridDim.x, 256);
+    if ((int)blockIdx.x < N) {
+        const int n = blockIdx.x, t = n / a.B, src = (a.T - 1 - t) * a.B + n % a.B;
+        const float* row = a.x ? a.M + (size_t)a.x[src] * H : nullptr;
+        const size_t from = (size_t)src * H, to = (size_t)n * H;
+        for (int j = tid; j < H; j += 256) {
+            const float c = a.C[from + j];
+            a.Crev[to + j] = row ? c + row[j] : c;
+            a.hrev[to + j] = a.Hs[from + j];
+        }
+        return;
+    }
+    __shared__ float tile[32][33];
+    const int side = (H + 31) / 32, b = blockIdx.x - N, r0 = b / side * 32, c0 = b % side * 32, tx = tid % 32, ty = tid / 32;
+    for (int i = ty; i < 32; i += 8)
+        if (r0 + i < H && c0 + tx < H) tile[i][tx] = a.Wh[(size_t)(r0 + i) * H + c0 + tx];
+    __syncthreads();
+    for (int i = ty; i < 32; i += 8)
+        if (c0 + i < H && r0 + tx < H) a.WhT[(size_t)(c0 + i) * H + r0 + tx] = tile[tx][i];
 }
 
 __global__ __launch_bounds__(256) void fill_zero_kernel(float* p, size_t n) {
@@ -129,9 +155,12 @@ hipError_t launch_reverse_rows(const float* src, float* dst, int T, int row, hip
     hipLaunchKernelGGL(reverse_rows_kernel, dim3(blocks_for((size_t)row), T), dim3(256), 0, s, src, dst, T, row);
     return hipGetLastError();
 }
-hipError_t launch_gather_add(const int32_t* x, const float* M, float* C, int N, int H, hipStream_t s) {
+hipError_t launch_gn_prepare(const int32_t* x, const float* M, const float* C, const float* Hs, const float* Wh, float* Crev,
+                             float* hrev, float* WhT, int T, int B, int H, FillJob ring, FillJob counters, hipStream_t s) {
+    const int side = (H + 31) / 32;
+    const GnPrepare a = {x, M, C, Hs, Wh, Crev, hrev, WhT, T, B, H, ring, counters};
     ProfileScope ps(K_MISC, s);
-    hipLaunchKernelGGL(gather_add_kernel, dim3(N), dim3(256), 0, s, x, M, C, H);
+    hipLaunchKernelGGL(gn_prepare_kernel, dim3((unsigned)(T * B + side * side)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 hipError_t launch_fill_zero(float* p, size_t n, hipStream_t s) {

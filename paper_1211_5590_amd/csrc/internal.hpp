@@ -140,12 +140,15 @@ struct RecXcdArgs {
     float* ring;          // rec_xcd_ring_bytes of workspace, 16-byte aligned (filled by the launcher)
     int32_t* status;      // device status word: set to 1 when a bounded wait expires
     int spin_limit;       // <= 0: default
+    bool cleared;         // ring and counters are as rec_xcd_fills wants them
     int slots, patience;  // workgroups of a group; 10 ns they wait for each other to come (filled in by the launcher)
 };
 bool rec_xcd_supported(int H, int B, int T, bool tokens);          // shape only (host)
 int rec_xcd_workgroups(int H, int B);
 size_t rec_xcd_ring_bytes(int H, int B);
 bool rec_xcd_ready(int H, int B, int act, bool bwd);             // and the current device can hold the grid at once
+// what the ring and the counters have to hold before a launch, for a kernel that sets it on the side
+void rec_xcd_fills(const RecXcdArgs& a, struct FillJob* ring, struct FillJob* counters);
 hipError_t launch_rec_xcd(const RecXcdArgs& a, bool bwd, hipStream_t s);
 
 // Launch of a kernel whose workgroups wait for each other: it takes turns with others of its kind on the device (gang.hip)
@@ -170,11 +173,16 @@ hipError_t launch_ce_merge_stats(const float* stats, int parts, const float* Z, 
 hipError_t launch_mse_partial(const float* Z, const float* Y, float* partial, int N, int O,
                               int* n_partial, hipStream_t s);
 hipError_t launch_loss_reduce(const float* rowloss, int N, double scale, float* loss, hipStream_t s);
-// Z -> dZ in place, plus per-row-chunk column sums into part[chunks][O]
+// n words of p to be set to v by a kernel that has other work (n == 0: none)
+struct FillJob { int32_t* p; size_t n; int32_t v; };
+// second stage of a column sum: 256 threads per group of columns
+struct ColsumJob { const float* part; float* out; int chunks, C, beta, txs, groups; };
+ColsumJob colsum_job(const float* part, float* out, int chunks, int C, int beta);
+// Z -> dZ in place, plus per-row-chunk column sums into part[chunks][O]; the fills ride along
 int colsum_chunks(int N);
 hipError_t launch_dz(float* Z, const float* lse, const int32_t* y, const float* Y, float* part,
-                     int N, int O, int loss_kind, hipStream_t s);
-hipError_t launch_colsum_partial(const float* M, float* part, int N, int C, hipStream_t s);
+                     int N, int O, int loss_kind, FillJob ring, FillJob counters, hipStream_t s);
+hipError_t launch_colsum_partial(const float* M, float* part, int N, int C, FillJob zero, hipStream_t s);
 hipError_t launch_colsum_finish(const float* part, float* out, int chunks, int C, int beta,
                                 hipStream_t s);
 
@@ -209,7 +217,9 @@ hipError_t launch_skinny_logits(const SkinnyArgs& a, hipStream_t s);   // logits
 // ---------------------------------------------------------------------------------------
 // Small kernels of the Gauss-Newton-vector product (gauss_newton.hip)
 hipError_t launch_reverse_rows(const float* src, float* dst, int T, int row, hipStream_t s);   // dst[t] = src[T-1-t]
-hipError_t launch_gather_add(const int32_t* x, const float* M, float* C, int N, int H, hipStream_t s);
+// Crev[t] = C[T-1-t] (+ M[x[T-1-t]]), hrev[t] = Hs[T-1-t], WhT = Wh^T; the fills ride along
+hipError_t launch_gn_prepare(const int32_t* x, const float* M, const float* C, const float* Hs, const float* Wh, float* Crev,
+                             float* hrev, float* WhT, int T, int B, int H, FillJob ring, FillJob counters, hipStream_t s);
 hipError_t launch_fill_zero(float* p, size_t n, hipStream_t s);
 hipError_t launch_scale(float* p, size_t n, float alpha, hipStream_t s);
 // RZ_n <- (p * RZ_n - p (p . RZ_n)) * scale, p = softmax(Z_n)
@@ -217,12 +227,13 @@ hipError_t launch_gn_softmax_metric(const float* Z, float* RZ, int N, int O, flo
 
 // ---------------------------------------------------------------------------------------
 // Token-keyed gradient of the input matrix and id validation
-// scratch (dwx_scratch_floats(N, H) floats) and slot_table (dwx_table_ints(N, NV) ints), both or neither,
-// enable the grouped form
 size_t dwx_scratch_floats(int N, int H);
 size_t dwx_table_ints(int N, int NV);
-hipError_t launch_dwx_tokens(const int32_t* x, const float* Delta, float* dWx, int N, int NV,
-                             int H, int beta, float* scratch, int32_t* slot_table, hipStream_t s);
+hipError_t launch_dwx_tokens(const int32_t* x, const float* Delta, float* dWx, int N, int NV, int H, int beta, hipStream_t s);
+// The grouped form: scratch holds dwx_scratch_floats(N, H) floats, slot_table dwx_table_ints(N, NV) zeros; the second stage of two
+// column sums is done on the side.
+hipError_t launch_dwx_tokens_grouped(const int32_t* x, const float* Delta, float* dWx, int N, int NV, int H, int beta,
+                                     float* scratch, int32_t* slot_table, const ColsumJob& a, const ColsumJob& b, hipStream_t s);
 hipError_t launch_check_tokens(const int32_t* ids, int64_t n, int32_t limit, int32_t* bad,
                                hipStream_t s);
 

@@ -2,6 +2,7 @@
 // d loss / d logits producer fused with its column sums (element-wise chain fused into one
 // pass, as the paper's loop-fusion rewrite does for scalar operations), and deterministic
 // column-sum / scalar reductions.  All of these are HBM-bandwidth bound.
+#include "colsum_dev.hpp"
 #include "common.hpp"
 #include "internal.hpp"
 #include "prof.hpp"
@@ -196,15 +197,21 @@ __device__ __forceinline__ void fold_row_lanes(const ColLayout& L, float (&cs)[V
 }
 
 // grid (column blocks, row chunks of rows_per_chunk(N)): turns z into d loss / d z in place and
-// keeps per-chunk column sums in part[chunk][O].
+// keeps per-chunk column sums in part[chunk][O].  Fills the reverse loop's exchange words on the side (a launch of their own is
+// 3 us).
 template <int LOSS, int VEC>
 __global__ __launch_bounds__(256) void dz_kernel(float* __restrict__ Z, const float* __restrict__ lse,
                                                  const int32_t* __restrict__ y,
                                                  const float* __restrict__ Y,
                                                  float* __restrict__ part, int N, int O, float scale,
-                                                 int txs) {
+                                                 int txs, FillJob ring, FillJob counters) {
     __shared__ float red[256 * VEC];
     constexpr int U = 4;
+    {
+        const size_t bid = (size_t)blockIdx.y * gridDim.x + blockIdx.x, nb = (size_t)gridDim.x * gridDim.y;
+        fill_share(ring.p, ring.n, ring.v, bid, nb, 256);
+        fill_share(counters.p, counters.n, counters.v, bid, nb, 256);
+    }
     const ColLayout L(txs);
     const int col = (blockIdx.x * L.tx + L.cx) * VEC;
     const int rpc = rows_per_chunk(N);
@@ -252,9 +259,10 @@ __global__ __launch_bounds__(256) void dz_kernel(float* __restrict__ Z, const fl
 template <int VEC>
 __global__ __launch_bounds__(256) void colsum_partial_kernel(const float* __restrict__ M,
                                                              float* __restrict__ part, int N, int C,
-                                                             int txs) {
+                                                             int txs, FillJob zero) {
     __shared__ float red[256 * VEC];
     constexpr int U = 8;
+    fill_share(zero.p, zero.n, zero.v, (size_t)blockIdx.y * gridDim.x + blockIdx.x, (size_t)gridDim.x * gridDim.y, 256);
     const ColLayout L(txs);
     const int col = (blockIdx.x * L.tx + L.cx) * VEC;
     const int rpc = rows_per_chunk(N);
@@ -279,34 +287,9 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const float* __rest
     fold_row_lanes<VEC>(L, cs, red, part + (size_t)blockIdx.y * C, col, C);
 }
 
-// out[col] = (beta ? out[col] : 0) + sum over chunks of part[chunk][col]; scalar columns, the
-// chunks spread over the row lanes
-__global__ __launch_bounds__(256) void colsum_finish_kernel(const float* __restrict__ part,
-                                                            float* __restrict__ out, int chunks,
-                                                            int C, int beta, int txs) {
+__global__ __launch_bounds__(256) void colsum_finish_kernel(ColsumJob j) {
     __shared__ float red[256];
-    constexpr int U = 8;
-    const ColLayout L(txs);
-    const int col = blockIdx.x * L.tx + L.cx;
-    float cs[1] = {0.f};
-    if (col < C) {
-        for (int k0 = L.ry; k0 < chunks; k0 += L.ty * U) {
-            float m[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                m[u] = part[(size_t)min(k0 + u * L.ty, chunks - 1) * C + col];
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (k0 + u * L.ty < chunks) cs[0] += m[u];
-        }
-    }
-    red[threadIdx.x] = cs[0];
-    __syncthreads();
-    if (L.ry == 0 && col < C) {
-        float s = 0.f;
-        for (int r = 0; r < L.ty; ++r) s += red[r * L.tx + L.cx];
-        out[col] = beta ? out[col] + s : s;
-    }
+    colsum_finish(j, blockIdx.x, threadIdx.x, red);
 }
 
 // log2 of the column lanes for a matrix of `cols` column groups: the smallest power of two
@@ -364,7 +347,7 @@ hipError_t launch_loss_reduce(const float* rowloss, int N, double scale, float* 
 }
 
 hipError_t launch_dz(float* Z, const float* lse, const int32_t* y, const float* Y, float* part,
-                     int N, int O, int loss_kind, hipStream_t s) {
+                     int N, int O, int loss_kind, FillJob ring, FillJob counters, hipStream_t s) {
     const bool vec = O % 4 == 0 && aligned16(Z) && (loss_kind == 0 || aligned16(Y));
     const int groups = vec ? O / 4 : O;
     const int txs = col_lane_shift(groups);
@@ -372,32 +355,36 @@ hipError_t launch_dz(float* Z, const float* lse, const int32_t* y, const float* 
     ProfileScope ps(K_DZ, s);
     const float scale = loss_kind == 0 ? 1.0f / (float)N : (float)(2.0 / ((double)N * (double)O));
 #define RNN_DZ(LOSS, VEC) \
-    hipLaunchKernelGGL((dz_kernel<LOSS, VEC>), grid, dim3(256), 0, s, Z, lse, y, Y, part, N, O, scale, txs)
+    hipLaunchKernelGGL((dz_kernel<LOSS, VEC>), grid, dim3(256), 0, s, Z, lse, y, Y, part, N, O, scale, txs, ring, counters)
     if (loss_kind == 0) { if (vec) RNN_DZ(0, 4); else RNN_DZ(0, 1); }
     else { if (vec) RNN_DZ(1, 4); else RNN_DZ(1, 1); }
 #undef RNN_DZ
     return hipGetLastError();
 }
 
-hipError_t launch_colsum_partial(const float* M, float* part, int N, int C, hipStream_t s) {
+hipError_t launch_colsum_partial(const float* M, float* part, int N, int C, FillJob zero, hipStream_t s) {
     const bool vec = C % 4 == 0 && aligned16(M);
     const int groups = vec ? C / 4 : C;
     const int txs = col_lane_shift(groups);
     dim3 grid((groups + (1 << txs) - 1) >> txs, colsum_chunks(N));
     ProfileScope ps(K_COLSUM_PARTIAL, s);
-    if (vec) hipLaunchKernelGGL(colsum_partial_kernel<4>, grid, dim3(256), 0, s, M, part, N, C, txs);
-    else hipLaunchKernelGGL(colsum_partial_kernel<1>, grid, dim3(256), 0, s, M, part, N, C, txs);
+    if (vec) hipLaunchKernelGGL(colsum_partial_kernel<4>, grid, dim3(256), 0, s, M, part, N, C, txs, zero);
+    else hipLaunchKernelGGL(colsum_partial_kernel<1>, grid, dim3(256), 0, s, M, part, N, C, txs, zero);
     return hipGetLastError();
+}
+
+ColsumJob colsum_job(const float* part, float* out, int chunks, int C, int beta) {
+    const int txs = col_lane_shift(C < 16 ? C : 16);
+    return {part, out, chunks, C, beta, txs, (C + (1 << txs) - 1) >> txs};
 }
 
 hipError_t launch_colsum_finish(const float* part, float* out, int chunks, int C, int beta,
                                 hipStream_t s) {
     // few column lanes per workgroup so that the chunks spread over many row lanes and many
     // workgroups share the columns
-    const int txs = col_lane_shift(C < 16 ? C : 16);
+    const ColsumJob j = colsum_job(part, out, chunks, C, beta);
     ProfileScope ps(K_COLSUM_FINISH, s);
-    hipLaunchKernelGGL(colsum_finish_kernel, dim3((C + (1 << txs) - 1) >> txs), dim3(256), 0, s, part,
-                       out, chunks, C, beta, txs);
+    hipLaunchKernelGGL(colsum_finish_kernel, dim3(j.groups), dim3(256), 0, s, j);
     return hipGetLastError();
 }
 

@@ -746,13 +746,18 @@ bool rec_xcd_ready(int H, int B, int act, bool bwd) {
     return ok;
 }
 
+void rec_xcd_fills(const RecXcdArgs& a, FillJob* ring, FillJob* counters) {
+    *ring = {reinterpret_cast<int32_t*>(a.ring), (size_t)RSLOTS * ring_state(a.B, xcd_kw(a.H)), (int32_t)kSentinel};
+    *counters = {a.counters, (size_t)(NXCD + NGRP), 0};
+}
+
 hipError_t launch_rec_xcd(const RecXcdArgs& a, bool bwd, hipStream_t s) {
     if (a.H > H_MAX || a.B < 1 || a.B > NGRP * RB || (a.H + 63) / 64 > xcd_slots(a.B)) return hipErrorInvalidValue;
     if (!rec_xcd_ready(a.H, a.B, a.act, bwd)) return hipErrorNotSupported;
     const void* fn = bwd ? xcd_kernel_for<true>(a.H, a.B, a.act) : xcd_kernel_for<false>(a.H, a.B, a.act);
     const size_t lds = xcd_lds_bytes();
 
-    {
+    if (!a.cleared) {
         ProfileScope ps(K_MISC, s);
         const int n4 = RSLOTS * ring_state(a.B, xcd_kw(a.H)) / 4;
         hipLaunchKernelGGL(xcd_clear_kernel, dim3((n4 + 255) / 256), dim3(256), 0, s, a.ring, n4, a.counters);

@@ -12,6 +12,7 @@
 //
 // Scan form (a short id list): every wavefront owns one
 // vocabulary row and scans the whole id list for its token.
+#include "colsum_dev.hpp"
 #include "common.hpp"
 #include "internal.hpp"
 #include "prof.hpp"
@@ -84,7 +85,8 @@ constexpr int kRowsInFlight = 8;
 
 // One range of CL ids by one slice of 64 columns per workgroup: sort, group, sum.  part: compact partial rows
 // [range*CL + group][H]; slot[token][range] = group + 1, or -(n + 1) for a single occurrence at
-// row n, where the token occurs in the range (the table is zeroed before this kernel).
+// row n, where the token occurs in the range (the table is zeroed before this kernel).  Further rows of
+// workgroups finish column sums.
 // What bounds it is the chain sort - group - sum of the longest group, and there are few ranges (700 ids: 3): so every slice of a
 // range sorts it again rather than wait for another, and 16 lanes have a group, 32 groups at a time.  (One workgroup
 // per range, all columns, bitonic sort: 14.9 us for 100 rows of 500, 25.4 for 800 of 500, 34.3 for 2310 of 650, 57.0 for 16384 of
@@ -96,7 +98,16 @@ __global__ __launch_bounds__(kGroupThreads) void dwx_group_kernel(const int32_t*
                                                                   const float* __restrict__ Delta,
                                                                   float* __restrict__ part,
                                                                   int32_t* __restrict__ slot,
-                                                                  int N, int NV, int H) {
+                                                                  int N, int NV, int H, int slices, ColsumJob sum_a,
+                                                                  ColsumJob sum_b) {
+    if ((int)blockIdx.y >= slices) {         // column sums to be finished on the side, two groups per workgroup
+        __shared__ float red[kGroupThreads];
+        static_assert(kGroupThreads == 512, "two groups of 256 threads");
+        const int half = threadIdx.x / 256, g = 2 * ((blockIdx.y - slices) * gridDim.x + blockIdx.x) + half;
+        const bool first = g < sum_a.groups;
+        colsum_finish(first ? sum_a : sum_b, first ? g : g - sum_a.groups, threadIdx.x % 256, red + 256 * half);
+        return;
+    }
     __shared__ __attribute__((aligned(16))) unsigned long long key[CL];   // (id << 32) | position in the range; padding = ~0
     __shared__ int seg_start[CL + 1];
     __shared__ int s_heads[kGroupThreads / kWave];
@@ -242,11 +253,6 @@ __global__ __launch_bounds__(256) void dwx_gather_kernel(const float* __restrict
     store4u(dst + c0, shifted(acc, c0 - c), H - c0);
 }
 
-__global__ void zero_table_kernel(int32_t* p, size_t n) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        p[i] = 0;
-}
-
 __global__ __launch_bounds__(256) void zero_i32_kernel(int32_t* p) {
     if (threadIdx.x == 0 && blockIdx.x == 0) *p = 0;
 }
@@ -277,28 +283,17 @@ int dwx_ranges(int N) { const int cl = dwx_range_len(N); return (N + cl - 1) / c
 size_t dwx_scratch_floats(int N, int H) { return (size_t)dwx_ranges(N) * dwx_range_len(N) * H; }
 size_t dwx_table_ints(int N, int NV) { return (size_t)dwx_ranges(N) * NV; }
 
-hipError_t launch_dwx_tokens(const int32_t* x, const float* Delta, float* dWx, int N, int NV, int H,
-                             int beta, float* scratch, int32_t* slot_table, hipStream_t s) {
-    const int rows_per_block = 256 / kWave;
-    const int blocks = (NV + rows_per_block - 1) / rows_per_block;
-    const int cl = dwx_range_len(N), ranges = dwx_ranges(N);
-    const bool grouped = scratch && slot_table;
-    if (!grouped) {
-        ProfileScope ps(K_DWX_TOKENS, s);
-        hipLaunchKernelGGL(dwx_tokens_kernel, dim3(blocks), dim3(256), 0, s, x, Delta, dWx, N, NV, H, beta);
-        return hipGetLastError();
-    }
+hipError_t launch_dwx_tokens_grouped(const int32_t* x, const float* Delta, float* dWx, int N, int NV, int H, int beta,
+                                     float* scratch, int32_t* slot_table, const ColsumJob& a, const ColsumJob& b, hipStream_t s) {
+    const int cl = dwx_range_len(N), ranges = dwx_ranges(N), slices = (H + kSliceCols - 1) / kSliceCols;
+    const int side = ((a.groups + b.groups + 1) / 2 + ranges - 1) / ranges;     // further rows of workgroups for the column sums
     {
         ProfileScope ps(K_DWX_TOKENS, s);
-        const size_t n = dwx_table_ints(N, NV);
-        size_t zb = (n + 2047) / 2048;
-        if (zb > 1024) zb = 1024;
-        hipLaunchKernelGGL(zero_table_kernel, dim3((unsigned)zb), dim3(256), 0, s, slot_table, n);
-        const int slices = (H + kSliceCols - 1) / kSliceCols;
+        const dim3 grid(ranges, slices + side);
 #define RNN_GROUP(CL)                                                                                    \
     do {                                                                                                 \
-        if (H >= 4) hipLaunchKernelGGL((dwx_group_kernel<CL, false>), dim3(ranges, slices), dim3(kGroupThreads), 0, s, x, Delta, scratch, slot_table, N, NV, H); \
-        else hipLaunchKernelGGL((dwx_group_kernel<CL, true>), dim3(ranges, slices), dim3(kGroupThreads), 0, s, x, Delta, scratch, slot_table, N, NV, H);         \
+        if (H >= 4) hipLaunchKernelGGL((dwx_group_kernel<CL, false>), grid, dim3(kGroupThreads), 0, s, x, Delta, scratch, slot_table, N, NV, H, slices, a, b); \
+        else hipLaunchKernelGGL((dwx_group_kernel<CL, true>), grid, dim3(kGroupThreads), 0, s, x, Delta, scratch, slot_table, N, NV, H, slices, a, b);         \
     } while (0)
         switch (cl) {
             case 256: RNN_GROUP(256); break;
@@ -308,17 +303,25 @@ hipError_t launch_dwx_tokens(const int32_t* x, const float* Delta, float* dWx, i
             default: RNN_GROUP(4096); break;
         }
 #undef RNN_GROUP
-        hipError_t e = hipGetLastError();
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     ProfileScope ps(K_DWX_TOKENS, s);
-    const int col_chunks = (H + 4 * kWave - 1) / (4 * kWave);
+    const int rows_per_block = 256 / kWave, col_chunks = (H + 4 * kWave - 1) / (4 * kWave);
     const long long tasks = (long long)NV * col_chunks;
     const unsigned gb = (unsigned)((tasks + rows_per_block - 1) / rows_per_block);
     if (H >= 4) hipLaunchKernelGGL(dwx_gather_kernel<false>, dim3(gb), dim3(256), 0, s, scratch, slot_table, Delta, dWx,
                                    NV, H, ranges, cl, beta, col_chunks);
     else hipLaunchKernelGGL(dwx_gather_kernel<true>, dim3(gb), dim3(256), 0, s, scratch, slot_table, Delta, dWx,
                             NV, H, ranges, cl, beta, col_chunks);
+    return hipGetLastError();
+}
+
+hipError_t launch_dwx_tokens(const int32_t* x, const float* Delta, float* dWx, int N, int NV, int H, int beta, hipStream_t s) {
+    const int rows_per_block = 256 / kWave;
+    const int blocks = (NV + rows_per_block - 1) / rows_per_block;
+    ProfileScope ps(K_DWX_TOKENS, s);
+    hipLaunchKernelGGL(dwx_tokens_kernel, dim3(blocks), dim3(256), 0, s, x, Delta, dWx, N, NV, H, beta);
     return hipGetLastError();
 }
 
