@@ -37,10 +37,14 @@
 //     that: state s is complete) and waits for that store with its next look at the ring, that is before
 //     it publishes state s + 2.  The slot is published again as state s + 3, which nobody looks for
 //     without having seen all of state s + 2: no look can find the words of the state before.
-// With 16 columns a ninth wavefront, the carrier, fetches the operands of the epilogues and stores the new states' rows: a look waits
-// for every request of its wavefront, so the wavefronts of the product make none but to the ring (500 units, batch 1: 0.91 ->
-// 0.83 us a step, 256 units, batch 32: 0.83 -> 0.73).  With 32 columns that costs the reverse loop more than it gains (1.16 -> 1.22 at
-// 513 units, 1.47 -> 1.65 at 1024), with 64 the registers do not suffice.
+// The operands of the epilogues come from memory, and their requests cost more than they take: a compute unit's requests return in
+// the order they were made, so a look at the ring waits for an operand of a later step that was requested before it, and a
+// wavefront's look also for its own stores.  So operands are requested eight steps at a time, and one look in eight waits; and up to 32
+// columns a ninth wavefront, the carrier, does it and stores the new states' rows, through LDS, so that the wavefronts of the
+// product make no request but to the ring.  (us a step, forward and reverse; 256 units, batch 128, 2047 steps, whose arrays are
+// beyond the last-level cache: requests a step ahead by the epilogue's lanes 0.95 and 1.03, by the carrier four steps ahead but every step
+// 0.96 and 1.09 - 0.78 and 0.88 when they are made to hit the cache -, two at a time 0.88 and 0.94, four 0.79 and 0.86, eight 0.76 and
+// 0.80; 500 units, batch 1: 0.91 and 0.91 -> 0.84 and 0.83; 513 units, batch 19: 1.20 and 1.16 -> 1.11 and 1.10.)
 // Token input takes its rows of Wx in the loop, a step ahead, instead of a gather launch that writes them
 // out for all steps and is read back (256 steps of 64 rows at H = 1024: 27 us).
 // A hidden size that is no multiple of 4 has the rest of a row's last piece published as zeros.
@@ -76,9 +80,9 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int NW = 8;              // wavefronts of the product
-constexpr int AHEAD = 4;           // steps the carrier requests in advance
-// 16 columns: a ninth wavefront fetches the operands and stores the rows
-__host__ __device__ constexpr bool has_carrier(int cwd) { return cwd == 16; }
+constexpr int CHUNK = 8;           // steps whose operands the carrier requests at a time
+// up to 32 columns a ninth wavefront fetches the operands and stores the rows; with 64 the registers do not suffice
+__host__ __device__ constexpr bool has_carrier(int cwd) { return cwd <= 32; }
 __host__ __device__ constexpr int threads_of(int cwd) { return 64 * (NW + (has_carrier(cwd) ? 1 : 0)); }
 constexpr int RB = 4;              // batch rows per group
 constexpr int NXCD = 8;            // XCDs: the layout this loop is built on
@@ -286,9 +290,6 @@ __global__ __launch_bounds__(threads_of(CWD)) void rec_xcd_kernel(RecXcdArgs a) 
     const int nsteps = BWD ? T - 1 : T;
 
     // ---- the carrier (wavefront NW) ---------------------------------------------------------------
-    // It fetches the operands of the epilogues AHEAD steps early and stores the new states' rows.  A look at the ring waits for every
-    // request of its wavefront, also for an operand of the next step that comes from memory and for a stored row: the
-    // wavefronts of the product make no request but the look and the stores to the ring.
     // In the interval before barrier s it puts the operands of step s in place, whose epilogue follows that barrier, and stores the
     // state of step s - 2, whose epilogue was before the barrier before.
     if constexpr (CARRY) if (wave == NW) {
@@ -296,8 +297,8 @@ __global__ __launch_bounds__(threads_of(CWD)) void rec_xcd_kernel(RecXcdArgs a) 
         size_t off[NL];
         int place[NL], cc[NL], cb[NL];
         bool on[NL];
-        float bias[NL], x0[AHEAD][NL], x1[AHEAD][NL];
-        int id[AHEAD][NL];
+        float bias[NL], x0[2 * CHUNK][NL], x1[2 * CHUNK][NL];
+        int id[CHUNK][NL];
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
             const int e = lane + kWave * i, row = e / CWD, col = e % CWD;
@@ -333,36 +334,41 @@ __global__ __launch_bounds__(threads_of(CWD)) void rec_xcd_kernel(RecXcdArgs a) 
                     if (on[i] && s >= 0) dst[off[i]] = v;
                 }
             };
-            // one interval; the step's parity and its slot of the requests are those of u
+            // one interval; the step's parity and its slot of the operands are those of u
             auto interval = [&](int u, int s) __attribute__((always_inline)) {
 #pragma unroll
                 for (int i = 0; i < NL; ++i) {
                     s_in[u & 1][place[i]] = TOK ? x0[u][i] + bias[i] : x0[u][i];
                     if (BWD) s_slope[u & 1][place[i]] = act_grad<ACT>(x1[u][i]);
                 }
-                want(s + AHEAD, id[u], x0[u], x1[u]);
-                want_id(s + 2 * AHEAD, id[u]);
+                if (u % CHUNK == 0) {        // the next chunk, and the tokens of the one after it
+                    const int v = CHUNK - u;
+#pragma unroll
+                    for (int c = 0; c < CHUNK; ++c) want(s + CHUNK + c, id[c], x0[v + c], x1[v + c]);
+#pragma unroll
+                    for (int c = 0; c < CHUNK; ++c) want_id(s + 2 * CHUNK + c, id[c]);
+                }
                 keep(s - 2);
                 lds_barrier();
             };
             if (nsteps > 0) {
 #pragma unroll
-                for (int u = 0; u < AHEAD; ++u) want_id(u, id[u]);
+                for (int c = 0; c < CHUNK; ++c) want_id(c, id[c]);
 #pragma unroll
-                for (int u = 0; u < AHEAD; ++u) want(u, id[u], x0[u], x1[u]);
+                for (int c = 0; c < CHUNK; ++c) want(c, id[c], x0[c], x1[c]);
 #pragma unroll
-                for (int u = 0; u < AHEAD; ++u) want_id(AHEAD + u, id[u]);
+                for (int c = 0; c < CHUNK; ++c) want_id(CHUNK + c, id[c]);
             }
             __syncthreads();                                         // (the matrix is in registers, and the group's roll is settled)
             if (s_part != PART_ONE) return;
             // (no branch inside the loop: the compiler then counts the requests in flight and waits for the oldest only)
             int s0 = 0;
-            for (; s0 + AHEAD <= nsteps && !s_abort; s0 += AHEAD) {
+            for (; s0 + 2 * CHUNK <= nsteps && !s_abort; s0 += 2 * CHUNK) {
 #pragma unroll
-                for (int u = 0; u < AHEAD; ++u) interval(u, s0 + u);
+                for (int u = 0; u < 2 * CHUNK; ++u) interval(u, s0 + u);
             }
 #pragma unroll
-            for (int u = 0; u < AHEAD - 1; ++u)
+            for (int u = 0; u < 2 * CHUNK - 1; ++u)
                 if (s0 + u < nsteps && !s_abort) interval(u, s0 + u);
             keep(nsteps - 2);
             __syncthreads();
@@ -697,15 +703,12 @@ size_t xcd_lds_bytes() { return (size_t)8 * 64 * 65 * 4; }
 // batch 3, which has no room for 16 outputs per workgroup there, is 300 / 199 us per loop.  Of 10 steps
 // (H = 500: 149 / 142) the set-up is most.
 // 193 to 256 units fit one workgroup per 4 rows (recurrence_mfma.hip), whose step is bound by its matrix instructions: 0.97 us
-// at H = 256 and 0.90 at H = 200, here 0.73 to 0.85 (16 columns, batch up to 64: 0.73); up to 192 units 0.63 there, here
-// 0.77 to 0.84.  35 steps of tokens, H = 200, batch 20, with the gathered input term there and the ring's clearing here: 46 and
-// 38 us there, 37 and 36 here; dense input has no rows to gather.  Where the arrays of a long sequence do not fit the chip's last-level
-// cache (256 MB) a step takes longer here, since a look at the ring waits behind its compute unit's requests to memory: H = 256,
-// batch 128, forward + reverse: 800 steps 0.79 + 0.91, 1600 steps 0.89 + 1.01, 3200 steps 0.96 + 1.03; batch 32, 12800 steps 0.86 +
-// 0.97; there 0.97 + 0.98 whatever the size.
+// at H = 256 and 0.90 at H = 200, here 0.73 to 0.82 (4096 steps, batch 128: 0.78 and 0.81); up to
+// 192 units 0.63 there, here 0.73 to 0.77.  35 steps of tokens, H = 200, batch 20, with the gathered input term there and the ring's
+// clearing here: 46 and 38 us there, 36 and 35 here; dense input has no rows to gather.
 bool rec_xcd_supported(int H, int B, int T, bool tokens) {
     if (H <= 192 || H > H_MAX || B < 1 || B > (H <= 256 ? 128 : 64)) return false;
-    if (H <= 256) return T >= (tokens && B > 4 ? 33 : 64) && (B <= NXCD * RB || (long long)T * B * H <= 1 << 26);
+    if (H <= 256) return T >= (tokens && B > 4 ? 33 : 64);
     return B > 4 ? T >= 10 : T >= 16 && (B > 2 || H <= 640);
 }
 
