@@ -81,6 +81,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int NW = 8;              // wavefronts of the product
 constexpr int CHUNK = 8;           // steps whose operands the carrier requests at a time
+constexpr int OWN_CHUNK = 4;       // the same of the epilogue's lanes where there is no carrier
 // up to 32 columns a ninth wavefront fetches the operands and stores the rows; with 64 the registers do not suffice
 __host__ __device__ constexpr bool has_carrier(int cwd) { return cwd <= 32; }
 __host__ __device__ constexpr int threads_of(int cwd) { return 64 * (NW + (has_carrier(cwd) ? 1 : 0)); }
@@ -506,32 +507,36 @@ __global__ __launch_bounds__(threads_of(CWD)) void rec_xcd_kernel(RecXcdArgs a) 
         }
     }
     const int e_at = 64 / S * (wave & 3) + ej;     // this lane's element in the tiles of the carrier
-    // Without a carrier: operands of the epilogue of step s, requested a step ahead (clamped: always valid).  Token input takes the
-    // row of Wx itself; the row's number is requested another step ahead.
-    auto step_of = [&](int s) { return max(min(s, nsteps - 1), 0); };
-    const float bias = !BWD && a.x && wave < 4 ? a.b[min(ec, H - 1)] : 0.f;
+    // Without a carrier: the operands of OWN_CHUNK steps are requested together, a chunk ahead (clamped: always valid), and kept in
+    // places of LDS of the lane's own.  Token input takes the rows of Wx itself; their numbers are requested another chunk ahead.
+    float* own = smem + 2 * NW * RB * 64 + tid;        // [OWN_CHUNK][2][256]
+    const float bias = !CARRY && !BWD && a.x && wave < 4 ? a.b[min(ec, H - 1)] : 0.f;
     const int eb = min(b0 + em, B - 1);
-    int id = 0;                            // token of this lane's row at the step after the one last requested
-    auto load_id = [&](int s) {
-        if (!BWD && a.x) id = a.x[(size_t)step_of(s) * B + eb];
+    int id[OWN_CHUNK];
+    float n0[OWN_CHUNK], n1[OWN_CHUNK];
+    auto step_of = [&](int s) { return max(min(s, nsteps - 1), 0); };
+    auto load_ids = [&](int s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < OWN_CHUNK; ++c) id[c] = !BWD && a.x ? a.x[(size_t)step_of(s + c) * B + eb] : 0;
     };
-    auto load_epi = [&](int s, float& x0, float& x1) {
-        const int sc = step_of(s);
-        const size_t base = (size_t)(BWD ? max(T - 2 - sc, 0) : sc) * bh;
-        if (BWD) {
-            x0 = a.G[base + e_off];
-            x1 = a.h_all[base + bh + e_off];
-        } else if (a.x) {
-            x0 = a.Wx[(size_t)id * H + min(ec, H - 1)];
-        } else {
-            x0 = a.U[base + e_off];
+    auto load_chunk = [&](int s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < OWN_CHUNK; ++c) {
+            const int sc = step_of(s + c);
+            const size_t base = (size_t)(BWD ? max(T - 2 - sc, 0) : sc) * bh;
+            n1[c] = 0.f;
+            if (BWD) {
+                n0[c] = a.G[base + e_off];
+                n1[c] = a.h_all[base + bh + e_off];
+            } else {
+                n0[c] = a.x ? a.Wx[(size_t)id[c] * H + min(ec, H - 1)] : a.U[base + e_off];
+            }
         }
     };
-    float n0[2] = {0.f, 0.f}, n1[2] = {0.f, 0.f};
     if (!CARRY && wave < 4) {
-        load_id(0);
-        load_epi(0, n0[0], n1[0]);
-        load_id(1);
+        load_ids(0);
+        load_chunk(0);
+        load_ids(OWN_CHUNK);
     }
 
     XT_DECL;
@@ -590,9 +595,14 @@ __global__ __launch_bounds__(threads_of(CWD)) void rec_xcd_kernel(RecXcdArgs a) 
     auto step = [&](int s, auto slot_c, bool fetch_next) __attribute__((always_inline)) {
         constexpr int SLOT = decltype(slot_c)::value;   // s & 1: partial buffer and operand slot
         XTM(0);
-        if (!CARRY && wave < 4) {
-            load_epi(s + 1, n0[SLOT ^ 1], n1[SLOT ^ 1]);
-            load_id(s + 2);
+        if (!CARRY && wave < 4 && s % OWN_CHUNK == 0) {
+#pragma unroll
+            for (int c = 0; c < OWN_CHUNK; ++c) {
+                own[512 * c] = BWD ? n0[c] : n0[c] + bias;
+                if (BWD) own[512 * c + 256] = act_grad<ACT>(n1[c]);
+            }
+            load_chunk(s + OWN_CHUNK);
+            load_ids(s + 2 * OWN_CHUNK);
         }
         park_partial(SLOT, product());
         XTM(1);
@@ -602,8 +612,8 @@ __global__ __launch_bounds__(threads_of(CWD)) void rec_xcd_kernel(RecXcdArgs a) 
         float* dst = BWD ? a.Delta + (size_t)t * bh : a.hist + (size_t)(s + 1) * bh;
         float* box = a.ring + (size_t)((s + 1) % RSLOTS) * rstate;
         if (wave < 4) {
-            const float in = CARRY ? s_in[SLOT][e_at] : BWD ? n0[SLOT] : n0[SLOT] + bias;
-            const float slope = !BWD ? 0.f : CARRY ? s_slope[SLOT][e_at] : act_grad<ACT>(n1[SLOT]);
+            const float in = CARRY ? s_in[SLOT][e_at] : own[512 * (s % OWN_CHUNK)];
+            const float slope = !BWD ? 0.f : CARRY ? s_slope[SLOT][e_at] : own[512 * (s % OWN_CHUNK) + 256];
             const float sum = tile_sum(SLOT);
             float v = BWD ? (sum + in) * slope : activate<ACT>(sum + in);
             if (__float_as_uint(v) == kSentinel) v = __uint_as_float(0x7FC00000u);   // a NaN that came in as all ones
