@@ -14,6 +14,9 @@
 // The reverse-loop workgroup combines the strips' shares of G with the weights
 // exp(strip max - lse), in strip order.
 //
+// The barriers order LDS only: nothing here reads back what it has stored to memory, and a store's acknowledgement takes longer than
+// a phase.  (32 rows of 16 units, 64 columns: 20.4 us with full barriers, halves combined by shuffles and a row of vy at a time.)
+//
 // Thread layout inside a strip: lane%32 = a quad of 4 adjacent columns, tid/32 = one of 16
 // groups that split the hidden dimension.  Requires NV % 4 == 0 (16-byte column quads).
 #include "common.hpp"
@@ -61,9 +64,9 @@ __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
     if (tid < N) s_y[tid] = a.y[tid];
 
     for (int n0 = 0; n0 < N; n0 += NR) {
-        __syncthreads();
+        lds_barrier();
         load_rows(a.Hs, hs, n0, N, H, tid);
-        __syncthreads();
+        lds_barrier();
         float4 acc[NR];
 #pragma unroll
         for (int r = 0; r < NR; ++r) acc[r] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -85,16 +88,13 @@ __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
                 }
             }
         }
-        // the two H-groups of a wavefront combine by shuffle, the four wavefronts through LDS
+        // the two H-groups of a wavefront combine by a lane swap, the wavefronts through LDS
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
-            acc[r].x += __shfl_xor(acc[r].x, 32, kWave);
-            acc[r].y += __shfl_xor(acc[r].y, 32, kWave);
-            acc[r].z += __shfl_xor(acc[r].z, 32, kWave);
-            acc[r].w += __shfl_xor(acc[r].w, 32, kWave);
+            acc[r] = make_float4(swap32_sum(acc[r].x), swap32_sum(acc[r].y), swap32_sum(acc[r].z), swap32_sum(acc[r].w));
             if (lane < 32) *reinterpret_cast<float4*>(red + (wave * NR + r) * CW + 4 * kq) = acc[r];
         }
-        __syncthreads();
+        lds_barrier();
         for (int e = tid; e < NR * CW; e += NTH) {   // NTH is a multiple of CW: column = tid % CW
             const int r = e / CW, c = e % CW;
             float z = red[r * CW + c];
@@ -104,7 +104,7 @@ __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
             red[r * CW + c] = z;
             if (kc_own < O && n0 + r < N) a.Z[(size_t)(n0 + r) * O + kc_own] = z;
         }
-        __syncthreads();
+        lds_barrier();
         // strip statistics: one wavefront per row; the row's exp(z - strip max) stays in LDS
         for (int r = wave; r < NR; r += NWV) {
             float e0 = 0.f, e1 = 0.f;
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
             es[r * ES + lane] = e0;
             es[r * ES + 64 + lane] = e1;
         }
-        __syncthreads();
+        lds_barrier();
         // Backward needs G = (softmax - onehot) V^T / N.  With w = exp(strip max - lse) the softmax
         // part is sum over strips of w * P, P[r][i] = sum_c exp(z[r][c] - strip max) V[i][c], and P
         // needs only what this workgroup already holds (its strip of V in registers, the
@@ -151,13 +151,12 @@ __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
 #pragma unroll
                 for (int u = 0; u < NB; ++u)     // rows past H are zeros
                     *reinterpret_cast<float4*>(Vs + (IG * u + ig) * ES + 4 * kq) = v[u];
-                __syncthreads();
+                lds_barrier();
                 if (any_y) {               // column y_n of V for the rows whose target is here
-                    for (int r = 0; r < NR && n0 + r < N; ++r) {
-                        const int y = s_y[n0 + r] - blockIdx.x * CW;
-                        if (y < 0 || y >= CW) continue;
-                        for (int i = tid; i < IG * NB && i0 + i < H; i += NTH)
-                            a.vy[(size_t)(n0 + r) * H + i0 + i] = Vs[i * ES + y];
+                    const int rows = min(NR, N - n0), len = min(IG * NB, H - i0);
+                    for (int e = tid; e < rows * len; e += NTH) {
+                        const int r = e / len, i = e - r * len, y = s_y[n0 + r] - blockIdx.x * CW;
+                        if (y >= 0 && y < CW) a.vy[(size_t)(n0 + r) * H + i0 + i] = Vs[i * ES + y];
                     }
                 }
                 const int itile = i0 + 16 * wave;          // first hidden row of this wavefront's tile
@@ -185,7 +184,7 @@ __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
                         }
                     }
                 }
-                __syncthreads();           // the next batch overwrites Vs
+                lds_barrier();           // the next batch overwrites Vs
             }
         }
     }
@@ -198,7 +197,7 @@ __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
     __shared__ float rl[32];
     __shared__ int s_fail;
     if (tid == 0) s_fail = 0;
-    __syncthreads();                     // also: `red` is free from here on
+    lds_barrier();                     // also: `red` is free from here on
     const int strips = gridDim.x;
     const int spin_limit = a.spin_limit;
     const unsigned epoch = a.epoch;
@@ -233,7 +232,7 @@ __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
             zys[tid] = tagged_value(wz);
         }
         consume(wz);
-        __syncthreads();
+        lds_barrier();
         for (int n = n_lo + wave; n < n_hi; n += NWV) {
             float m = -INFINITY, sum = 0.f;
             for (int g = lane; g < strips; g += kWave) {
@@ -250,7 +249,7 @@ __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
                 rl[n] = l - zys[n];
             }
         }
-        __syncthreads();
+        lds_barrier();
     }
     if (tid == 0) {
         if (s_fail) atomicExch(a.status, 1);
