@@ -15,7 +15,9 @@
 // exp(strip max - lse), in strip order.
 //
 // The barriers order LDS only: nothing here reads back what it has stored to memory, and a store's acknowledgement takes longer than
-// a phase.  (32 rows of 16 units, 64 columns: 20.4 us with full barriers, halves combined by shuffles and a row of vy at a time.)
+// a phase.  (32 rows of 16 units, 64 columns: 20.4 us with full barriers, halves combined by shuffles and a row of vy at a time; 14.4
+// with those gone; 12.2 with rows and vy addressed without divisions, the second pass's rows requested early and the
+// statistics of a single strip merged from LDS.)
 //
 // Thread layout inside a strip: lane%32 = a quad of 4 adjacent columns, tid/32 = one of 16
 // groups that split the hidden dimension.  Requires NV % 4 == 0 (16-byte column quads).
@@ -33,6 +35,7 @@ using namespace skinny;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int ES = CW + 4;   // padded LDS row of 128 columns
+constexpr int AHEAD = 4;     // words of the next pass's rows a thread holds (128 hidden units)
 
 __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
     extern __shared__ __attribute__((aligned(16))) float smem[];
@@ -62,10 +65,23 @@ __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
     const bool one_batch = H <= IG * NB;
     __shared__ int s_y[32];
     if (tid < N) s_y[tid] = a.y[tid];
+    // The statistics of a single strip do not leave the workgroup: they are merged from here.
+    __shared__ float s_own[2 * 32], zys[32];
+    __shared__ int s_fail;
+    const bool alone = gridDim.x == 1;
+    if (alone && tid == 0) s_fail = 0;
 
+    // The rows of the second pass are requested in front of the first one's stores: memory answers a wavefront in order, so behind
+    // them they would wait for their acknowledgements.
+    float rows[AHEAD];
+    const bool ahead = (NR << row_shift(H)) <= AHEAD * NTH;
     for (int n0 = 0; n0 < N; n0 += NR) {
         lds_barrier();
-        load_rows(a.Hs, hs, n0, N, H, tid);
+        if (ahead && n0 > 0) {
+            park_rows(rows, hs, 0, H, tid);
+        } else {
+            load_rows(a.Hs, hs, n0, N, H, tid);
+        }
         lds_barrier();
         float4 acc[NR];
 #pragma unroll
@@ -95,6 +111,7 @@ __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
             if (lane < 32) *reinterpret_cast<float4*>(red + (wave * NR + r) * CW + 4 * kq) = acc[r];
         }
         lds_barrier();
+        if (ahead && n0 + NR < N) request_rows(a.Hs, rows, 0, n0 + NR, N, H, tid);
         for (int e = tid; e < NR * CW; e += NTH) {   // NTH is a multiple of CW: column = tid % CW
             const int r = e / CW, c = e % CW;
             float z = red[r * CW + c];
@@ -123,6 +140,12 @@ __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
                     tagged_store(st + 1, a.epoch, s);
                     if (y >= 0 && y < CW)
                         tagged_store(a.stat_box + (size_t)N * gridDim.x * 2 + n0 + r, a.epoch, zy);
+                    if (alone) {
+                        s_own[2 * (n0 + r)] = m;
+                        s_own[2 * (n0 + r) + 1] = s;
+                        zys[n0 + r] = zy;
+                        if (!(y >= 0 && y < CW)) s_fail = 1;   // as the word that nobody sends
+                    }
                 }
             }
             es[r * ES + lane] = e0;
@@ -140,11 +163,9 @@ __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
         // group g = lane/16 walks the columns 32g..32g+31, so both operands are 16-byte LDS reads
         // (rows are ES = CW+4 words apart: 16 rows spread over all banks).
         {
-            bool any_y = false;            // does a target of this pass fall into this strip?
-            for (int r = 0; r < NR && n0 + r < N; ++r) {
-                const int y = s_y[n0 + r] - blockIdx.x * CW;
-                any_y = any_y || (y >= 0 && y < CW);
-            }
+            // does a target of this pass fall into this strip?
+            const int y_lane = lane < NR && n0 + lane < N ? s_y[n0 + lane] - (int)blockIdx.x * CW : -1;
+            const bool any_y = __ballot(y_lane >= 0 && y_lane < CW) != 0;
             const int mrow = lane % 16, g = lane / 16;
             for (int i0 = 0; i0 < H; i0 += IG * NB) {
                 if (!one_batch) load_v(i0 + ig, v);
@@ -154,9 +175,10 @@ __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
                 lds_barrier();
                 if (any_y) {               // column y_n of V for the rows whose target is here
                     const int rows = min(NR, N - n0), len = min(IG * NB, H - i0);
-                    for (int e = tid; e < rows * len; e += NTH) {
-                        const int r = e / len, i = e - r * len, y = s_y[n0 + r] - blockIdx.x * CW;
-                        if (y >= 0 && y < CW) a.vy[(size_t)(n0 + r) * H + i0 + i] = Vs[i * ES + y];
+                    const int sh = row_shift(len);
+                    for (int e = tid; e < rows << sh; e += NTH) {
+                        const int r = e >> sh, i = e & ((1 << sh) - 1), y = s_y[n0 + r] - (int)blockIdx.x * CW;
+                        if (i < len && y >= 0 && y < CW) a.vy[(size_t)(n0 + r) * H + i0 + i] = Vs[i * ES + y];
                     }
                 }
                 const int itile = i0 + 16 * wave;          // first hidden row of this wavefront's tile
@@ -195,8 +217,7 @@ __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
     // bounded all the same.
     if (blockIdx.x != gridDim.x - 1) return;
     __shared__ float rl[32];
-    __shared__ int s_fail;
-    if (tid == 0) s_fail = 0;
+    if (!alone && tid == 0) s_fail = 0;
     lds_barrier();                     // also: `red` is free from here on
     const int strips = gridDim.x;
     const int spin_limit = a.spin_limit;
@@ -205,16 +226,16 @@ __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
     // LDS, and merged from there: the waiting costs about one memory round trip in total.
     int span = 1;                        // lanes that hold strips: a power of two
     while (span < strips && span < kWave) span *= 2;
-    float* stage = red;                  // NWV*NR*CW floats >= 2*strips (checked by the host)
-    __shared__ float zys[32];
+    float* stage = alone ? s_own : red;  // NWV*NR*CW floats >= 2*strips (checked by the host)
     const unsigned long long* zybox = a.stat_box + (size_t)N * strips * 2;
-    unsigned long long wz = tagged_load(zybox + min(tid, N - 1));   // in flight with the rest
+    unsigned long long wz = 0;
+    if (!alone) wz = tagged_load(zybox + min(tid, N - 1));   // in flight with the rest
     const int rows_per_pass = max(1, (NWV * NR * CW) / (2 * strips));
     for (int n_lo = 0; n_lo < N; n_lo += rows_per_pass) {
         const int n_hi = min(N, n_lo + rows_per_pass);
         const int cnt = (n_hi - n_lo) * strips * 2;
         const unsigned long long* src = a.stat_box + (size_t)n_lo * strips * 2;
-        for (int w0 = tid; w0 < cnt; w0 += 4 * NTH) {
+        for (int w0 = alone ? cnt : tid; w0 < cnt; w0 += 4 * NTH) {
             unsigned long long w[4];
             long long idx[4];
 #pragma unroll
@@ -224,7 +245,7 @@ __global__ __launch_bounds__(NTH) void skinny_logits_kernel(SkinnyArgs a) {
             for (int u = 0; u < 4; ++u)
                 if (idx[u] >= 0) stage[idx[u]] = tagged_value(w[u]);
         }
-        if (n_lo == 0 && tid < N) {
+        if (!alone && n_lo == 0 && tid < N) {
             for (int spins = 0; !tagged_ok(wz, epoch); ++spins) {
                 if (spins > spin_limit) { s_fail = 1; break; }
                 wz = tagged_load(zybox + tid);

@@ -18,24 +18,36 @@ constexpr int IG = NTH / QW;   // groups splitting the H dimension (16)
 constexpr int NWV = NTH / 64;  // wavefronts per workgroup (8)
 constexpr int NB = 8;          // independent 16-byte loads in flight per thread
 
-// hidden rows of one pass into LDS as hs[i][NR] (zero padded rows)
+// Hidden rows of one pass: word e of them is unit e % P of row e / P, P the power of two from H on (a division by H takes
+// longer than the words it saves).
+__device__ __forceinline__ int row_shift(int H) { return 32 - __builtin_clz(H - 1 | 1) - (H == 1); }
+// words base .. (M a thread; zeros past the last row), and their place in LDS, hs[i][NR]
+template <int M>
+__device__ __forceinline__ void request_rows(const float* __restrict__ Hs, float (&t)[M], int base, int n0, int N, int H, int tid) {
+    const int sh = row_shift(H);
+#pragma unroll
+    for (int u = 0; u < M; ++u) {
+        const int e = base + tid + u * NTH;
+        const int r = e >> sh, i = e & ((1 << sh) - 1);     // coalesced along i
+        t[u] = (r < NR && i < H && n0 + r < N) ? Hs[(size_t)(n0 + r) * H + i] : 0.f;
+    }
+}
+template <int M>
+__device__ __forceinline__ void park_rows(const float (&t)[M], float* hs, int base, int H, int tid) {
+    const int sh = row_shift(H);
+#pragma unroll
+    for (int u = 0; u < M; ++u) {
+        const int e = base + tid + u * NTH;
+        const int r = e >> sh, i = e & ((1 << sh) - 1);
+        if (r < NR && i < H) hs[i * NR + r] = t[u];
+    }
+}
 __device__ __forceinline__ void load_rows(const float* __restrict__ Hs, float* hs, int n0, int N,
                                           int H, int tid) {
-    const int n = H * NR;
-    for (int base = tid; base < n; base += NB * NTH) {
+    for (int base = 0; base < NR << row_shift(H); base += NB * NTH) {
         float t[NB];
-#pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            const int e = base + u * NTH;
-            const int r = e / H, i = e - r * H;            // coalesced along i
-            t[u] = (e < n && n0 + r < N) ? Hs[(size_t)(n0 + r) * H + i] : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            const int e = base + u * NTH;
-            const int r = e / H, i = e - r * H;
-            if (e < n) hs[i * NR + r] = t[u];
-        }
+        request_rows(Hs, t, base, n0, N, H, tid);
+        park_rows(t, hs, base, H, tid);
     }
 }
 

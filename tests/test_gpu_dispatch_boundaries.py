@@ -183,3 +183,19 @@ def test_the_one_launch_wide_loop_below_257_units(H):
         last.forward()
         torch.cuda.synchronize()
         assert np.max(np.abs(last.h_last.cpu().numpy() - ref["h_all"][-1])) <= 2e-5
+
+
+@pytest.mark.parametrize("NV,H,T", ((4, 1, 17), (64, 2, 16), (64, 16, 32), (128, 17, 16), (128, 33, 17), (128, 128, 32), (132, 1, 32),
+                                    (132, 64, 17), (260, 65, 31), (260, 128, 33)))
+def test_the_column_strips_of_short_sequences_at_their_edges(NV, H, T):
+    """One strip of 128 columns and more, one pass of 16 rows and two, hidden sizes at and beside powers of two; 33 rows are
+    beyond the strips. Twice, the second time with the words of the first still in the exchange boxes."""
+    case = ri.make_case(in_dim=NV, hidden=H, out_dim=NV, seq_len=T, batch=1, act=T % 2, with_h0=bool(T % 2),
+                        wdist=("normal", 0.5 / np.sqrt(H)), bias_std=0.1, seed=77000 + 100 * H + T)
+    r = Runner(case)
+    ref = oracle.fwd_bptt(case, h0=case.get("h0"))
+    for _ in range(2):
+        print(f"NV={NV} H={H} T={T}", flush=True)
+        r.step()
+        assert rnn.rnn_workspace_status(r.dims, r.ws) == 0
+        compare(r.results(), ref)
