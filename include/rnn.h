@@ -175,12 +175,32 @@ int rnn_check_tokens(const void *ids, int64_t n, int32_t limit, int32_t *bad_cou
  * the process, read when a call is enqueued; default 2^22, about a second; polls <= 0 restores the
  * default).  For callers that share the GPU and prefer an early status 1 to a long spin, and for
  * tests of the failure path.
+ *
+ * The wide loop (rnn_recurrence_variant "xcd_mfma") first waits until the workgroups of a group have all
+ * started.  That wait is bounded by time and not by this limit, and its end is no failure: if other work
+ * keeps a part of the group off the GPU, one of the workgroups that did start computes the group by itself,
+ * up to a hundred times as slowly, the status stays 0 and the results are valid.  The time is what that
+ * workgroup would take, 0.2 ms at least and 2 s at most.  The limit holds for the waits of the loop that
+ * follows.
  */
 int rnn_set_wait_limit(int polls);
 int rnn_workspace_init(const rnn_dims *dims, void *workspace, size_t workspace_bytes,
                        void *hip_stream);
 int rnn_workspace_status(const rnn_dims *dims, const void *workspace, size_t workspace_bytes,
                          void *hip_stream, int32_t *status_host);
+
+/*
+ * For tests and reports of the wide loop's first wait.
+ * rnn_workspace_groups_alone: how many groups of the last wide loop on this workspace one workgroup
+ * computed by itself (copied to *groups_host; synchronises the stream); RNN_EUNSUPPORTED if these sizes
+ * are served by another loop.
+ * rnn_test_roll_call: for launches that the calling thread enqueues from now on, microseconds >= 0
+ * replaces the time of that wait, and with absent != 0 every group waits for one workgroup more than it
+ * has, as if that one never started.  (-1, 0) restores the normal behaviour.
+ */
+int rnn_workspace_groups_alone(const rnn_dims *dims, const void *workspace, size_t workspace_bytes,
+                               void *hip_stream, int32_t *groups_host);
+int rnn_test_roll_call(int microseconds, int absent);
 
 /*
  * Many consecutive truncated-BPTT windows of ONE token stream with a plain SGD update after

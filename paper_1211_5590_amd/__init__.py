@@ -10,6 +10,7 @@ from .binding import (  # noqa: F401
     exported_symbols, lib, lib_path, rnn_bptt, rnn_check_tokens, rnn_forward, rnn_loss, rnn_measure_ceilings,
     rnn_profile_begin, rnn_profile_end, rnn_recurrence_variant, rnn_recurrence_workgroups, rnn_strerror,
     rnn_workspace_bytes, rnn_workspace_init, rnn_workspace_status, rnn_set_wait_limit,
+    rnn_workspace_groups_alone, rnn_test_roll_call,
     rnn_train_stream, rnn_train_stream_status, rnn_train_stream_workspace_bytes,
     rnn_window, rnn_window_one_launch, rnn_window_workspace_bytes, rnn_window_workspace_init, rnn_window_static, WINDOW_STATIC_BYTES,
     GN_METRIC_IDENTITY, GN_METRIC_LOSS, rnn_gauss_newton_vec, rnn_gauss_newton_workspace_bytes,

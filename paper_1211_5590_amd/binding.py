@@ -25,7 +25,8 @@ EXPORTS = ("rnn_workspace_bytes", "rnn_forward", "rnn_loss", "rnn_bptt", "rnn_ch
            "rnn_workspace_status", "rnn_train_stream_workspace_bytes", "rnn_train_stream",
            "rnn_train_stream_status", "rnn_window_one_launch", "rnn_window_workspace_bytes", "rnn_window_workspace_init",
            "rnn_window", "rnn_window_static", "rnn_gauss_newton_workspace_bytes", "rnn_gauss_newton_vec",
-           "rnn_mlp_workspace_bytes", "rnn_mlp_train", "rnn_measure_ceilings")
+           "rnn_mlp_workspace_bytes", "rnn_mlp_train", "rnn_measure_ceilings",
+           "rnn_workspace_groups_alone", "rnn_test_roll_call")
 MLP_MAX_LAYERS = 16
 GN_METRIC_LOSS, GN_METRIC_IDENTITY = 0, 1
 
@@ -105,6 +106,10 @@ def lib():
         L.rnn_workspace_status.argtypes = [ctypes.POINTER(Dims), vp, sz, vp, ctypes.POINTER(ctypes.c_int32)]
         L.rnn_set_wait_limit.argtypes = [ctypes.c_int]
         L.rnn_set_wait_limit.restype = ctypes.c_int
+        L.rnn_workspace_groups_alone.argtypes = [ctypes.POINTER(Dims), vp, sz, vp, ctypes.POINTER(ctypes.c_int32)]
+        L.rnn_workspace_groups_alone.restype = ctypes.c_int
+        L.rnn_test_roll_call.argtypes = [ctypes.c_int, ctypes.c_int]
+        L.rnn_test_roll_call.restype = ctypes.c_int
         L.rnn_workspace_init.restype = ctypes.c_int
         L.rnn_workspace_status.restype = ctypes.c_int
         L.rnn_profile_begin.argtypes = [ctypes.c_int]
@@ -316,6 +321,17 @@ def rnn_profile_end() -> dict:
 
 def rnn_set_wait_limit(polls: int) -> None:
     _check(lib().rnn_set_wait_limit(int(polls)))
+
+
+def rnn_workspace_groups_alone(dims, workspace, stream=None) -> int:
+    wp, wb = _ws(workspace)
+    out = ctypes.c_int32(-1)
+    _check(lib().rnn_workspace_groups_alone(ctypes.byref(dims), wp, wb, _stream(stream), ctypes.byref(out)))
+    return int(out.value)
+
+
+def rnn_test_roll_call(microseconds: int = -1, absent: int = 0) -> None:
+    _check(lib().rnn_test_roll_call(int(microseconds), int(absent)))
 
 
 def rnn_workspace_init(dims, workspace, stream=None) -> None:

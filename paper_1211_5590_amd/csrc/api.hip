@@ -748,6 +748,27 @@ int rnn_workspace_status(const rnn_dims* dims, const void* workspace, size_t wor
     return hipStreamSynchronize(s) == hipSuccess ? RNN_OK : RNN_EHIP;
 }
 
+int rnn_workspace_groups_alone(const rnn_dims* dims, const void* workspace, size_t workspace_bytes,
+                               void* hip_stream, int32_t* groups_host) {
+    if (!dims_valid(dims) || !groups_host) return RNN_EINVAL;
+    Plan pl;
+    const int rc = check_ws(dims, const_cast<void*>(workspace), workspace_bytes, &pl);
+    if (rc != RNN_OK) return rc;
+    if (!pick_variant(dims).xcd) return RNN_EUNSUPPORTED;
+    hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    int32_t counters[REC_XCD_COUNTERS];
+    if (hipMemcpyAsync(counters, at<int32_t>(const_cast<void*>(workspace), pl.flags), sizeof counters,
+                       hipMemcpyDeviceToHost, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
+        return RNN_EHIP;
+    *groups_host = rec_xcd_groups_alone(counters);
+    return RNN_OK;
+}
+
+int rnn_test_roll_call(int microseconds, int absent) {
+    rec_xcd_test_roll_call(microseconds, absent);
+    return RNN_OK;
+}
+
 int rnn_workspace_init(const rnn_dims* dims, void* workspace, size_t workspace_bytes, void* hip_stream) {
     if (!dims_valid(dims)) return RNN_EINVAL;
     Plan pl;

@@ -142,11 +142,17 @@ struct RecXcdArgs {
     int spin_limit;       // <= 0: default
     bool cleared;         // ring and counters are as rec_xcd_fills wants them
     int slots, patience;  // workgroups of a group; 10 ns they wait for each other to come (filled in by the launcher)
+    int absent;           // workgroups a group waits for beyond those it has (filled in by the launcher: 0 but in tests)
 };
 bool rec_xcd_supported(int H, int B, int T, bool tokens);          // shape only (host)
 int rec_xcd_workgroups(int H, int B);
 size_t rec_xcd_ring_bytes(int H, int B);
 bool rec_xcd_ready(int H, int B, int act, bool bwd);             // and the current device can hold the grid at once
+// groups of the launch that left these counters that one workgroup computed by itself
+constexpr int REC_XCD_COUNTERS = 40;
+int rec_xcd_groups_alone(const int32_t* counters);
+// in launches of the calling thread: microseconds to wait for a group (< 0: the rule), workgroups that never come
+void rec_xcd_test_roll_call(int microseconds, int absent);
 // what the ring and the counters have to hold before a launch, for a kernel that sets it on the side
 void rec_xcd_fills(const RecXcdArgs& a, struct FillJob* ring, struct FillJob* counters);
 hipError_t launch_rec_xcd(const RecXcdArgs& a, bool bwd, hipStream_t s);

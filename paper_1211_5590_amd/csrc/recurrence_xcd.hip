@@ -54,7 +54,9 @@
 // others of its kind (gang.hip).  Where other work keeps a part of a group off the chip for longer than the loop would
 // take on one workgroup, one of those that did come runs it by itself and the others leave, so the launch ends with right
 // results whatever else the GPU does (run_alone below).
-// Every wait is bounded, and an expired wait for a state sets the status word.
+// Every wait is bounded, the one for the group by time, and an expired wait for a state sets the status word: the wavefront that gave
+// up sets s_abort, and the workgroup's others leave at their next look at it, the carrier up to 16 steps later.  Each passes at
+// most one barrier per step and then ends, and a barrier does not wait for wavefronts that have ended.
 //
 // Measured (a loop of 256 steps, batch 64, H = 1024): 600 us with the state read from the history and
 // device-scope stores, 475 now (1000 words; 540 right behind the large products of 10000 words, which
@@ -90,6 +92,7 @@ constexpr int NXCD = 8;            // XCDs: the layout this loop is built on
 constexpr int WG_PER_XCD = 32;     // compute units per XCD = workgroups per XCD
 constexpr int NGRP = 32;           // groups at most: x, x + 8, x + 16 and x + 24 on XCD x
 constexpr int H_MAX = 1024;
+static_assert(REC_XCD_COUNTERS == NXCD + NGRP, "a slice counter per XCD, a roll per group");
 constexpr int RSLOTS = 4;          // states the exchange ring holds
 constexpr unsigned kSentinel = 0xFFFFFFFFu;
 constexpr int ROLL_CLOSED = 1 << 16;
@@ -261,16 +264,17 @@ __global__ __launch_bounds__(threads_of(CWD)) void rec_xcd_kernel(RecXcdArgs a) 
     if (b0 >= B || c0 >= H) return;              // nothing to do here, and nobody waits for this workgroup
     const int nrows = min(RB, B - b0);
 
-    // ---- the group's roll: how many of its workgroups have come; ROLL_CLOSED once one of them has stopped waiting for the rest
-    const int whole = (H + CWD - 1) / CWD;
+    // ---- the group's roll: how many of its workgroups have come; ROLL_CLOSED once one of them has stopped waiting for the rest.
+    //      It is complete or closed for good: nobody closes a complete one, and who comes to a closed one leaves -------------
+    const int whole = (H + CWD - 1) / CWD + a.absent;
     int* roll = a.counters + NXCD + grp;
     long long came = 0;
     auto settle = [&]() {                        // thread 0: what this workgroup does
-        for (int polls = 1;; ++polls) {
+        for (;;) {
             int w = __hip_atomic_load(roll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (w == whole) return PART_ONE;
             if (w & ROLL_CLOSED) return PART_NONE;
-            if (polls >= a.spin_limit || wall_clock64() - came > a.patience) {
+            if (wall_clock64() - came > a.patience) {
                 if (__hip_atomic_compare_exchange_strong(roll, &w, w | ROLL_CLOSED, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                          __HIP_MEMORY_SCOPE_AGENT))
                     return PART_ALL;
@@ -282,8 +286,7 @@ __global__ __launch_bounds__(threads_of(CWD)) void rec_xcd_kernel(RecXcdArgs a) 
     if (tid == 0) {
         came = wall_clock64();
         const int before = atomicAdd(roll, 1);
-        // (a bound of one poll is used up on arrival: the first to come does everything)
-        s_part = a.spin_limit <= 1 ? before == 0 ? PART_ALL : PART_NONE : before & ROLL_CLOSED ? PART_NONE : PART_OPEN;
+        s_part = before & ROLL_CLOSED ? PART_NONE : PART_OPEN;
     }
 
     // ---- resident weights: wreg[64 / S * q + j] = M[k][c0 + lane % CWD], k = kb + 64 q + nq / S * (lane / CWD) + j with nq
@@ -674,7 +677,7 @@ __global__ __launch_bounds__(256) void xcd_clear_kernel(float* __restrict__ ring
     const float s = __uint_as_float(kSentinel);
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < n4) reinterpret_cast<float4*>(ring)[i] = make_float4(s, s, s, s);
-    if (i < NXCD + NGRP) counters[i] = 0;
+    if (i < REC_XCD_COUNTERS) counters[i] = 0;
 }
 
 // k per wavefront: an eighth of H in whole blocks of 16
@@ -700,7 +703,20 @@ const void* pick_xcd_kernel(int kw, int cwd) {
 // partial tiles of a step; the forward kernel first stages its matrix slice there
 size_t xcd_lds_bytes() { return (size_t)8 * 64 * 65 * 4; }
 
+// of the calling thread (rec_xcd_test_roll_call)
+thread_local int t_roll_us = -1, t_roll_absent = 0;
+
 }  // namespace
+
+int rec_xcd_groups_alone(const int32_t* counters) {
+    int n = 0;
+    for (int g = 0; g < NGRP; ++g) n += (counters[NXCD + g] & ROLL_CLOSED) != 0;
+    return n;
+}
+void rec_xcd_test_roll_call(int microseconds, int absent) {
+    t_roll_us = microseconds < 0 ? -1 : microseconds < 1000000 ? microseconds : 1000000;
+    t_roll_absent = absent != 0;
+}
 
 // Shapes the one-launch loop serves and is the faster choice for.  The launch has a fixed cost (the ring's clearing and
 // every workgroup loading its part of the matrix: 10 us at H = 300, 18 at H = 1024, batch 64; 10 us more when it was
@@ -761,7 +777,7 @@ bool rec_xcd_ready(int H, int B, int act, bool bwd) {
 
 void rec_xcd_fills(const RecXcdArgs& a, FillJob* ring, FillJob* counters) {
     *ring = {reinterpret_cast<int32_t*>(a.ring), (size_t)RSLOTS * ring_state(a.B, xcd_kw(a.H)), (int32_t)kSentinel};
-    *counters = {a.counters, (size_t)(NXCD + NGRP), 0};
+    *counters = {a.counters, (size_t)REC_XCD_COUNTERS, 0};
 }
 
 hipError_t launch_rec_xcd(const RecXcdArgs& a, bool bwd, hipStream_t s) {
@@ -784,7 +800,8 @@ hipError_t launch_rec_xcd(const RecXcdArgs& a, bool bwd, hipStream_t s) {
     // As long as one workgroup would take by itself: waiting costs at most as much again.  (100 steps at H = 300, 500, 700 and 1024:
     // 1.5, 2.3, 6.5 and 13.2 ms)
     const double alone_us = a.T * (5.0 + 125.0 * a.H / H_MAX * a.H / H_MAX);
-    args.patience = (int)(100.0 * fmin(fmax(alone_us, 200.0), 2e6));
+    args.patience = (int)(100.0 * (t_roll_us >= 0 ? t_roll_us : fmin(fmax(alone_us, 200.0), 2e6)));
+    args.absent = t_roll_absent;
     void* kargs[] = {&args};
     return launch_gang(fn, dim3(NXCD * WG_PER_XCD), dim3(threads_of(xcd_columns(a.H, a.B))), kargs, lds, s);
 }

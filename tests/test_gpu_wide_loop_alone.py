@@ -1,5 +1,5 @@
-"""The wide loop when not all workgroups of a group come: one of them runs the group's recurrence by itself.  With a wait limit of
-one poll the first workgroup of a group waits for nobody."""
+"""The wide loop when not all workgroups of a group come: one of them closes the group's roll and runs its recurrence by itself.
+And when all come but a wait for a state expires: the launch ends, with status 1."""
 import threading
 
 import numpy as np
@@ -27,16 +27,89 @@ def test_one_workgroup_runs_a_group_whose_others_are_missing(H, B, T, kind):
     r = Runner(case)
     print(f"H={H} B={B} T={T} kind={kind}", flush=True)
     assert rnn.rnn_recurrence_variant(r.dims) == "xcd_mfma"
+    ref = oracle.fwd_bptt(case, h0=case.get("h0"), dh_last=case.get("dh_last"))
+    groups = (B + 3) // 4
+    # the roll is closed as soon as somebody looks at it, and after 300 us
+    for wait in (0, 300):
+        rnn.rnn_test_roll_call(wait, 1)
+        try:
+            r.forward()
+            assert rnn.rnn_workspace_groups_alone(r.dims, r.ws) == groups
+            r.loss_()
+            r.bptt()
+        finally:
+            rnn.rnn_test_roll_call()
+        assert rnn.rnn_workspace_groups_alone(r.dims, r.ws) == groups
+        assert rnn.rnn_workspace_status(r.dims, r.ws) == 0
+        compare(r.results(), ref)
+    r.step()
+    assert rnn.rnn_workspace_groups_alone(r.dims, r.ws) == 0
+    assert rnn.rnn_workspace_status(r.dims, r.ws) == 0
+    compare(r.results(), ref)
+
+
+@pytest.mark.parametrize("H,B,T", ((260, 7, 40), (500, 30, 43), (513, 5, 40), (256, 128, 70), (600, 40, 41), (1024, 64, 40)))
+@pytest.mark.parametrize("kind", (0, 1))
+def test_smallest_wait_limit_on_every_width_of_the_wide_loop_never_hangs(H, B, T, kind):
+    """16, 32 and 64 columns per workgroup, more and fewer steps than the carrier takes between two looks at the abort word.  With a
+    bound of one poll a wait for a state may expire (status 1, results invalid) or not (status 0, right results); the first wait,
+    for the group, is not bounded by it."""
+    case = make(H, B, T, kind, seed=3)
+    ref = oracle.fwd_bptt(case, h0=case.get("h0"), dh_last=case.get("dh_last"))
+    r = Runner(case)
+    assert rnn.rnn_recurrence_variant(r.dims) == "xcd_mfma"
+    seen = []
     rnn.rnn_set_wait_limit(1)
     try:
-        r.step()
+        for _ in range(3):
+            rnn.rnn_workspace_init(r.dims, r.ws)
+            r.step()
+            seen.append(rnn.rnn_workspace_status(r.dims, r.ws))
+            assert rnn.rnn_workspace_groups_alone(r.dims, r.ws) == 0
+            if seen[-1] == 0:
+                compare(r.results(), ref)
     finally:
         rnn.rnn_set_wait_limit(0)
-    assert rnn.rnn_workspace_status(r.dims, r.ws) == 0
-    compare(r.results(), oracle.fwd_bptt(case, h0=case.get("h0"), dh_last=case.get("dh_last")))
+    print(f"H={H} B={B} T={T} kind={kind}: status {seen}", flush=True)
+    assert set(seen) <= {0, 1}
+    rnn.rnn_workspace_init(r.dims, r.ws)
     r.step()
     assert rnn.rnn_workspace_status(r.dims, r.ws) == 0
-    compare(r.results(), oracle.fwd_bptt(case, h0=case.get("h0"), dh_last=case.get("dh_last")))
+    compare(r.results(), ref)
+    if 1 not in seen:
+        pytest.skip("no wait expired, so nothing was seen of what follows")
+
+
+@pytest.mark.parametrize("H,B,T", ((500, 32, 40), (1024, 64, 12)))
+def test_workgroups_that_come_late_to_a_closed_roll(H, B, T):
+    """A loop of 16 workgroups on another stream holds two compute units of every die, and the first workgroup that looks closes its
+    group's roll: those that start later find it closed and leave.  Right results, whichever groups that was."""
+    case = make(H, B, T, 0, seed=5)
+    ref = oracle.fwd_bptt(case, h0=case.get("h0"))
+    r = Runner(case)
+    long = Runner(make(192, 64, 4000, 1))
+    assert rnn.rnn_recurrence_variant(long.dims) == "batch_mfma"
+    r.step()
+    other = torch.cuda.Stream()
+    alone = 0
+    rnn.rnn_test_roll_call(0)
+    try:
+        for _ in range(5):
+            with torch.cuda.stream(other):
+                long.forward()
+            r.forward()
+            n = rnn.rnn_workspace_groups_alone(r.dims, r.ws)
+            r.loss_()
+            r.bptt()
+            print("groups alone:", n, rnn.rnn_workspace_groups_alone(r.dims, r.ws), flush=True)
+            alone += n
+            assert rnn.rnn_workspace_status(r.dims, r.ws) == 0
+            compare(r.results(), ref)
+            torch.cuda.synchronize()
+    finally:
+        rnn.rnn_test_roll_call()
+    if alone == 0:
+        pytest.skip("every group came together")
 
 
 def test_wide_loops_of_two_threads_on_two_streams():
