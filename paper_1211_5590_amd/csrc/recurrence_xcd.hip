@@ -52,8 +52,8 @@
 // counter, so all workgroups of a group share one L2 by construction whenever the 256 workgroups are
 // co-resident (one workgroup per compute unit: checked before the launch).  The launch is not cooperative but takes turns with
 // others of its kind (gang.hip).  Where other work keeps a part of a group off the chip for longer than the loop would
-// take on one workgroup, one of those that did come runs it by itself and the others leave, so the launch ends with right
-// results whatever else the GPU does (run_alone below).
+// take on one workgroup, one of those that did come runs it by itself and the others leave, so the launch ends with the same
+// results, bit for bit, whatever else the GPU does (run_alone below).
 // Every wait is bounded, the one for the group by time, and an expired wait for a state sets the status word: the wavefront that gave
 // up sets s_abort, and the workgroup's others leave at their next look at it, the carrier up to 16 steps later.  Each passes at
 // most one barrier per step and then ends, and a barrier does not wait for wavefronts that have ended.
@@ -124,15 +124,15 @@ __device__ __forceinline__ bool fresh(float4 v) {
 }
 
 // the four values of one state piece against the matrix: every 64 / S lanes have the state of block AB of their own 16 / S
-// (abid), k = 4 AB + e of their share of the piece
-template <int S, int... AB>
+// (abid), k = 4 AB + e of their share of the piece; w: from the weights of block FIRST on
+template <int S, int FIRST, int... AB>
 __device__ __forceinline__ void mfma_blocks(const float4 st, const float* __restrict__ w, f32x4 (&acc)[4],
                                             std::integer_sequence<int, AB...>) {
     constexpr int CB = S == 1 ? 4 : S == 2 ? 3 : 2;
-    ((acc[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(st.x, w[4 * AB + 0], acc[0], CB, AB, 0),
-      acc[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(st.y, w[4 * AB + 1], acc[1], CB, AB, 0),
-      acc[2] = __builtin_amdgcn_mfma_f32_4x4x1f32(st.z, w[4 * AB + 2], acc[2], CB, AB, 0),
-      acc[3] = __builtin_amdgcn_mfma_f32_4x4x1f32(st.w, w[4 * AB + 3], acc[3], CB, AB, 0)),
+    ((acc[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(st.x, w[4 * AB + 0], acc[0], CB, FIRST + AB, 0),
+      acc[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(st.y, w[4 * AB + 1], acc[1], CB, FIRST + AB, 0),
+      acc[2] = __builtin_amdgcn_mfma_f32_4x4x1f32(st.z, w[4 * AB + 2], acc[2], CB, FIRST + AB, 0),
+      acc[3] = __builtin_amdgcn_mfma_f32_4x4x1f32(st.w, w[4 * AB + 3], acc[3], CB, FIRST + AB, 0)),
      ...);
 }
 
@@ -140,16 +140,73 @@ __device__ __forceinline__ void mfma_blocks(const float4 st, const float* __rest
 // inside a group, the order in which a wavefront's lanes want them
 __host__ __device__ inline int ring_state(int B, int kw) { return (B + RB - 1) / RB * RB * 8 * kw; }
 
-// The whole recurrence of one group on one workgroup, the matrix read from the caches every step: for a group of which not all
-// workgroups came.  sm: 2 RB ceil4(H) floats.
-template <int ACT, bool BWD, int XT>
+// Partial tile of a wavefront's K slice: element i = row i at column c0 + lane % CWD, of the lane's part of K.
+// w[64 / S * q + j] = M[k][c0 + lane % CWD], k = kb + 64 q + nq / S * (lane / CWD) + j with nq the k of piece q.
+template <int KW, int S>
+__device__ __forceinline__ f32x4 slice_product(const float4 (&st)[(KW + 63) / 64], const float (&w)[KW / S]) {
+    constexpr int N0 = KW < 64 ? KW : 64, N1 = KW - N0;
+    f32x4 acc[4] = {};
+    mfma_blocks<S, 0>(st[0], w, acc, std::make_integer_sequence<int, N0 / S / 4>{});
+    if constexpr (N1 > 0) mfma_blocks<S, 0>(st[1], w + 64 / S, acc, std::make_integer_sequence<int, N1 / S / 4>{});
+    return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+}
+// The wavefronts' partial sums of an element (pp: the first one's, of this lane's part of K), then those of the S parts.  All
+// lanes of the wavefront call it.
+template <int S>
+__device__ __forceinline__ float tile_sum(const float* pp) {
+    float v[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) v[w] = pp[w * RB * 64];
+    float sum = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+    if constexpr (S == 4) sum = swap16_sum(sum);
+    if constexpr (S >= 2) sum = swap32_sum(sum);
+    return sum;
+}
+
+// slice_product's part of one piece of NBLK blocks, from block FIRST on, with the weights M[k0 + ..][col] fetched here, four blocks
+// at a time (more would not fit the registers beside what the kernel holds)
+template <bool BWD, int S, int NBLK, int FIRST = 0>
+__device__ __forceinline__ void fetched_product(const float* __restrict__ Wh, int H, int k0, int col, const float4 st, f32x4 (&acc)[4]) {
+    if constexpr (FIRST < NBLK) {
+        constexpr int M = NBLK - FIRST < 4 ? NBLK - FIRST : 4;
+        float w[4 * M];
+        asm volatile("" : "+s"(H));      // the offsets are formed here each time, not kept for all blocks
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            const int k = k0 + 4 * (FIRST + m), left = col < H ? H - k : 0;
+            if (BWD) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[4 * m + e] = e < left ? Wh[(k + e) * H + col] : 0.f;
+            } else {
+                const float4 p = piece(Wh + col * H + k, left);
+                w[4 * m] = p.x; w[4 * m + 1] = p.y; w[4 * m + 2] = p.z; w[4 * m + 3] = p.w;
+            }
+        }
+        mfma_blocks<S, FIRST>(st, w, acc, std::make_integer_sequence<int, M>{});
+        __builtin_amdgcn_sched_barrier(0);
+        fetched_product<BWD, S, NBLK, FIRST + M>(Wh, H, k0, col, st, acc);
+    }
+}
+
+// floats of LDS that run_alone takes: two sets of partial tiles and two states
+template <int KW>
+constexpr int alone_floats() { return 2 * NW * RB * 64 + 2 * RB * (8 * KW + 4); }
+
+// The whole recurrence of one group on one workgroup's wavefronts of the product, for a group of which not all workgroups came.  The
+// columns of each workgroup in turn, the matrix read from the caches every step: the same products in the same order, so the results
+// are those of the group, bit for bit.
+template <int ACT, bool BWD, int KW, int CWD>
 __device__ __forceinline__ void run_alone(const RecXcdArgs& a, int b0, int nrows, float* sm) {
-    const int H = a.H, T = a.T, HP = (H + 3) / 4 * 4, tid = threadIdx.x;
+    constexpr int NQ = (KW + 63) / 64, S = 64 / CWD, N0 = KW < 64 ? KW : 64, N1 = KW - N0;
+    constexpr int XT = NW * kWave, PITCH = 8 * KW + 4;
+    const int H = a.H, T = a.T, tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    const int kb = KW * wave, part_k = lane / CWD, part_c = lane % CWD, ri = lane % 4, block = (lane / 4) % (16 / S);
+    const int ej = lane % (64 / S), ep = lane / (64 / S), em = (ej >> 2) & 3, et = CWD / 4 * (wave & 3) + 4 * (ej >> 4) + (ej & 3);
     const size_t bh = (size_t)a.B * H;
-    float *cur = sm, *nxt = sm + RB * HP;
+    float *part = sm, *cur = sm + 2 * NW * RB * 64, *nxt = cur + RB * PITCH;
     __syncthreads();
-    for (int e = tid; e < RB * HP; e += XT) {
-        const int r = e / HP, c = e - r * HP;
+    for (int e = tid; e < RB * PITCH; e += XT) {
+        const int r = e / PITCH, c = e - r * PITCH;
         float v = 0.f;
         if (r < nrows && c < H) {
             const size_t off = (size_t)(b0 + r) * H + c;
@@ -169,55 +226,46 @@ __device__ __forceinline__ void run_alone(const RecXcdArgs& a, int b0, int nrows
     const int nsteps = BWD ? T - 1 : T;
 #pragma unroll 1
     for (int s = 0; s < nsteps + (BWD && a.dh0 ? 1 : 0); ++s) {
+        float4 st[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int nq = q ? N1 : N0, k = kb + 64 * q + nq / S * part_k + 4 * block;
+            st[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (4 * block < nq / S) st[q] = *reinterpret_cast<const float4*>(cur + ri * PITCH + k);
+        }
 #pragma unroll 1
-        for (int col = tid; col < H; col += XT) {
-            float acc[RB][4];
-#pragma unroll
-            for (int r = 0; r < RB; ++r)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[r][e] = 0.f;
-#pragma unroll 2
-            for (int k = 0; k < HP; k += 4) {
-                float w[4];
-                if (BWD) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) w[e] = k + e < H ? a.Wh[(size_t)(k + e) * H + col] : 0.f;
-                } else {
-                    const float4 p = piece(a.Wh + (size_t)col * H + k, H - k);
-                    w[0] = p.x; w[1] = p.y; w[2] = p.z; w[3] = p.w;
-                }
-#pragma unroll
-                for (int r = 0; r < RB; ++r) {
-                    const float4 x = *reinterpret_cast<const float4*>(cur + r * HP + k);
-                    acc[r][0] = fmaf(x.x, w[0], acc[r][0]);
-                    acc[r][1] = fmaf(x.y, w[1], acc[r][1]);
-                    acc[r][2] = fmaf(x.z, w[2], acc[r][2]);
-                    acc[r][3] = fmaf(x.w, w[3], acc[r][3]);
-                }
+        for (int c0 = 0, par = 0; c0 < H; c0 += CWD, par ^= 1) {
+            const int col = c0 + part_c, ec = c0 + et;
+            f32x4 acc[4] = {};
+            fetched_product<BWD, S, N0 / S / 4>(a.Wh, H, kb + N0 / S * part_k, col, st[0], acc);
+            if constexpr (N1 > 0) fetched_product<BWD, S, N1 / S / 4>(a.Wh, H, kb + 64 + N1 / S * part_k, col, st[1], acc);
+            float* tiles = part + par * NW * RB * 64;
+            *reinterpret_cast<f32x4*>(tiles + wave * RB * 64 + RB * lane) = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+            __syncthreads();                             // (the set written next was read in front of this)
+            if (wave >= 4) continue;
+            const float sum = tile_sum<S>(tiles + RB * (CWD * ep + et) + em);
+            if (ep != 0 || em >= nrows || ec >= H) continue;
+            const size_t off = (size_t)(b0 + em) * H + ec;
+            if (s == nsteps) {                           // reverse: the gradient of the initial state
+                a.dh0[off] = sum;
+                continue;
             }
-#pragma unroll
-            for (int r = 0; r < RB; ++r) {
-                if (r >= nrows) continue;
-                const float sum = (acc[r][0] + acc[r][1]) + (acc[r][2] + acc[r][3]);
-                const size_t off = (size_t)(b0 + r) * H + col;
-                float v;
-                if (s == nsteps) {                       // reverse: the gradient of the initial state
-                    a.dh0[off] = sum;
-                    continue;
-                }
-                if (BWD) {
-                    const size_t i = (size_t)(T - 2 - s) * bh + off;
-                    v = (sum + a.G[i]) * act_grad<ACT>(a.h_all[i + bh]);
-                    a.Delta[i] = v;
-                } else {
-                    const size_t n = (size_t)s * a.B + b0 + r;
-                    const float u = a.x ? a.Wx[(size_t)a.x[n] * H + col] + a.b[col] : a.U[n * H + col];
-                    v = activate<ACT>(sum + u);
-                    a.hist[(size_t)(s + 1) * bh + off] = v;
-                    if (a.h_last && s == nsteps - 1) a.h_last[off] = v;
-                }
-                nxt[r * HP + col] = v;
+            float v;
+            if (BWD) {
+                const size_t i = (size_t)(T - 2 - s) * bh + off;
+                v = (sum + a.G[i]) * act_grad<ACT>(a.h_all[i + bh]);
+            } else {
+                const size_t n = (size_t)s * a.B + b0 + em;
+                v = activate<ACT>(sum + (a.x ? a.Wx[(size_t)a.x[n] * H + ec] + a.b[ec] : a.U[n * H + ec]));
             }
+            if (__float_as_uint(v) == kSentinel) v = __uint_as_float(0x7FC00000u);   // as the group publishes it
+            if (BWD) {
+                a.Delta[(size_t)(T - 2 - s) * bh + off] = v;
+            } else {
+                a.hist[(size_t)(s + 1) * bh + off] = v;
+                if (a.h_last && s == nsteps - 1) a.h_last[off] = v;
+            }
+            nxt[em * PITCH + ec] = v;
         }
         __syncthreads();
         float* t = cur; cur = nxt; nxt = t;
@@ -289,8 +337,7 @@ __global__ __launch_bounds__(threads_of(CWD)) void rec_xcd_kernel(RecXcdArgs a) 
         s_part = before & ROLL_CLOSED ? PART_NONE : PART_OPEN;
     }
 
-    // ---- resident weights: wreg[64 / S * q + j] = M[k][c0 + lane % CWD], k = kb + 64 q + nq / S * (lane / CWD) + j with nq
-    //      the k of piece q; M = Wh^T (forward) or Wh (reverse); zero outside the matrix ----------------
+    // ---- resident weights, laid out as slice_product takes them: M = Wh^T (forward) or Wh (reverse); zero outside the matrix ----
     const int nsteps = BWD ? T - 1 : T;
 
     // ---- the carrier (wavefront NW) ---------------------------------------------------------------
@@ -382,7 +429,6 @@ __global__ __launch_bounds__(threads_of(CWD)) void rec_xcd_kernel(RecXcdArgs a) 
         };
         if (!BWD && a.x) carry(std::true_type{});
         else carry(std::false_type{});
-        if (s_part == PART_ALL) run_alone<ACT, BWD, threads_of(CWD)>(a, b0, nrows, smem);
         return;
     }
 
@@ -447,7 +493,7 @@ __global__ __launch_bounds__(threads_of(CWD)) void rec_xcd_kernel(RecXcdArgs a) 
     __syncthreads();
     const int mine = s_part;
     if (mine != PART_ONE) {
-        if (mine == PART_ALL) run_alone<ACT, BWD, threads_of(CWD)>(a, b0, nrows, smem);
+        if (mine == PART_ALL) run_alone<ACT, BWD, KW, CWD>(a, b0, nrows, smem);
         return;
     }
 
@@ -543,27 +589,12 @@ __global__ __launch_bounds__(threads_of(CWD)) void rec_xcd_kernel(RecXcdArgs a) 
     }
 
     XT_DECL;
-    // partial tile of this wavefront's K slice: element i = row i at column c0 + lane % CWD, of this lane's part of K
-    auto product = [&]() __attribute__((always_inline)) {
-        f32x4 acc[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e] = (f32x4){0.f, 0.f, 0.f, 0.f};
-        mfma_blocks<S>(st[0], wreg, acc, std::make_integer_sequence<int, N0 / S / 4>{});
-        if constexpr (NQ > 1) mfma_blocks<S>(st[NQ - 1], wreg + 64 / S, acc, std::make_integer_sequence<int, N1 / S / 4>{});
-        return (acc[0] + acc[1]) + (acc[2] + acc[3]);
-    };
+    auto product = [&]() __attribute__((always_inline)) { return slice_product<KW, S>(st, wreg); };
     auto park_partial = [&](int par, const f32x4 p4) __attribute__((always_inline)) {
         *reinterpret_cast<f32x4*>(part + (par * 8 + wave) * RB * 64 + RB * lane) = p4;
     };
-    auto tile_sum = [&](int par) __attribute__((always_inline)) {            // epilogue lanes: the eight wavefronts' partial sums, then the S parts'
-        const float* pp = part + par * 8 * RB * 64 + RB * (CWD * ep + et) + em;
-        float v[8];
-#pragma unroll
-        for (int w = 0; w < 8; ++w) v[w] = pp[w * RB * 64];
-        float sum = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
-        if constexpr (S == 4) sum = swap16_sum(sum);
-        if constexpr (S >= 2) sum = swap32_sum(sum);
-        return sum;
+    auto element_sum = [&](int par) __attribute__((always_inline)) {   // epilogue lanes
+        return tile_sum<S>(part + par * NW * RB * 64 + RB * (CWD * ep + et) + em);
     };
     // The lane's pieces of the state at `src` in the ring, waiting until no "not written yet" word is left.
     auto collect = [&](const float* src) __attribute__((always_inline)) {
@@ -617,7 +648,7 @@ __global__ __launch_bounds__(threads_of(CWD)) void rec_xcd_kernel(RecXcdArgs a) 
         if (wave < 4) {
             const float in = CARRY ? s_in[SLOT][e_at] : own[512 * (s % OWN_CHUNK)];
             const float slope = !BWD ? 0.f : CARRY ? s_slope[SLOT][e_at] : own[512 * (s % OWN_CHUNK) + 256];
-            const float sum = tile_sum(SLOT);
+            const float sum = element_sum(SLOT);
             float v = BWD ? (sum + in) * slope : activate<ACT>(sum + in);
             if (__float_as_uint(v) == kSentinel) v = __uint_as_float(0x7FC00000u);   // a NaN that came in as all ones
             if (e_pub) ring_store(box + e_ring, e_on ? v : 0.f);
@@ -666,7 +697,7 @@ __global__ __launch_bounds__(threads_of(CWD)) void rec_xcd_kernel(RecXcdArgs a) 
         park_partial(0, product());
         __syncthreads();
         if (wave < 4) {
-            const float sum = tile_sum(0);
+            const float sum = element_sum(0);
             if (e_on) a.dh0[e_off] = sum;
         }
     }
@@ -701,7 +732,8 @@ const void* pick_xcd_kernel(int kw, int cwd) {
 }
 
 // partial tiles of a step; the forward kernel first stages its matrix slice there
-size_t xcd_lds_bytes() { return (size_t)8 * 64 * 65 * 4; }
+constexpr size_t xcd_lds_bytes() { return (size_t)8 * 64 * 65 * 4; }
+static_assert(alone_floats<H_MAX / 8>() * sizeof(float) <= xcd_lds_bytes(), "run_alone's tiles and states");
 
 // of the calling thread (rec_xcd_test_roll_call)
 thread_local int t_roll_us = -1, t_roll_absent = 0;
@@ -797,8 +829,8 @@ hipError_t launch_rec_xcd(const RecXcdArgs& a, bool bwd, hipStream_t s) {
     RecXcdArgs args = a;
     if (args.spin_limit <= 0) args.spin_limit = wait_limit();
     args.slots = xcd_slots(a.B);
-    // As long as one workgroup would take by itself: waiting costs at most as much again.  (100 steps at H = 300, 500, 700 and 1024:
-    // 1.5, 2.3, 6.5 and 13.2 ms)
+    // As long as one workgroup would take by itself: waiting costs at most as much again.  (100 steps at H = 200, 300, 500, 700 and
+    // 1024, by batch and direction: 0.9 to 1.3, 1.2 to 2.1, 2.9 to 4.0, 4.5 to 6.0 and 12 to 16 ms)
     const double alone_us = a.T * (5.0 + 125.0 * a.H / H_MAX * a.H / H_MAX);
     args.patience = (int)(100.0 * (t_roll_us >= 0 ? t_roll_us : fmin(fmax(alone_us, 200.0), 2e6)));
     args.absent = t_roll_absent;

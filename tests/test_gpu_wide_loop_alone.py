@@ -112,6 +112,28 @@ def test_workgroups_that_come_late_to_a_closed_roll(H, B, T):
         pytest.skip("every group came together")
 
 
+@pytest.mark.parametrize("H,B,T", ((193, 3, 64), (256, 30, 64), (255, 127, 64), (257, 5, 17), (384, 32, 10), (384, 33, 10), (512, 33, 11),
+                                   (515, 64, 12), (640, 17, 10), (769, 40, 10), (897, 64, 10), (1023, 6, 10), (1024, 61, 10)))
+@pytest.mark.parametrize("kind", (0, 1))
+def test_a_group_run_alone_gives_the_same_bits(H, B, T, kind):
+    """Which way a group is computed depends on what else the GPU does, the results do not: every number of K per wavefront and of
+    columns per workgroup, tokens and dense input, with and without an initial state and a gradient from later."""
+    r = Runner(make(H, B, T, kind, seed=9))
+    assert rnn.rnn_recurrence_variant(r.dims) == "xcd_mfma"
+    r.step()
+    assert rnn.rnn_workspace_groups_alone(r.dims, r.ws) == 0
+    together = r.results()
+    rnn.rnn_test_roll_call(0, 1)
+    try:
+        r.step()
+    finally:
+        rnn.rnn_test_roll_call()
+    assert rnn.rnn_workspace_groups_alone(r.dims, r.ws) == (B + 3) // 4
+    alone = r.results()
+    for name, v in together.items():
+        assert np.array_equal(v, alone[name]), name
+
+
 def test_wide_loops_of_two_threads_on_two_streams():
     """Each loop needs all compute units of the dies it uses: those of two streams take turns."""
     cases = [make(600, 40, 40, 0), make(1000, 64, 30, 1)]
