@@ -180,7 +180,7 @@ int rnn_check_tokens(const void *ids, int64_t n, int32_t limit, int32_t *bad_cou
  * started.  That wait is bounded by time and not by this limit, and its end is no failure: if other work
  * keeps a part of the group off the GPU, one of the workgroups that did start computes the group by itself,
  * up to a hundred times as slowly; the status stays 0 and the results are the same, bit for bit.  The time is what that
- * workgroup would take, 0.2 ms at least and 2 s at most.  The limit holds for the waits of the loop that
+ * workgroup would take, 0.2 ms at least and 0.25 s at most.  The limit holds for the waits of the loop that
  * follows.
  */
 int rnn_set_wait_limit(int polls);

@@ -157,8 +157,9 @@ void rec_xcd_test_roll_call(int microseconds, int absent);
 void rec_xcd_fills(const RecXcdArgs& a, struct FillJob* ring, struct FillJob* counters);
 hipError_t launch_rec_xcd(const RecXcdArgs& a, bool bwd, hipStream_t s);
 
-// Launch of a kernel whose workgroups wait for each other: it takes turns with others of its kind on the device (gang.hip)
-hipError_t launch_gang(const void* fn, dim3 grid, dim3 block, void** args, size_t lds, hipStream_t s);
+// Launch of a kernel whose workgroups wait for each other: it takes turns with others of its kind on the device (gang.hip).
+// finishes_with_any: it ends with right results whatever part of its workgroups runs at once, and need not be cooperative
+hipError_t launch_gang(const void* fn, dim3 grid, dim3 block, void** args, size_t lds, hipStream_t s, bool finishes_with_any = false);
 // before a launch of `fn` with that much dynamic LDS on the current device (lds_limit.hip)
 hipError_t allow_lds(const void* fn, size_t bytes);
 hipError_t launch_zero_words(int32_t* p, int n, hipStream_t s);

@@ -917,7 +917,7 @@ hipError_t run_mlp_one(const rnn_mlp_dims* d, const rnn_mlp_params* p, const flo
         }
         ProfileScope ps(K_MLP_ONE, s);
         void* args[] = {&a};
-        e = hid ? hipLaunchCooperativeKernel(fn, dim3(a.P), dim3(OT), args, 0, s) : hipLaunchKernel(fn, dim3(1), dim3(OT), args, 0, s);
+        e = hid ? launch_gang(fn, dim3(a.P), dim3(OT), args, 0, s) : hipLaunchKernel(fn, dim3(1), dim3(OT), args, 0, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

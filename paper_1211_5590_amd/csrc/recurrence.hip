@@ -734,7 +734,7 @@ hipError_t launch_rec_resident(RecResArgs a, const RecResPlan& pl, bool bwd, hip
     }
     if (pl.P > 1) {
         void* args[] = {&a};
-        return hipLaunchCooperativeKernel(fn, grid, block, args, (unsigned)pl.smem, s);
+        return launch_gang(fn, grid, block, args, pl.smem, s);
     }
     if (!bwd) {
         if (a.act == 0) hipLaunchKernelGGL((rec_resident_kernel<0, false>), grid, block, pl.smem, s, a);

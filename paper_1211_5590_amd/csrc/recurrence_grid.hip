@@ -415,7 +415,7 @@ hipError_t launch_rec_grid(RecResArgs a, const RecGridPlan& pl, bool bwd, hipStr
         grid.x = pl.P * 8;
     }
     void* args[] = {&a};
-    return hipLaunchCooperativeKernel(fn, grid, block, args, (unsigned)pl.smem, s);
+    return launch_gang(fn, grid, block, args, pl.smem, s);
 }
 
 }  // namespace rnn

@@ -829,13 +829,14 @@ hipError_t launch_rec_xcd(const RecXcdArgs& a, bool bwd, hipStream_t s) {
     RecXcdArgs args = a;
     if (args.spin_limit <= 0) args.spin_limit = wait_limit();
     args.slots = xcd_slots(a.B);
-    // As long as one workgroup would take by itself: waiting costs at most as much again.  (100 steps at H = 200, 300, 500, 700 and
+    // As long as one workgroup would take by itself: waiting costs at most as much again.  A quarter of a second at most: a replayed
+    // graph may have brought a loop here beside another that waits for about a second and then gives up.  (100 steps at H = 200, 300, 500, 700 and
     // 1024, by batch and direction: 0.9 to 1.3, 1.2 to 2.1, 2.9 to 4.0, 4.5 to 6.0 and 12 to 16 ms)
     const double alone_us = a.T * (5.0 + 125.0 * a.H / H_MAX * a.H / H_MAX);
-    args.patience = (int)(100.0 * (t_roll_us >= 0 ? t_roll_us : fmin(fmax(alone_us, 200.0), 2e6)));
+    args.patience = (int)(100.0 * (t_roll_us >= 0 ? t_roll_us : fmin(fmax(alone_us, 200.0), 2.5e5)));
     args.absent = t_roll_absent;
     void* kargs[] = {&args};
-    return launch_gang(fn, dim3(NXCD * WG_PER_XCD), dim3(threads_of(xcd_columns(a.H, a.B))), kargs, lds, s);
+    return launch_gang(fn, dim3(NXCD * WG_PER_XCD), dim3(threads_of(xcd_columns(a.H, a.B))), kargs, lds, s, true);
 }
 
 }  // namespace rnn

@@ -1467,7 +1467,7 @@ int launch_window(const rnn_dims* dims, const rnn_params* params, const int32_t*
         ProfileScope ps(K_WINDOW, s);
         void* args[] = {&a};
         const bool coop = (dims->flags & RNN_FLAG_COOPERATIVE) || !fits_the_chip(fn, lds, 1 + a.S);
-        e = coop ? hipLaunchCooperativeKernel(fn, dim3(1 + a.S), dim3(NT), args, (unsigned)lds, s)
+        e = coop ? launch_gang(fn, dim3(1 + a.S), dim3(NT), args, lds, s)
                  : hipLaunchKernel(fn, dim3(1 + a.S), dim3(NT), args, lds, s);
     }
     if (e != hipSuccess) return RNN_EHIP;
@@ -1791,7 +1791,7 @@ int rnn_train_stream(const rnn_dims* dims, const rnn_params_inout* params, const
     {
         ProfileScope ps(K_TRAIN_STREAM, s);
         void* args[] = {&a};
-        e = hipLaunchCooperativeKernel(fn, dim3(1 + a.S), dim3(NT), args, (unsigned)lds, s);
+        e = launch_gang(fn, dim3(1 + a.S), dim3(NT), args, lds, s);
     }
     if (e != hipSuccess) return RNN_EHIP;
     if (dims->flags & RNN_FLAG_SYNC)

@@ -134,6 +134,77 @@ def test_a_group_run_alone_gives_the_same_bits(H, B, T, kind):
         assert np.array_equal(v, alone[name]), name
 
 
+@pytest.mark.parametrize("beside", ("wide_loop", "train_stream", "grid_loop", "classifier"))
+def test_launches_that_wait_inside_take_turns(beside):
+    """A wide loop on one stream beside, on another, each launch of the library whose workgroups wait for each other: they share the
+    chip one after the other, so no group is ever run alone and no wait expires."""
+    case = make(1000, 64, 30, 0, seed=2)
+    ref = oracle.fwd_bptt(case, h0=case.get("h0"))
+    r = Runner(case)
+    status = lambda: 0                                       # noqa: E731
+    if beside == "wide_loop":
+        other = Runner(make(500, 32, 200, 1))
+        call, status = other.forward, lambda: rnn.rnn_workspace_status(other.dims, other.ws)   # noqa: E731
+    elif beside == "grid_loop":
+        other = Runner(make(900, 1, 200, 1))
+        assert rnn.rnn_recurrence_variant(other.dims) == "grid_resident"
+        call, status = other.forward, lambda: rnn.rnn_workspace_status(other.dims, other.ws)   # noqa: E731
+    elif beside == "train_stream":
+        stream = ri.make_config("C2", windows=400)
+        dims = rnn.Dims.of(stream)
+        params = {k: torch.from_numpy(stream[k]).cuda() for k in ("Wx", "Wh", "b", "V", "c")}
+        ids = torch.from_numpy(np.ascontiguousarray(ri.stream_ids(stream)).reshape(-1)).cuda()
+        losses = torch.empty(400, device="cuda")
+        ws = torch.zeros(rnn.rnn_train_stream_workspace_bytes(dims), dtype=torch.uint8, device="cuda")
+        call = lambda: rnn.rnn_train_stream(dims, params, ids, 400, 0.01, None, None, losses, ws)   # noqa: E731
+        status = lambda: rnn.rnn_train_stream_status(ws)    # noqa: E731
+    else:
+        mlp = dict(in_dim=784, hidden=500, n_hidden=1, out_dim=10, batch=1, act=0)
+        dims = rnn.MlpDims.of(mlp)
+        W = [torch.randn(500, 784, device="cuda") / 28, torch.randn(10, 500, device="cuda") / 23]
+        b = [torch.zeros(500, device="cuda"), torch.zeros(10, device="cuda")]
+        X, y = torch.rand(400, 784, device="cuda"), torch.zeros(400, dtype=torch.int32, device="cuda")
+        losses = torch.empty(400, device="cuda")
+        ws = torch.zeros(rnn.rnn_mlp_workspace_bytes(dims), dtype=torch.uint8, device="cuda")
+        call = lambda: rnn.rnn_mlp_train(dims, W, b, X, y, 400, 0.01, losses, ws)   # noqa: E731
+    call()
+    r.step()
+    torch.cuda.synchronize()
+    errors, done = [], threading.Event()
+
+    def work():
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                while not done.is_set():
+                    call()
+                    torch.cuda.current_stream().synchronize()
+        except Exception as e:                              # noqa: BLE001 -- shown by the assert below
+            errors.append(e)
+
+    t = threading.Thread(target=work)
+    t.start()
+    alone = []
+    try:
+        rnn.rnn_test_roll_call(1000)     # much longer than the small kernels in between, shorter than a loop of the other stream
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(20):
+                r.forward()
+                alone.append(rnn.rnn_workspace_groups_alone(r.dims, r.ws))
+                r.loss_()
+                r.bptt()
+                alone.append(rnn.rnn_workspace_groups_alone(r.dims, r.ws))
+            torch.cuda.current_stream().synchronize()
+    finally:
+        rnn.rnn_test_roll_call()
+        done.set()
+        t.join()
+    torch.cuda.synchronize()
+    assert not errors, errors
+    assert alone == [0] * 40, alone
+    assert rnn.rnn_workspace_status(r.dims, r.ws) == 0 and status() == 0
+    compare(r.results(), ref)
+
+
 def test_wide_loops_of_two_threads_on_two_streams():
     """Each loop needs all compute units of the dies it uses: those of two streams take turns."""
     cases = [make(600, 40, 40, 0), make(1000, 64, 30, 1)]
