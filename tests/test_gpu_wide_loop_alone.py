@@ -143,10 +143,10 @@ def test_launches_that_wait_inside_take_turns(beside):
     r = Runner(case)
     status = lambda: 0                                       # noqa: E731
     if beside == "wide_loop":
-        other = Runner(make(500, 32, 200, 1))
+        other = Runner(make(500, 32, 2500, 1))
         call, status = other.forward, lambda: rnn.rnn_workspace_status(other.dims, other.ws)   # noqa: E731
     elif beside == "grid_loop":
-        other = Runner(make(900, 1, 200, 1))
+        other = Runner(make(900, 1, 1200, 1))
         assert rnn.rnn_recurrence_variant(other.dims) == "grid_resident"
         call, status = other.forward, lambda: rnn.rnn_workspace_status(other.dims, other.ws)   # noqa: E731
     elif beside == "train_stream":
@@ -185,7 +185,7 @@ def test_launches_that_wait_inside_take_turns(beside):
     t.start()
     alone = []
     try:
-        rnn.rnn_test_roll_call(1000)     # much longer than the small kernels in between, shorter than a loop of the other stream
+        rnn.rnn_test_roll_call(300)      # much longer than the small kernels in between, much shorter than a launch of the other stream
         with torch.cuda.stream(torch.cuda.Stream()):
             for _ in range(20):
                 r.forward()
