@@ -398,7 +398,8 @@ const char *rnn_strerror(int code);
  * batch 1 and 2: hidden <= 640 -, or 192 < hidden <= 256, batch <= 128, at least 64 steps - 33 of tokens with
  * batch > 4 -, and with the full history, on
  * a device of 8 x 32 compute units: one persistent launch, groups of 4 batch rows, one to four
- * per XCD),
+ * per XCD; a call that is captured into a graph takes batch_mfma up to 256 hidden units if it has fewer than
+ * 2048 steps, and that loop adds in another order),
  * "step_mfma" (other batched sizes: one fused matrix-core launch per step) or "reference". */
 const char *rnn_recurrence_variant(const rnn_dims *dims);
 

@@ -206,10 +206,20 @@ RecXcdArgs xcd_args(const rnn_dims* d, void* ws, const Plan& pl) {
     return m;
 }
 
+// does the wide loop serve this call on this device and stream
+bool takes_xcd(const rnn_dims* d, const Variant& v, bool bwd, hipStream_t s) {
+    if (!v.xcd || !rec_xcd_ready(d->hidden, d->batch, d->act, bwd)) return false;
+    if (!v.batch_mfma || rec_xcd_pays_captured(d->hidden, d->seq_len)) return true;
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(s, &capturing);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e != hipSuccess || capturing == hipStreamCaptureStatusNone;
+}
+
 // what an earlier kernel can set on the side for run_reverse_loop; false (and nothing to set) if its loop needs nothing
-bool reverse_fills(const rnn_dims* d, void* ws, const Plan& pl, FillJob* ring, FillJob* counters) {
+bool reverse_fills(const rnn_dims* d, void* ws, const Plan& pl, FillJob* ring, FillJob* counters, hipStream_t s) {
     *ring = *counters = FillJob{};
-    if (!pick_variant(d).xcd || !rec_xcd_ready(d->hidden, d->batch, d->act, true)) return false;
+    if (!takes_xcd(d, pick_variant(d), true, s)) return false;
     rec_xcd_fills(xcd_args(d, ws, pl), ring, counters);
     return true;
 }
@@ -239,7 +249,7 @@ hipError_t run_forward(const rnn_dims* d, const rnn_params* P, const void* x, co
         a.U = at<float>(ws, pl.U);
     }
     const Variant v = pick_variant(d);
-    if (v.xcd && h_all && rec_xcd_ready(z.H, z.B, d->act, false)) {
+    if (h_all && takes_xcd(d, v, false, s)) {
         RecXcdArgs m = xcd_args(d, ws, pl);
         m.Wh = P->Wh;
         m.x = a.x; m.Wx = P->Wx; m.b = P->b; m.U = a.U; m.h0 = h0; m.hist = h_all; m.h_last = h_last;
@@ -333,7 +343,7 @@ hipError_t run_reverse_loop(const rnn_dims* d, const float* Wh, const float* WhT
     if (v.skinny) {   // the plain plan of the resident loop
         if (!rec_resident_plan(z.H, z.B, z.T, true, false, 0, &v.bwd)) v.resident = false;
     }
-    if (v.xcd && rec_xcd_ready(z.H, z.B, d->act, true)) {
+    if (takes_xcd(d, v, true, s)) {
         RecXcdArgs m = xcd_args(d, ws, pl);
         m.Wh = Wh; m.cleared = cleared;
         m.G = G; m.h_all = h_all; m.dh_last = dh_last; m.Delta = Delta; m.dh0 = dh0;
@@ -478,7 +488,7 @@ hipError_t run_bptt(const rnn_dims* d, const rnn_params* P, const void* x, const
 
     // logits -> d loss / d logits (in place) and their columns' sums per chunk
     FillJob ring, counters;
-    const bool cleared = reverse_fills(d, ws, pl, &ring, &counters);
+    const bool cleared = reverse_fills(d, ws, pl, &ring, &counters, s);
     RNN_TRY(launch_dz(Z, at<float>(ws, pl.lse), z.ce ? static_cast<const int32_t*>(targets) : nullptr,
                       z.ce ? nullptr : static_cast<const float*>(targets), part, N, O,
                       d->loss_kind, ring, counters, s));
@@ -558,7 +568,7 @@ hipError_t run_gauss_newton(const rnn_dims* d, const rnn_params* P, const rnn_pa
     }
     // time-reversed rows: Crev[t] = C[T-1-t], hrev[t+1] = h_{T-1-t}
     FillJob ring, counters;
-    const bool cleared = reverse_fills(d, ws, pl, &ring, &counters);
+    const bool cleared = reverse_fills(d, ws, pl, &ring, &counters, s);
     RNN_TRY(launch_gn_prepare(z.tokens ? static_cast<const int32_t*>(x) : nullptr, Ga->Wx, C, Hs, P->Wh, Crev, hrev + BH, WhT,
                               z.T, z.B, H, ring, counters, s));
     RNN_TRY(run_reverse_loop(d, WhT, P->Wh, nullptr, Crev, hrev, nullptr, Rhrev, nullptr, ws, pl, cleared, s));

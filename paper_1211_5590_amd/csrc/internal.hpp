@@ -145,6 +145,8 @@ struct RecXcdArgs {
     int absent;           // workgroups a group waits for beyond those it has (filled in by the launcher: 0 but in tests)
 };
 bool rec_xcd_supported(int H, int B, int T, bool tokens);          // shape only (host)
+// ... also in a captured call (whose launch is cooperative), where rec_batch_mfma_supported sizes are concerned
+bool rec_xcd_pays_captured(int H, int T);
 int rec_xcd_workgroups(int H, int B);
 size_t rec_xcd_ring_bytes(int H, int B);
 bool rec_xcd_ready(int H, int B, int act, bool bwd);             // and the current device can hold the grid at once

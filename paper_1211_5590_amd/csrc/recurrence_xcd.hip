@@ -770,6 +770,13 @@ bool rec_xcd_supported(int H, int B, int T, bool tokens) {
     return B > 4 ? T >= 10 : T >= 16 && (B > 2 || H <= 640);
 }
 
+// A captured loop is a cooperative launch (gang.hip), and the loop of one workgroup per 4 rows is plain in any case: up to 256 units a
+// captured call takes that one until the steps make up for the launch.  How much that is depends on what the program has launched
+// before: 26 us a loop, or 235 if it has replayed two graphs without a cooperative launch in them first.  Three captured calls, that loop and
+// this one: 128 steps of 193 units, 1 row: 317 us and 305 or 711; of 256 units, 20 dense rows: 355 and 338 or 880; 2048 steps, 20 rows, 193
+// units: 3931 and, in the slower state, 3775, of 256 units 4249 and 3703.
+bool rec_xcd_pays_captured(int H, int T) { return H > 256 || T >= 2048; }
+
 // compute units the loop of these sizes keeps busy
 int rec_xcd_workgroups(int H, int B) {
     const int c = xcd_columns(H, B);

@@ -205,6 +205,37 @@ def test_launches_that_wait_inside_take_turns(beside):
     compare(r.results(), ref)
 
 
+@pytest.mark.parametrize("H,B,T,kind,wide", ((200, 20, 35, 0, False), (193, 1, 64, 1, False), (256, 2, 2047, 0, False),
+                                             (256, 2, 2048, 0, True), (193, 5, 2047, 1, False), (193, 5, 2048, 1, True), (256, 127, 70, 0, False),
+                                             (257, 5, 16, 0, True)))
+def test_which_loop_a_captured_call_takes(H, B, T, kind, wide):
+    """A wide loop in a graph is a cooperative launch, so that shorter sequences of up to 256 units stay with the loop of one workgroup
+    per 4 rows.  It leaves the wide loop's words in the workspace as the last eager call left them."""
+    case = make(H, B, T, kind, seed=4)
+    ref = oracle.fwd_bptt(case, h0=case.get("h0"), dh_last=case.get("dh_last"))
+    r = Runner(case)
+    r.step()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        r.forward(); r.loss_(); r.bptt()
+    for rep in range(3):
+        rnn.rnn_test_roll_call(0, 1)                        # an eager call between the replays, all groups alone
+        try:
+            r.step()
+        finally:
+            rnn.rnn_test_roll_call()
+        assert rnn.rnn_workspace_groups_alone(r.dims, r.ws) == (B + 3) // 4
+        for t in (r.h_all, r.h_last, r.loss, r.dh0, *r.grads.values()):
+            t.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert rnn.rnn_workspace_groups_alone(r.dims, r.ws) == (0 if wide else (B + 3) // 4)
+        assert rnn.rnn_workspace_status(r.dims, r.ws) == 0
+        compare(r.results(), ref)
+
+
 def test_wide_loops_of_two_threads_on_two_streams():
     """Each loop needs all compute units of the dies it uses: those of two streams take turns."""
     cases = [make(600, 40, 40, 0), make(1000, 64, 30, 1)]
