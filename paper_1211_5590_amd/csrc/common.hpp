@@ -199,6 +199,10 @@ __device__ __forceinline__ bool tagged_wait(const unsigned long long* p, unsigne
 }
 
 
+// number of this workgroup in a grid of grid_of, and how many those are
+__device__ __forceinline__ size_t workgroup() { return (size_t)blockIdx.y * gridDim.x + blockIdx.x; }
+__device__ __forceinline__ size_t workgroups() { return (size_t)gridDim.x * gridDim.y; }
+
 // words [0, n) = v, by block `bid` of `nb` with `threads` threads each: a fill that rides on another kernel
 __device__ __forceinline__ void fill_share(int32_t* p, size_t n, int32_t v, size_t bid, size_t nb, int threads) {
     for (size_t i = bid * threads + threadIdx.x; i < n; i += nb * threads) p[i] = v;

@@ -30,10 +30,11 @@ struct GnPrepare {
 };
 __global__ __launch_bounds__(256) void gn_prepare_kernel(GnPrepare a) {
     const int H = a.H, N = a.T * a.B, tid = threadIdx.x;
-    fill_share(a.ring.p, a.ring.n, a.ring.v, blockIdx.x, gridDim.x, 256);
-    fill_share(a.counters.p, a.counters.n, a.counters.v, blockIdx.x, gridDim.x, 256);
-    if ((int)blockIdx.x < N) {
-        const int n = blockIdx.x, t = n / a.B, src = (a.T - 1 - t) * a.B + n % a.B;
+    fill_share(a.ring.p, a.ring.n, a.ring.v, workgroup(), workgroups(), 256);
+    fill_share(a.counters.p, a.counters.n, a.counters.v, workgroup(), workgroups(), 256);
+    const int wg = (int)workgroup();
+    if (wg < N) {
+        const int n = wg, t = n / a.B, src = (a.T - 1 - t) * a.B + n % a.B;
         const float* row = a.x ? a.M + (size_t)a.x[src] * H : nullptr;
         const size_t from = (size_t)src * H, to = (size_t)n * H;
         for (int j = tid; j < H; j += 256) {
@@ -44,7 +45,8 @@ __global__ __launch_bounds__(256) void gn_prepare_kernel(GnPrepare a) {
         return;
     }
     __shared__ float tile[32][33];
-    const int side = (H + 31) / 32, b = blockIdx.x - N, r0 = b / side * 32, c0 = b % side * 32, tx = tid % 32, ty = tid / 32;
+    // (past the last tile: r0 >= H, nothing to move)
+    const int side = (H + 31) / 32, b = wg - N, r0 = b / side * 32, c0 = b % side * 32, tx = tid % 32, ty = tid / 32;
     for (int i = ty; i < 32; i += 8)
         if (r0 + i < H && c0 + tx < H) tile[i][tx] = a.Wh[(size_t)(r0 + i) * H + c0 + tx];
     __syncthreads();
@@ -68,10 +70,11 @@ __global__ __launch_bounds__(256) void scale_kernel(float* p, size_t n, float al
 constexpr int GN_T = 512;                              // threads
 template <int P>
 __global__ __launch_bounds__(GN_T) void gn_softmax_metric_kernel(const float* __restrict__ Z, float* __restrict__ RZ,
-                                                                 int O, float scale) {
+                                                                 int N, int O, float scale) {
+    if (workgroup() >= (size_t)N) return;
     constexpr int NW = GN_T / kWave;
     __shared__ float red[3][NW];
-    const size_t base = (size_t)blockIdx.x * O;
+    const size_t base = workgroup() * O;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const float* z = Z + base;
     float* rz = RZ + base;
@@ -160,7 +163,7 @@ hipError_t launch_gn_prepare(const int32_t* x, const float* M, const float* C, c
     const int side = (H + 31) / 32;
     const GnPrepare a = {x, M, C, Hs, Wh, Crev, hrev, WhT, T, B, H, ring, counters};
     ProfileScope ps(K_MISC, s);
-    hipLaunchKernelGGL(gn_prepare_kernel, dim3((unsigned)(T * B + side * side)), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(gn_prepare_kernel, grid_of((size_t)T * B + (size_t)side * side), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 hipError_t launch_fill_zero(float* p, size_t n, hipStream_t s) {
@@ -175,7 +178,7 @@ hipError_t launch_scale(float* p, size_t n, float alpha, hipStream_t s) {
 }
 hipError_t launch_gn_softmax_metric(const float* Z, float* RZ, int N, int O, float scale, hipStream_t s) {
     ProfileScope ps(K_GN_METRIC, s);
-#define RNN_GN(P) hipLaunchKernelGGL(gn_softmax_metric_kernel<P>, dim3(N), dim3(GN_T), 0, s, Z, RZ, O, scale)
+#define RNN_GN(P) hipLaunchKernelGGL(gn_softmax_metric_kernel<P>, grid_of((size_t)N), dim3(GN_T), 0, s, Z, RZ, N, O, scale)
     const int pieces = (O - 1) / (4 * GN_T) + 1;       // of a thread
     if (pieces <= 1) RNN_GN(1);
     else if (pieces <= 3) RNN_GN(3);

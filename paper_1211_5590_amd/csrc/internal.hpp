@@ -182,6 +182,12 @@ hipError_t launch_ce_merge_stats(const float* stats, int parts, const float* Z, 
 hipError_t launch_mse_partial(const float* Z, const float* Y, float* partial, int N, int O,
                               int* n_partial, hipStream_t s);
 hipError_t launch_loss_reduce(const float* rowloss, int N, double scale, float* loss, hipStream_t s);
+// A grid of n workgroups and a few more, for kernels that have one per row and take `workgroup()` (common.hpp) for its number: a
+// dimension of a grid holds 2^32 threads at most, and what is beyond is left out without an error
+inline dim3 grid_of(size_t n) {
+    const size_t x = n < (1u << 20) ? n : (1u << 20);
+    return dim3((unsigned)x, (unsigned)((n + x - 1) / x));
+}
 // n words of p to be set to v by a kernel that has other work (n == 0: none)
 struct FillJob { int32_t* p; size_t n; int32_t v; };
 // second stage of a column sum: 256 threads per group of columns

@@ -158,3 +158,14 @@ def test_metric_of_this_many_classes(O):
             assert np.abs(got["d" + k]).max() <= 1e-6
         else:
             grad_close("G" + k, got["d" + k], ref["G" + k])
+
+
+@pytest.mark.parametrize("T,B,loss", ((9, 932068, ri.LOSS_SOFTMAX_CE), (17, 986896, ri.LOSS_LINEAR_MSE)))
+def test_more_rows_than_a_grid_of_a_workgroup_each_holds(T, B, loss):
+    """A grid holds 2^32 threads at most: 8.4 million rows with 512 threads each, 16.8 million with 256."""
+    case = ri.make_case(1, 2, 2, T, B, input_kind=ri.INPUT_DENSE, loss_kind=loss, wdist=("normal", 0.5), bias_std=0.1, seed=79)
+    gamma = ri.make_direction(case, 9)
+    r = GnRunner(case)
+    r.forward()
+    got = r.gauss_newton(gamma, rnn.GN_METRIC_LOSS)
+    check(got, r.Rz.cpu().numpy(), oracle.gauss_newton_vec(case, gamma, metric=0, want_Rz=True))
