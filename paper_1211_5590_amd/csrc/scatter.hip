@@ -100,12 +100,16 @@ __global__ __launch_bounds__(kGroupThreads) void dwx_group_kernel(const int32_t*
                                                                   int32_t* __restrict__ slot,
                                                                   int N, int NV, int H, int slices, ColsumJob sum_a,
                                                                   ColsumJob sum_b) {
-    if ((int)blockIdx.y >= slices) {         // column sums to be finished on the side, two groups per workgroup
+    if ((int)blockIdx.y >= slices) {         // column sums to be finished on the side, two groups per workgroup at a time
         __shared__ float red[kGroupThreads];
         static_assert(kGroupThreads == 512, "two groups of 256 threads");
-        const int half = threadIdx.x / 256, g = 2 * ((blockIdx.y - slices) * gridDim.x + blockIdx.x) + half;
-        const bool first = g < sum_a.groups;
-        colsum_finish(first ? sum_a : sum_b, first ? g : g - sum_a.groups, threadIdx.x % 256, red + 256 * half);
+        const int half = threadIdx.x / 256, groups = sum_a.groups + sum_b.groups, step = 2 * (gridDim.y - slices) * gridDim.x;
+        for (int g0 = 2 * ((blockIdx.y - slices) * gridDim.x + blockIdx.x); g0 < groups; g0 += step) {
+            const int g = g0 + half;
+            const bool first = g < sum_a.groups;
+            colsum_finish(first ? sum_a : sum_b, first ? g : g - sum_a.groups, threadIdx.x % 256, red + 256 * half);
+            if (g0 + step < groups) __syncthreads();     // `red` is taken again
+        }
         return;
     }
     __shared__ __attribute__((aligned(16))) unsigned long long key[CL];   // (id << 32) | position in the range; padding = ~0
@@ -286,7 +290,8 @@ size_t dwx_table_ints(int N, int NV) { return (size_t)dwx_ranges(N) * NV; }
 hipError_t launch_dwx_tokens_grouped(const int32_t* x, const float* Delta, float* dWx, int N, int NV, int H, int beta,
                                      float* scratch, int32_t* slot_table, const ColsumJob& a, const ColsumJob& b, hipStream_t s) {
     const int cl = dwx_range_len(N), ranges = dwx_ranges(N), slices = (H + kSliceCols - 1) / kSliceCols;
-    const int side = ((a.groups + b.groups + 1) / 2 + ranges - 1) / ranges;     // further rows of workgroups for the column sums
+    // further rows of workgroups for the column sums, as many as a grid's second dimension is sure to hold
+    const int side = min(((a.groups + b.groups + 1) / 2 + ranges - 1) / ranges, 32768);
     {
         ProfileScope ps(K_DWX_TOKENS, s);
         const dim3 grid(ranges, slices + side);

@@ -43,3 +43,15 @@ def test_token_gradient_of_this_many_ids(T, B, H):
     # every token's own row: the tolerance above is one for the whole matrix
     scale = np.abs(ref["dWx"]).max(axis=1, keepdims=True)
     assert (np.abs(got - ref["dWx"]) <= 1e-3 * scale + 1e-12).all()
+
+
+def test_token_gradient_beside_the_column_sums_of_very_many_outputs():
+    """Workgroups of the same launch finish the column sums of dc: with one range of ids and 2.2 million outputs more of them than a
+    grid's second dimension holds."""
+    case = ri.make_case(30, 4, 2_200_004, 33, 1, wdist=("normal", 0.5), bias_std=0.1, seed=78)
+    ref = oracle.fwd_bptt(case)
+    r = Runner(case)
+    r.step()
+    got = r.results()
+    for k in ("dWx", "dc", "db", "dV"):
+        grad_close(k, got[k], ref[k])
