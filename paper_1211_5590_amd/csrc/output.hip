@@ -34,9 +34,11 @@ __device__ __forceinline__ double lse_of(float m, float s) { return (double)m + 
 __global__ __launch_bounds__(256) void ce_row_stats_kernel(const float* __restrict__ Z,
                                                            const int32_t* __restrict__ y,
                                                            float* __restrict__ lse,
-                                                           float* __restrict__ rowloss, int O) {
+                                                           float* __restrict__ rowloss, int N, int O) {
     __shared__ float sm[4], ss[4];
-    const int n = blockIdx.x, tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    const int n = (int)workgroup();
+    if (n >= N) return;
+    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const float* z = Z + (size_t)n * O;
     float m = -INFINITY, s = 0.f;
     for (int k = tid; k < O; k += blockDim.x) {
@@ -72,7 +74,7 @@ __global__ __launch_bounds__(256) void ce_merge_stats_kernel(const float* __rest
                                                              float* __restrict__ lse,
                                                              float* __restrict__ rowloss, int N, int O) {
     const int lane = threadIdx.x % kWave;
-    const int n = blockIdx.x * 4 + threadIdx.x / kWave;
+    const int n = (int)workgroup() * 4 + threadIdx.x / kWave;
     if (n >= N) return;
     const float2* st = reinterpret_cast<const float2*>(stats) + (size_t)n * parts;
     float m = -INFINITY, s = 0.f;
@@ -309,14 +311,14 @@ int colsum_chunks(int N) { const int r = rows_per_chunk(N); return (N + r - 1) /
 hipError_t launch_ce_row_stats(const float* Z, const int32_t* y, float* lse, float* rowloss, int N,
                                int O, hipStream_t s) {
     ProfileScope ps(K_CE_ROW_STATS, s);
-    hipLaunchKernelGGL(ce_row_stats_kernel, dim3(N), dim3(256), 0, s, Z, y, lse, rowloss, O);
+    hipLaunchKernelGGL(ce_row_stats_kernel, grid_of((size_t)N), dim3(256), 0, s, Z, y, lse, rowloss, N, O);
     return hipGetLastError();
 }
 
 hipError_t launch_ce_merge_stats(const float* stats, int parts, const float* Z, const int32_t* y,
                                  float* lse, float* rowloss, int N, int O, hipStream_t s) {
     ProfileScope ps(K_CE_ROW_STATS, s);
-    hipLaunchKernelGGL(ce_merge_stats_kernel, dim3((N + 3) / 4), dim3(256), 0, s, stats, parts, Z, y, lse,
+    hipLaunchKernelGGL(ce_merge_stats_kernel, grid_of(((size_t)N + 3) / 4), dim3(256), 0, s, stats, parts, Z, y, lse,
                        rowloss, N, O);
     return hipGetLastError();
 }

@@ -56,8 +56,9 @@ __global__ __launch_bounds__(256) void dwx_tokens_kernel(const int32_t* __restri
                                                          float* __restrict__ dWx, int N, int NV,
                                                          int H, int beta) {
     const int lane = threadIdx.x % kWave;
-    const int v = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-    if (v >= NV) return;
+    const long long task = (long long)workgroup() * (blockDim.x / kWave) + threadIdx.x / kWave;
+    if (task >= NV) return;
+    const int v = (int)task;
     for (int c0 = 0; c0 < H; c0 += kColsPerPass) {
         float acc[kQ];
         const bool seen = scan_token(x, Delta, v, 0, N, H, c0, lane, acc);
@@ -217,9 +218,9 @@ __global__ __launch_bounds__(256) void dwx_gather_kernel(const float* __restrict
                                                          float* __restrict__ dWx, int NV, int H,
                                                          int ranges, int CL, int beta, int col_chunks) {
     const int lane = threadIdx.x % kWave;
-    const long long task = (long long)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
+    const long long task = (long long)workgroup() * (blockDim.x / kWave) + threadIdx.x / kWave;
+    if (task >= (long long)NV * col_chunks) return;
     const int v = (int)(task / col_chunks), chunk = (int)(task % col_chunks);
-    if (v >= NV) return;
     const int c0 = chunk * 4 * kWave + 4 * lane, c = max(min(c0, H - 4), 0);
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     bool any = false;
@@ -314,19 +315,19 @@ hipError_t launch_dwx_tokens_grouped(const int32_t* x, const float* Delta, float
     ProfileScope ps(K_DWX_TOKENS, s);
     const int rows_per_block = 256 / kWave, col_chunks = (H + 4 * kWave - 1) / (4 * kWave);
     const long long tasks = (long long)NV * col_chunks;
-    const unsigned gb = (unsigned)((tasks + rows_per_block - 1) / rows_per_block);
-    if (H >= 4) hipLaunchKernelGGL(dwx_gather_kernel<false>, dim3(gb), dim3(256), 0, s, scratch, slot_table, Delta, dWx,
+    const dim3 gb = grid_of((size_t)((tasks + rows_per_block - 1) / rows_per_block));
+    if (H >= 4) hipLaunchKernelGGL(dwx_gather_kernel<false>, gb, dim3(256), 0, s, scratch, slot_table, Delta, dWx,
                                    NV, H, ranges, cl, beta, col_chunks);
-    else hipLaunchKernelGGL(dwx_gather_kernel<true>, dim3(gb), dim3(256), 0, s, scratch, slot_table, Delta, dWx,
+    else hipLaunchKernelGGL(dwx_gather_kernel<true>, gb, dim3(256), 0, s, scratch, slot_table, Delta, dWx,
                             NV, H, ranges, cl, beta, col_chunks);
     return hipGetLastError();
 }
 
 hipError_t launch_dwx_tokens(const int32_t* x, const float* Delta, float* dWx, int N, int NV, int H, int beta, hipStream_t s) {
     const int rows_per_block = 256 / kWave;
-    const int blocks = (NV + rows_per_block - 1) / rows_per_block;
+    const dim3 blocks = grid_of(((size_t)NV + rows_per_block - 1) / rows_per_block);
     ProfileScope ps(K_DWX_TOKENS, s);
-    hipLaunchKernelGGL(dwx_tokens_kernel, dim3(blocks), dim3(256), 0, s, x, Delta, dWx, N, NV, H, beta);
+    hipLaunchKernelGGL(dwx_tokens_kernel, blocks, dim3(256), 0, s, x, Delta, dWx, N, NV, H, beta);
     return hipGetLastError();
 }
 

@@ -45,6 +45,20 @@ def test_token_gradient_of_this_many_ids(T, B, H):
     assert (np.abs(got - ref["dWx"]) <= 1e-3 * scale + 1e-12).all()
 
 
+@pytest.mark.parametrize("T,B,H,NV,O", ((4097, 4096, 2, 20, 3), (3, 5, 1, 67_108_900, 4), (11, 4, 1, 67_108_900, 4)))
+def test_more_rows_and_more_tokens_than_one_dimension_of_a_grid_holds(T, B, H, NV, O):
+    """A grid holds 2^32 threads per dimension: 16.8 million workgroups of 256 threads, one per row or one per four tokens."""
+    case = ri.make_case(NV, H, O, T, B, wdist=("normal", 0.5), bias_std=0.1, seed=80, with_h0=True)
+    case["x"].reshape(-1)[-1] = NV - 1                    # the last token occurs
+    ref = oracle.fwd_bptt(case, h0=case["h0"])
+    r = Runner(case)
+    r.step()
+    got = r.results()
+    assert abs(got["loss"] - ref["loss"]) <= 1e-4 * abs(ref["loss"])
+    for k in ("dWx", "dWh", "db", "dV", "dc", "dh0"):
+        grad_close(k, got[k], ref[k])
+
+
 def test_token_gradient_beside_the_column_sums_of_very_many_outputs():
     """Workgroups of the same launch finish the column sums of dc: with one range of ids and 2.2 million outputs more of them than a
     grid's second dimension holds."""
