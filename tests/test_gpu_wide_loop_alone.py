@@ -205,6 +205,50 @@ def test_launches_that_wait_inside_take_turns(beside):
     compare(r.results(), ref)
 
 
+@pytest.mark.parametrize("replayed", ("wide_loop", "grid_loop"))
+def test_eager_wide_loops_beside_a_replayed_graph(replayed):
+    """A graph's launches take no turns: they may find the chip partly taken by an eager loop and the other way round.  Both end, with
+    right results and status 0, whichever groups were run alone."""
+    eager, graph = Runner(make(600, 40, 40, 0, seed=6)), Runner(make(500, 33, 40, 1) if replayed == "wide_loop" else make(900, 1, 40, 1))
+    assert rnn.rnn_recurrence_variant(graph.dims) == ("xcd_mfma" if replayed == "wide_loop" else "grid_resident")
+    refs = [oracle.fwd_bptt(r.case, h0=r.case.get("h0"), dh_last=r.case.get("dh_last")) for r in (eager, graph)]
+    eager.step()
+    graph.step()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    captured = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side), torch.cuda.graph(captured, stream=side):
+        graph.forward(); graph.loss_(); graph.bptt()
+    errors, alone = [], []
+
+    def work():
+        try:
+            with torch.cuda.stream(side):
+                for _ in range(20):
+                    captured.replay()
+                    side.synchronize()
+        except Exception as e:                              # noqa: BLE001 -- shown by the assert below
+            errors.append(e)
+
+    t = threading.Thread(target=work)
+    t.start()
+    try:
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(20):
+                eager.forward()
+                alone.append(rnn.rnn_workspace_groups_alone(eager.dims, eager.ws))
+                eager.loss_(); eager.bptt()
+            torch.cuda.current_stream().synchronize()
+    finally:
+        t.join()
+    torch.cuda.synchronize()
+    print("groups alone:", alone, flush=True)
+    assert not errors, errors
+    for r, ref in zip((eager, graph), refs):
+        assert rnn.rnn_workspace_status(r.dims, r.ws) == 0
+        compare(r.results(), ref)
+
+
 @pytest.mark.parametrize("H,B,T,kind,wide", ((200, 20, 35, 0, False), (193, 1, 64, 1, False), (256, 2, 2047, 0, False),
                                              (256, 2, 2048, 0, True), (193, 5, 2047, 1, False), (193, 5, 2048, 1, True), (256, 127, 70, 0, False),
                                              (257, 5, 16, 0, True)))
