@@ -84,17 +84,16 @@ __device__ __forceinline__ float4 columns(const float* __restrict__ row, int c, 
 constexpr int kGroupThreads = 512;
 constexpr int kRowsInFlight = 8;
 
-// One range of CL ids by one slice of 64 columns per workgroup: sort, group, sum.  part: compact partial rows
+// One range of CL ids by one slice of 4 LANES columns per workgroup: sort, group, sum.  part: compact partial rows
 // [range*CL + group][H]; slot[token][range] = group + 1, or -(n + 1) for a single occurrence at
 // row n, where the token occurs in the range (the table is zeroed before this kernel).  Further rows of
 // workgroups finish column sums.
-// What bounds it is the chain sort - group - sum of the longest group, and there are few ranges (700 ids: 3): so every slice of a
-// range sorts it again rather than wait for another, and 16 lanes have a group, 32 groups at a time.  (One workgroup
+// With few ranges (700 ids: 3) what bounds it is the chain sort - group - sum of the longest group: so every slice of 64 columns
+// sorts its range again rather than wait for another, and 16 lanes have a group, 32 groups at a time.  (One workgroup
 // per range, all columns, bitonic sort: 14.9 us for 100 rows of 500, 25.4 for 800 of 500, 34.3 for 2310 of 650, 57.0 for 16384 of
-// 1024; now 8.3, 13.5, 12.9 and 25.4.  Sixteen rows in flight: 7.8, 13.0, 12.1 and 29.7.)
-constexpr int kSliceCols = 64, kLanes = kSliceCols / 4;   // columns of a workgroup, lanes of a group's row
-
-template <int CL, bool SHORT>
+// 1024; in slices 8.3, 13.5, 12.9 and 25.4.  Sixteen rows in flight: 7.8, 13.0, 12.1 and 29.7.)
+// With many it is the memory it moves, a wavefront has a group, 256 columns at a time, and there are fewer slices that sort the same.
+template <int CL, int LANES, bool SHORT>
 __global__ __launch_bounds__(kGroupThreads) void dwx_group_kernel(const int32_t* __restrict__ x,
                                                                   const float* __restrict__ Delta,
                                                                   float* __restrict__ part,
@@ -181,14 +180,14 @@ __global__ __launch_bounds__(kGroupThreads) void dwx_group_kernel(const int32_t*
     }
     if (tid == 0) seg_start[ngroups] = nvalid;
     __syncthreads();
-    // 16 lanes per group: rows added in ascending position, four columns per lane (at 4-byte alignment; the lane of a
+    // LANES lanes per group: rows added in ascending position, four columns per lane (at 4-byte alignment; the lane of a
     // ragged end reads the row's last four), eight rows in flight.
     // A token that occurs once in the range needs no partial row: the table points at its
     // Delta row instead (negative entry).
     const int ranges = gridDim.x;
-    const bool notes = blockIdx.y == 0 && tid % kLanes == 0;      // enters the group in the table
-    const int c0 = blockIdx.y * kSliceCols + 4 * (tid % kLanes), c = max(min(c0, H - 4), 0);
-    for (int grp = tid / kLanes; grp < ngroups; grp += kGroupThreads / kLanes) {
+    const bool notes = blockIdx.y == 0 && tid % LANES == 0;      // enters the group in the table
+    const int c0 = 4 * (blockIdx.y * LANES + tid % LANES), c = max(min(c0, H - 4), 0);
+    for (int grp = tid / LANES; grp < ngroups; grp += kGroupThreads / LANES) {
         const int i0 = seg_start[grp], i1 = seg_start[grp + 1];
         const int v = (int)(key[i0] >> 32);
         const bool once = i1 - i0 == 1;
@@ -290,16 +289,26 @@ size_t dwx_table_ints(int N, int NV) { return (size_t)dwx_ranges(N) * NV; }
 
 hipError_t launch_dwx_tokens_grouped(const int32_t* x, const float* Delta, float* dWx, int N, int NV, int H, int beta,
                                      float* scratch, int32_t* slot_table, const ColsumJob& a, const ColsumJob& b, hipStream_t s) {
-    const int cl = dwx_range_len(N), ranges = dwx_ranges(N), slices = (H + kSliceCols - 1) / kSliceCols;
+    const int cl = dwx_range_len(N), ranges = dwx_ranges(N);
+    // A wavefront for a group, and 256 columns for a workgroup, where that leaves enough workgroups for the chip's 256 compute units and
+    // three quarters of the lanes have columns.  (us of both launches, 64 columns and 256, 10000 tokens by Zipf's law: 2000 ids,
+    // H = 1024: 29 and 32; 16384 ids, H = 512: 39 and 40, H = 1024: 46 and 44; 65536 ids, H = 256, 512, 1024: 82 and 78, 108 and 94, 153
+    // and 124; 140000 ids, H = 256: 97 and 107; 1048576 ids, H = 100, 256, 512, 1024: 335 and 366, 643 and 469, 1200 and 751, 1904 and 1306.)
+    const bool wide = H > 192 && ranges * ((H + 255) / 256) >= 192;
+    const int cols = wide ? 256 : 64, slices = (H + cols - 1) / cols;
     // further rows of workgroups for the column sums, as many as a grid's second dimension is sure to hold
     const int side = min(((a.groups + b.groups + 1) / 2 + ranges - 1) / ranges, 32768);
     {
         ProfileScope ps(K_DWX_TOKENS, s);
         const dim3 grid(ranges, slices + side);
-#define RNN_GROUP(CL)                                                                                    \
-    do {                                                                                                 \
-        if (H >= 4) hipLaunchKernelGGL((dwx_group_kernel<CL, false>), grid, dim3(kGroupThreads), 0, s, x, Delta, scratch, slot_table, N, NV, H, slices, a, b); \
-        else hipLaunchKernelGGL((dwx_group_kernel<CL, true>), grid, dim3(kGroupThreads), 0, s, x, Delta, scratch, slot_table, N, NV, H, slices, a, b);         \
+#define RNN_GROUP_OF(CL, LANES, SHORT)                                                                                         \
+    hipLaunchKernelGGL((dwx_group_kernel<CL, LANES, SHORT>), grid, dim3(kGroupThreads), 0, s, x, Delta, scratch, slot_table, N, NV, H, \
+                       slices, a, b)
+#define RNN_GROUP(CL)                                   \
+    do {                                                \
+        if (wide) RNN_GROUP_OF(CL, 64, false);          \
+        else if (H >= 4) RNN_GROUP_OF(CL, 16, false);   \
+        else RNN_GROUP_OF(CL, 16, true);                \
     } while (0)
         switch (cl) {
             case 256: RNN_GROUP(256); break;
@@ -309,6 +318,7 @@ hipError_t launch_dwx_tokens_grouped(const int32_t* x, const float* Delta, float
             default: RNN_GROUP(4096); break;
         }
 #undef RNN_GROUP
+#undef RNN_GROUP_OF
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

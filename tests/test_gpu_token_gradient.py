@@ -27,10 +27,12 @@ def test_token_gradient_at_this_row_width(H, NV):
     grad_close("2x dWx", r.results()["dWx"], 2.0 * ref["dWx"])
 
 
-@pytest.mark.parametrize("T,B,H", [(5, 7, 63), (16, 16, 64), (257, 1, 65), (771, 5, 129), (1024, 64, 9), (1025, 64, 9), (2049, 64, 9)])
+@pytest.mark.parametrize("T,B,H", [(5, 7, 63), (16, 16, 64), (257, 1, 65), (771, 5, 129), (1024, 64, 9), (1025, 64, 9), (2049, 64, 9),
+                                   (250, 256, 192), (191, 256, 193), (3, 16299, 193), (95, 256, 257), (11, 2211, 257), (1, 65537, 257),
+                                   (3, 43691, 257)])
 def test_token_gradient_of_this_many_ids(T, B, H):
     """One and several ranges of ids, a range that is full and one of a single id, ranges of 256, 512 and 1024 ids, and slices of
-    64 columns; one token makes up most of the ids."""
+    64 columns and, from 192 ranges by 256 columns on, of 256; one token makes up most of the ids."""
     case = ri.make_case(40, H, 8, T, B, wdist=("normal", 0.5 / np.sqrt(H)), bias_std=0.1, seed=60 + T)
     x = case["x"].reshape(-1)
     x[np.arange(x.size) % 3 > 0] = 17
