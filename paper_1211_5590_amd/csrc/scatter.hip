@@ -118,8 +118,9 @@ __global__ __launch_bounds__(kGroupThreads) void dwx_group_kernel(const int32_t*
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const int base = blockIdx.x * CL;
     const int nvalid = min(CL, N - base);
-    if constexpr (CL <= 512) {
-        // an id's place is the number of ids before it: CL / 4 looks per thread and two barriers
+    if constexpr (CL <= 256) {
+        // an id's place is the number of ids before it: 32 looks per thread and two barriers.  (512 ids are 128 looks, more than the 45
+        // stages of the other form take: 100000 ids of 64 columns 77 and 71 us for both launches, of 512 columns 112 and 104)
         __shared__ __attribute__((aligned(16))) int ids[CL];
         constexpr int TPK = kGroupThreads / CL, SPAN = CL / TPK;      // threads per id, ids each of them looks at
         const int i = tid / TPK, q = tid % TPK;
