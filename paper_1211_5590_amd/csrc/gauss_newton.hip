@@ -62,26 +62,31 @@ __global__ __launch_bounds__(256) void scale_kernel(float* p, size_t n, float al
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] *= alpha;
 }
 
-// One workgroup per row n: RZ_n <- (p * RZ_n - p (p . RZ_n)) * scale with p = softmax(Z_n), the
-// product of the cross-entropy's Hessian with respect to the logits and RZ_n.
+// RZ_n <- (p * RZ_n - p (p . RZ_n)) * scale with p = softmax(Z_n), the product of the cross-entropy's Hessian with respect to the
+// logits and RZ_n; R rows per workgroup: one, or one per wavefront.
 // What bounds it is the memory it reads and writes, so both rows stay in registers between the three passes over them: P pieces
 // of four per thread, all requested at once, at 4-byte alignment (a row starts anywhere).  Rows of more than 16384 classes
-// are read again, a piece at a time.  (800 rows of 10000, one float at a time and every pass from memory: 41.8 us; now 12.5)
+// are read again, a piece at a time.  (800 rows of 10000, one float at a time and every pass from memory: 41.8 us; now 12.5.)
+// A wavefront holds rows of up to 1024 classes, and then needs no barrier: four pieces a lane.  (Rows with a workgroup and with a
+// wavefront each, us: 524288 of 16 classes 939 and 129, 131072 of 300, 512, 800 and 1000 classes 256 and 74, 238 and 128, 316
+// and 219, 338 and 292; 800 rows 6 to 8 either way.)
 constexpr int GN_T = 512;                              // threads
-template <int P>
+template <int P, int R>
 __global__ __launch_bounds__(GN_T) void gn_softmax_metric_kernel(const float* __restrict__ Z, float* __restrict__ RZ,
                                                                  int N, int O, float scale) {
-    if (workgroup() >= (size_t)N) return;
-    constexpr int NW = GN_T / kWave;
+    constexpr int TR = GN_T / R, NW = TR / kWave;      // threads and wavefronts of a row
+    static_assert(R == 1 || NW == 1, "rows share no barrier");
+    const size_t n = R == 1 ? workgroup() : workgroup() * R + __builtin_amdgcn_readfirstlane(threadIdx.x / TR);
+    if (n >= (size_t)N) return;
     __shared__ float red[3][NW];
-    const size_t base = workgroup() * O;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const size_t base = n * O;
+    const int tid = R == 1 ? threadIdx.x : threadIdx.x % TR, lane = tid & 63, wave = tid >> 6;
     const float* z = Z + base;
     float* rz = RZ + base;
     constexpr bool KEPT = P > 0;
     float4 e[KEPT ? P : 1], r[KEPT ? P : 1];
-    const int steps = KEPT ? P : (O + 4 * GN_T - 1) / (4 * GN_T);
-    auto at = [&](int u) { return 4 * (u * GN_T + tid); };
+    const int steps = KEPT ? P : (O + 4 * TR - 1) / (4 * TR);
+    auto at = [&](int u) { return 4 * (u * TR + tid); };
     auto logits = [&](int u) {                         // what does not exist takes no part: exp(-inf) = 0
         const int k = at(u), left = O - k;
         float4 v = piece(z + k, left);
@@ -103,11 +108,13 @@ __global__ __launch_bounds__(GN_T) void gn_softmax_metric_kernel(const float* __
         for (int u = 0; u < steps; ++u) { const float4 v = logits(u); m = fmaxf(m, fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w))); }
     }
     m = max64(m);
-    if (lane == 0) red[0][wave] = m;
-    __syncthreads();
-    m = red[0][0];
+    if constexpr (R == 1) {
+        if (lane == 0) red[0][wave] = m;
+        __syncthreads();
+        m = red[0][0];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) m = fmaxf(m, red[0][w]);
+        for (int w = 1; w < NW; ++w) m = fmaxf(m, red[0][w]);
+    }
     float s = 0.f, dot = 0.f;
     auto take = [&](float4& v, const float4& q) {      // v <- exp(v - m)
         v.x = exp_exact(v.x - m); v.y = exp_exact(v.y - m); v.z = exp_exact(v.z - m); v.w = exp_exact(v.w - m);
@@ -122,11 +129,13 @@ __global__ __launch_bounds__(GN_T) void gn_softmax_metric_kernel(const float* __
     }
     s = sum64(s);
     dot = sum64(dot);
-    if (lane == 0) { red[1][wave] = s; red[2][wave] = dot; }
-    __syncthreads();
-    s = dot = 0.f;
+    if constexpr (R == 1) {
+        if (lane == 0) { red[1][wave] = s; red[2][wave] = dot; }
+        __syncthreads();
+        s = dot = 0.f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) { s += red[1][w]; dot += red[2][w]; }
+        for (int w = 0; w < NW; ++w) { s += red[1][w]; dot += red[2][w]; }
+    }
     const float inv = 1.0f / s;
     const float pdot = dot * inv;                      // p . RZ
     auto out = [&](int u, const float4& v, const float4& q) {
@@ -178,13 +187,17 @@ hipError_t launch_scale(float* p, size_t n, float alpha, hipStream_t s) {
 }
 hipError_t launch_gn_softmax_metric(const float* Z, float* RZ, int N, int O, float scale, hipStream_t s) {
     ProfileScope ps(K_GN_METRIC, s);
-#define RNN_GN(P) hipLaunchKernelGGL(gn_softmax_metric_kernel<P>, grid_of((size_t)N), dim3(GN_T), 0, s, Z, RZ, N, O, scale)
-    const int pieces = (O - 1) / (4 * GN_T) + 1;       // of a thread
-    if (pieces <= 1) RNN_GN(1);
-    else if (pieces <= 3) RNN_GN(3);
-    else if (pieces <= 5) RNN_GN(5);
-    else if (pieces <= 8) RNN_GN(8);
-    else RNN_GN(0);
+#define RNN_GN(P, R) hipLaunchKernelGGL((gn_softmax_metric_kernel<P, R>), grid_of(((size_t)N + R - 1) / R), dim3(GN_T), 0, s, Z, RZ, N, O, scale)
+    constexpr int ROWS = GN_T / kWave;
+    const int pieces = (O - 1) / (4 * GN_T) + 1;       // of a thread, where a row has a workgroup
+    if (O <= 4 * kWave) RNN_GN(1, ROWS);
+    else if (O <= 8 * kWave) RNN_GN(2, ROWS);
+    else if (O <= 16 * kWave) RNN_GN(4, ROWS);
+    else if (pieces <= 1) RNN_GN(1, 1);
+    else if (pieces <= 3) RNN_GN(3, 1);
+    else if (pieces <= 5) RNN_GN(5, 1);
+    else if (pieces <= 8) RNN_GN(8, 1);
+    else RNN_GN(0, 1);
 #undef RNN_GN
     return hipGetLastError();
 }

@@ -141,10 +141,10 @@ def test_gauss_newton_vec_at_configuration_size(name, overrides, flags):
     check(got, r.Rz.cpu().numpy(), _config_refs[name])
 
 
-@pytest.mark.parametrize("O", [1, 2, 3, 5, 2047, 2048, 2049, 6145, 10243, 16384, 16387])
+@pytest.mark.parametrize("O", [1, 2, 3, 5, 255, 256, 257, 512, 513, 1024, 1025, 2047, 2048, 2049, 6145, 10243, 16384, 16387])
 def test_metric_of_this_many_classes(O):
-    """The softmax metric's kernel: fewer classes than a piece, ragged rows, every count of pieces a thread keeps, and rows that
-    are read again."""
+    """The softmax metric's kernel: fewer classes than a piece, ragged rows, a row to a wavefront and to a workgroup (12 rows: one and a
+    half workgroups of the former), every count of pieces a thread keeps, and rows that are read again."""
     case = ri.make_case(30, 7, O, 3, 4, act=1, wdist=("normal", 0.3), bias_std=0.5, seed=300 + O)
     case["y"][:] %= O
     gamma = ri.make_direction(case, 11)
