@@ -18,26 +18,29 @@ __global__ __launch_bounds__(256) void reverse_rows_kernel(const float* __restri
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < row; i += gridDim.x * blockDim.x) d[i] = s[i];
 }
 
-// What the R-operator's sweep needs before its loop, in one launch of 256 threads per workgroup: the first T B workgroups turn a row
-// of C (with the row of M that its token picks) and one of Hs round in time, the next transpose a 32 x 32 tile of Wh each, and all
-// fill a share of the loop's exchange words.  (Four launches before, 3 us each.)
+// What the R-operator's sweep needs before its loop, in one launch of 256 threads per workgroup: the first workgroups turn rows
+// of C (with the row of M that its token picks) and of Hs round in time, 2^txs threads a row, the next transpose a 32 x 32 tile of Wh
+// each, and all fill a share of the loop's exchange words.  (Four launches before, 3 us each.  With a workgroup for every row
+// however narrow, 524288 rows of 64 took 324 us, the four launches 273; now 168.)
 struct GnPrepare {
     const int32_t* x; const float* M;          // x NULL: no gathered rows
     const float *C, *Hs, *Wh;
     float *Crev, *hrev, *WhT;
-    int T, B, H;
+    int T, B, H, txs;
     FillJob ring, counters;
 };
+__host__ __device__ inline int gn_row_workgroups(int N, int txs) { return (int)(((size_t)N + (256 >> txs) - 1) >> (8 - txs)); }
 __global__ __launch_bounds__(256) void gn_prepare_kernel(GnPrepare a) {
     const int H = a.H, N = a.T * a.B, tid = threadIdx.x;
     fill_share(a.ring.p, a.ring.n, a.ring.v, workgroup(), workgroups(), 256);
     fill_share(a.counters.p, a.counters.n, a.counters.v, workgroup(), workgroups(), 256);
-    const int wg = (int)workgroup();
-    if (wg < N) {
-        const int n = wg, t = n / a.B, src = (a.T - 1 - t) * a.B + n % a.B;
+    const int wg = (int)workgroup(), row_wgs = gn_row_workgroups(N, a.txs);
+    if (wg < row_wgs) {
+        if (((size_t)wg << (8 - a.txs)) + (tid >> a.txs) >= (size_t)N) return;
+        const int n = (wg << (8 - a.txs)) + (tid >> a.txs), t = n / a.B, src = (a.T - 1 - t) * a.B + n % a.B;
         const float* row = a.x ? a.M + (size_t)a.x[src] * H : nullptr;
         const size_t from = (size_t)src * H, to = (size_t)n * H;
-        for (int j = tid; j < H; j += 256) {
+        for (int j = tid & ((1 << a.txs) - 1); j < H; j += 1 << a.txs) {
             const float c = a.C[from + j];
             a.Crev[to + j] = row ? c + row[j] : c;
             a.hrev[to + j] = a.Hs[from + j];
@@ -46,7 +49,7 @@ __global__ __launch_bounds__(256) void gn_prepare_kernel(GnPrepare a) {
     }
     __shared__ float tile[32][33];
     // (past the last tile: r0 >= H, nothing to move)
-    const int side = (H + 31) / 32, b = wg - N, r0 = b / side * 32, c0 = b % side * 32, tx = tid % 32, ty = tid / 32;
+    const int side = (H + 31) / 32, b = wg - row_wgs, r0 = b / side * 32, c0 = b % side * 32, tx = tid % 32, ty = tid / 32;
     for (int i = ty; i < 32; i += 8)
         if (r0 + i < H && c0 + tx < H) tile[i][tx] = a.Wh[(size_t)(r0 + i) * H + c0 + tx];
     __syncthreads();
@@ -170,9 +173,11 @@ hipError_t launch_reverse_rows(const float* src, float* dst, int T, int row, hip
 hipError_t launch_gn_prepare(const int32_t* x, const float* M, const float* C, const float* Hs, const float* Wh, float* Crev,
                              float* hrev, float* WhT, int T, int B, int H, FillJob ring, FillJob counters, hipStream_t s) {
     const int side = (H + 31) / 32;
-    const GnPrepare a = {x, M, C, Hs, Wh, Crev, hrev, WhT, T, B, H, ring, counters};
+    int txs = 0;
+    while (txs < 8 && (1 << txs) < H) ++txs;
+    const GnPrepare a = {x, M, C, Hs, Wh, Crev, hrev, WhT, T, B, H, txs, ring, counters};
     ProfileScope ps(K_MISC, s);
-    hipLaunchKernelGGL(gn_prepare_kernel, grid_of((size_t)T * B + (size_t)side * side), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(gn_prepare_kernel, grid_of((size_t)gn_row_workgroups(T * B, txs) + (size_t)side * side), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 hipError_t launch_fill_zero(float* p, size_t n, hipStream_t s) {

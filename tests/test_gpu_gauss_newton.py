@@ -160,6 +160,19 @@ def test_metric_of_this_many_classes(O):
             grad_close("G" + k, got["d" + k], ref["G" + k])
 
 
+@pytest.mark.parametrize("H", [1, 2, 3, 4, 5, 33, 64, 65, 129, 257])
+@pytest.mark.parametrize("kind", (0, 1))
+def test_rows_turned_round_at_this_width(H, kind):
+    """The launch in front of the R-operator's loop gives a row as many threads as its width, up to 256: whole and ragged widths, and
+    a number of rows that fills no workgroup."""
+    case = ri.make_case(30, H, 30, 7, 13, input_kind=kind, wdist=("normal", 0.4 / np.sqrt(H)), bias_std=0.2, seed=500 + H)
+    gamma = ri.make_direction(case, 12)
+    r = GnRunner(case)
+    r.forward()
+    got = r.gauss_newton(gamma, rnn.GN_METRIC_LOSS)
+    check(got, r.Rz.cpu().numpy(), oracle.gauss_newton_vec(case, gamma, metric=0, want_Rz=True))
+
+
 @pytest.mark.parametrize("T,B,loss", ((9, 932068, ri.LOSS_SOFTMAX_CE), (17, 986896, ri.LOSS_LINEAR_MSE)))
 def test_more_rows_than_a_grid_of_a_workgroup_each_holds(T, B, loss):
     """A grid holds 2^32 threads at most: 8.4 million rows with 512 threads each, 16.8 million with 256."""
