@@ -182,6 +182,11 @@ int rnn_check_tokens(const void *ids, int64_t n, int32_t limit, int32_t *bad_cou
  * up to a hundred times as slowly; the status stays 0 and the results are the same, bit for bit.  The time is what that
  * workgroup would take, 0.2 ms at least and 0.25 s at most.  The limit holds for the waits of the loop that
  * follows.
+ *
+ * Launches of the library whose workgroups wait for each other ("xcd_mfma", "grid_resident", rnn_train_stream,
+ * rnn_mlp_train with one hidden layer, rnn_window with RNN_FLAG_COOPERATIVE) run one after another on a device, whatever
+ * streams and threads they come from; only those of replayed graphs do not wait for their turn.  Loops of
+ * "batch_mfma" and "wg_resident" on several streams run side by side.
  */
 int rnn_set_wait_limit(int polls);
 int rnn_workspace_init(const rnn_dims *dims, void *workspace, size_t workspace_bytes,

@@ -45,12 +45,14 @@
 // beyond the last-level cache: requests a step ahead by the epilogue's lanes 0.95 and 1.03, by the carrier four steps ahead but every step
 // 0.96 and 1.09 - 0.78 and 0.88 when they are made to hit the cache -, two at a time 0.88 and 0.94, four 0.79 and 0.86, eight 0.76 and
 // 0.80; 500 units, batch 1: 0.91 and 0.91 -> 0.84 and 0.83; 513 units, batch 19: 1.20 and 1.16 -> 1.11 and 1.10.)
-// Token input takes its rows of Wx in the loop, a step ahead, instead of a gather launch that writes them
+// Token input takes its rows of Wx in the loop, as the other operands, instead of a gather launch that writes them
 // out for all steps and is read back (256 steps of 64 rows at H = 1024: 27 us).
 // A hidden size that is no multiple of 4 has the rest of a row's last piece published as zeros.
 // A workgroup takes its group from the XCD it finds itself on and its column slice from a per-XCD
 // counter, so all workgroups of a group share one L2 by construction whenever the 256 workgroups are
-// co-resident (one workgroup per compute unit: checked before the launch).  The launch is not cooperative but takes turns with
+// co-resident (checked before the launch).  That is all the exchange asks for: its looks pass the first-level cache, so it does not
+// matter to it whether two workgroups of a group share a compute unit, which the LDS they take rules out.  (Two on each would have half
+// the columns, and twice as many parts of K to add up: other sums in the last bits.)  The launch is not cooperative but takes turns with
 // others of its kind (gang.hip).  Where other work keeps a part of a group off the chip for longer than the loop would
 // take on one workgroup, one of those that did come runs it by itself and the others leave, so the launch ends with the same
 // results, bit for bit, whatever else the GPU does (run_alone below).
@@ -58,14 +60,14 @@
 // up sets s_abort, and the workgroup's others leave at their next look at it, the carrier up to 16 steps later.  Each passes at
 // most one barrier per step and then ends, and a barrier does not wait for wavefronts that have ended.
 //
-// Measured (a loop of 256 steps, batch 64, H = 1024): 600 us with the state read from the history and
-// device-scope stores, 475 now (1000 words; 540 right behind the large products of 10000 words, which
-// leave the chip at a lower clock); 100 steps at H = 513, batch 33: 207 -> 161, at H = 512, batch 64:
-// 158 -> 132.  A step at H = 1024, batch 64 takes about 3900 clocks: 2050 for the matrix instructions of the
+// Measured (a forward loop of 256 steps, batch 64, H = 1024): 600 us with the state read from the history and
+// device-scope stores, 455 now (1000 words; 512 right behind the large products of 10000 words, which
+// leave the chip at a lower clock); 100 steps at H = 513, batch 33: 207 -> 148, at H = 512, batch 64:
+// 158 -> 101.  A step at H = 1024, batch 64 takes about 3700 clocks: 2050 for the matrix instructions of the
 // two wavefronts of a SIMD at the rate of float32, 550 from the last of them to the store, the rest for the
 // store and the look.  With fewer columns the instructions are less of it (100 steps, us of a forward loop with 64, 32, 16
-// columns): H = 500, batch 1: 134, 113, 110; H = 513, batch 19: 165, 136; H = 1024, batch 32: 200, 154;
-// H = 400, batch 40: 137, 117; H = 300, batch 20: 122, 110, 109.
+// columns before the carrier, and now with the fewest): H = 500, batch 1: 134, 113, 110, 91; H = 513, batch 19: 165, 136, 117; H = 1024,
+// batch 32: 200, 154, 146; H = 400, batch 40: 137, 117, 99; H = 300, batch 20: 122, 110, 109, 88.
 #include "common.hpp"
 #include "internal.hpp"
 #include "prof.hpp"
@@ -731,7 +733,7 @@ const void* pick_xcd_kernel(int kw, int cwd) {
     return nullptr;
 }
 
-// partial tiles of a step; the forward kernel first stages its matrix slice there
+// partial tiles of a step; the forward kernel first stages its matrix slice there.  (More than half of a compute unit's)
 constexpr size_t xcd_lds_bytes() { return (size_t)8 * 64 * 65 * 4; }
 static_assert(alone_floats<H_MAX / 8>() * sizeof(float) <= xcd_lds_bytes(), "run_alone's tiles and states");
 
@@ -750,20 +752,20 @@ void rec_xcd_test_roll_call(int microseconds, int absent) {
     t_roll_absent = absent != 0;
 }
 
-// Shapes the one-launch loop serves and is the faster choice for.  The launch has a fixed cost (the ring's clearing and
-// every workgroup loading its part of the matrix: 10 us at H = 300, 18 at H = 1024, batch 64; 10 us more when it was
-// cooperative) and then takes 0.8 to 1.8 us per step, against 5.5 us per step at H = 1024 for a launch per step, so the shortest
-// sequences stay with the latter (cross-over at H = 1024, batch 64, with the cooperative launch: 8 to 10 steps).
-// Batch 1 to 4 has the loops that give every sequence its own workgroups.  Forward, loss and backward of
-// 100 steps with 1000 words, those against this one: H = 500, batch 1: 412 / 366 us, batch 4: 492 / 411;
-// H = 600, batch 2: 476 / 448; H = 700, batch 1: 456 / 450; but H = 1000, batch 1: 475 / 509 and H = 1024,
-// batch 2: 496 / 534 (a wavefront's matrix instructions cost the same for 1 row as for 4), while H = 1024,
-// batch 3, which has no room for 16 outputs per workgroup there, is 300 / 199 us per loop.  Of 10 steps
-// (H = 500: 149 / 142) the set-up is most.
+// Shapes the one-launch loop serves.  Above 256 units it takes 10 us (H = 300) to 18 (H = 1024, batch 64) for the ring's clearing and
+// every workgroup's part of the matrix, and then 0.8 to 1.8 us per step, a launch per step (batch above 4) up to 5.5 and the loops that
+// give every sequence its own workgroups (batch 1 to 4) 1.7.  Forward, loss and backward with 1000 words, the other loop
+// and this one, us: 100 steps, H = 641, 800 and 1024, batch 1: 420 and 307, 428 and 320, 435 and 339, batch 2: 463 and 326, 442 and
+// 339, 459 and 358; batch 1, H = 500, 10 and 15 steps: 145 and 85, 160 and 94; batch 3, H = 700, 15 steps: 221 and 113; batch 5, H = 300,
+// 4 and 9 steps: 97 and 76, 138 and 88; batch 16, H = 500: 102 and 79, 160 and 105; batch 64, H = 1024: 146 and 127, 243 and 177.  The
+// lines below are where this loop began to win when it was a cooperative launch with 64 columns a workgroup; by these figures
+// there is no such line from 4 steps on.
 // 193 to 256 units fit one workgroup per 4 rows (recurrence_mfma.hip), whose step is bound by its matrix instructions: 0.97 us
 // at H = 256 and 0.90 at H = 200, here 0.73 to 0.82 (4096 steps, batch 128: 0.78 and 0.81); up to
 // 192 units 0.63 there, here 0.73 to 0.77.  35 steps of tokens, H = 200, batch 20, with the gathered input term there and the ring's
-// clearing here: 46 and 38 us there, 36 and 35 here; dense input has no rows to gather.
+// clearing here: 46 and 38 us there, 36 and 35 here; dense input has no rows to gather.  What it costs: there a loop has a compute unit per 4
+// rows and those of several streams run side by side, here they take turns (1000 steps of H = 256, batch 128 on one, two and four
+// streams: 1034, 1082 and 1216 us there, 812, 1685 and 3388 here).
 bool rec_xcd_supported(int H, int B, int T, bool tokens) {
     if (H <= 192 || H > H_MAX || B < 1 || B > (H <= 256 ? 128 : 64)) return false;
     if (H <= 256) return T >= (tokens && B > 4 ? 33 : 64);
