@@ -175,7 +175,8 @@ def test_rows_turned_round_at_this_width(H, kind):
 
 @pytest.mark.parametrize("T,B,loss", ((9, 932068, ri.LOSS_SOFTMAX_CE), (17, 986896, ri.LOSS_LINEAR_MSE)))
 def test_more_rows_than_a_grid_of_a_workgroup_each_holds(T, B, loss):
-    """A grid holds 2^32 threads at most: 8.4 million rows with 512 threads each, 16.8 million with 256."""
+    """A grid holds 2^32 threads at most: 8.4 million rows with 512 threads each, 16.8 million with 256.  (Narrow rows share a workgroup; the
+    first of these sizes is one workgroup of eight rows more than the first dimension of the metric's grid has.)"""
     case = ri.make_case(1, 2, 2, T, B, input_kind=ri.INPUT_DENSE, loss_kind=loss, wdist=("normal", 0.5), bias_std=0.1, seed=79)
     gamma = ri.make_direction(case, 9)
     r = GnRunner(case)
